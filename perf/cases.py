@@ -78,6 +78,7 @@ def draw(rng):
     M, B = _log(rng, 2, 256 if same else 128), rng.choice((8, 12, 16, 24, 32, 48, 64))
     if rng.random() < 0.08:
         M = rng.randint(257, 1024)                     # a very large cluster
+    R = min(R, 4096 * M)
     most = {"light": 1 << 28, "sweep": 1 << 30, "children": 1 << 30}.get(kind, 1 << 26)
     if M > 256:
         most = 1 << 24
