@@ -24,10 +24,12 @@
 // ap_children.hpp (sparse candidates), ap_split.hpp (replicas that differ or come and go: listed and streamed
 // part), ap_roofline.hpp (roofline cost tables, trace time) and ap_agentic.hpp (agentic workflows); ap_common.hpp
 // has what they share.
+#include <cmath>
 #include <mutex>
 
 #include "ap_common.hpp"
 #include "ap_screen.hpp"
+#include "ap_counts.hpp"
 #include "ap_replay.hpp"
 #include "ap_pipeline.hpp"
 #include "ap_children.hpp"
@@ -139,6 +141,9 @@ struct ap_workload {
     ScreenParams screen_params{};
     uint32_t lds_bytes = 0;
     uint32_t screen_lds_bytes = 0;
+    uint32_t* d_count_lo = nullptr;   // counting screen: first bucket of every bucket's window
+    bool counts = false;              // the counting screen runs in front of the slot rings
+    CountParams count_params{};
     bool screen_wide = false;         // eight wavefronts per candidate (large replica tables)
     uint32_t screen_wide_lds_bytes = 0;
     uint32_t max_grid = 0;
@@ -211,8 +216,40 @@ static PendingWord take_pending_word(const ap_workload* w) {
     return PendingWord{w->d_pending + t, w->d_pending + (t ^ 1u)};
 }
 
+// The counting screen on C rows.
+static ap_status launch_counts(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out, hipStream_t stream,
+                               PendingWord flags) {
+    typedef void (*count_fn)(CountParams, const uint16_t*, ap_metrics*, uint32_t, PendingWord);
+    CountParams p = w->count_params;
+    const bool quad = p.w_log2 >= 9u;                        // buckets of 512 requests or more: 16-byte loads
+    static const count_fn variants[6] = {k_screen_counts<1u, 2u>, k_screen_counts<1u, 3u>, k_screen_counts<1u, 4u>,
+                                         k_screen_counts<4u, 2u>, k_screen_counts<4u, 3u>, k_screen_counts<4u, 4u>};
+    const count_fn kernel = variants[p.columns_log2 - 2u + (quad ? 3u : 0u)];
+    // Several wavefronts per row while there are fewer rows than the chip holds wavefronts (8192 at eight per SIMD), as long as
+    // a wavefront's share stays at least four steps and at least as long as what it has to count again before it.
+    const uint32_t step = quad ? 512u : 128u, again = (p.ring_mask + 1u) << p.w_log2;
+    uint32_t per_row = 1u;
+    while (per_row < kCountMaxWaves && (uint64_t)C * per_row * 2u <= (uint64_t)w->n_cu * 32u &&
+           w->R / (per_row * 2u) >= std::max(4u * step, again / 2u) &&
+           std::max(4u, per_row * 2u) * p.wave_words * 4u <= kCountLdsBytes)
+        per_row *= 2u;
+    p.waves_per_row = per_row;
+    const uint32_t waves = std::max(4u, per_row);
+    const uint32_t grid = (C + waves / per_row - 1u) / (waves / per_row);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kWave), waves * p.wave_words * 4u, stream, p, d_assign, d_out, C, flags);
+    return hipGetLastError() == hipSuccess ? AP_OK : device_error();
+}
+
 static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out,
                               hipStream_t stream, bool marked, PendingWord flags) {
+    // The counting screen is one launch more in front of the rings, 2 us, which calls of 12 to 30 us do not get back.  It pays
+    // from about 2^25 requests (38 against 22 us at 34 million requests on 127 replicas; 30 against 33 us at 26 million on 38)
+    // and on long rows, which are a chain of blocks of 512 or 1024 requests for the rings.
+    if (w->counts && !marked && (w->R >= 32768u || (uint64_t)C * w->R >= (1u << 25))) {
+        const ap_status st = launch_counts(w, d_assign, C, d_out, stream, flags);
+        if (st != AP_OK) return st;
+        marked = true;                                       // the rings look at what it has left
+    }
     if (w->screen) {
         const uint32_t blocks = std::min((C + kScreenWaves - 1u) / kScreenWaves, w->n_cu * 64u);
         // rows start on 4-byte boundaries when R is even and the batch itself does
@@ -365,6 +402,7 @@ ap_status ap_workload_create(const uint64_t* arrival_us, const int32_t* prompt_l
                         hipMalloc(&w->d_span, bytes) != hipSuccess ||
                         hipMalloc(&w->d_span_t, padded) != hipSuccess ||
                         hipMalloc(&w->d_pair, ((size_t)R + 1u) / 2u * 4u) != hipSuccess ||
+                        hipMalloc(&w->d_count_lo, ((size_t)R + kCountShift + kCountMinBucket) / kCountMinBucket * 4u) != hipSuccess ||
                         hipMalloc(&w->d_nominal, sizeof(ap_metrics)) != hipSuccess ||
                         hipMalloc(&w->d_nominal_sums, kNominalSumsBytes) != hipSuccess ||
                         hipMalloc(&w->d_pending, 4u * sizeof(uint32_t)) != hipSuccess))
@@ -655,6 +693,66 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
     w->split_expect_lazy = penalty_on_top && expect_rejected / M >= sp.lazy_from;
     w->split = true;
     return AP_OK;
+}
+
+// Plan of the counting screen (ap_counts.hpp): the bucket size and, per bucket, the first bucket with a request that is
+// still in service when it begins.  Leaves w->counts false where no bucket size makes a row that is spread evenly over the
+// replicas likely to pass.  worst_service: every request's service time (one kind of replica).
+static ap_status plan_counts(ap_workload* w, const std::vector<uint32_t>& worst_service) {
+    const uint32_t R = w->R, M = w->params.M, B = w->params.B;
+    // first request still in service when request max(0, 16 k - kCountShift) arrives; it only moves forward
+    const uint32_t n_marks = (R + kCountShift) / kCountMinBucket + 1u;
+    std::vector<uint32_t> first(n_marks);
+    const uint32_t* arr = w->h_arrival.data();
+    for (uint32_t k = 0, q = 0; k < n_marks; ++k) {
+        const uint32_t i = std::min(R - 1u, k * kCountMinBucket < kCountShift ? 0u : k * kCountMinBucket - kCountShift);
+        while (q < i && (uint64_t)arr[q] + worst_service[q] <= arr[i]) ++q;
+        first[k] = q;
+    }
+    // Coarse buckets cost fewer checks, fine ones make a tighter window: the coarsest for which a replica with its even
+    // share of every window has less than one chance in 10^4 per row of more than B requests in one (Chernoff's bound on
+    // a Poisson count, summed over replicas and buckets).
+    const uint32_t n_rows = M / 4u + 1u, columns_log2 = n_rows <= 40u ? 4u : n_rows <= 80u ? 3u : 2u;
+    for (uint32_t w_log2 = 11u; w_log2 >= 7u; --w_log2) {
+        const uint32_t per = (1u << w_log2) / kCountMinBucket;
+        const uint32_t n_buckets = ((R + kCountShift) >> w_log2) + 1u;
+        uint32_t window = 1u;
+        for (uint32_t b = 0; b < n_buckets; ++b) window = std::max(window, b + 1u - (first[b * per] >> w_log2));
+        uint32_t copies = 2u;
+        while (copies < window + 1u) copies *= 2u;
+        const uint32_t words = align_up(n_rows << columns_log2, 4u) + align_up(copies * n_rows, 4u);
+        if (4u * words * 4u > kCountLdsBytes) continue;
+        const double mean = std::min((double)window * (1u << w_log2), (double)R) / M, most = (double)B + 1.0;
+        if (most <= mean || most - mean - most * std::log(most / mean) + std::log((double)M * n_buckets) > -9.2) continue;
+        std::vector<uint32_t> lo(n_buckets);
+        for (uint32_t b = 0; b < n_buckets; ++b) lo[b] = first[b * per] >> w_log2;
+        if (hipMemcpy(w->d_count_lo, lo.data(), 4u * (size_t)n_buckets, hipMemcpyHostToDevice) != hipSuccess) return device_error();
+        CountParams cp{};
+        cp.lo = w->d_count_lo;
+        cp.nominal = w->d_nominal;
+        cp.R = R; cp.M = M; cp.B = B;
+        cp.w_log2 = w_log2;
+        cp.ring_mask = copies - 1u;
+        cp.n_rows = n_rows;
+        cp.columns_log2 = columns_log2;
+        cp.wave_words = words;
+        w->count_params = cp;
+        w->counts = true;
+        return AP_OK;
+    }
+    return AP_OK;
+}
+
+// Slots per replica of the one-wavefront ring screen: a power of two, at most B, as long as that wavefront's slot state
+// (rings and counters of M + 1 replicas) stays small enough for many wavefronts per compute unit.  wide: the state
+// leaves room for fewer slots than are worth having, so the eight-wavefront kernel, whose workgroup holds one row's
+// rings, takes the table.
+static uint32_t narrow_ring_slots_log2(uint32_t M, uint32_t B, bool& wide) {
+    uint32_t most = 0, S_log2 = 0;
+    while ((2u << most) <= kScreenMaxSlots && (M + 1u) * ((2u << most) + 1u) * 4u <= kScreenLdsPerWave) ++most;
+    while (S_log2 < most && (2u << S_log2) <= B) ++S_log2;
+    wide = (1u << most) < std::min(B, kScreenMinSlots);
+    return S_log2;
 }
 
 // Shared by ap_costmodel_set (rep_type == nullptr: the coefficients of `replicas` apply) and
@@ -989,15 +1087,18 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     // the trace goes straight to the listed evaluation, which replays every queue.
     const bool crowded = w->span_us == 0 || (double)service_sum / (double)w->span_us / M >= 0.25 * B;
     if (w->screen && crowded && w->d_req8) w->screen = false;
+    w->counts = false;
+    if (w->screen) {
+        const ap_status st = plan_counts(w, worst_service);
+        if (st != AP_OK) return st;
+    }
     // The one-wavefront screening kernel hands a step's 64 requests to rings of S slots in no particular order: with
     // few replicas and few slots (64 / M requests per ring and step against S slots) a ring wraps within one step
     // and hardly any candidate passes.  Such tables go to the listed evaluation as well.
     {
-        const uint32_t want = std::min(B, kScreenMaxSlots);
-        uint32_t S_log2 = 0;
-        while ((2u << S_log2) <= want && (M + 1u) * ((2u << S_log2) + 1u) * 4u <= kScreenLdsPerWave) ++S_log2;
-        const bool wide = (1u << S_log2) < std::min(want, kScreenMinSlots);
-        if (w->screen && !wide && 128u >= M * (1u << S_log2) && w->d_req8) w->screen = false;
+        bool wide = false;
+        const uint32_t S_log2 = narrow_ring_slots_log2(M, B, wide);
+        if (w->screen && !w->counts && !wide && 128u >= M * (1u << S_log2) && w->d_req8) w->screen = false;
     }
     if (w->screen) {
         ScreenParams sp{};
@@ -1014,10 +1115,7 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
         // long as that wavefront's slot state (rings and counters of M + 1 replicas) stays small
         // enough for many wavefronts per compute unit with a useful number of slots; otherwise
         // the eight-wavefront kernel, whose workgroup holds one candidate's rings.
-        const uint32_t want = std::min(B, kScreenMaxSlots);
-        uint32_t S_log2 = 0;
-        while ((2u << S_log2) <= want && (M + 1u) * ((2u << S_log2) + 1u) * 4u <= kScreenLdsPerWave) ++S_log2;
-        w->screen_wide = (1u << S_log2) < std::min(want, kScreenMinSlots);
+        uint32_t S_log2 = narrow_ring_slots_log2(M, B, w->screen_wide);
         if (w->screen_wide) {
             S_log2 = 0;
             while ((2u << S_log2) <= std::min(B, kWideMaxSlots) && M * (2u << S_log2) * 4u <= kWideLdsBytes) ++S_log2;
@@ -1688,6 +1786,7 @@ ap_status ap_workload_destroy(ap_workload* w) {
     if (w->d_span) ok = (hipFree(w->d_span) == hipSuccess) && ok;
     if (w->d_span_t) ok = (hipFree(w->d_span_t) == hipSuccess) && ok;
     if (w->d_pair) ok = (hipFree(w->d_pair) == hipSuccess) && ok;
+    if (w->d_count_lo) ok = (hipFree(w->d_count_lo) == hipSuccess) && ok;
     if (w->d_nominal) ok = (hipFree(w->d_nominal) == hipSuccess) && ok;
     if (w->d_nominal_sums) ok = (hipFree(w->d_nominal_sums) == hipSuccess) && ok;
     if (w->d_pending) ok = (hipFree(w->d_pending) == hipSuccess) && ok;

@@ -239,6 +239,9 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 __device__ __forceinline__ uint32_t lds_max_rtn(uint32_t byte_address, uint32_t v) {
     return __hip_atomic_fetch_max((lds_word*)(uintptr_t)byte_address, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+__device__ __forceinline__ void lds_add(uint32_t byte_address, uint32_t v) {
+    (void)__hip_atomic_fetch_add((lds_word*)(uintptr_t)byte_address, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 __device__ __forceinline__ uint32_t lds_add_rtn(uint32_t byte_address, uint32_t v) {
     return __hip_atomic_fetch_add((lds_word*)(uintptr_t)byte_address, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
