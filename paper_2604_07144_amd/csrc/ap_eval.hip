@@ -1215,7 +1215,7 @@ ap_status ap_parent_set(ap_workload* w, const uint16_t* parent, uint32_t max_chi
     if ((uint64_t)max_children > (UINT64_MAX / sizeof(uint16_t)) / w->R) return AP_ERR_ALLOC;     // the rows cannot exist
     const size_t need = (size_t)max_children * w->R * sizeof(uint16_t);
     const size_t row_bytes = (size_t)w->R * sizeof(uint16_t), peak_bytes = sizeof(uint32_t) * (AP_MAX_REPLICAS + 1u);
-    if ((!w->d_parent && hipMalloc(&w->d_parent, row_bytes) != hipSuccess) ||
+    if ((!w->d_parent && hipMalloc(&w->d_parent, row_bytes + 16u) != hipSuccess) ||
         (!w->d_peak && hipMalloc(&w->d_peak, peak_bytes) != hipSuccess) ||
         (!w->d_room && hipMalloc(&w->d_room, sizeof(uint32_t) * AP_MAX_REPLICAS) != hipSuccess) ||
         (!w->h_stage && hipHostMalloc(reinterpret_cast<void**>(&w->h_stage), std::max(row_bytes, peak_bytes), hipHostMallocDefault) != hipSuccess)) {
@@ -1281,10 +1281,15 @@ ap_status ap_eval_children(const ap_workload* w, const uint32_t* d_edit_first, c
     if (C > w->max_children) return AP_ERR_RANGE;
     w->n_scored += C;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    const uint32_t blocks = std::min((C + kChildWaves - 1u) / kChildWaves, w->n_cu * 64u);
     const PendingWord flags = take_pending_word(w);
-    hipLaunchKernelGGL(k_certify_children, dim3(blocks), dim3(kChildThreads), (kChildWaves + 1u) * w->child_params.M * 4u, stream,
-                       w->child_params, d_edit_first, d_edit_request, d_edit_replica, d_out, C, flags);
+    if (w->child_params.certify != 0u) {
+        const uint32_t blocks = std::min((C + kChildWaves - 1u) / kChildWaves, w->n_cu * 64u);
+        hipLaunchKernelGGL(k_certify_children, dim3(blocks), dim3(kChildThreads), (kChildWaves + 1u) * w->child_params.M * 4u, stream,
+                           w->child_params, d_edit_first, d_edit_request, d_edit_replica, d_out, C, flags);
+    } else {
+        hipLaunchKernelGGL(k_write_children, dim3(std::min(C, w->n_cu * 64u)), dim3(kRowThreads), 0, stream, w->child_params,
+                           d_edit_first, d_edit_request, d_edit_replica, C, flags);
+    }
     if (hipGetLastError() != hipSuccess) return device_error();
     return launch_dense(w, w->d_rows, C, d_out, stream, w->child_params.certify != 0u, flags);
 }

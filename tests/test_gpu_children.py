@@ -345,3 +345,19 @@ def test_configs4_mutation_sweep_every_child():
         got = g.eval_children(*lists)
     assert_same(got, want, "configs[4] as children")
     assert (got["n_rejected"] == 0).all()
+
+
+# ------------------------------------------------------------------ rows written for children that need them
+@pytest.mark.parametrize("R", [1, 7, 8, 9, 63, 520, 521, 1033, 4099])
+def test_rows_of_any_length_are_the_parent_with_its_edits(R):
+    """Replicas that differ: every child's row is written out, each on another 2-byte boundary when R is odd."""
+    rng = np.random.default_rng(R)
+    M, C = 5, 11
+    tr = traces.custom_trace(np.cumsum(rng.integers(0, 3000, R)), rng.integers(1, 3000, R), rng.integers(1, 300, R),
+                             [(traces.COEF_STANDARD, traces.COEF_FAST, traces.COEF_SLOW)[m % 3] for m in range(M)], B=3)
+    parent = rng.integers(0, M, R).astype(np.uint16)
+    first, request, replica = traces.draw_edit_lists(R, C, R, M, min(200.0, 0.5 * R), request_range=R + 2, replica_range=M + 1)
+    with GpuWorkload(tr) as g:
+        g.set_parent(parent, C)
+        got = g.eval_children(first, request, replica)
+    assert_same(got, oracle_for(tr).eval_children(parent, first, request, replica), f"R={R}")
