@@ -34,6 +34,7 @@
 #include "ap_pipeline.hpp"
 #include "ap_children.hpp"
 #include "ap_split.hpp"
+#include "ap_stream.hpp"
 #include "ap_roofline.hpp"
 #include "ap_agentic.hpp"
 
@@ -170,6 +171,12 @@ struct ap_workload {
     uint32_t max_children = 0;
     bool has_parent = false;
     ChildParams child_params{};
+    // streamed evaluation (replicas always there, nobody expected to wait): its own tables, one allocation
+    bool stream = false;
+    uint32_t* d_stream_tab = nullptr;
+    size_t stream_tab_bytes = 0;
+    StreamParams stream_params{};
+    uint32_t stream_lds_bytes = 0;
     // split evaluation (replicas that differ or have windows): listed part replayed, streamed part scored on arrival
     uint2* d_req8 = nullptr;          // [R] {arrival, prompt | out << 16}; only when every length is below 65536
     uint2* d_tab_pair = nullptr;      // [T][R] the cost tables side by side, for the split evaluation of a tabulated model
@@ -240,6 +247,61 @@ static ap_status launch_counts(const ap_workload* w, const uint16_t* d_assign, u
     return hipGetLastError() == hipSuccess ? AP_OK : device_error();
 }
 
+// The listed / streamed evaluation, a batch of candidates at a time; what it hands back carries the pending mark.
+// pending: only candidates that carry the pending mark already (behind the streamed evaluation).
+static ap_status launch_split(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out, hipStream_t stream,
+                              PendingWord flags, bool pending) {
+    SplitParams sp = w->split_params;
+    const replay_lists_fn replay_lean = replay_lists_kernel(w->split_slots, false, w->tabled);
+    const replay_lists_fn replay_bins = replay_lists_kernel(w->split_slots, true, w->tabled);
+    // batches of equal size (whole wavefronts of the list replay), none above what the scratch area holds
+    const uint32_t n_batches = (C + w->split_batch - 1u) / w->split_batch;
+    const uint32_t per_batch = std::min(w->split_batch, ((C + n_batches - 1u) / n_batches + 63u) / 64u * 64u);
+    for (uint32_t c0 = 0; c0 < C; c0 += per_batch) {
+        const uint32_t n = std::min(per_batch, C - c0);
+        if (pending) {
+            sp.pending = d_out + c0;
+            sp.pending_word = flags.mine;
+        }
+        const uint32_t grid = std::min(n, w->n_cu * 16u);
+        // First without histograms where the candidates are expected to be settled by penalty, or where nothing is
+        // streamed at all; then with histograms, for every candidate or for those the first pass marked.
+        const int narrow = sp.M <= 64u ? 1 : 0;
+        const bool plain_first = w->split_expect_lazy || sp.any_streamed == 0u;
+        if (plain_first)
+            hipLaunchKernelGGL(split_kernel(0u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads), w->split_lds_bytes, stream, sp,
+                               d_assign, c0, n, 0u, flags);
+        if (sp.any_streamed != 0u)
+            hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads),
+                               w->split_lds_bytes_hist, stream, sp, d_assign, c0, n, plain_first ? 1u : 0u, flags);
+        // the list replay: where most candidates are settled by penalty, those go through the variant that
+        // leaves no bins, and the wavefronts of the other variant find the few that remain
+        if (sp.n_queues != 0u) {
+            const dim3 groups(sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads));
+            if (w->split_expect_lazy)
+                hipLaunchKernelGGL(replay_lean, groups, dim3(kReplayListThreads), 0, stream, sp, n, 1u);
+            hipLaunchKernelGGL(replay_bins, groups, dim3(kReplayListThreads), 0, stream, sp, n,
+                               w->split_expect_lazy ? 2u : 0u);
+        }
+        hipLaunchKernelGGL(sp.wide ? k_merge_candidates<false> : k_merge_candidates<true>,
+                           dim3(std::min(n, w->n_cu * 8u)), dim3(kThreads), w->reduce_lds_bytes,
+                           stream, w->reduce_eval, sp, d_out, c0, n, flags);
+    }
+    return hipGetLastError() == hipSuccess ? AP_OK : device_error();
+}
+
+static ap_status launch_stream(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out, hipStream_t stream,
+                               PendingWord flags) {
+    // A workgroup per row: four wavefronts, or more where rows are fewer than the chip holds wavefronts and long enough that
+    // each still has four steps.
+    uint32_t waves = 4u;
+    while (waves < kStreamMaxThreads / kWave && (uint64_t)C * waves * 2u <= (uint64_t)w->n_cu * 32u && w->R / 128u >= 8u * waves) waves *= 2u;
+    const uint32_t grid = std::min(C, w->n_cu * 64u);
+    hipLaunchKernelGGL(w->tabled ? k_stream_candidates<true> : k_stream_candidates<false>, dim3(grid), dim3(waves * kWave),
+                       w->stream_lds_bytes, stream, w->stream_params, d_assign, d_out, C, flags);
+    return hipGetLastError() == hipSuccess ? AP_OK : device_error();
+}
+
 static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out,
                               hipStream_t stream, bool marked, PendingWord flags) {
     // The counting screen is one launch more in front of the rings, 2 us, which calls of 12 to 30 us do not get back.  It pays
@@ -278,43 +340,18 @@ static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, ui
         }
         if (hipGetLastError() != hipSuccess) return device_error();
     }
-    if (w->split && !marked) {
-        // the listed / streamed evaluation, a batch of candidates at a time; what it hands back carries the pending mark
-        const SplitParams& sp = w->split_params;
-        const replay_lists_fn replay_lean = replay_lists_kernel(w->split_slots, false, w->tabled);
-        const replay_lists_fn replay_bins = replay_lists_kernel(w->split_slots, true, w->tabled);
-        // batches of equal size (whole wavefronts of the list replay), none above what the scratch area holds
-        const uint32_t n_batches = (C + w->split_batch - 1u) / w->split_batch;
-        const uint32_t per_batch = std::min(w->split_batch, ((C + n_batches - 1u) / n_batches + 63u) / 64u * 64u);
-        for (uint32_t c0 = 0; c0 < C; c0 += per_batch) {
-            const uint32_t n = std::min(per_batch, C - c0);
-            const uint32_t grid = std::min(n, w->n_cu * 16u);
-            // First without histograms where the candidates are expected to be settled by penalty, or where nothing is
-            // streamed at all; then with histograms, for every candidate or for those the first pass marked.
-            const int narrow = sp.M <= 64u ? 1 : 0;
-            const bool plain_first = w->split_expect_lazy || sp.any_streamed == 0u;
-            if (plain_first)
-                hipLaunchKernelGGL(split_kernel(0u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads), w->split_lds_bytes, stream, sp,
-                                   d_assign, c0, n, 0u, flags);
-            if (sp.any_streamed != 0u)
-                hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads),
-                                   w->split_lds_bytes_hist, stream, sp, d_assign, c0, n, plain_first ? 1u : 0u, flags);
-            // the list replay: where most candidates are settled by penalty, those go through the variant that
-            // leaves no bins, and the wavefronts of the other variant find the few that remain
-            if (sp.n_queues != 0u) {
-                const dim3 groups(sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads));
-                if (w->split_expect_lazy)
-                    hipLaunchKernelGGL(replay_lean, groups, dim3(kReplayListThreads), 0, stream, sp, n, 1u);
-                hipLaunchKernelGGL(replay_bins, groups, dim3(kReplayListThreads), 0, stream, sp, n,
-                                   w->split_expect_lazy ? 2u : 0u);
-            }
-            hipLaunchKernelGGL(sp.wide ? k_merge_candidates<false> : k_merge_candidates<true>,
-                               dim3(std::min(n, w->n_cu * 8u)), dim3(kThreads), w->reduce_lds_bytes,
-                               stream, w->reduce_eval, sp, d_out, c0, n, flags);
-        }
-        if (hipGetLastError() != hipSuccess) return device_error();
+    bool split_behind = false;
+    if (w->stream && !marked) {
+        const ap_status st = launch_stream(w, d_assign, C, d_out, stream, flags);
+        if (st != AP_OK) return st;
+        split_behind = true;
     }
-    const uint32_t pending_only = (w->screen || (w->split && !marked)) ? 1u : 0u;
+    if (w->split && !marked) {
+        const ap_status st = launch_split(w, d_assign, C, d_out, stream, flags, split_behind);
+        if (st != AP_OK) return st;
+        if (split_behind) return AP_OK;                      // with every request listed nothing is handed back
+    }
+    const uint32_t pending_only = (w->screen || ((w->split || w->stream) && !marked)) ? 1u : 0u;
     if (w->pipeline) {
         for (uint32_t c0 = 0; c0 < C; c0 += w->batch) {
             const uint32_t n = std::min(w->batch, C - c0);
@@ -450,17 +487,41 @@ ap_status ap_workload_create(const uint64_t* arrival_us, const int32_t* prompt_l
     return AP_OK;
 }
 
+// The cost tables side by side for the evaluations that read them in pairs, rows up to the highest type in use.
+// ready: false where there is no room for them (the general replay scores the calls then).
+static ap_status pair_tables(ap_workload* w, const uint32_t* rep_type, uint32_t M, bool& ready) {
+    ready = false;
+    size_t entries = 0;
+    for (uint32_t m = 0; m < M; ++m) entries = std::max(entries, ((size_t)rep_type[m] + 1u) * w->R);
+    if (entries > w->tab_pair_entries) {
+        if (w->d_tab_pair && hipFree(w->d_tab_pair) != hipSuccess) return device_error();
+        w->d_tab_pair = nullptr;
+        w->tab_pair_entries = 0;
+        if (hipMalloc(&w->d_tab_pair, entries * sizeof(uint2)) != hipSuccess) {
+            (void)hipGetLastError();
+            return AP_OK;
+        }
+        w->tab_pair_entries = entries;
+    }
+    hipLaunchKernelGGL(k_pair_tables, dim3((uint32_t)std::min<size_t>(4096u, (entries + kThreads - 1u) / kThreads)), dim3(kThreads), 0,
+                       nullptr, w->d_tab_prefill, w->d_tab_tpot, w->d_tab_pair, entries);
+    if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess) return device_error();
+    ready = true;
+    return AP_OK;
+}
+
 // Plan of the split evaluation (ap_split.hpp) - replicas that differ or have windows, crowded traces, tables too
 // small for the one-wavefront screen; linear cost models (rep_type == nullptr) and tabulated ones:
 // the index ranges of every replica, the bound D on requests in service that started on arrival, the
 // scratch area for one batch of candidates.  Leaves w->split false where the path does not apply.
+// list_all: no streamed part at all (the evaluation runs behind the streamed one, on what that has left).
 // rep_type: the tabulated cost model (replica m reads row rep_type[m] of the tables, which are on the device by
 // now); table_longest_prefill / table_longest_tpot are then the largest entries of the rows in use.
 static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, const ap_replica* replicas,
                             const std::vector<uint32_t>& kinds, const std::vector<uint32_t>& worst_service,
                             const std::vector<uint64_t>& kind_sum, const std::vector<uint64_t>& kind_longest,
                             uint64_t latest_finish_bound, const uint32_t* rep_type, uint64_t table_longest_prefill,
-                            uint64_t table_longest_tpot) {
+                            uint64_t table_longest_tpot, bool list_all) {
     const uint32_t R = w->R, M = w->params.M, B = w->params.B;
     if (!w->d_req8) return AP_OK;                            // request records with 16-bit lengths only
     const bool tabled = rep_type != nullptr;
@@ -488,7 +549,7 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
         // D(r): sweep in arrival order over a min-heap of the finish times of requests that start on arrival
         std::vector<uint64_t> heap;
         heap.reserve(1024);
-        for (uint32_t r = 0; r < R; ++r) {
+        for (uint32_t r = 0; r < (list_all ? 0u : R); ++r) {
             const uint64_t a = w->h_arrival[r];
             while (!heap.empty() && heap.front() <= a) {
                 std::pop_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
@@ -535,7 +596,7 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
             const uint64_t t_target = (uint64_t)d.t_on + (uint64_t)std::min(drain, 4.0e9);
             i_list = (uint32_t)(std::lower_bound(arr, arr + R, (uint32_t)std::min<uint64_t>(t_target, kNever)) - arr);
         }
-        i_list = std::min(std::max(i_list, i_calm), i_off);
+        i_list = list_all ? i_off : std::min(std::max(i_list, i_calm), i_off);
         tab[m] = wide ? i_list : (i_list | (i_off << 16));
         tab[AP_MAX_REPLICAS + 1u + m] = i_off;
         tab[2u * (AP_MAX_REPLICAS + 1u) + m] = tabled ? rep_type[m] : (uint32_t)ki;
@@ -661,25 +722,7 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
     sp.tab.kind = w->d_split_tab + 2u * (AP_MAX_REPLICAS + 1u);
     sp.tab.coef = reinterpret_cast<const uint4*>(w->d_split_tab + 3u * (AP_MAX_REPLICAS + 1u));
     sp.tab.n_kinds = tabled ? 0u : (uint32_t)kinds.size();
-    sp.tab_pair = nullptr;
-    if (tabled) {
-        size_t entries = 0;                                  // rows up to the highest type in use
-        for (uint32_t m = 0; m < M; ++m) entries = std::max(entries, ((size_t)rep_type[m] + 1u) * R);
-        if (entries > w->tab_pair_entries) {
-            if (w->d_tab_pair && hipFree(w->d_tab_pair) != hipSuccess) return device_error();
-            w->d_tab_pair = nullptr;
-            w->tab_pair_entries = 0;
-            if (hipMalloc(&w->d_tab_pair, entries * sizeof(uint2)) != hipSuccess) {
-                (void)hipGetLastError();
-                return AP_OK;                                // no room: the general replay scores the calls
-            }
-            w->tab_pair_entries = entries;
-        }
-        hipLaunchKernelGGL(k_pair_tables, dim3((uint32_t)std::min<size_t>(4096u, (entries + kThreads - 1u) / kThreads)),
-                           dim3(kThreads), 0, nullptr, w->d_tab_prefill, w->d_tab_tpot, w->d_tab_pair, entries);
-        if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess) return device_error();
-        sp.tab_pair = w->d_tab_pair;
-    }
+    sp.tab_pair = tabled ? w->d_tab_pair : nullptr;
     sp.queue = w->d_split_queue;
     sp.order = w->d_split_order;
     sp.lists = reinterpret_cast<uint16_t*>(w->d_split_scratch + o_lists);
@@ -695,23 +738,35 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
     return AP_OK;
 }
 
+// For every multiple k of `grain`: the first request still in service, nobody waiting, when request k * grain - shift (0 if
+// that is negative) arrives.  It only moves forward.
+static std::vector<uint32_t> first_in_service(const ap_workload* w, const std::vector<uint32_t>& worst_service, uint32_t grain,
+                                              uint32_t shift) {
+    std::vector<uint32_t> first((w->R + shift) / grain + 1u);
+    const uint32_t* arr = w->h_arrival.data();
+    for (uint32_t k = 0, q = 0; k < first.size(); ++k) {
+        const uint32_t i = std::min(w->R - 1u, k * grain < shift ? 0u : k * grain - shift);
+        while (q < i && (uint64_t)arr[q] + worst_service[q] <= arr[i]) ++q;
+        first[k] = q;
+    }
+    return first;
+}
+
+// Is a row that is spread evenly over the replicas all but sure to have at most B requests per replica in every one of
+// n_windows windows of `window` requests?  Chernoff's bound on a Poisson count: one chance in 10^7 per row, because a single
+// row that fails makes its call wait for the serial replay of the row's queues.
+static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_windows) {
+    const double mean = window / M, most = (double)B + 1.0;
+    return most > mean && most - mean - most * std::log(most / mean) + std::log((double)M * n_windows) <= -16.0;
+}
+
 // Plan of the counting screen (ap_counts.hpp): the bucket size and, per bucket, the first bucket with a request that is
 // still in service when it begins.  Leaves w->counts false where no bucket size makes a row that is spread evenly over the
 // replicas likely to pass.  worst_service: every request's service time (one kind of replica).
 static ap_status plan_counts(ap_workload* w, const std::vector<uint32_t>& worst_service) {
     const uint32_t R = w->R, M = w->params.M, B = w->params.B;
-    // first request still in service when request max(0, 16 k - kCountShift) arrives; it only moves forward
-    const uint32_t n_marks = (R + kCountShift) / kCountMinBucket + 1u;
-    std::vector<uint32_t> first(n_marks);
-    const uint32_t* arr = w->h_arrival.data();
-    for (uint32_t k = 0, q = 0; k < n_marks; ++k) {
-        const uint32_t i = std::min(R - 1u, k * kCountMinBucket < kCountShift ? 0u : k * kCountMinBucket - kCountShift);
-        while (q < i && (uint64_t)arr[q] + worst_service[q] <= arr[i]) ++q;
-        first[k] = q;
-    }
-    // Coarse buckets cost fewer checks, fine ones make a tighter window: the coarsest for which a replica with its even
-    // share of every window has less than one chance in 10^4 per row of more than B requests in one (Chernoff's bound on
-    // a Poisson count, summed over replicas and buckets).
+    const std::vector<uint32_t> first = first_in_service(w, worst_service, kCountMinBucket, kCountShift);
+    // Coarse buckets cost fewer checks, fine ones make a tighter window: the coarsest that will do.
     const uint32_t n_rows = M / 4u + 1u, columns_log2 = n_rows <= 40u ? 4u : n_rows <= 80u ? 3u : 2u;
     for (uint32_t w_log2 = 11u; w_log2 >= 7u; --w_log2) {
         const uint32_t per = (1u << w_log2) / kCountMinBucket;
@@ -722,8 +777,7 @@ static ap_status plan_counts(ap_workload* w, const std::vector<uint32_t>& worst_
         while (copies < window + 1u) copies *= 2u;
         const uint32_t words = align_up(n_rows << columns_log2, 4u) + align_up(copies * n_rows, 4u);
         if (4u * words * 4u > kCountLdsBytes) continue;
-        const double mean = std::min((double)window * (1u << w_log2), (double)R) / M, most = (double)B + 1.0;
-        if (most <= mean || most - mean - most * std::log(most / mean) + std::log((double)M * n_buckets) > -9.2) continue;
+        if (!windows_fit(std::min((double)window * (1u << w_log2), (double)R), M, B, n_buckets)) continue;
         std::vector<uint32_t> lo(n_buckets);
         for (uint32_t b = 0; b < n_buckets; ++b) lo[b] = first[b * per] >> w_log2;
         if (hipMemcpy(w->d_count_lo, lo.data(), 4u * (size_t)n_buckets, hipMemcpyHostToDevice) != hipSuccess) return device_error();
@@ -740,6 +794,116 @@ static ap_status plan_counts(ap_workload* w, const std::vector<uint32_t>& worst_
         w->counts = true;
         return AP_OK;
     }
+    return AP_OK;
+}
+
+// Plan of the streamed evaluation (ap_stream.hpp): bucket size, window table, the bins from which large values are counted.
+// Leaves w->stream false where it does not apply.  cost(k, r, prefill, tpot): the cost of request r on the kind of replica
+// whose first replica is k; rep_type: tabulated cost model.
+extern "C++" template <typename Cost>
+static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const std::vector<uint32_t>& kinds,
+                             const std::vector<uint32_t>& kind_of, const std::vector<uint32_t>& worst_service, const uint32_t* rep_type,
+                             const Cost& cost) {
+    const uint32_t R = w->R, M = w->params.M, B = w->params.B;
+    const bool tabled = rep_type != nullptr;
+    if (!w->d_req8) return AP_OK;                            // request records with 16-bit lengths only
+    for (uint32_t m = 0; m < M && !tabled; ++m)              // the kernel multiplies with 24-bit factors
+        if (replicas[m].prefill_per_tok_us >= (1u << 24) || replicas[m].decode_per_kctx_us >= (1u << 24) ||
+            (uint64_t)replicas[m].decode_base_us + 64ull * replicas[m].decode_per_kctx_us >= (1u << 24))
+            return AP_OK;
+    for (uint32_t r = 0; r < R; ++r)                         // and adds up eight latencies in 32 bits
+        if (worst_service[r] >= (1u << 28)) return AP_OK;
+    // bucket size: the coarsest that will do and whose counts fit (32 KiB: four workgroups per compute unit)
+    const uint32_t words = (M + 4u) / 4u;
+    const std::vector<uint32_t> first = first_in_service(w, worst_service, 2u, 1u);
+    uint32_t w_log2 = 7u, n_buckets = 0;
+    for (;; --w_log2) {
+        if (w_log2 == 0u) return AP_OK;
+        n_buckets = ((R + 1u) >> w_log2) + 1u;
+        if ((uint64_t)n_buckets * (words * 4u + 2u) > 32768u) return AP_OK;
+        const uint32_t per = (1u << w_log2) / 2u;
+        uint32_t window = 1u;
+        for (uint32_t b = 0; b < n_buckets; ++b) window = std::max(window, b + 1u - (first[b * per] >> w_log2));
+        if (windows_fit(std::min((double)window * (1u << w_log2), (double)R), M, B, n_buckets)) break;
+    }
+    // Values per bin when the requests are spread over the kinds as the replicas are (in units of 1 / M), and the largest.
+    std::vector<uint32_t> share(kinds.size(), 0u);
+    for (uint32_t m = 0; m < M; ++m) ++share[kind_of[m]];
+    std::vector<uint64_t> weight(3u * kBins, 0u);
+    uint32_t highest[3] = {0u, 0u, 0u};
+    for (size_t k = 0; k < kinds.size(); ++k)
+        for (uint32_t r = 0; r < R; ++r) {
+            uint64_t prefill, tpot;
+            cost(kinds[k], r, prefill, tpot);
+            if (tabled && tpot >= (1u << 24)) return AP_OK;
+            const uint64_t value[3] = {prefill, tpot, prefill + (uint64_t)w->h_out[r] * tpot};
+            for (uint32_t h = 0; h < 3u; ++h) {
+                // ap_hist_bin for values below 2^32, without its loop: this runs three times per request and kind
+                const uint32_t v = (uint32_t)std::min<uint64_t>(value[h], kNever), s = 24u - std::min(v ? (uint32_t)__builtin_clz(v) : 32u, 24u);
+                const uint32_t bin = (s << 7) + (v >> s);
+                weight[h * kBins + bin] += share[k];
+                highest[h] = std::max(highest[h], bin);
+            }
+        }
+    StreamParams sp{};
+    sp.need_top = R - w->params.k99 + 1u;
+    // twice what is needed, and room for the spread of a small number of requests
+    const double want = (2.0 * sp.need_top + 8.0 * std::sqrt((double)sp.need_top) + 8.0) * M;
+    uint32_t total_bins = 0;
+    for (uint32_t h = 0; h < 3u; ++h) {
+        uint32_t from = highest[h] + 1u;
+        double reached = 0.0;
+        while (from > 1u && reached < want) reached += (double)weight[h * kBins + --from];
+        sp.from[h] = from;
+        sp.least[h] = (uint32_t)ap_hist_lower(from);
+        sp.n_bins[h] = std::max(highest[h] + 1u, from + 1u) - from;
+        total_bins += sp.n_bins[h];
+    }
+    uint32_t off = align_up((M + 1u) * 4u, 16u);
+    sp.off_coef = off; off += tabled ? 0u : (uint32_t)kinds.size() * 16u;
+    sp.off_lo = off;   off += align_up(n_buckets * 2u, 16u);
+    sp.off_cnt = off;  off += align_up(n_buckets * words * 4u, 16u);
+    sp.off_hist = off; off += align_up(total_bins * 4u, 16u);
+    sp.off_acc = off;  off += 64u;
+    if (off > 65536u) return AP_OK;
+    // one buffer: coefficients, kinds, window table
+    std::vector<uint32_t> tab(4u * kinds.size() + (M + 1u) + n_buckets, 0u);
+    for (size_t k = 0; k < kinds.size() && !tabled; ++k) {
+        const ap_replica& rp = replicas[kinds[k]];
+        tab[4u * k] = rp.prefill_base_us; tab[4u * k + 1u] = rp.prefill_per_tok_us;
+        tab[4u * k + 2u] = rp.decode_base_us; tab[4u * k + 3u] = rp.decode_per_kctx_us;
+    }
+    uint32_t* kind_words = &tab[4u * kinds.size()];
+    for (uint32_t m = 0; m < M; ++m) kind_words[m] = tabled ? rep_type[m] * R : kind_of[m];
+    kind_words[M] = tabled ? rep_type[0] * R : 0u;           // unknown ids: any entry, its cost is not used
+    for (uint32_t b = 0; b < n_buckets; ++b) kind_words[M + 1u + b] = first[b * ((1u << w_log2) / 2u)] >> w_log2;
+    if (4u * tab.size() > w->stream_tab_bytes) {
+        if (w->d_stream_tab && hipFree(w->d_stream_tab) != hipSuccess) return device_error();
+        w->d_stream_tab = nullptr;
+        w->stream_tab_bytes = 0;
+        if (hipMalloc(&w->d_stream_tab, 4u * tab.size()) != hipSuccess) {
+            (void)hipGetLastError();
+            w->d_stream_tab = nullptr;
+            return AP_OK;                                    // no room: the listed evaluation scores the calls
+        }
+        w->stream_tab_bytes = 4u * tab.size();
+    }
+    if (hipMemcpy(w->d_stream_tab, tab.data(), 4u * tab.size(), hipMemcpyHostToDevice) != hipSuccess) return device_error();
+    sp.req8 = w->d_req8;
+    sp.coef = reinterpret_cast<const uint4*>(w->d_stream_tab);
+    sp.tab_pair = tabled ? w->d_tab_pair : nullptr;
+    sp.kind = w->d_stream_tab + 4u * kinds.size();
+    sp.lo = sp.kind + (M + 1u);
+    sp.n_kinds = tabled ? 0u : (uint32_t)kinds.size();
+    sp.R = R; sp.M = M; sp.B = B;
+    sp.w_log2 = w_log2; sp.n_buckets = n_buckets; sp.words = words;
+    sp.slo_ttft = w->params.slo_ttft; sp.slo_tpot = w->params.slo_tpot;
+    sp.all_within = highest[0] < ap_hist_bin(sp.slo_ttft) && highest[1] < ap_hist_bin(sp.slo_tpot) ? 1u : 0u;
+    sp.penalty_bin = w->params.penalty_bin;
+    sp.penalty = w->params.penalty;
+    w->stream_params = sp;
+    w->stream_lds_bytes = off;
+    w->stream = true;
     return AP_OK;
 }
 
@@ -798,14 +962,16 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     if (latest > limit) return AP_ERR_RANGE;
     // distinct kinds of replica (coefficient sets, or types with tables), each by its first replica
     std::vector<uint32_t> kinds;
+    auto same_kind = [&](uint32_t x, uint32_t y) {
+        return tabled ? rep_type[x] == rep_type[y]
+                      : (replicas[x].prefill_base_us == replicas[y].prefill_base_us &&
+                         replicas[x].prefill_per_tok_us == replicas[y].prefill_per_tok_us &&
+                         replicas[x].decode_base_us == replicas[y].decode_base_us &&
+                         replicas[x].decode_per_kctx_us == replicas[y].decode_per_kctx_us);
+    };
     for (uint32_t m = 0; m < M; ++m) {
         bool seen = false;
-        for (uint32_t k : kinds)
-            seen = seen || (tabled ? rep_type[k] == rep_type[m]
-                                   : (replicas[k].prefill_base_us == replicas[m].prefill_base_us &&
-                                      replicas[k].prefill_per_tok_us == replicas[m].prefill_per_tok_us &&
-                                      replicas[k].decode_base_us == replicas[m].decode_base_us &&
-                                      replicas[k].decode_per_kctx_us == replicas[m].decode_per_kctx_us));
+        for (uint32_t k : kinds) seen = seen || same_kind(k, m);
         if (!seen) kinds.push_back(m);
     }
     // prefill time and time per token of request r on the kind whose first replica is k
@@ -1148,10 +1314,23 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
         }
     }
     // ---- split evaluation: replicas that differ or have windows ---------------------------
-    w->split = false;
-    if (!w->screen) {
+    w->split = w->stream = false;
+    bool tables_ready = true;
+    if (!w->screen && tabled && w->d_req8) {
+        const ap_status st = pair_tables(w, rep_type, M, tables_ready);
+        if (st != AP_OK) return st;
+    }
+    if (!w->screen && always_on && !on_device && tables_ready) {
+        std::vector<uint32_t> kind_of(M);
+        for (uint32_t m = 0; m < M; ++m)
+            for (size_t k = 0; k < kinds.size(); ++k)
+                if (same_kind(kinds[k], m)) kind_of[m] = (uint32_t)k;
+        const ap_status st = plan_stream(w, replicas, kinds, kind_of, worst_service, tabled ? rep_type : nullptr, host_cost);
+        if (st != AP_OK) return st;
+    }
+    if (!w->screen && tables_ready) {
         const ap_status st = plan_split(w, dev, replicas, kinds, worst_service, kind_sum, kind_longest, total,
-                                        tabled ? rep_type : nullptr, table_longest_prefill, table_longest_tpot);
+                                        tabled ? rep_type : nullptr, table_longest_prefill, table_longest_tpot, w->stream);
         if (st != AP_OK) return st;
     }
     w->has_model = true;
@@ -1791,6 +1970,7 @@ ap_status ap_workload_destroy(ap_workload* w) {
     if (w->d_span) ok = (hipFree(w->d_span) == hipSuccess) && ok;
     if (w->d_span_t) ok = (hipFree(w->d_span_t) == hipSuccess) && ok;
     if (w->d_pair) ok = (hipFree(w->d_pair) == hipSuccess) && ok;
+    if (w->d_stream_tab) ok = (hipFree(w->d_stream_tab) == hipSuccess) && ok;
     if (w->d_count_lo) ok = (hipFree(w->d_count_lo) == hipSuccess) && ok;
     if (w->d_nominal) ok = (hipFree(w->d_nominal) == hipSuccess) && ok;
     if (w->d_nominal_sums) ok = (hipFree(w->d_nominal_sums) == hipSuccess) && ok;

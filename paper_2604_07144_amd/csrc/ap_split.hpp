@@ -94,6 +94,10 @@ struct SplitParams {
                                                   //   x = ttft bin | e2e bin << 12 | kBinServed, y = tpot bin
     const uint2* tab_pair;                        // tabulated cost model: [T][R] {prefill time, time per token}; the kind
                                                   //   word of a replica then holds its type, SplitQueue::a type * R
+    // Set when the listed evaluation runs behind the streamed one (ap_stream.hpp): only candidates whose record in `pending`
+    // (the batch's) carries the pending mark are looked at, and none if the call has not raised its word.
+    const ap_metrics* pending;
+    const uint32_t* pending_word;
     uint32_t hist_words;                          // 3 * kBins / 2 (16-bit counts, R < 65536) or 3 * kBins
     uint32_t wide;                                // R >= 65536: two range words per replica
     uint32_t any_streamed;                        // some replica has a streamed part
@@ -106,6 +110,12 @@ struct SplitParams {
     uint32_t off_range, off_range_off, off_kind, off_coef, off_acc, off_wave, wave_bytes, w_pos, w_queue, w_list, w_same, w_tile,
         off_hist;
 };
+
+// Is candidate cb of the batch one to look at?
+__device__ __forceinline__ bool split_wanted(const SplitParams& p, uint32_t cb) { return p.pending == nullptr || is_pending(p.pending[cb]); }
+__device__ __forceinline__ bool split_nothing_pending(const SplitParams& p) {
+    return p.pending != nullptr && __hip_atomic_load(p.pending_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+}
 
 // The two cost tables of a tabulated model side by side, so that a request's prefill time and time per token come
 // with one 8-byte load.
@@ -133,6 +143,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                                                                     PendingWord flags) {
     extern __shared__ __align__(16) unsigned char lds[];
     pending_clear_next(flags);
+    if (split_nothing_pending(p)) return;
     constexpr bool kHist = kHistMode != 0u, kHist16 = kHistMode == 1u;
     uint32_t* hist = reinterpret_cast<uint32_t*>(lds + p.off_hist);          // kHist only
     uint32_t* range_of = reinterpret_cast<uint32_t*>(lds + p.off_range);
@@ -171,6 +182,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
 
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
         if (only_flagged && (p.part[cb].flags & kFlagNeedHist) == 0u) continue;     // the same word for every thread
+        if (!split_wanted(p, cb)) continue;                                         // the same record for every thread
         __syncthreads();                                                            // the last candidate's totals were read
         if (kHist)
             for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) hist[i] = 0u;
@@ -428,11 +440,12 @@ template <uint32_t kSlots, bool kBinsOut, bool kTabled>
 __global__ __launch_bounds__(kReplayListThreads) void k_replay_lists(SplitParams p, uint32_t n_cand, uint32_t which) {
     using staged_t = typename std::conditional<kTabled, uint4, uint2>::type;         // {arrival, out, prefill, tpot} or {arrival, lengths}
     __shared__ staged_t recs[kReplayTiles * kTile];
+    if (split_nothing_pending(p)) return;
     const uint32_t tid = threadIdx.x;
     const uint32_t n_blocks = (n_cand + kReplayListThreads - 1u) / kReplayListThreads;
     const uint32_t m = p.order[blockIdx.x / n_blocks];
     const uint32_t cb = (blockIdx.x % n_blocks) * kReplayListThreads + tid;
-    bool live = cb < n_cand;
+    bool live = cb < n_cand && split_wanted(p, cb);
     const bool lazy = live && (p.part[cb].flags & kFlagLazy) != 0u;
     if (which == 1u) live = lazy;
     if (which == 2u) live = live && !lazy;
@@ -564,11 +577,12 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
     uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_misc + 24);
     uint32_t* wtot = reinterpret_cast<uint32_t*>(lds + p.off_misc + 64);
     const uint32_t tid = threadIdx.x;
+    if (split_nothing_pending(sp)) return;
     // One workgroup per candidate that needs its histograms; the others are one thread's work each, so a
     // workgroup first settles a run of kThreads of them.
     for (uint32_t base = blockIdx.x * kThreads; base < n_cand; base += gridDim.x * kThreads) {
         const uint32_t cb = base + tid;
-        if (cb < n_cand) {
+        if (cb < n_cand && split_wanted(sp, cb)) {
             const SplitPartial part = sp.part[cb];
             if (part.flags & kFlagFallback) {
                 unsigned long long* dst = reinterpret_cast<unsigned long long*>(&out[c0 + cb]);
@@ -594,7 +608,7 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
     }
     for (uint32_t c = blockIdx.x; c < n_cand; c += gridDim.x) {
         const SplitPartial part = sp.part[c];                                       // the same for every thread
-        if (part.flags & (kFlagFallback | kFlagLazy)) continue;
+        if (!split_wanted(sp, c) || (part.flags & (kFlagFallback | kFlagLazy))) continue;
         const uint32_t* src = sp.hist + (size_t)c * sp.hist_words;
         const bool parked = (part.flags & kFlagNoStreamHist) == 0u;
         for (uint32_t i = tid; i < sp.hist_words; i += kThreads) hist[i] = parked ? src[i] : 0u;

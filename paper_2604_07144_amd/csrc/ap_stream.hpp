@@ -1,0 +1,256 @@
+// Scoring in one pass over the row, for replicas that are always there: nobody waits, proved by counting.
+#ifndef AP_STREAM_HPP
+#define AP_STREAM_HPP
+
+#include "ap_common.hpp"
+#include "ap_counts.hpp"
+#include "ap_screen.hpp"
+
+namespace {
+
+// ----------------------------------------------------------------------------------
+// streamed evaluation
+// ----------------------------------------------------------------------------------
+// For replicas that are available throughout but differ (or a table too small for the slot rings).  Every request is scored
+// where its id is read, as one that starts on arrival: ttft = prefill, e2e = prefill + decode on its replica's kind.  That
+// is its record in the B-slot queue too if nobody waits, which is proved as in the counting screen (ap_counts.hpp): no
+// replica gets more than B requests in the buckets lo(b) .. b, for any bucket b, where lo(b) is the first bucket with a
+// request that could still be in service when b begins, on the slowest kind.  Here a candidate belongs to one workgroup and
+// the counts of all buckets stay in LDS (a byte each, a bucket has at most 128 requests), so the windows are looked at once,
+// at the end, and buckets can be as small as two requests.
+//
+// A p99 value is the need_top-th largest of R values, so only large ones have to be told apart.  The host picks a bin
+// from[h] per metric that twice the needed number of requests reaches when the row is spread over the kinds as the replicas
+// are; values from that bin on are counted, one in fifty, instead of every request in three histograms (three LDS atomics
+// per request, time per token on a handful of addresses).  If fewer than need_top values turn out to lie there the guess was
+// too high for this row.
+//
+// A candidate that fails the proof or the guess gets the pending mark; the listed evaluation, with every request
+// listed, scores it next.
+struct StreamParams {
+    const uint2* req8;            // [R + 1] {arrival, prompt | out << 16}
+    const uint32_t* lo;           // [n_buckets] for rows that begin up to one position into their first 4-byte unit
+    const uint32_t* kind;         // [M + 1] index into coef; tabulated cost model: first table entry of the replica's type
+    const uint4* coef;            // [n_kinds] a, b, c, d
+    const uint2* tab_pair;        // tabulated cost model: [T][R] {prefill time, time per token}
+    uint32_t n_kinds;
+    uint32_t R, M, B;
+    uint32_t w_log2, n_buckets;
+    uint32_t words;               // 4-byte words of counts per bucket: a byte per replica and one for unknown ids
+    uint32_t slo_ttft, slo_tpot, all_within;
+    uint32_t from[3], least[3], n_bins[3];   // first counted bin of ttft, tpot, e2e, its lower edge, bins that can occur from there on
+    uint32_t need_top;            // R - k99 + 1
+    uint32_t penalty_bin;
+    uint64_t penalty;
+    uint32_t off_coef, off_lo, off_cnt, off_hist, off_acc;   // byte offsets into dynamic LDS
+};
+constexpr uint32_t kStreamMaxThreads = 1024;
+
+template <bool kTabled>
+__global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(StreamParams p, const uint16_t* __restrict__ assign,
+                                                                            ap_metrics* __restrict__ out, uint32_t C,
+                                                                            PendingWord flags) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    pending_clear_next(flags);
+    uint32_t* kind_of = reinterpret_cast<uint32_t*>(lds);
+    uint4* coef_of = reinterpret_cast<uint4*>(lds + p.off_coef);
+    uint16_t* lo_of = reinterpret_cast<uint16_t*>(lds + p.off_lo);
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + p.off_cnt);            // [n_buckets][words]
+    uint32_t* hist = reinterpret_cast<uint32_t*>(lds + p.off_hist);          // the three counted parts, one after the other
+    unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_acc);   // e2e, ttft, tpot
+    uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);     // latest finish, within objectives, rejected, failed, p99 bins[3]
+    const uint32_t tid = threadIdx.x, n_threads = blockDim.x, lane = tid & 63u, wv = wave_index(), n_waves = n_threads >> 6;
+    const uint32_t R = p.R, M = p.M;
+    const uint32_t hist_at[3] = {0u, p.n_bins[0], p.n_bins[0] + p.n_bins[1]};
+    const uint32_t n_hist = hist_at[2] + p.n_bins[2], n_cnt = p.n_buckets * p.words;
+    for (uint32_t i = tid; i <= M; i += n_threads) kind_of[i] = p.kind[i];
+    for (uint32_t i = tid; i < p.n_kinds; i += n_threads) coef_of[i] = p.coef[i];
+    for (uint32_t i = tid; i < p.n_buckets; i += n_threads) lo_of[i] = (uint16_t)p.lo[i];
+
+    for (uint32_t c = blockIdx.x; c < C; c += gridDim.x) {
+        for (uint32_t i = tid; i < n_cnt; i += n_threads) cnt[i] = 0u;
+        for (uint32_t i = tid; i < n_hist; i += n_threads) hist[i] = 0u;
+        if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
+        __syncthreads();
+        const uint16_t* row = assign + (size_t)c * R;
+        const uint32_t a = (uint32_t)(reinterpret_cast<uintptr_t>(row) >> 1) & 1u, n = R + a;   // positions, as in the counting screen
+        const uint32_t n_steps = (n + 127u) / 128u;
+        unsigned long long s_e2e = 0, s_ttft = 0, s_tpot = 0;
+        uint32_t t_e2e = 0, t_ttft = 0, t_tpot = 0, last_fin = 0, n_ok = 0;  // a wavefront's sums of up to four steps: 8 values below 2^28
+
+        // A lane takes two requests of every 128; the wavefronts take the steps in turn.  The next step's ids and records
+        // are requested before the current one is worked on.
+        typedef uint32_t two_records __attribute__((ext_vector_type(4), aligned(8)));
+        struct Step {
+            uint32_t ids;
+            two_records rec;
+        };
+        auto whole = [&](uint32_t s) { return (s != 0u || a == 0u) && (s + 1u) * 128u <= n; };
+        auto fetch = [&](uint32_t s) {
+            Step st;
+            const uint32_t pos = s * 128u + 2u * lane;
+            if (whole(s)) {
+                st.ids = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(row - a + pos));
+                st.rec = *reinterpret_cast<const two_records*>(p.req8 + (pos - a));
+            } else {                                                         // positions outside the row: an id no replica has, told apart below
+                const bool in0 = pos >= a && pos < n, in1 = pos + 1u < n;
+                const uint2 r0 = in0 ? p.req8[pos - a] : make_uint2(0u, 0u), r1 = in1 ? p.req8[pos + 1u - a] : make_uint2(0u, 0u);
+                st.ids = (in0 ? (uint32_t)row[pos - a] : 0u) | ((in1 ? (uint32_t)row[pos + 1u - a] : 0u) << 16);
+                st.rec = two_records{r0.x, r0.y, r1.x, r1.y};
+            }
+            return st;
+        };
+        auto score = [&](auto whole_tag, const Step& st, uint32_t s) {
+            constexpr bool kWhole = decltype(whole_tag)::value;
+            const uint32_t pos = s * 128u + 2u * lane;
+            uint32_t* mine = cnt + (pos >> p.w_log2) * p.words;              // w is even: both requests are in one bucket
+            const uint32_t id[2] = {(uint32_t)min(st.ids & 0xFFFFu, M), (uint32_t)min(st.ids >> 16, M)};
+            const uint32_t kind[2] = {kind_of[id[0]], kind_of[id[1]]};
+            const bool in[2] = {kWhole || (pos >= a && pos < n), kWhole || pos + 1u < n};
+            uint2 cost[2];
+            if (kTabled) {
+#pragma unroll
+                for (uint32_t e = 0; e < 2u; ++e) {
+                    const uint32_t r = kWhole ? pos + e - a : (in[e] ? pos + e - a : 0u);
+                    cost[e] = p.tab_pair[kind[e] + r];
+                }
+            }
+#pragma unroll
+            for (uint32_t e = 0; e < 2u; ++e) {
+                if (!kWhole && !in[e]) continue;
+                atomicAdd(&mine[id[e] >> 2], 1u << ((id[e] & 3u) * 8u));
+                const uint32_t arrival = e ? st.rec.z : st.rec.x, lens = e ? st.rec.w : st.rec.y;
+                const uint32_t prompt = lens & 0xFFFFu, len = lens >> 16;
+                uint32_t prefill, tpot;
+                if (kTabled) {
+                    prefill = cost[e].x;
+                    tpot = cost[e].y;
+                } else {
+                    const uint4 co = coef_of[kind[e]];
+                    prefill = co.x + __umul24(co.y, prompt);                 // the host keeps all factors below 2^24
+                    tpot = co.z + __umul24(co.w, (prompt + 1023u) >> 10);
+                }
+                uint32_t e2e = prefill + __umul24(len, tpot);
+                if (id[e] >= M) prefill = tpot = e2e = 0u;                   // rejected: adds nothing here
+                else last_fin = max(last_fin, arrival + e2e);
+                t_ttft += prefill;
+                t_e2e += e2e;
+                t_tpot += tpot;
+                if (p.all_within == 0u && id[e] < M) n_ok += (prefill <= p.slo_ttft && tpot <= p.slo_tpot) ? 1u : 0u;
+                if (prefill >= p.least[0] || tpot >= p.least[1] || e2e >= p.least[2]) {
+                    if (prefill >= p.least[0]) atomicAdd(&hist[hist_at[0] + min(hist_bin_u32(prefill) - p.from[0], p.n_bins[0] - 1u)], 1u);
+                    if (tpot >= p.least[1]) atomicAdd(&hist[hist_at[1] + min(hist_bin_u32(tpot) - p.from[1], p.n_bins[1] - 1u)], 1u);
+                    if (e2e >= p.least[2]) atomicAdd(&hist[hist_at[2] + min(hist_bin_u32(e2e) - p.from[2], p.n_bins[2] - 1u)], 1u);
+                }
+            }
+        };
+        if (wv < n_steps) {
+            Step next = fetch(wv);
+            uint32_t turn = 0;
+            for (uint32_t s = wv; s < n_steps; s += n_waves) {
+                const Step now = next;
+                if (s + n_waves < n_steps) next = fetch(s + n_waves);
+                if (whole(s)) score(std::true_type{}, now, s);
+                else score(std::false_type{}, now, s);
+                if ((++turn & 3u) == 0u) {
+                    s_e2e += t_e2e;
+                    s_ttft += t_ttft;
+                    s_tpot += t_tpot;
+                    t_e2e = t_ttft = t_tpot = 0u;
+                }
+            }
+            s_e2e = wave_sum_u64(s_e2e + t_e2e);
+            s_ttft = wave_sum_u64(s_ttft + t_ttft);
+            s_tpot = wave_sum_u64(s_tpot + t_tpot);
+            last_fin = wave_max_u32(last_fin);
+            if (p.all_within == 0u) n_ok = wave_sum_u32(n_ok);
+            if (lane == 0u) {
+                atomicAdd(&acc64[0], s_e2e);
+                atomicAdd(&acc64[1], s_ttft);
+                atomicAdd(&acc64[2], s_tpot);
+                atomicMax(&acc32[0], last_fin);
+                atomicAdd(&acc32[1], n_ok);
+            }
+        }
+        __syncthreads();
+
+        // The windows: a thread takes one word of the buckets (four replicas) and a share of the buckets, and keeps the
+        // window's sum as it moves.  No byte can run over: it is looked at whenever something was added, and a bucket adds
+        // at most 128 to a sum of at most 127 that has passed.
+        bool bad = false;
+        {
+            const uint32_t shares = max(1u, n_threads / p.words), per = (p.n_buckets + shares - 1u) / shares;
+            for (uint32_t job = tid; job < shares * p.words; job += n_threads) {
+                const uint32_t q = job % p.words, b0 = job / p.words * per, b1 = min(b0 + per, p.n_buckets);
+                if (b0 >= b1) continue;
+                uint32_t room = (127u - p.B) * 0x01010101u, top = 0x80808080u, unknown_shift = 32u;
+                if (4u * q + 4u > M) {                                       // the last word: byte M counts unknown ids, without a limit
+                    unknown_shift = 8u * (M - 4u * q);
+                    const uint32_t known = (1u << unknown_shift) - 1u;
+                    room &= known;
+                    top &= known;
+                }
+                uint32_t l = lo_of[b0], sum = 0, n_unknown = 0;
+                for (uint32_t b = l; b < b0; ++b) {
+                    sum += cnt[b * p.words + q];
+                    bad = bad || ((sum | (sum + room)) & top) != 0u;
+                }
+                for (uint32_t b = b0; b < b1; ++b) {
+                    for (const uint32_t lo = lo_of[b]; l < lo; ++l) sum -= cnt[l * p.words + q];
+                    const uint32_t here = cnt[b * p.words + q];
+                    sum += here;
+                    bad = bad || ((sum | (sum + room)) & top) != 0u;
+                    if (unknown_shift < 32u) n_unknown += (here >> unknown_shift) & 0xFFu;
+                }
+                if (n_unknown != 0u) atomicAdd(&acc32[2], n_unknown);
+            }
+        }
+        if (bad) acc32[3] = 1u;
+        __syncthreads();
+
+        // p99: from the top down, the rejected requests at the penalty's bin
+        const uint32_t rejected = acc32[2];
+        for (uint32_t h = wv; h < 3u; h += n_waves) {
+            const uint32_t* counts = hist + hist_at[h];
+            uint32_t above = p.penalty_bin >= p.from[h] + p.n_bins[h] ? rejected : 0u, found = kNoKey;
+            if (above >= p.need_top) found = p.penalty_bin;
+            for (uint32_t k = 0; k < p.n_bins[h] && found == kNoKey; k += kWave) {
+                const uint32_t down = k + lane, i = p.n_bins[h] - 1u - down;
+                uint32_t v = down < p.n_bins[h] ? counts[i] : 0u;
+                if (down < p.n_bins[h] && p.from[h] + i == p.penalty_bin) v += rejected;
+                const uint32_t upto = above + wave_inclusive_scan(v, lane);
+                const unsigned long long reached = __ballot(down < p.n_bins[h] && upto >= p.need_top);
+                if (reached != 0ull) found = p.from[h] + p.n_bins[h] - 1u - (k + (uint32_t)__ffsll((long long)reached) - 1u);
+                above = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+            }
+            if (lane == 0u) {
+                if (found == kNoKey) acc32[3] = 1u;                          // the row has fewer large values than the host expected
+                else acc32[4u + h] = found;
+            }
+        }
+        __syncthreads();
+        if (tid == 0u) {
+            ap_metrics mt;
+            if (acc32[3] != 0u) {
+                __builtin_memset(&mt, 0xFF, sizeof(mt));
+                pending_raise(flags);
+            } else {
+                mt.sum_e2e_us = acc64[0] + (unsigned long long)rejected * p.penalty;
+                mt.sum_ttft_us = acc64[1] + (unsigned long long)rejected * p.penalty;
+                mt.sum_tpot_us = acc64[2] + (unsigned long long)rejected * p.penalty;
+                mt.makespan_us = acc32[0];
+                mt.p99_ttft_us = hist_lower_edge(acc32[4]);
+                mt.p99_tpot_us = hist_lower_edge(acc32[5]);
+                mt.p99_e2e_us = hist_lower_edge(acc32[6]);
+                mt.slo_ok = p.all_within != 0u ? R - rejected : acc32[1];
+                mt.n_rejected = rejected;
+            }
+            out[c] = mt;
+        }
+        __syncthreads();                                                     // the totals were read
+    }
+}
+
+}  // namespace
+
+#endif  // AP_STREAM_HPP
