@@ -1787,8 +1787,21 @@ struct ap_agentic {
     AgenticParams params{};
     uint32_t lds_bytes = 0;
     uint32_t n_cu = 0;
+    uint32_t chunks = 0;              // which kernel
+    uint32_t waves = 0;               // wavefronts (candidates) per workgroup
     void* d_block = nullptr;          // one allocation behind all the tables
 };
+
+typedef void (*agentic_fn)(AgenticParams, const uint16_t*, const uint16_t*, const uint32_t*, ap_agentic_metrics*, uint32_t);
+static uint32_t agentic_chunks(uint32_t K) {
+    const uint32_t n = (K + kWave - 1u) / kWave;
+    return n <= 4u ? n : n <= 6u ? 6u : n <= 8u ? 8u : n <= 12u ? 12u : 16u;
+}
+static agentic_fn agentic_kernel(uint32_t chunks) {
+    return chunks == 1u ? k_agentic_eval<1u> : chunks == 2u ? k_agentic_eval<2u> : chunks == 3u ? k_agentic_eval<3u>
+           : chunks == 4u ? k_agentic_eval<4u> : chunks == 6u ? k_agentic_eval<6u> : chunks == 8u ? k_agentic_eval<8u>
+           : chunks == 12u ? k_agentic_eval<12u> : k_agentic_eval<16u>;
+}
 
 ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, uint32_t W, const uint32_t* wf,
                             const uint32_t* in_len, const uint32_t* out_len, const uint32_t* pred_first, const uint32_t* pred,
@@ -1881,9 +1894,53 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
     }
     for (uint32_t i = 0; i < P; ++i) { pa[i] = prefill[i].base_us; pb[i] = prefill[i].per_tok_us; }
     for (uint32_t i = 0; i < Q; ++i) { qc[i] = decode[i].base_us; qd[i] = decode[i].per_kctx_us; cap[i] = decode[i].capacity_tokens; }
-    // one block: slo (8-byte entries) first, then the 4-byte tables
-    const size_t n_words = (size_t)W + 4u * K + (K + 1u) + std::max(1u, n_pred) + 2u * P + 3u * Q;
-    const size_t bytes = 8u * (size_t)W + 4u * n_words;
+    // what every workgroup keeps in LDS, laid out as it is copied there
+    std::vector<unsigned char> blob;
+    AgenticParams& p = a->params;
+    try {
+        std::vector<uint32_t> by_arrival(W);
+        for (uint32_t w = 0; w < W; ++w) by_arrival[w] = w;
+        std::stable_sort(by_arrival.begin(), by_arrival.end(), [&](uint32_t x, uint32_t y) { return rel[x] < rel[y]; });
+        std::vector<uint16_t> order(by_arrival.begin(), by_arrival.end()), wf16(wf, wf + K), root_first(W + 1u, 0u), root;
+        for (uint32_t k = 0; k < K; ++k)
+            if (n_pred_of[k] == 0u) ++root_first[wf[k] + 1u];
+        for (uint32_t w = 0; w < W; ++w) root_first[w + 1u] = (uint16_t)(root_first[w + 1u] + root_first[w]);
+        root.assign(std::max<uint32_t>(1u, root_first[W]), 0u);
+        std::vector<uint16_t> fill(root_first.begin(), root_first.end() - 1);
+        for (uint32_t k = 0; k < K; ++k)
+            if (n_pred_of[k] == 0u) root[fill[wf[k]]++] = (uint16_t)k;
+        std::vector<uint16_t> succ16(succ.begin(), succ.begin() + std::max(1u, succ_first[K]));
+        std::vector<unsigned char> left(n_pred_of.begin(), n_pred_of.end());
+        std::vector<uint32_t> lens(2u * (size_t)K);
+        for (uint32_t k = 0; k < K; ++k) {
+            lens[2u * k] = in_len[k];
+            lens[2u * k + 1u] = out_len[k];
+        }
+        auto put = [&](const void* src, size_t n) {
+            const uint32_t at = (uint32_t)blob.size();
+            blob.resize((blob.size() + n + 15u) / 16u * 16u, 0u);
+            std::memcpy(blob.data() + at, src, n);
+            return at;
+        };
+        p.o_lens = put(lens.data(), 8u * (size_t)K);
+        p.o_arrival = put(rel.data(), 4u * (size_t)W);
+        p.o_succ_first = put(succ_first.data(), 4u * ((size_t)K + 1u));
+        p.o_wf = put(wf16.data(), 2u * (size_t)K);
+        p.o_order = put(order.data(), 2u * (size_t)W);
+        p.o_root_first = put(root_first.data(), 2u * ((size_t)W + 1u));
+        p.o_root = put(root.data(), 2u * root.size());
+        p.o_n_pred = put(left.data(), left.size());
+        p.blob_bytes = (uint32_t)blob.size();
+        const uint32_t o_succ = put(succ16.data(), 2u * succ16.size());
+        p.o_succ = succ16.size() <= kAgenticLdsSuccessors ? o_succ : 0u;      // not 0: it is never the first piece
+        if (p.o_succ != 0u) p.blob_bytes = (uint32_t)blob.size();
+        p.succ = reinterpret_cast<const uint16_t*>((size_t)o_succ);           // the device address once there is one
+    } catch (const std::bad_alloc&) {
+        delete a;
+        return AP_ERR_ALLOC;
+    }
+    // one block on the device: the blob, the objectives (8-byte entries), the instances
+    const size_t o_slo = blob.size(), o_inst = o_slo + 8u * (size_t)W, bytes = o_inst + 4u * (2u * (size_t)P + 3u * (size_t)Q);
     if (hipGetDevice(&a->device) != hipSuccess) st = AP_ERR_DEVICE;
     if (st == AP_OK && hipMalloc(&a->d_block, bytes) != hipSuccess) st = AP_ERR_ALLOC;
     int n_cu = 0, lds_cap = 0;
@@ -1892,24 +1949,19 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
         st = AP_ERR_DEVICE;
     if (st == AP_OK) {
         unsigned char* base = static_cast<unsigned char*>(a->d_block);
-        unsigned long long* d_slo = reinterpret_cast<unsigned long long*>(base);
-        uint32_t* at = reinterpret_cast<uint32_t*>(base + 8u * (size_t)W);
+        uint32_t* at = reinterpret_cast<uint32_t*>(base + o_inst);
         auto put = [&](const uint32_t* src, size_t n) {
             uint32_t* here = at;
             if (n && hipMemcpy(here, src, 4u * n, hipMemcpyHostToDevice) != hipSuccess) st = AP_ERR_DEVICE;
             at += n;
             return here;
         };
-        if (hipMemcpy(d_slo, slo_us, 8u * (size_t)W, hipMemcpyHostToDevice) != hipSuccess) st = AP_ERR_DEVICE;
-        AgenticParams& p = a->params;
-        p.slo = d_slo;
-        p.arrival = put(rel.data(), W);
-        p.wf = put(wf, K);
-        p.in_len = put(in_len, K);
-        p.out_len = put(out_len, K);
-        p.n_pred = put(n_pred_of.data(), K);
-        p.succ_first = put(succ_first.data(), K + 1u);
-        p.succ = put(succ.data(), std::max(1u, n_pred));
+        if (hipMemcpy(base, blob.data(), blob.size(), hipMemcpyHostToDevice) != hipSuccess ||
+            hipMemcpy(base + o_slo, slo_us, 8u * (size_t)W, hipMemcpyHostToDevice) != hipSuccess)
+            st = AP_ERR_DEVICE;
+        p.blob = reinterpret_cast<const uint4*>(base);
+        p.succ = reinterpret_cast<const uint16_t*>(base + reinterpret_cast<size_t>(p.succ));
+        p.slo = reinterpret_cast<const unsigned long long*>(base + o_slo);
         p.pa = put(pa.data(), P);
         p.pb = put(pb.data(), P);
         p.qc = put(qc.data(), Q);
@@ -1917,14 +1969,24 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
         p.cap = put(cap.data(), Q);
         p.penalty = penalty_permille;
         p.W = W; p.K = K; p.P = P; p.Q = Q;
-        // per wavefront: key u32[max(K, 2W)] (later ratio u64[W]) | tev u32[K] | comp u32[W] | used u32[Q] | ids u16[2K] |
-        // phase, left u8[K] each | busy u8[P] | failed u8[W]
-        const uint32_t wave_bytes = align_up(4u * (std::max(K, 2u * W) + K + W + Q) + 2u * 2u * K + 2u * K + P + W, 16u);
-        p.wave_bytes = wave_bytes;
-        a->lds_bytes = wave_bytes * kAgenticWaves;
+        a->chunks = agentic_chunks(K);
+        uint32_t off = align_up(std::max(8u * W, 4u * K), 16u);
+        p.o_over = 0u;
+        p.o_call = off;   off += align_up(2u * K, 16u);
+        p.o_rank = off;   off += align_up(2u * K, 16u);
+        p.o_ids = off;    off += align_up(2u * K, 16u);
+        p.o_left = off;   off += align_up(K, 16u);
+        p.o_comp = off;   off += align_up(4u * W, 16u);
+        p.o_failed = off; off += align_up(W, 16u);
+        p.o_over_phase = off; off += align_up(K, 16u);
+        p.o_queue = off;  off += (P + Q) * 2u * a->chunks * 4u;
+        p.wave_bytes = align_up(off, 16u);
+        a->waves = kAgenticWaves;
+        while (a->waves > 1u && p.blob_bytes + a->waves * p.wave_bytes > (uint32_t)lds_cap) a->waves /= 2u;
+        a->lds_bytes = p.blob_bytes + a->waves * p.wave_bytes;
         a->n_cu = (uint32_t)n_cu;
         if (a->lds_bytes > (uint32_t)lds_cap) st = AP_ERR_RANGE;
-        else if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_agentic_eval), hipFuncAttributeMaxDynamicSharedMemorySize,
+        else if (hipFuncSetAttribute(reinterpret_cast<const void*>(agentic_kernel(a->chunks)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)a->lds_bytes) != hipSuccess)
             st = AP_ERR_DEVICE;
     }
@@ -1942,9 +2004,9 @@ ap_status ap_agentic_eval(const ap_agentic* a, const uint16_t* d_prefill, const 
     if (!a) return AP_ERR_INVALID;
     if (C == 0) return AP_OK;
     if (!d_prefill || !d_decode || !d_key || !d_out) return AP_ERR_INVALID;
-    const uint32_t blocks = std::min((C + kAgenticWaves - 1u) / kAgenticWaves, a->n_cu * 64u);
-    hipLaunchKernelGGL(k_agentic_eval, dim3(blocks), dim3(kAgenticThreads), a->lds_bytes, static_cast<hipStream_t>(hip_stream),
-                       a->params, d_prefill, d_decode, d_key, d_out, C);
+    const uint32_t blocks = std::min((C + a->waves - 1u) / a->waves, a->n_cu * 64u);
+    hipLaunchKernelGGL(agentic_kernel(a->chunks), dim3(blocks), dim3(a->waves * kWave), a->lds_bytes,
+                       static_cast<hipStream_t>(hip_stream), a->params, d_prefill, d_decode, d_key, d_out, C);
     if (hipGetLastError() != hipSuccess) return device_error();
     return AP_OK;
 }
