@@ -101,6 +101,18 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return v;
 }
 
+// The maximum over the lanes, as a uniform value, on the vector ALU's cross-lane path: inside each row of 16 lanes, the last
+// lane of rows 0 and 2 into rows 1 and 3, then lane 31 into rows 2 and 3; lane 63 has it.
+__device__ __forceinline__ uint32_t wave_all_max(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111 /* row_shr:1 */, 0xF, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112 /* row_shr:2 */, 0xF, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114 /* row_shr:4 */, 0xF, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118 /* row_shr:8 */, 0xF, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142 /* row_bcast:15 */, 0xA, 0xF, false));
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xC, 0xF, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
 #pragma unroll
     for (uint32_t d = 32; d >= 1; d >>= 1) v += (unsigned long long)__shfl_xor((long long)v, d);
@@ -210,7 +222,8 @@ __device__ __forceinline__ void hist_clear(uint32_t* hist) {
 
 // Block-wide end of one candidate: fold the per-lane sums, add the rejected requests at the
 // penalty value, find the three p99 bins by a prefix sum over the histograms and write the
-// record.  Called by all kThreads threads; `hist` holds the served requests' counts.
+// record.  Called by all kThreads threads; `hist` holds the served requests' counts (those that are known to
+// lie below the p99 value of their metric may be missing).
 template <bool kHist16>
 __device__ __forceinline__ void finish_candidate(const EvalParams& p, uint32_t* hist, unsigned long long* acc64,
                                                  uint32_t* acc32, uint32_t* wtot, unsigned long long s_e2e,
@@ -251,8 +264,8 @@ __device__ __forceinline__ void finish_candidate(const EvalParams& p, uint32_t* 
     __syncthreads();
 #pragma unroll
     for (uint32_t h = 0; h < 3u; ++h) {
-        uint32_t before = 0;
-        for (uint32_t ww = 0; ww < w; ++ww) before += wtot[h * kWaves + ww];
+        uint32_t before = p.R;                       // requests that were not counted come first: they lie below every p99 value
+        for (uint32_t ww = 0; ww < kWaves; ++ww) before -= ww < w ? 0u : wtot[h * kWaves + ww];
         const uint32_t hi = before + incl[h], lo = hi - part[h];
         if (lo < p.k99 && p.k99 <= hi) {
             uint32_t run = lo, b = 0;

@@ -108,6 +108,19 @@ struct RoofBuffers {
 };
 }  // namespace
 
+// One plan of the listed / streamed evaluation.
+struct SplitPlan {
+    bool short_chain = false;         // calls of few rows are left to the fused replay
+    uint32_t lds_bytes_list = 0;      // k_list_candidates
+    bool expect_lazy = false;         // stream without histograms first
+    uint32_t batch = 0;               // candidates per batch (what the scratch area holds)
+    uint32_t lds_bytes = 0, lds_bytes_hist = 0;
+    unsigned char* tables = nullptr;  // ranges, kinds, coefficients, queues, order
+    size_t tables_bytes = 0;
+    size_t o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0, scratch_bytes = 0;   // where its parts lie in the scratch area
+    SplitParams params{};
+};
+
 struct ap_workload {
     int device = 0;
     uint32_t R = 0;
@@ -160,6 +173,7 @@ struct ap_workload {
     ReduceParams reduce_params{};
     EvalParams reduce_eval{};
     uint32_t group_lds_bytes = 0, replay_lds_bytes = 0, reduce_lds_bytes = 0;
+    bool small_table = false;         // identical replicas, but too few and too small for the slot rings
     bool pipeline = false;
     // sparse candidates (ap_parent_set / ap_eval_children)
     uint16_t* d_parent = nullptr;     // [R]
@@ -181,17 +195,10 @@ struct ap_workload {
     uint2* d_req8 = nullptr;          // [R] {arrival, prompt | out << 16}; only when every length is below 65536
     uint2* d_tab_pair = nullptr;      // [T][R] the cost tables side by side, for the split evaluation of a tabulated model
     size_t tab_pair_entries = 0;
-    uint32_t* d_split_tab = nullptr;       // range and kind words [2][AP_MAX_REPLICAS + 1], then the coefficients of every kind
-    SplitQueue* d_split_queue = nullptr;   // [AP_MAX_REPLICAS]
-    uint32_t* d_split_order = nullptr;     // [AP_MAX_REPLICAS]
     unsigned char* d_split_scratch = nullptr;
     size_t split_scratch_bytes = 0;
     bool split = false;               // the split evaluation runs in front of the general replay
-    bool split_expect_lazy = false;   // stream without histograms first
-    uint32_t split_batch = 0;         // candidates per batch (what the scratch area holds)
-    uint32_t split_lds_bytes = 0, split_lds_bytes_hist = 0;
-    uint32_t split_slots = 0;         // B rounded up to 8, 16, 32 or 64
-    SplitParams split_params{};
+    SplitPlan split_plan{};
 };
 
 typedef void (*split_fn)(SplitParams, const uint16_t*, uint32_t, uint32_t, uint32_t, PendingWord);
@@ -205,14 +212,11 @@ static split_fn split_kernel(uint32_t hist_mode, int narrow, bool tabled) {
 }
 
 typedef void (*replay_lists_fn)(SplitParams, uint32_t, uint32_t);
-template <bool kBinsOut, bool kTabled>
-static replay_lists_fn replay_lists_kernel_of(uint32_t slots) {
-    return slots == 8u ? k_replay_lists<8u, kBinsOut, kTabled> : slots == 16u ? k_replay_lists<16u, kBinsOut, kTabled>
-           : slots == 32u ? k_replay_lists<32u, kBinsOut, kTabled> : k_replay_lists<64u, kBinsOut, kTabled>;
-}
-static replay_lists_fn replay_lists_kernel(uint32_t slots, bool bins_out, bool tabled) {
-    if (tabled) return bins_out ? replay_lists_kernel_of<true, true>(slots) : replay_lists_kernel_of<false, true>(slots);
-    return bins_out ? replay_lists_kernel_of<true, false>(slots) : replay_lists_kernel_of<false, false>(slots);
+template <uint32_t kBins_>
+static replay_lists_fn replay_lists_kernel_of(uint32_t B) {
+    return B <= 8u ? k_replay_lists<8u, kBins_> : B <= 12u ? k_replay_lists<12u, kBins_> : B <= 16u ? k_replay_lists<16u, kBins_>
+           : B <= 24u ? k_replay_lists<24u, kBins_> : B <= 32u ? k_replay_lists<32u, kBins_>
+           : B <= 48u ? k_replay_lists<48u, kBins_> : k_replay_lists<64u, kBins_>;
 }
 
 // The dense path on C rows: screening where it applies, then the exact replay of what is left.
@@ -249,14 +253,19 @@ static ap_status launch_counts(const ap_workload* w, const uint16_t* d_assign, u
 
 // The listed / streamed evaluation, a batch of candidates at a time; what it hands back carries the pending mark.
 // pending: only candidates that carry the pending mark already (behind the streamed evaluation).
-static ap_status launch_split(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out, hipStream_t stream,
-                              PendingWord flags, bool pending) {
-    SplitParams sp = w->split_params;
-    const replay_lists_fn replay_lean = replay_lists_kernel(w->split_slots, false, w->tabled);
-    const replay_lists_fn replay_bins = replay_lists_kernel(w->split_slots, true, w->tabled);
+static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out,
+                              hipStream_t stream, PendingWord flags, bool pending) {
+    SplitParams sp = plan.params;
+    sp.lists = reinterpret_cast<uint16_t*>(w->d_split_scratch + plan.o_lists);
+    sp.bins = w->d_split_scratch + plan.o_bins;
+    sp.desc = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_desc);
+    sp.part = reinterpret_cast<SplitPartial*>(w->d_split_scratch + plan.o_part);
+    sp.hist = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_hist);
+    const replay_lists_fn replay_lean = replay_lists_kernel_of<0u>(sp.B);
+    const replay_lists_fn replay_bins = sp.wide_bins ? replay_lists_kernel_of<2u>(sp.B) : replay_lists_kernel_of<1u>(sp.B);
     // batches of equal size (whole wavefronts of the list replay), none above what the scratch area holds
-    const uint32_t n_batches = (C + w->split_batch - 1u) / w->split_batch;
-    const uint32_t per_batch = std::min(w->split_batch, ((C + n_batches - 1u) / n_batches + 63u) / 64u * 64u);
+    const uint32_t n_batches = (C + plan.batch - 1u) / plan.batch;
+    const uint32_t per_batch = std::min(plan.batch, ((C + n_batches - 1u) / n_batches + 63u) / 64u * 64u);
     for (uint32_t c0 = 0; c0 < C; c0 += per_batch) {
         const uint32_t n = std::min(per_batch, C - c0);
         if (pending) {
@@ -264,28 +273,29 @@ static ap_status launch_split(const ap_workload* w, const uint16_t* d_assign, ui
             sp.pending_word = flags.mine;
         }
         const uint32_t grid = std::min(n, w->n_cu * 16u);
-        // First without histograms where the candidates are expected to be settled by penalty, or where nothing is
-        // streamed at all; then with histograms, for every candidate or for those the first pass marked.
+        // Where something is streamed: first without histograms if the candidates are expected to be settled by penalty; then
+        // with histograms, for every candidate or for those the first pass marked.
         const int narrow = sp.M <= 64u ? 1 : 0;
-        const bool plain_first = w->split_expect_lazy || sp.any_streamed == 0u;
-        if (plain_first)
-            hipLaunchKernelGGL(split_kernel(0u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads), w->split_lds_bytes, stream, sp,
-                               d_assign, c0, n, 0u, flags);
-        if (sp.any_streamed != 0u)
-            hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads),
-                               w->split_lds_bytes_hist, stream, sp, d_assign, c0, n, plain_first ? 1u : 0u, flags);
-        // the list replay: where most candidates are settled by penalty, those go through the variant that
-        // leaves no bins, and the wavefronts of the other variant find the few that remain
+        const bool plain_first = plan.expect_lazy;
+        if (sp.any_streamed == 0u)
+            hipLaunchKernelGGL(k_list_candidates, dim3(grid), dim3(kSplitThreads), plan.lds_bytes_list, stream, sp, d_assign, c0, n, flags);
+        else if (plain_first)
+            hipLaunchKernelGGL(split_kernel(0u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads), plan.lds_bytes, stream,
+                               sp, d_assign, c0, n, 0u, flags);
+        if (sp.any_streamed != 0u)              // (behind a plain pass: usually nothing to do, so few workgroups)
+            hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, narrow, w->tabled),
+                               dim3(plain_first ? std::min(n, w->n_cu * 3u) : grid), dim3(kSplitThreads),
+                               plan.lds_bytes_hist, stream, sp, d_assign, c0, n, plain_first ? 1u : 0u, flags);
+        // the list replay: where most candidates are settled by penalty, those go through the variant that leaves no bins, and
+        // the wavefronts of the other variant find the few that remain
         if (sp.n_queues != 0u) {
-            const dim3 groups(sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads));
-            if (w->split_expect_lazy)
-                hipLaunchKernelGGL(replay_lean, groups, dim3(kReplayListThreads), 0, stream, sp, n, 1u);
-            hipLaunchKernelGGL(replay_bins, groups, dim3(kReplayListThreads), 0, stream, sp, n,
-                               w->split_expect_lazy ? 2u : 0u);
+            const uint32_t groups = sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads);
+            const bool lean = plan.expect_lazy;
+            if (lean) hipLaunchKernelGGL(replay_lean, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, 1u);
+            hipLaunchKernelGGL(replay_bins, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, lean ? 2u : 0u);
         }
-        hipLaunchKernelGGL(sp.wide ? k_merge_candidates<false> : k_merge_candidates<true>,
-                           dim3(std::min(n, w->n_cu * 8u)), dim3(kThreads), w->reduce_lds_bytes,
-                           stream, w->reduce_eval, sp, d_out, c0, n, flags);
+        hipLaunchKernelGGL(sp.wide ? k_merge_candidates<false> : k_merge_candidates<true>, dim3(std::min(n, w->n_cu * 8u)),
+                           dim3(kThreads), w->reduce_lds_bytes, stream, w->reduce_eval, sp, d_out, c0, n, flags);
     }
     return hipGetLastError() == hipSuccess ? AP_OK : device_error();
 }
@@ -340,18 +350,19 @@ static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, ui
         }
         if (hipGetLastError() != hipSuccess) return device_error();
     }
+    const bool fused = w->split && !marked && w->split_plan.short_chain && C <= w->n_cu * 2u;
     bool split_behind = false;
     if (w->stream && !marked) {
         const ap_status st = launch_stream(w, d_assign, C, d_out, stream, flags);
         if (st != AP_OK) return st;
         split_behind = true;
     }
-    if (w->split && !marked) {
-        const ap_status st = launch_split(w, d_assign, C, d_out, stream, flags, split_behind);
+    if (w->split && !marked && !fused) {
+        const ap_status st = launch_split(w, w->split_plan, d_assign, C, d_out, stream, flags, split_behind);
         if (st != AP_OK) return st;
-        if (split_behind) return AP_OK;                      // with every request listed nothing is handed back
+        if (split_behind || w->split_plan.params.any_streamed == 0u) return AP_OK;   // with every request listed nothing is handed back
     }
-    const uint32_t pending_only = (w->screen || ((w->split || w->stream) && !marked)) ? 1u : 0u;
+    const uint32_t pending_only = (w->screen || split_behind || (w->split && !marked && !fused)) ? 1u : 0u;
     if (w->pipeline) {
         for (uint32_t c0 = 0; c0 < C; c0 += w->batch) {
             const uint32_t n = std::min(w->batch, C - c0);
@@ -510,18 +521,43 @@ static ap_status pair_tables(ap_workload* w, const uint32_t* rep_type, uint32_t 
     return AP_OK;
 }
 
+// For every multiple k of `grain`: the first request still in service, nobody waiting, when request k * grain - shift (0 if
+// that is negative) arrives.  It only moves forward.
+static std::vector<uint32_t> first_in_service(const ap_workload* w, const std::vector<uint32_t>& worst_service, uint32_t grain,
+                                              uint32_t shift) {
+    std::vector<uint32_t> first((w->R + shift) / grain + 1u);
+    const uint32_t* arr = w->h_arrival.data();
+    for (uint32_t k = 0, q = 0; k < first.size(); ++k) {
+        const uint32_t i = std::min(w->R - 1u, k * grain < shift ? 0u : k * grain - shift);
+        while (q < i && (uint64_t)arr[q] + worst_service[q] <= arr[i]) ++q;
+        first[k] = q;
+    }
+    return first;
+}
+
+// Is a row that is spread evenly over the replicas all but sure to have at most B requests per replica in every one of
+// n_windows windows of `window` requests?  Chernoff's bound on a Poisson count: one chance in 10^7 per row, because a single
+// row that fails makes its call wait for the serial replay of the row's queues.
+static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_windows) {
+    const double mean = window / M, most = (double)B + 1.0;
+    return most > mean && most - mean - most * std::log(most / mean) + std::log((double)M * n_windows) <= -16.0;
+}
+
 // Plan of the split evaluation (ap_split.hpp) - replicas that differ or have windows, crowded traces, tables too
 // small for the one-wavefront screen; linear cost models (rep_type == nullptr) and tabulated ones:
 // the index ranges of every replica, the bound D on requests in service that started on arrival, the
 // scratch area for one batch of candidates.  Leaves w->split false where the path does not apply.
-// list_all: no streamed part at all (the evaluation runs behind the streamed one, on what that has left).
+// least_bin: per metric a bin that at least R - k99 + 1 requests reach on whichever kind of replica, without waiting.
+// list_all: no streamed part at all (the evaluation runs behind the streamed one, on what that has left).  applies: the plan
+// can be used.
 // rep_type: the tabulated cost model (replica m reads row rep_type[m] of the tables, which are on the device by
 // now); table_longest_prefill / table_longest_tpot are then the largest entries of the rows in use.
-static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, const ap_replica* replicas,
+static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool list_all, bool& applies, const std::vector<DevReplica>& dev, const ap_replica* replicas,
                             const std::vector<uint32_t>& kinds, const std::vector<uint32_t>& worst_service,
                             const std::vector<uint64_t>& kind_sum, const std::vector<uint64_t>& kind_longest,
                             uint64_t latest_finish_bound, const uint32_t* rep_type, uint64_t table_longest_prefill,
-                            uint64_t table_longest_tpot, bool list_all) {
+                            uint64_t table_longest_tpot, const uint32_t* least_bin) {
+    applies = false;
     const uint32_t R = w->R, M = w->params.M, B = w->params.B;
     if (!w->d_req8) return AP_OK;                            // request records with 16-bit lengths only
     const bool tabled = rep_type != nullptr;
@@ -635,6 +671,12 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
     const bool penalty_on_top = w->params.penalty_bin > ap_hist_bin(latest_finish_bound);
     sp.lazy_from = penalty_on_top ? R - w->params.k99 + 1u : kNever;
     sp.all_within = (longest_prefill <= w->params.slo_ttft && longest_tpot <= w->params.slo_tpot) ? 1u : 0u;
+    sp.tpot_within = longest_tpot <= w->params.slo_tpot ? 1u : 0u;
+    for (uint32_t h = 0; h < 3u; ++h) {
+        sp.least_bin[h] = std::min(least_bin[h], w->params.penalty_bin);
+        sp.least_us[h] = (uint32_t)std::min<uint64_t>(ap_hist_lower(sp.least_bin[h]), kNever);
+    }
+    sp.wide_bins = ap_hist_bin(longest_tpot) >= sp.least_bin[1] + kTpotSpan ? 1u : 0u;
     sp.wide = wide ? 1u : 0u;
     sp.any_streamed = any_streamed ? 1u : 0u;
     sp.hist_words = wide ? 3u * kBins : 3u * kBins / 2u;
@@ -657,36 +699,42 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
     sp.wave_bytes = wb;
     off += kSplitWaves * wb;
     sp.off_hist = off;
+    sp.l_wave = sp.off_wave;
+    sp.l_list = align_up((M + 1u) * 4u, 16u);
+    sp.l_wave_bytes = sp.l_list + align_up(sp.tile_cap * 2u, 16u);
+    plan.lds_bytes_list = sp.l_wave + kSplitWaves * sp.l_wave_bytes;
     int lds_cap = 0;
     if (hipDeviceGetAttribute(&lds_cap, hipDeviceAttributeMaxSharedMemoryPerBlock, w->device) != hipSuccess) return device_error();
     if (off + hist_bytes > (uint32_t)lds_cap) return AP_OK;  // a replica table that large stays with the general replay
-    w->split_lds_bytes = off;
-    w->split_lds_bytes_hist = off + hist_bytes;
+    plan.lds_bytes = off;
+    plan.lds_bytes_hist = off + hist_bytes;
     const int narrow = M <= 64u ? 1 : 0;
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled)),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_list_candidates), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)plan.lds_bytes_list) != hipSuccess ||
+        hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled)),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)off) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled)),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(off + hist_bytes)) != hipSuccess) {
         (void)hipGetLastError();
         return device_error();
     }
-    w->split_slots = B <= 8u ? 8u : B <= 16u ? 16u : B <= 32u ? 32u : 64u;
 
     // scratch for one batch of candidates: lists, run descriptors, partial records, histograms
-    const size_t per_cand = (size_t)sp.n_list_tiles * sp.tile_cap * (2u + 8u) + (size_t)sp.n_list_tiles * (M + 1u) * 4u +
+    const size_t bins_bytes = sp.wide_bins ? 8u : 4u;
+    const size_t per_cand = (size_t)sp.n_list_tiles * sp.tile_cap * (2u + bins_bytes) + (size_t)sp.n_list_tiles * (M + 1u) * 4u +
                             sizeof(SplitPartial) + hist_bytes;
     if (per_cand > ((size_t)8 << 30) / 64u) return AP_OK;       // a trace so long that 64 candidates' lists take over 8 GiB
     uint32_t batch = (uint32_t)std::min<size_t>(16384u, std::max<size_t>(64u, ((size_t)4 << 30) / per_cand));
     batch = batch / 64u * 64u;
     auto carve = [](size_t& at, size_t bytes) { const size_t here = at; at = (at + bytes + 255u) / 256u * 256u; return here; };
-    size_t total = 0, o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0;
+    size_t total = 0;
     for (;; batch = std::max(64u, batch / 2u / 64u * 64u)) {        // a device short of memory gets smaller batches
         total = 0;
-        o_lists = carve(total, (size_t)batch * sp.n_list_tiles * sp.tile_cap * 2u);
-        o_bins = carve(total, (size_t)batch * sp.n_list_tiles * sp.tile_cap * 8u);
-        o_desc = carve(total, (size_t)batch * sp.n_list_tiles * (M + 1u) * 4u);
-        o_part = carve(total, (size_t)batch * sizeof(SplitPartial));
-        o_hist = carve(total, (size_t)batch * hist_bytes);
+        plan.o_lists = carve(total, (size_t)batch * sp.n_list_tiles * sp.tile_cap * 2u);
+        plan.o_bins = carve(total, (size_t)batch * sp.n_list_tiles * sp.tile_cap * bins_bytes);
+        plan.o_desc = carve(total, (size_t)batch * sp.n_list_tiles * (M + 1u) * 4u);
+        plan.o_part = carve(total, (size_t)batch * sizeof(SplitPartial));
+        plan.o_hist = carve(total, (size_t)batch * hist_bytes);
         if (total <= w->split_scratch_bytes) break;
         if (w->d_split_scratch && hipFree(w->d_split_scratch) != hipSuccess) return device_error();
         w->d_split_scratch = nullptr;
@@ -699,65 +747,62 @@ static ap_status plan_split(ap_workload* w, const std::vector<DevReplica>& dev, 
         w->d_split_scratch = nullptr;
         if (batch == 64u) return AP_OK;                         // no room for the lists: the general replay scores the calls
     }
-    const size_t tab_bytes = 4u * (3u * (AP_MAX_REPLICAS + 1u) + 4u * (size_t)AP_MAX_REPLICAS + 4u);
-    if ((!w->d_split_tab && hipMalloc(&w->d_split_tab, tab_bytes) != hipSuccess) ||
-        (!w->d_split_queue && hipMalloc(&w->d_split_queue, sizeof(SplitQueue) * AP_MAX_REPLICAS) != hipSuccess) ||
-        (!w->d_split_order && hipMalloc(&w->d_split_order, sizeof(uint32_t) * AP_MAX_REPLICAS) != hipSuccess)) {
-        (void)hipGetLastError();
-        return AP_ERR_ALLOC;
+    plan.scratch_bytes = total;
+    // the tables in one buffer: coefficients at a multiple of 16 bytes, like the queues
+    std::vector<uint32_t> words(tab.size() + 4u + 12u * (size_t)M + order.size() + 16u, 0u);
+    size_t at = 0;
+    auto put = [&](const void* src, size_t n_words) {
+        at = (at + 3u) / 4u * 4u;
+        const size_t here = at;
+        if (n_words) std::memcpy(&words[here], src, 4u * n_words);
+        at += n_words;
+        return here;
+    };
+    const size_t n_ranges = 3u * (AP_MAX_REPLICAS + 1u);
+    const size_t o_tab = put(tab.data(), n_ranges), o_coef = put(tab.data() + n_ranges, tab.size() - n_ranges);
+    const size_t o_queue = put(queue.data(), sizeof(SplitQueue) / 4u * M), o_order = put(order.data(), order.size());
+    if (4u * words.size() > plan.tables_bytes) {
+        if (plan.tables && hipFree(plan.tables) != hipSuccess) return device_error();
+        plan.tables = nullptr;
+        plan.tables_bytes = 0;
+        if (hipMalloc(&plan.tables, 4u * words.size()) != hipSuccess) {
+            (void)hipGetLastError();
+            plan.tables = nullptr;
+            return AP_ERR_ALLOC;
+        }
+        plan.tables_bytes = 4u * words.size();
     }
-    if (hipMemcpy(w->d_split_tab, tab.data(), 4u * tab.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(w->d_split_queue, queue.data(), sizeof(SplitQueue) * M, hipMemcpyHostToDevice) != hipSuccess ||
-        (!order.empty() &&
-         hipMemcpy(w->d_split_order, order.data(), sizeof(uint32_t) * order.size(), hipMemcpyHostToDevice) != hipSuccess) ||
+    if (hipMemcpy(plan.tables, words.data(), 4u * words.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipFuncSetAttribute(wide ? reinterpret_cast<const void*>(&k_merge_candidates<false>)
                                  : reinterpret_cast<const void*>(&k_merge_candidates<true>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)w->reduce_lds_bytes) != hipSuccess) {
         (void)hipGetLastError();
         return device_error();
     }
+    const uint32_t* base = reinterpret_cast<const uint32_t*>(plan.tables);
     sp.req8 = w->d_req8;
-    sp.tab.range = w->d_split_tab;
-    sp.tab.range_off = w->d_split_tab + (AP_MAX_REPLICAS + 1u);
-    sp.tab.kind = w->d_split_tab + 2u * (AP_MAX_REPLICAS + 1u);
-    sp.tab.coef = reinterpret_cast<const uint4*>(w->d_split_tab + 3u * (AP_MAX_REPLICAS + 1u));
+    sp.tab.range = base + o_tab;
+    sp.tab.range_off = base + o_tab + (AP_MAX_REPLICAS + 1u);
+    sp.tab.kind = base + o_tab + 2u * (AP_MAX_REPLICAS + 1u);
+    sp.tab.coef = reinterpret_cast<const uint4*>(base + o_coef);
     sp.tab.n_kinds = tabled ? 0u : (uint32_t)kinds.size();
     sp.tab_pair = tabled ? w->d_tab_pair : nullptr;
-    sp.queue = w->d_split_queue;
-    sp.order = w->d_split_order;
-    sp.lists = reinterpret_cast<uint16_t*>(w->d_split_scratch + o_lists);
-    sp.bins = reinterpret_cast<uint2*>(w->d_split_scratch + o_bins);
-    sp.desc = reinterpret_cast<uint32_t*>(w->d_split_scratch + o_desc);
-    sp.part = reinterpret_cast<SplitPartial*>(w->d_split_scratch + o_part);
-    sp.hist = reinterpret_cast<uint32_t*>(w->d_split_scratch + o_hist);
-    w->split_params = sp;
-    w->split_batch = batch;
+    sp.queue = reinterpret_cast<const SplitQueue*>(base + o_queue);
+    sp.order = base + o_order;
+    plan.params = sp;
+    plan.batch = batch;
+    // A small call - few rows, and the fused replay's wavefront per queue has little more to do than a lane of the list replay -
+    // is left to the fused replay: one launch instead of three.  It takes 65 ns a request and works on four queues of a row at a
+    // time (12 us + R * 0.016 us a row); the list replay takes 115 ns a request of the longest list while the chip is nearly
+    // empty, and its launches 25 us together.
+    // 64 rows of 256 requests on 4 replicas: 14.4 against 20 us; 65 rows of 16384 on 4, most of them on one: 278 against 1100 us.
+    // The lists count only for tables that are too small for the screen: with windows the longest list says little about the
+    // others, and a crowded trace is reported as listed (ap_eval_counts_get) whatever the number of its rows.
+    plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull);
     // stream without histograms first when an even spread of the requests over the replicas would reject enough
-    w->split_expect_lazy = penalty_on_top && expect_rejected / M >= sp.lazy_from;
-    w->split = true;
+    plan.expect_lazy = penalty_on_top && expect_rejected / M >= sp.lazy_from;
+    applies = true;
     return AP_OK;
-}
-
-// For every multiple k of `grain`: the first request still in service, nobody waiting, when request k * grain - shift (0 if
-// that is negative) arrives.  It only moves forward.
-static std::vector<uint32_t> first_in_service(const ap_workload* w, const std::vector<uint32_t>& worst_service, uint32_t grain,
-                                              uint32_t shift) {
-    std::vector<uint32_t> first((w->R + shift) / grain + 1u);
-    const uint32_t* arr = w->h_arrival.data();
-    for (uint32_t k = 0, q = 0; k < first.size(); ++k) {
-        const uint32_t i = std::min(w->R - 1u, k * grain < shift ? 0u : k * grain - shift);
-        while (q < i && (uint64_t)arr[q] + worst_service[q] <= arr[i]) ++q;
-        first[k] = q;
-    }
-    return first;
-}
-
-// Is a row that is spread evenly over the replicas all but sure to have at most B requests per replica in every one of
-// n_windows windows of `window` requests?  Chernoff's bound on a Poisson count: one chance in 10^7 per row, because a single
-// row that fails makes its call wait for the serial replay of the row's queues.
-static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_windows) {
-    const double mean = window / M, most = (double)B + 1.0;
-    return most > mean && most - mean - most * std::log(most / mean) + std::log((double)M * n_windows) <= -16.0;
 }
 
 // Plan of the counting screen (ap_counts.hpp): the bucket size and, per bucket, the first bucket with a request that is
@@ -795,6 +840,36 @@ static ap_status plan_counts(ap_workload* w, const std::vector<uint32_t>& worst_
         return AP_OK;
     }
     return AP_OK;
+}
+
+// ap_hist_bin for values below 2^32, without its loop: the plans take it several times per request.
+static uint32_t bin_of(uint64_t value) {
+    const uint32_t v = (uint32_t)std::min<uint64_t>(value, kNever), s = 24u - std::min(v ? (uint32_t)__builtin_clz(v) : 32u, 24u);
+    return (s << 7) + (v >> s);
+}
+
+// Per metric (ttft, tpot, e2e) the highest bin that at least R - k99 + 1 requests reach on their cheapest kind of replica
+// without waiting: no candidate's p99 value of served requests lies below it.
+extern "C++" template <typename Cost>
+static void least_bins(uint32_t R, uint32_t k99, const std::vector<uint32_t>& kinds, const Cost& cost, const std::vector<int32_t>& out_len,
+                       uint32_t (&least)[3]) {
+    std::vector<uint32_t> count(3u * kBins, 0u);
+    for (uint32_t r = 0; r < R; ++r) {
+        uint64_t low[3] = {UINT64_MAX, UINT64_MAX, UINT64_MAX};
+        for (uint32_t k : kinds) {
+            uint64_t prefill, tpot;
+            cost(k, r, prefill, tpot);
+            low[0] = std::min(low[0], prefill);
+            low[1] = std::min(low[1], tpot);
+            low[2] = std::min(low[2], prefill + (uint64_t)out_len[r] * tpot);
+        }
+        for (uint32_t h = 0; h < 3u; ++h) ++count[h * kBins + bin_of(low[h])];
+    }
+    for (uint32_t h = 0; h < 3u; ++h) {
+        uint32_t bin = kBins, reached = 0;
+        while (bin > 0u && reached < R - k99 + 1u) reached += count[h * kBins + --bin];
+        least[h] = bin;
+    }
 }
 
 // Plan of the streamed evaluation (ap_stream.hpp): bucket size, window table, the bins from which large values are counted.
@@ -838,9 +913,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
             if (tabled && tpot >= (1u << 24)) return AP_OK;
             const uint64_t value[3] = {prefill, tpot, prefill + (uint64_t)w->h_out[r] * tpot};
             for (uint32_t h = 0; h < 3u; ++h) {
-                // ap_hist_bin for values below 2^32, without its loop: this runs three times per request and kind
-                const uint32_t v = (uint32_t)std::min<uint64_t>(value[h], kNever), s = 24u - std::min(v ? (uint32_t)__builtin_clz(v) : 32u, 24u);
-                const uint32_t bin = (s << 7) + (v >> s);
+                const uint32_t bin = bin_of(value[h]);
                 weight[h * kBins + bin] += share[k];
                 highest[h] = std::max(highest[h], bin);
             }
@@ -1264,7 +1337,8 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     {
         bool wide = false;
         const uint32_t S_log2 = narrow_ring_slots_log2(M, B, wide);
-        if (w->screen && !w->counts && !wide && 128u >= M * (1u << S_log2) && w->d_req8) w->screen = false;
+        w->small_table = w->screen && !w->counts && !wide && 128u >= M * (1u << S_log2) && w->d_req8;
+        if (w->small_table) w->screen = false;
     }
     if (w->screen) {
         ScreenParams sp{};
@@ -1329,8 +1403,10 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
         if (st != AP_OK) return st;
     }
     if (!w->screen && tables_ready) {
-        const ap_status st = plan_split(w, dev, replicas, kinds, worst_service, kind_sum, kind_longest, total,
-                                        tabled ? rep_type : nullptr, table_longest_prefill, table_longest_tpot, w->stream);
+        uint32_t least_bin[3] = {0u, 0u, 0u};
+        if (!on_device) least_bins(w->R, w->params.k99, kinds, host_cost, w->h_out, least_bin);
+        const ap_status st = plan_split(w, w->split_plan, w->stream, w->split, dev, replicas, kinds, worst_service, kind_sum, kind_longest,
+                                        total, tabled ? rep_type : nullptr, table_longest_prefill, table_longest_tpot, least_bin);
         if (st != AP_OK) return st;
     }
     w->has_model = true;
@@ -2043,9 +2119,7 @@ ap_status ap_workload_destroy(ap_workload* w) {
     if (w->d_room) ok = (hipFree(w->d_room) == hipSuccess) && ok;
     if (w->d_rows) ok = (hipFree(w->d_rows) == hipSuccess) && ok;
     if (w->d_req8) ok = (hipFree(w->d_req8) == hipSuccess) && ok;
-    if (w->d_split_tab) ok = (hipFree(w->d_split_tab) == hipSuccess) && ok;
-    if (w->d_split_queue) ok = (hipFree(w->d_split_queue) == hipSuccess) && ok;
-    if (w->d_split_order) ok = (hipFree(w->d_split_order) == hipSuccess) && ok;
+    if (w->split_plan.tables) ok = (hipFree(w->split_plan.tables) == hipSuccess) && ok;
     if (w->d_split_scratch) ok = (hipFree(w->d_split_scratch) == hipSuccess) && ok;
     if (w->d_bounds) ok = (hipFree(w->d_bounds) == hipSuccess) && ok;
     if (w->d_tab_pair) ok = (hipFree(w->d_tab_pair) == hipSuccess) && ok;

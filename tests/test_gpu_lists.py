@@ -1,0 +1,85 @@
+"""GPU parity of the lists' edges (tile and run remainders, rows that list everything or nothing, replicas gone early), of small
+calls that are left to the fused replay, and of the list replay's register groups, against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from paper_2604_07144_amd import traces                    # noqa: E402
+from tests.gpu_harness import GpuWorkload, assert_same, oracle_for   # noqa: E402
+
+KINDS = (traces.COEF_STANDARD, traces.COEF_FAST, traces.COEF_SLOW)
+U64MAX = 0xFFFFFFFFFFFFFFFF
+
+
+def _elastic(R, M, B, gap, seed, steady, **kw):
+    rng = np.random.default_rng(seed)
+    arrival = np.cumsum(rng.integers(0, 2 * gap, R)).astype(np.uint64) + np.uint64(1_000_003)
+    at = rng.integers(int(arrival[0]), int(arrival[-1]) + 1, size=(M, 2))
+    stays = rng.random(M) < steady
+    t_on = np.where(stays, 0, at.min(axis=1)).astype(np.uint64)
+    t_off = np.where(stays, np.uint64(U64MAX), at.max(axis=1).astype(np.uint64))
+    return traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[m % 3] for m in range(M)], t_on, t_off,
+                               B=B, **kw)
+
+
+def _rows(tr, C, seed):
+    """Even rows; rows on few replicas (lists are long); rows that only use replicas as long as they are there
+    (nothing rejected, so the histograms are needed); unknown ids."""
+    rng = np.random.default_rng(seed)
+    rows = rng.integers(0, tr.M, size=(C, tr.R)).astype(np.uint16)
+    third = C // 3
+    for i, c in enumerate(range(third, 2 * third)):
+        rows[c] %= max(1, tr.M >> (i % 5))
+    there = (tr.arrival_us[:, None] >= tr.t_on_us[None]) & (tr.arrival_us[:, None] + np.uint64(10_000_000) < tr.t_off_us[None])
+    for c in range(2 * third, C - 1):
+        pick = rng.random((tr.R, tr.M)) * there
+        rows[c] = pick.argmax(axis=1).astype(np.uint16)
+    rows[C - 1][rng.random(tr.R) < 0.02] = tr.M
+    return rows
+
+
+@pytest.mark.parametrize("R,M,B,gap,steady", [
+    (6000, 50, 24, 1200, 0.5), (6001, 33, 24, 1500, 0.9), (5000, 70, 16, 1500, 0.5), (2047, 20, 12, 4000, 0.7), (2048, 12, 8, 9000, 0.7),
+    (1025, 64, 32, 900, 0.9), (1024, 65, 32, 900, 0.9), (66000, 40, 48, 600, 0.8), (300, 5, 16, 30000, 0.6),
+    # nothing streamed: crowded, so that every request is listed; few and many bits in an id, a row a tile and one more
+    (1023, 3, 8, 20, 0.5), (2049, 64, 16, 3, 0.0), (3000, 65, 16, 3, 0.5), (4097, 129, 8, 2, 0.3), (70001, 300, 64, 1, 0.3)])
+@pytest.mark.parametrize("tabled", [False, True])
+def test_elastic_rows_match_the_oracle(R, M, B, gap, steady, tabled):
+    tr = _elastic(R, M, B, gap, R + M, steady)
+    rows = _rows(tr, 13 if R < 20000 else 7, R)
+    tables, want = None, oracle_for(tr)
+    if tabled:
+        rng = np.random.default_rng(R)
+        tables = (np.arange(M, dtype=np.uint32) % 3, rng.integers(0, 9000, (3, R)).astype(np.uint32), rng.integers(0, 60, (3, R)).astype(np.uint32))
+        want.set_cost_tables(*tables)
+    with GpuWorkload(tr, tables=tables) as g:
+        for part in (rows, rows[:5], rows[5:]):
+            assert_same(g.eval(part), want.eval_batch(part, nthreads=8), f"R={R} M={M} B={B} gap={gap} steady={steady} tabled={tabled}")
+
+
+@pytest.mark.parametrize("B", [1, 7, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 47, 48, 49, 63, 64])
+@pytest.mark.parametrize("slow", [False, True])
+def test_queues_that_fill_drain_and_fill_again(B, slow):
+    """Quiet stretches and bursts in turn, so that a queue has few, half or all of its slots in use: every group of slot registers
+    holds still at some time.  `slow`: tokens so slow that the tpot bins span more than a byte."""
+    rng = np.random.default_rng(B)
+    R, M = 4000, 4
+    gap = np.repeat(rng.choice([60, 400, 1500, 6000], 40), R // 40)
+    coef = [(2000, 3, 25, 5), (1200, 2, 15, 3), (3500, 5, 40, 2000 if slow else 8), (2000, 3, 25, 5)]
+    tr = traces.custom_trace(np.cumsum(rng.integers(0, 2 * gap)), rng.integers(1, 8000, R), rng.integers(1, 60 if slow else 300, R), coef, B=B)
+    rows = rng.integers(0, M, size=(70, R)).astype(np.uint16)
+    rows[1], rows[2] = 2, np.arange(R) // 1000
+    with GpuWorkload(tr) as g:
+        assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"B={B} slow={slow}")
+
+
+@pytest.mark.parametrize("R,C", [(800, 9), (801, 9), (800, 512), (800, 513), (5, 1)])
+def test_small_calls_on_either_side_of_the_line(R, C):
+    tr = _elastic(R, 6, 8, 3000, R, 0.5)
+    rows = np.random.default_rng(C).integers(0, 6, size=(C, R)).astype(np.uint16)
+    with GpuWorkload(tr) as g:
+        want = oracle_for(tr).eval_batch(rows, nthreads=8)
+        for _ in range(2):
+            assert_same(g.eval(rows), want, f"R={R} C={C}")
