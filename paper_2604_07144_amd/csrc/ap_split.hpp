@@ -598,7 +598,7 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // start when they are ready and only those K registers move.  That is so while a queue fills up, after its backlog has
 // drained and on a light trace.  Together with bins in one word instead of two and none below the bins that a p99 value can
 // reach, 1024 rows of 131072 requests on 128 crowded replicas of 64 slots take 1226 us instead of 1569 (and k_merge_candidates 340
-// instead of 803); on light traces and odd B 1.1 to 1.5 times less.
+// instead of 803, before the change described there); on light traces and odd B 1.1 to 1.5 times less.
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
 constexpr uint32_t kListWaves = 4;
@@ -844,8 +844,14 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
         if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
         const size_t tiles_at = (size_t)c * sp.n_list_tiles;
-        for (uint32_t j = 0; j < sp.n_list_tiles; ++j) {
-            const uint32_t used = min(sp.desc[(tiles_at + j) * (sp.M + 1u) + sp.M], sp.tile_cap);
+        // A tile per wavefront at a time, the size of the next one requested ahead: with all wavefronts on one tile the kernel waits
+        // for memory twice per tile (1024 rows of 128 tiles, every request listed: 340 against 199 us).
+        const uint32_t lane = tid & 63u;
+        auto used_of = [&](uint32_t j) { return j < sp.n_list_tiles ? sp.desc[(tiles_at + j) * (sp.M + 1u) + sp.M] : 0u; };
+        uint32_t used_next = used_of(wave_index());
+        for (uint32_t j = wave_index(); j < sp.n_list_tiles; j += kThreads / kWave) {
+            const uint32_t used = min(used_next, sp.tile_cap);
+            used_next = used_of(j + kThreads / kWave);
             const size_t at = (tiles_at + j) * sp.tile_cap;
             auto add = [&](uint32_t te, uint32_t tpot) {
                 if ((te & 0xFFFu) != 0u) hist_add<kHist16>(hist, 0u, min(sp.least_bin[0] + (te & 0xFFFu) - 1u, kBins - 1u), 1u);
@@ -853,13 +859,16 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
                 if (((te >> 12) & 0xFFFu) != 0u) hist_add<kHist16>(hist, 2u, min(sp.least_bin[2] + ((te >> 12) & 0xFFFu) - 1u, kBins - 1u), 1u);
             };
             if (sp.wide_bins != 0u) {
-                for (uint32_t i = tid; i < used; i += kThreads) {
+                for (uint32_t i = lane; i < used; i += kWave) {
                     const uint2 word = reinterpret_cast<const uint2*>(sp.bins)[at + i];
                     if ((word.x | word.y) != 0u) add(word.x, word.y);
                 }
             } else {                                                                // four positions at a time: runs are whole multiples of 8
-                for (uint32_t i = tid; i < used / 4u; i += kThreads) {
-                    const uint4 v = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(sp.bins) + at)[i];
+                const uint4* src4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(sp.bins) + at);
+                uint4 next = lane < used / 4u ? src4[lane] : make_uint4(0u, 0u, 0u, 0u);
+                for (uint32_t i = lane; i < used / 4u; i += kWave) {
+                    const uint4 v = next;
+                    if (i + kWave < used / 4u) next = src4[i + kWave];
                     if (v.x != 0u) add(v.x, v.x >> 24);
                     if (v.y != 0u) add(v.y, v.y >> 24);
                     if (v.z != 0u) add(v.z, v.z >> 24);
