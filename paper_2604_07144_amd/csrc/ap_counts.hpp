@@ -103,7 +103,7 @@ __global__ __launch_bounds__(kCountMaxWaves * kWave) void k_screen_counts(CountP
             return (room & ((1u << shift) - 1u)) | (127u << shift);
         };
         const uint32_t my_room = lane < n_rows ? room_of(lane) : 0u;
-        auto check_row = [&](uint32_t r, uint32_t room, const uint32_t* old, uint32_t* now, bool judge) {
+        auto check_row = [&](uint32_t r, uint32_t room, const uint32_t* old, uint32_t* now, bool full) {
             const uint4* line = reinterpret_cast<const uint4*>(cnt + r * kColumns);
             uint32_t sum = 0;
 #pragma unroll
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(kCountMaxWaves * kWave) void k_screen_counts(CountP
             }
             now[r] = sum;
             const uint32_t got = sum - old[r];
-            if (judge) {
+            if (full) {
                 bad = bad || ((got | ((got & 0x7F7F7F7Fu) + room)) & 0x80808080u) != 0u;
                 seen = __builtin_amdgcn_sad_u8(got, 0u, seen);               // the four bytes added up
             }
@@ -122,13 +122,13 @@ __global__ __launch_bounds__(kCountMaxWaves * kWave) void k_screen_counts(CountP
             const uint32_t lo = count_lo(p.lo, b);
             const uint32_t* old = ring + ((lo - 1u) & ring_mask) * n_rows;
             uint32_t* now = ring + (b & ring_mask) * n_rows;
-            const bool judge = b >= b_first;
+            const bool full = b >= b_first;
             if (kOnePass) {
-                if (lane < n_rows) check_row(lane, my_room, old, now, judge);
+                if (lane < n_rows) check_row(lane, my_room, old, now, full);
             } else {
-                for (uint32_t r = lane; r < n_rows; r += kWave) check_row(r, room_of(r), old, now, judge);
+                for (uint32_t r = lane; r < n_rows; r += kWave) check_row(r, room_of(r), old, now, full);
             }
-            if (judge) meant += min((b + 1u) << p.w_log2, n) - max(lo << p.w_log2, a);
+            if (full) meant += min((b + 1u) << p.w_log2, n) - max(lo << p.w_log2, a);
         };
         auto step_done = [&](uint32_t s) {
             if (((s + 1u) & ((1u << steps_log2) - 1u)) == 0u || s + 1u == n_steps) check(s >> steps_log2);

@@ -20,7 +20,7 @@
 // ap_costmodel_set proves that no finish time can overflow before it enables the path.
 //
 // This file holds the host side: planning, the workload object and the C ABI.  The kernels are in
-// ap_screen.hpp (screening), ap_replay.hpp (fused replay), ap_pipeline.hpp (three-kernel replay) and
+// ap_counts.hpp and ap_screen.hpp (screening), ap_stream.hpp (replicas that are always there), ap_replay.hpp (fused replay), ap_pipeline.hpp (three-kernel replay) and
 // ap_children.hpp (sparse candidates), ap_split.hpp (replicas that differ or come and go: listed and streamed
 // part), ap_roofline.hpp (roofline cost tables, trace time) and ap_agentic.hpp (agentic workflows); ap_common.hpp
 // has what they share.
@@ -552,7 +552,8 @@ static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_window
 // can be used.
 // rep_type: the tabulated cost model (replica m reads row rep_type[m] of the tables, which are on the device by
 // now); table_longest_prefill / table_longest_tpot are then the largest entries of the rows in use.
-static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool list_all, bool& applies, const std::vector<DevReplica>& dev, const ap_replica* replicas,
+static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool list_all, bool& applies,
+                            const std::vector<DevReplica>& dev, const ap_replica* replicas,
                             const std::vector<uint32_t>& kinds, const std::vector<uint32_t>& worst_service,
                             const std::vector<uint64_t>& kind_sum, const std::vector<uint64_t>& kind_longest,
                             uint64_t latest_finish_bound, const uint32_t* rep_type, uint64_t table_longest_prefill,

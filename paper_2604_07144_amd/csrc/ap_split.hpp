@@ -152,8 +152,9 @@ __device__ __forceinline__ uint2 lanes_alike(uint32_t id, unsigned long long all
     return make_uint2(lo, hi);
 }
 
-// Streaming kernel (never behind the streamed evaluation, where nothing is streamed).  One workgroup per candidate at a time; its wavefronts take the tiles of the row in turn
-// and share nothing but the accumulators (and the histograms), so there is no barrier inside a candidate.
+// Streaming kernel (never behind the streamed evaluation, where every request is listed).  One workgroup per candidate at a time;
+// its wavefronts take the tiles of the row in turn and share nothing but the accumulators (and the histograms), so there is no barrier inside a
+// candidate.
 // Per tile a wavefront classifies its 1024 requests, accumulates the streamed ones, counts the listed ones per
 // replica, queues them in arrival order, ranks them (one ballot per bit of the replica id among 64 queued
 // requests at a time) into per-replica runs that start on multiples of 8 list positions, and writes the runs
@@ -594,8 +595,9 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // (the request's prefill and decode time on this replica, from coefficients or tables), records are read from LDS four at a
 // time before they are needed, a tile's steps are counted once (the longest run sets the pace).  And registers that hold
 // free slots need no medians: slots that are free when a request is ready stay free for later ones, whatever time they
-// hold (a group is 16 registers, or 32 of 64: more groups cost a test and a branch each), so if the lowest four of the upper K registers are free for the first of four requests - in every lane - all four
-// start when they are ready and only those K registers move.  That is so while a queue fills up, after its backlog has
+// hold (a group is 16 registers, or 32 of 64: more groups cost a test and a branch each), so if the lowest
+// four of the upper K registers are free for the first of four requests - in every lane - all four start when they
+// are ready and only those K registers move.  That is so while a queue fills up, after its backlog has
 // drained and on a light trace.  Together with bins in one word instead of two and none below the bins that a p99 value can
 // reach, 1024 rows of 131072 requests on 128 crowded replicas of 64 slots take 1226 us instead of 1569 (and k_merge_candidates 340
 // instead of 803, before the change described there); on light traces and odd B 1.1 to 1.5 times less.
