@@ -836,13 +836,21 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
     bool any = false;
     for (uint32_t c = blockIdx.x + tid * gridDim.x; c < n_cand; c += kThreads * gridDim.x)
         any = any || (sp.part[c].flags & (kFlagFallback | kFlagLazy)) == 0u;
-    if (__syncthreads_or(any ? 1 : 0) == 0) return;
+    if ((tid & 63u) == 0u) wtot[wave_index()] = 0u;
+    if (any) wtot[wave_index()] = 1u;
+    __syncthreads();
+    uint32_t n_any = 0u;
+    for (uint32_t ww = 0; ww < kThreads / kWave; ++ww) n_any += wtot[ww];
+    if (n_any == 0u) return;
     for (uint32_t c = blockIdx.x; c < n_cand; c += gridDim.x) {
         const SplitPartial part = sp.part[c];                                       // the same for every thread
         if (!split_wanted(sp, c) || (part.flags & (kFlagFallback | kFlagLazy))) continue;
         const uint32_t* src = sp.hist + (size_t)c * sp.hist_words;
         const bool parked = (part.flags & kFlagNoStreamHist) == 0u;
-        for (uint32_t i = tid; i < sp.hist_words; i += kThreads) hist[i] = parked ? src[i] : 0u;
+        // (a word at a time this is 20 waits in a row: 54 against 42 us for 3895 rows of 1920 requests)
+        static_assert(3u * kBins / 2u % 4u == 0u, "histograms are copied 16 bytes at a time");
+        for (uint32_t i = tid; i < sp.hist_words / 4u; i += kThreads)
+            reinterpret_cast<uint4*>(hist)[i] = parked ? reinterpret_cast<const uint4*>(src)[i] : make_uint4(0u, 0u, 0u, 0u);
         if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
         const size_t tiles_at = (size_t)c * sp.n_list_tiles;
