@@ -38,6 +38,11 @@ constexpr uint32_t kScreenBlock = kWave * 8u;     // requests per wavefront per 
 constexpr uint32_t kScreenMaxSlots = 64;          // slots per replica worth having
 constexpr uint32_t kScreenMinSlots = 32;          // fewer (with B allowing more) and the one-wavefront kernel is not used
 constexpr uint32_t kScreenLdsPerWave = 9216;      // bytes of slot state one wavefront may hold
+// Where the rings begin in LDS, whatever else a kernel keeps there: a multiple of the largest ring, so that every ring is aligned
+// to its size (screen_search flips address bits).  Stated as the array's alignment and not tested in the kernel: of such a test,
+// used both ways round, hipcc 7.2 made one use the wrong way round where the rings begin behind other LDS (the marked variants),
+// and the eight-wavefront kernel left every marked row to the replay.
+constexpr uint32_t kScreenRingAlign = kScreenMaxSlots * 4u;
 
 // Position of request r in the lane-major tables: in its block of 512, request
 // 128k + 2l + h is element 2k + h of lane l.
@@ -328,18 +333,17 @@ template <bool kAligned, bool kMarked>
 __global__ __launch_bounds__(kScreenThreads) void k_screen_candidates(ScreenParams p, const uint16_t* __restrict__ assign,
                                                                        ap_metrics* __restrict__ out, uint32_t C,
                                                                        PendingWord flags) {
-    extern __shared__ __align__(16) unsigned char lds[];
+    extern __shared__ __align__(kScreenRingAlign) unsigned char rings[];
     pending_clear_next(flags);
     if (kMarked && pending_none(flags)) return;                              // nobody has left a mark
     const uint32_t lane = threadIdx.x & 63u, w = wave_index();
     const uint32_t M = p.M, R = p.R, S = 1u << p.slots_log2;
     const uint32_t ring_shift = p.slots_log2 + 2u;                           // bytes per ring, log2
-    uint32_t* mine = reinterpret_cast<uint32_t*>(lds + w * p.wave_bytes);    // M + 1 rings, then M + 1 counters
+    uint32_t* mine = reinterpret_cast<uint32_t*>(rings + w * p.wave_bytes);    // M + 1 rings, then M + 1 counters
     const uint32_t n_ring_words = (M + 1u) << p.slots_log2;
     const uint32_t ring0_addr = lds_address(mine);
     const uint32_t cursor0_addr = ring0_addr + n_ring_words * 4u;
     const uint32_t n_full = R / kScreenBlock;
-    const bool rings_aligned = (ring0_addr & ((S << 2) - 1u)) == 0u;
 
     // kMarked: a workgroup owns a run of consecutive candidates (at most one per thread), looks at all
     // their records at once and leaves when none is marked - the usual case
@@ -357,11 +361,11 @@ __global__ __launch_bounds__(kScreenThreads) void k_screen_candidates(ScreenPara
         const uint16_t* row = assign + (size_t)c * R;
         for (uint32_t i = lane; i < n_ring_words + M + 1u; i += kWave)
             mine[i] = (i < n_ring_words && (i >> p.slots_log2) == M) ? kNever : 0u;
-        bool bad = !rings_aligned;
+        bool bad = false;
 
         // full blocks, two register sets: one is processed while the other is being loaded
         ScreenRegs ga, gb;
-        if (n_full > 0u && !bad) screen_fetch<kAligned>(ga, p, row, 0u, lane);
+        if (n_full > 0u) screen_fetch<kAligned>(ga, p, row, 0u, lane);
         for (uint32_t b = 0; b < n_full && !bad; b += 2u) {
             if (b + 1u < n_full) screen_fetch<kAligned>(gb, p, row, (b + 1u) * kScreenBlock, lane);
             {
@@ -419,7 +423,7 @@ __global__ __launch_bounds__(kScreenThreads) void k_screen_candidates(ScreenPara
 constexpr uint32_t kWideWaves = 8;
 constexpr uint32_t kWideThreads = kWideWaves * kWave;
 constexpr uint32_t kWideBlock = kWideWaves * 128u;
-constexpr uint32_t kWideMaxSlots = 64;
+constexpr uint32_t kWideMaxSlots = kScreenMaxSlots;
 constexpr uint32_t kWideLdsBytes = 32768;         // rings of the M real replicas of the one candidate a workgroup holds
 
 // Slots of this kernel hold bare finish ticks.  Is the slot whose old content is `old` still
@@ -468,14 +472,14 @@ __global__ __launch_bounds__(kWideThreads) void k_screen_candidates_wide(ScreenP
                                                                           const uint16_t* __restrict__ assign,
                                                                           ap_metrics* __restrict__ out, uint32_t C,
                                                                           PendingWord flags) {
-    extern __shared__ __align__(16) unsigned char lds[];
+    extern __shared__ __align__(kScreenRingAlign) unsigned char rings[];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, j = wave_index();
     pending_clear_next(flags);
     if (kMarked && pending_none(flags)) return;                              // nobody has left a mark
     const uint32_t M = p.M, R = p.R, S = 1u << p.slots_log2;
     const uint32_t ring_shift = p.slots_log2 + 2u;
     const uint32_t n_words = (M + 1u) << p.slots_log2;                       // M rings and the unknown-replica ring
-    uint32_t* slot = reinterpret_cast<uint32_t*>(lds);
+    uint32_t* slot = reinterpret_cast<uint32_t*>(rings);
     uint32_t* flag = slot + n_words;
     const uint32_t ring0_addr = lds_address(slot);
     // First choices come from the lower half of a ring only, which leaves the upper half (where the
@@ -491,8 +495,6 @@ __global__ __launch_bounds__(kWideThreads) void k_screen_candidates_wide(ScreenP
         second[h] = ((S >> 1) + ((lane + (lane >> 5) + 2u * j + 16u * h) & lower) - (lane & lower)) * 4u;
     const uint32_t n_full = R / kWideBlock;
     const uint32_t mine = 128u * j + 2u * lane;                              // offset of this lane's pair in a block
-    // alternatives are reached by flipping address bits, which needs the rings aligned to their size
-    const bool rings_aligned = (ring0_addr & ((S << 2) - 1u)) == 0u;
 
     // kMarked: a workgroup owns a run of consecutive candidates (at most one per thread), looks at all
     // their records at once and leaves when none is marked - the usual case
@@ -508,7 +510,7 @@ __global__ __launch_bounds__(kWideThreads) void k_screen_candidates_wide(ScreenP
         if (kMarked && !is_pending(out[c])) continue;                        // the same for the whole workgroup
         const uint16_t* row = assign + (size_t)c * R;
         for (uint32_t i = tid; i < n_words; i += kWideThreads) slot[i] = (i >> p.slots_log2) == M ? kNever : 0u;
-        if (tid < 2u) flag[tid] = rings_aligned ? 0u : 1u;
+        if (tid < 2u) flag[tid] = 0u;
         __syncthreads();
 
         // Full blocks go in groups of kDepth.  While a group is processed the loads of the next
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(kWideThreads) void k_screen_candidates_wide(ScreenP
             old = lds_max_rtn(at, finish);
         };
         const uint32_t n_groups = n_full / kDepth;
-        bool bad = !rings_aligned;
+        bool bad = false;
         uint32_t turn = 0;                                                   // which flag word the next verdict uses
         auto run_group = [&](const Loaded& now, Loaded& next, uint32_t g) {
             bool lane_bad = false;
@@ -574,7 +576,7 @@ __global__ __launch_bounds__(kWideThreads) void k_screen_candidates_wide(ScreenP
             ++turn;
         };
         Loaded set_a, set_b;
-        if (n_groups > 0u && !bad) {
+        if (n_groups > 0u) {
 #pragma unroll
             for (uint32_t d = 0; d < kDepth; ++d) fetch(set_a, d, d);
         }

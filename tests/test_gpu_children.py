@@ -361,3 +361,25 @@ def test_rows_of_any_length_are_the_parent_with_its_edits(R):
         g.set_parent(parent, C)
         got = g.eval_children(first, request, replica)
     assert_same(got, oracle_for(tr).eval_children(parent, first, request, replica), f"R={R}")
+
+
+# ------------------------------------------------------------------ rows that only the slot rings can settle
+@pytest.mark.parametrize("n", [5000, 5001, 1023, 12288])
+@pytest.mark.parametrize("M,B,gap", [(16, 32, 3000), (128, 64, 400), (200, 48, 400), (600, 8, 3000)],
+                         ids=["one_wavefront", "eight_wavefronts", "eight_wavefronts_32_slots", "eight_wavefronts_8_slots"])
+def test_children_beyond_the_bound_that_never_wait_are_settled_by_the_rings(n, M, B, gap):
+    """More edits per replica than the parent leaves room for, yet nobody waits: the pass of the rings over the marked rows
+    has to settle every child, and leave none to the replay."""
+    tr = _mk(n, M, B, gap, seed=n + M, coef=[STD] * M)
+    parent = (np.arange(n) % M).astype(np.uint16)
+    keep = M // 3
+    lists = (np.arange(8, dtype=np.uint32) * n, np.tile(np.arange(n, dtype=np.uint32), 7),
+             np.concatenate([(np.arange(n) + c) % keep for c in range(7)]).astype(np.uint16))
+    want = oracle_for(tr).eval_children(parent, *lists, nthreads=8)
+    assert len(set(want["sum_ttft_us"].tolist())) == 1                # the same record for all: nobody waits
+    with GpuWorkload(tr) as g:
+        g.set_parent(parent, 7)
+        got = g.eval_children(*lists)
+        counts = g.counts()
+    assert_same(got, want, f"n={n} M={M} B={B}")
+    assert counts == (7, 0)
