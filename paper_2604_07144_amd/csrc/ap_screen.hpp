@@ -21,11 +21,13 @@ struct PendingWord {
     uint32_t* mine;
     uint32_t* next;
 };
-__device__ __forceinline__ void pending_raise(const PendingWord& f) {
-    __hip_atomic_store(f.mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ bool pending_none(const PendingWord& f) {
     return __hip_atomic_load(f.mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u;
+}
+// Looks before it stores: the stores of many rows to one word follow one another (1677 rows that fail the counting screen:
+// 70 us with a store each, 17 so).
+__device__ __forceinline__ void pending_raise(const PendingWord& f) {
+    if (pending_none(f)) __hip_atomic_store(f.mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void pending_clear_next(const PendingWord& f) {
     if (blockIdx.x == 0u && threadIdx.x == 0u) __hip_atomic_store(f.next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
