@@ -222,9 +222,10 @@ __device__ __forceinline__ void hist_clear(uint32_t* hist) {
 
 // Block-wide end of one candidate: fold the per-lane sums, add the rejected requests at the
 // penalty value, find the three p99 bins by a prefix sum over the histograms and write the
-// record.  Called by all kThreads threads; `hist` holds the served requests' counts (those that are known to
-// lie below the p99 value of their metric may be missing).
-template <bool kHist16>
+// record.  Called by all kThreads threads; `hist` holds the served requests' counts.  kPartial: those that are known to lie
+// below the p99 value of their metric may be missing.  (A case of its own: counting the missing ones costs k_eval_candidates
+// eleven more spilled scalars and 5 % of its time with 32-bit counts.)
+template <bool kHist16, bool kPartial = false>
 __device__ __forceinline__ void finish_candidate(const EvalParams& p, uint32_t* hist, unsigned long long* acc64,
                                                  uint32_t* acc32, uint32_t* wtot, unsigned long long s_e2e,
                                                  unsigned long long s_ttft, unsigned long long s_tpot,
@@ -264,8 +265,13 @@ __device__ __forceinline__ void finish_candidate(const EvalParams& p, uint32_t* 
     __syncthreads();
 #pragma unroll
     for (uint32_t h = 0; h < 3u; ++h) {
-        uint32_t before = p.R;                       // requests that were not counted come first: they lie below every p99 value
-        for (uint32_t ww = 0; ww < kWaves; ++ww) before -= ww < w ? 0u : wtot[h * kWaves + ww];
+        uint32_t before = 0;
+        if (kPartial) {                              // requests that were not counted come first: they lie below every p99 value
+            before = p.R;
+            for (uint32_t ww = w; ww < kWaves; ++ww) before -= wtot[h * kWaves + ww];
+        } else {
+            for (uint32_t ww = 0; ww < w; ++ww) before += wtot[h * kWaves + ww];
+        }
         const uint32_t hi = before + incl[h], lo = hi - part[h];
         if (lo < p.k99 && p.k99 <= hi) {
             uint32_t run = lo, b = 0;

@@ -888,10 +888,10 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
         }
         __syncthreads();
         const bool first_thread = tid == 0u;
-        finish_candidate<kHist16>(p, hist, acc64, acc32, wtot, first_thread ? part.s_e2e : 0ull,
-                                  first_thread ? part.s_ttft : 0ull, first_thread ? part.s_tpot : 0ull,
-                                  first_thread ? part.last_fin : 0u, first_thread ? part.n_ok : 0u,
-                                  first_thread ? part.n_rej : 0u, &out[c0 + c]);
+        finish_candidate<kHist16, true>(p, hist, acc64, acc32, wtot, first_thread ? part.s_e2e : 0ull,
+                                        first_thread ? part.s_ttft : 0ull, first_thread ? part.s_tpot : 0ull,
+                                        first_thread ? part.last_fin : 0u, first_thread ? part.n_ok : 0u,
+                                        first_thread ? part.n_rej : 0u, &out[c0 + c]);
         __syncthreads();
     }
 }
