@@ -836,12 +836,7 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
     bool any = false;
     for (uint32_t c = blockIdx.x + tid * gridDim.x; c < n_cand; c += kThreads * gridDim.x)
         any = any || (sp.part[c].flags & (kFlagFallback | kFlagLazy)) == 0u;
-    if ((tid & 63u) == 0u) wtot[wave_index()] = 0u;
-    if (any) wtot[wave_index()] = 1u;
-    __syncthreads();
-    uint32_t n_any = 0u;
-    for (uint32_t ww = 0; ww < kThreads / kWave; ++ww) n_any += wtot[ww];
-    if (n_any == 0u) return;
+    if (__syncthreads_or(any ? 1 : 0) == 0) return;
     for (uint32_t c = blockIdx.x; c < n_cand; c += gridDim.x) {
         const SplitPartial part = sp.part[c];                                       // the same for every thread
         if (!split_wanted(sp, c) || (part.flags & (kFlagFallback | kFlagLazy))) continue;

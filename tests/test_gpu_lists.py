@@ -83,3 +83,22 @@ def test_small_calls_on_either_side_of_the_line(R, C):
         want = oracle_for(tr).eval_batch(rows, nthreads=8)
         for _ in range(2):
             assert_same(g.eval(rows), want, f"R={R} C={C}")
+
+
+@pytest.mark.parametrize("stride", [2048, 2049])
+def test_a_workgroup_whose_first_candidate_needs_no_merge(stride):
+    """More candidates than the merge has workgroups: one goes through several, and the first of them, settled by penalty, must
+    not keep the others from their histograms (all rows up to `stride` rejected, then one in 64 with nothing rejected)."""
+    R, M, C = 130, 4, 3 * 2048
+    tr = _elastic(R, M, 8, 3000, 7, 1.0, penalty_us=3_600_000_000)
+    tr = traces.custom_trace(tr.arrival_us, tr.prompt_len, tr.out_len, [KINDS[m % 3] for m in range(M)],
+                             np.where(np.arange(M) == 0, int(tr.arrival_us[R // 2]), 0), np.full(M, U64MAX, dtype=np.uint64), B=8)
+    rows = np.full((C, R), M, dtype=np.uint16)
+    some = np.random.default_rng(3).integers(0, M, size=(48, R)).astype(np.uint16)
+    at = np.arange(stride, C, 64)[:48]
+    rows[at] = some[:at.shape[0]]
+    with GpuWorkload(tr) as g:
+        got = g.eval(rows)
+    want = np.repeat(oracle_for(tr).eval_batch(rows[:1]), C)
+    want[at] = oracle_for(tr).eval_batch(some[:at.shape[0]])
+    assert_same(got, want, f"stride {stride}")
