@@ -187,6 +187,7 @@ struct ap_workload {
     ChildParams child_params{};
     // streamed evaluation (replicas always there, nobody expected to wait): its own tables, one allocation
     bool stream = false;
+    bool stream_settles = false;      // nobody can wait: it leaves nothing behind
     uint32_t* d_stream_tab = nullptr;
     size_t stream_tab_bytes = 0;
     StreamParams stream_params{};
@@ -307,8 +308,9 @@ static ap_status launch_stream(const ap_workload* w, const uint16_t* d_assign, u
     uint32_t waves = 4u;
     while (waves < kStreamMaxThreads / kWave && (uint64_t)C * waves * 2u <= (uint64_t)w->n_cu * 32u && w->R / 128u >= 8u * waves) waves *= 2u;
     const uint32_t grid = std::min(C, w->n_cu * 64u);
-    hipLaunchKernelGGL(w->tabled ? k_stream_candidates<true> : k_stream_candidates<false>, dim3(grid), dim3(waves * kWave),
-                       w->stream_lds_bytes, stream, w->stream_params, d_assign, d_out, C, flags);
+    const auto kernel = w->stream_settles ? (w->tabled ? k_stream_candidates<true, false> : k_stream_candidates<false, false>)
+                                          : (w->tabled ? k_stream_candidates<true, true> : k_stream_candidates<false, true>);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kWave), w->stream_lds_bytes, stream, w->stream_params, d_assign, d_out, C, flags);
     return hipGetLastError() == hipSuccess ? AP_OK : device_error();
 }
 
@@ -354,7 +356,7 @@ static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, ui
     bool split_behind = false;
     if (w->stream && !marked) {
         const ap_status st = launch_stream(w, d_assign, C, d_out, stream, flags);
-        if (st != AP_OK) return st;
+        if (st != AP_OK || w->stream_settles) return st;
         split_behind = true;
     }
     if (w->split && !marked && !fused) {
@@ -543,6 +545,27 @@ static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_window
     return most > mean && most - mean - most * std::log(most / mean) + std::log((double)M * n_windows) <= -16.0;
 }
 
+// depth[i]: the largest number of requests of the whole trace, i or later, that are in service at an arrival when nobody waits
+// and all are on their slowest kind of replica, the arriving one included; depth[R] = 0.
+static std::vector<uint32_t> service_depths(const ap_workload* w, const std::vector<uint32_t>& worst_service) {
+    const uint32_t R = w->R;
+    std::vector<uint32_t> depth((size_t)R + 1u, 0u);
+    std::vector<uint64_t> heap;                              // finish times, the earliest first
+    heap.reserve(1024);
+    for (uint32_t r = 0; r < R; ++r) {
+        const uint64_t a = w->h_arrival[r];
+        while (!heap.empty() && heap.front() <= a) {
+            std::pop_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
+            heap.pop_back();
+        }
+        heap.push_back(a + worst_service[r]);
+        std::push_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
+        depth[r] = (uint32_t)heap.size();
+    }
+    for (uint32_t r = R; r-- > 0u;) depth[r] = std::max(depth[r], depth[r + 1u]);
+    return depth;
+}
+
 // Plan of the split evaluation (ap_split.hpp) - replicas that differ or have windows, crowded traces, tables too
 // small for the one-wavefront screen; linear cost models (rep_type == nullptr) and tabulated ones:
 // the index ranges of every replica, the bound D on requests in service that started on arrival, the
@@ -557,7 +580,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool list_all, bool
                             const std::vector<uint32_t>& kinds, const std::vector<uint32_t>& worst_service,
                             const std::vector<uint64_t>& kind_sum, const std::vector<uint64_t>& kind_longest,
                             uint64_t latest_finish_bound, const uint32_t* rep_type, uint64_t table_longest_prefill,
-                            uint64_t table_longest_tpot, const uint32_t* least_bin) {
+                            uint64_t table_longest_tpot, const uint32_t* least_bin, const std::vector<uint32_t>& depth_from) {
     applies = false;
     const uint32_t R = w->R, M = w->params.M, B = w->params.B;
     if (!w->d_req8) return AP_OK;                            // request records with 16-bit lengths only
@@ -575,31 +598,9 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool list_all, bool
         if (rep_type[m] >= 1024u) return AP_OK;              // the type rides in ten bits of a tile word
     for (uint32_t r = 0; r < R; ++r)
         if (worst_service[r] >= (1u << 28)) return AP_OK;
-    std::vector<uint32_t> depth_from;                        // depth_from[i] = max over r >= i of D(r); [R] = 0
-    std::vector<uint32_t> tab;                               // range words, kind words, coefficients
-    std::vector<SplitQueue> queue;
+    std::vector<uint32_t> tab(3u * (AP_MAX_REPLICAS + 1u) + 4u * kinds.size(), 0u);   // range words, kind words, coefficients
+    std::vector<SplitQueue> queue(M);
     std::vector<uint32_t> order;
-    try {
-        depth_from.assign((size_t)R + 1u, 0u);
-        tab.assign(3u * (AP_MAX_REPLICAS + 1u) + 4u * kinds.size(), 0u);
-        queue.resize(M);
-        // D(r): sweep in arrival order over a min-heap of the finish times of requests that start on arrival
-        std::vector<uint64_t> heap;
-        heap.reserve(1024);
-        for (uint32_t r = 0; r < (list_all ? 0u : R); ++r) {
-            const uint64_t a = w->h_arrival[r];
-            while (!heap.empty() && heap.front() <= a) {
-                std::pop_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
-                heap.pop_back();
-            }
-            heap.push_back(a + worst_service[r]);
-            std::push_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
-            depth_from[r] = (uint32_t)std::min<size_t>(heap.size(), kNever);
-        }
-    } catch (const std::bad_alloc&) {
-        return AP_ERR_ALLOC;
-    }
-    for (uint32_t r = R; r-- > 0u;) depth_from[r] = std::max(depth_from[r], depth_from[r + 1u]);
 
     // The streamed part of a replica may begin where the bound leaves an eighth of the slots to the listed part.
     const uint32_t reserve = B / 8u;
@@ -875,11 +876,12 @@ static void least_bins(uint32_t R, uint32_t k99, const std::vector<uint32_t>& ki
 
 // Plan of the streamed evaluation (ap_stream.hpp): bucket size, window table, the bins from which large values are counted.
 // Leaves w->stream false where it does not apply.  cost(k, r, prefill, tpot): the cost of request r on the kind of replica
-// whose first replica is k; rep_type: tabulated cost model.
+// whose first replica is k; rep_type: tabulated cost model; least_bin: as for plan_split; most_in_service: the largest of
+// service_depths.
 extern "C++" template <typename Cost>
 static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const std::vector<uint32_t>& kinds,
                              const std::vector<uint32_t>& kind_of, const std::vector<uint32_t>& worst_service, const uint32_t* rep_type,
-                             const Cost& cost) {
+                             const Cost& cost, const uint32_t* least_bin, uint32_t most_in_service) {
     const uint32_t R = w->R, M = w->params.M, B = w->params.B;
     const bool tabled = rep_type != nullptr;
     if (!w->d_req8) return AP_OK;                            // request records with 16-bit lengths only
@@ -889,11 +891,13 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
             return AP_OK;
     for (uint32_t r = 0; r < R; ++r)                         // and adds up eight latencies in 32 bits
         if (worst_service[r] >= (1u << 28)) return AP_OK;
+    // With no more than B requests in service at once nobody waits on any row: nothing to count.
+    const bool settles = most_in_service <= B;
     // bucket size: the coarsest that will do and whose counts fit (32 KiB: four workgroups per compute unit)
     const uint32_t words = (M + 4u) / 4u;
-    const std::vector<uint32_t> first = first_in_service(w, worst_service, 2u, 1u);
+    const std::vector<uint32_t> first = settles ? std::vector<uint32_t>() : first_in_service(w, worst_service, 2u, 1u);
     uint32_t w_log2 = 7u, n_buckets = 0;
-    for (;; --w_log2) {
+    for (; !settles; --w_log2) {
         if (w_log2 == 0u) return AP_OK;
         n_buckets = ((R + 1u) >> w_log2) + 1u;
         if ((uint64_t)n_buckets * (words * 4u + 2u) > 32768u) return AP_OK;
@@ -927,11 +931,38 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     for (uint32_t h = 0; h < 3u; ++h) {
         uint32_t from = highest[h] + 1u;
         double reached = 0.0;
-        while (from > 1u && reached < want) reached += (double)weight[h * kBins + --from];
-        sp.from[h] = from;
-        sp.least[h] = (uint32_t)ap_hist_lower(from);
-        sp.n_bins[h] = std::max(highest[h] + 1u, from + 1u) - from;
+        while (from > 0u && reached < want) reached += (double)weight[h * kBins + --from];
+        sp.from[h] = std::min(std::min(least_bin[h], w->params.penalty_bin), highest[h]);
+        const uint32_t counted_from[2] = {std::max(from, sp.from[h]), sp.from[h]};
+        for (uint32_t i = 0; i < 2u; ++i) {
+            sp.least[i][h] = (uint32_t)ap_hist_lower(counted_from[i]);
+            sp.n_counted[i][h] = highest[h] + 1u - counted_from[i];
+        }
+        sp.n_bins[h] = sp.n_counted[1][h];
         total_bins += sp.n_bins[h];
+    }
+    // A sample of a row tells which bins to count from, where the row is long enough to pay for it: it takes 2 us, a reading
+    // 1 us per thousand requests.
+    std::vector<uint32_t> sample_weight;
+    if (R >= 8192u && std::memcmp(sp.least[0], sp.least[1], sizeof(sp.least[0])) != 0) {
+        const uint32_t most = 16u * kStreamWeight;
+        sample_weight.assign(M + 1u, 0u);
+        std::vector<uint32_t> kind_weight(kinds.size(), most);
+        for (size_t k = 0; k < kinds.size(); ++k) {
+            uint64_t large[3] = {0u, 0u, 0u};
+            for (uint32_t r = 0; r < R; ++r) {
+                uint64_t prefill, tpot;
+                cost(kinds[k], r, prefill, tpot);
+                const uint64_t value[3] = {prefill, tpot, prefill + (uint64_t)w->h_out[r] * tpot};
+                for (uint32_t h = 0; h < 3u; ++h) large[h] += value[h] >= sp.least[0][h] ? 1u : 0u;
+            }
+            for (uint32_t h = 0; h < 3u; ++h)
+                kind_weight[k] = (uint32_t)std::min<uint64_t>(kind_weight[k], large[h] * kStreamWeight / sp.need_top);
+        }
+        for (uint32_t m = 0; m < M; ++m) sample_weight[m] = kind_weight[kind_of[m]];
+        bool rejected_is_large = true;
+        for (uint32_t h = 0; h < 3u; ++h) rejected_is_large = rejected_is_large && ap_hist_lower(w->params.penalty_bin) >= sp.least[0][h];
+        sample_weight[M] = rejected_is_large ? most : 0u;
     }
     uint32_t off = align_up((M + 1u) * 4u, 16u);
     sp.off_coef = off; off += tabled ? 0u : (uint32_t)kinds.size() * 16u;
@@ -940,8 +971,8 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     sp.off_hist = off; off += align_up(total_bins * 4u, 16u);
     sp.off_acc = off;  off += 64u;
     if (off > 65536u) return AP_OK;
-    // one buffer: coefficients, kinds, window table
-    std::vector<uint32_t> tab(4u * kinds.size() + (M + 1u) + n_buckets, 0u);
+    // one buffer: coefficients, kinds, window table, weights
+    std::vector<uint32_t> tab(4u * kinds.size() + (M + 1u) + n_buckets + sample_weight.size(), 0u);
     for (size_t k = 0; k < kinds.size() && !tabled; ++k) {
         const ap_replica& rp = replicas[kinds[k]];
         tab[4u * k] = rp.prefill_base_us; tab[4u * k + 1u] = rp.prefill_per_tok_us;
@@ -951,6 +982,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     for (uint32_t m = 0; m < M; ++m) kind_words[m] = tabled ? rep_type[m] * R : kind_of[m];
     kind_words[M] = tabled ? rep_type[0] * R : 0u;           // unknown ids: any entry, its cost is not used
     for (uint32_t b = 0; b < n_buckets; ++b) kind_words[M + 1u + b] = first[b * ((1u << w_log2) / 2u)] >> w_log2;
+    std::copy(sample_weight.begin(), sample_weight.end(), kind_words + M + 1u + n_buckets);
     if (4u * tab.size() > w->stream_tab_bytes) {
         if (w->d_stream_tab && hipFree(w->d_stream_tab) != hipSuccess) return device_error();
         w->d_stream_tab = nullptr;
@@ -968,6 +1000,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     sp.tab_pair = tabled ? w->d_tab_pair : nullptr;
     sp.kind = w->d_stream_tab + 4u * kinds.size();
     sp.lo = sp.kind + (M + 1u);
+    sp.weight = sample_weight.empty() ? nullptr : sp.lo + n_buckets;
     sp.n_kinds = tabled ? 0u : (uint32_t)kinds.size();
     sp.R = R; sp.M = M; sp.B = B;
     sp.w_log2 = w_log2; sp.n_buckets = n_buckets; sp.words = words;
@@ -978,6 +1011,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     w->stream_params = sp;
     w->stream_lds_bytes = off;
     w->stream = true;
+    w->stream_settles = settles;
     return AP_OK;
 }
 
@@ -1388,27 +1422,32 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
             return device_error();
         }
     }
-    // ---- split evaluation: replicas that differ or have windows ---------------------------
-    w->split = w->stream = false;
+    // ---- streamed and split evaluation: replicas that differ or have windows, crowded traces, small tables ----
+    w->split = w->stream = w->stream_settles = false;
     bool tables_ready = true;
     if (!w->screen && tabled && w->d_req8) {
         const ap_status st = pair_tables(w, rep_type, M, tables_ready);
         if (st != AP_OK) return st;
     }
-    if (!w->screen && always_on && !on_device && tables_ready) {
-        std::vector<uint32_t> kind_of(M);
-        for (uint32_t m = 0; m < M; ++m)
-            for (size_t k = 0; k < kinds.size(); ++k)
-                if (same_kind(kinds[k], m)) kind_of[m] = (uint32_t)k;
-        const ap_status st = plan_stream(w, replicas, kinds, kind_of, worst_service, tabled ? rep_type : nullptr, host_cost);
-        if (st != AP_OK) return st;
-    }
-    if (!w->screen && tables_ready) {
+    if (!w->screen && w->d_req8 && tables_ready) {
+        const std::vector<uint32_t> depths = service_depths(w, worst_service);
         uint32_t least_bin[3] = {0u, 0u, 0u};
         if (!on_device) least_bins(w->R, w->params.k99, kinds, host_cost, w->h_out, least_bin);
-        const ap_status st = plan_split(w, w->split_plan, w->stream, w->split, dev, replicas, kinds, worst_service, kind_sum, kind_longest,
-                                        total, tabled ? rep_type : nullptr, table_longest_prefill, table_longest_tpot, least_bin);
-        if (st != AP_OK) return st;
+        if (always_on && !on_device) {
+            std::vector<uint32_t> kind_of(M);
+            for (uint32_t m = 0; m < M; ++m)
+                for (size_t k = 0; k < kinds.size(); ++k)
+                    if (same_kind(kinds[k], m)) kind_of[m] = (uint32_t)k;
+            const ap_status st = plan_stream(w, replicas, kinds, kind_of, worst_service, tabled ? rep_type : nullptr, host_cost,
+                                             least_bin, depths[0]);
+            if (st != AP_OK) return st;
+        }
+        if (!w->stream_settles) {
+            const ap_status st = plan_split(w, w->split_plan, w->stream, w->split, dev, replicas, kinds, worst_service, kind_sum,
+                                            kind_longest, total, tabled ? rep_type : nullptr, table_longest_prefill, table_longest_tpot,
+                                            least_bin, depths);
+            if (st != AP_OK) return st;
+        }
     }
     w->has_model = true;
     return AP_OK;

@@ -13,20 +13,22 @@ namespace {
 // ----------------------------------------------------------------------------------
 // For replicas that are available throughout but differ (or a table too small for the slot rings).  Every request is scored
 // where its id is read, as one that starts on arrival: ttft = prefill, e2e = prefill + decode on its replica's kind.  That
-// is its record in the B-slot queue too if nobody waits, which is proved as in the counting screen (ap_counts.hpp): no
-// replica gets more than B requests in the buckets lo(b) .. b, for any bucket b, where lo(b) is the first bucket with a
-// request that could still be in service when b begins, on the slowest kind.  Here a candidate belongs to one workgroup and
-// the counts of all buckets stay in LDS (a byte each, a bucket has at most 128 requests), so the windows are looked at once,
-// at the end, and buckets can be as small as two requests.
+// is its record in the B-slot queue too if nobody waits.  Where no more than B requests of the whole trace are ever in service
+// at once, on the slowest kind, nobody can, whatever the row, and nothing is left to prove (kCounted false).  Elsewhere it is
+// proved for each row as in the counting screen (ap_counts.hpp): no replica gets more than B requests in the buckets lo(b) .. b,
+// for any bucket b, where lo(b) is the first bucket with a request that could still be in service when b begins, on the slowest
+// kind.  Here a candidate belongs to one workgroup and the counts of all buckets stay in LDS (a byte each, a bucket has at most
+// 128 requests), so the windows are looked at once, at the end, and buckets can be as small as two requests.  A candidate that
+// fails the proof gets the pending mark; the listed evaluation scores it next.
 //
-// A p99 value is the need_top-th largest of R values, so only large ones have to be told apart.  The host picks a bin
-// from[h] per metric that twice the needed number of requests reaches when the row is spread over the kinds as the replicas
-// are; values from that bin on are counted, one in fifty, instead of every request in three histograms (three LDS atomics
-// per request, time per token on a handful of addresses).  If fewer than need_top values turn out to lie there the guess was
-// too high for this row.
-//
-// A candidate that fails the proof or the guess gets the pending mark; the listed evaluation, with every request
-// listed, scores it next.
+// A p99 value is the need_top-th largest of R values, so only large ones have to be told apart.  The host picks a bin per metric
+// (and its lower edge, least[0]) that twice the needed number of requests reaches when the row is spread over the kinds as the
+// replicas are; values from that bin on are counted, one in fifty, instead of every request in three histograms (three LDS
+// atomics per request, time per token on a handful of addresses).  A row that prefers the fast kinds has fewer than need_top
+// values there.  Its values are counted from the bin that enough requests reach on whichever kind (least[1]), where the p99
+// value always is.  On long rows a sample of the row, a request per thread, tells; where there is no sample, or it was wrong, the
+// row is read a second time.  4096 rows of 16384 requests on the fast third of 48 replicas take 132 us (231 without the
+// sample, 1009 when such rows went to the listed evaluation), even rows 144.
 struct StreamParams {
     const uint2* req8;            // [R + 1] {arrival, prompt | out << 16}
     const uint32_t* lo;           // [n_buckets] for rows that begin up to one position into their first 4-byte unit
@@ -38,15 +40,20 @@ struct StreamParams {
     uint32_t w_log2, n_buckets;
     uint32_t words;               // 4-byte words of counts per bucket: a byte per replica and one for unknown ids
     uint32_t slo_ttft, slo_tpot, all_within;
-    uint32_t from[3], least[3], n_bins[3];   // first counted bin of ttft, tpot, e2e, its lower edge, bins that can occur from there on
+    // Per metric (ttft, tpot, e2e): the lowest bin that is ever counted and the bins that can occur from there on; for the first
+    // and the second reading of a row, the lower edge of the first counted bin and the bins from that one on.
+    uint32_t from[3], n_bins[3], least[2][3], n_counted[2][3];
     uint32_t need_top;            // R - k99 + 1
+    const uint32_t* weight;       // [M + 1] or null: what a request on the replica adds to a sample of the row, kStreamWeight if a row
+                                  //   of such requests has just need_top large values
     uint32_t penalty_bin;
     uint64_t penalty;
     uint32_t off_coef, off_lo, off_cnt, off_hist, off_acc;   // byte offsets into dynamic LDS
 };
 constexpr uint32_t kStreamMaxThreads = 1024;
+constexpr uint32_t kStreamWeight = 64;
 
-template <bool kTabled>
+template <bool kTabled, bool kCounted>
 __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(StreamParams p, const uint16_t* __restrict__ assign,
                                                                             ap_metrics* __restrict__ out, uint32_t C,
                                                                             PendingWord flags) {
@@ -55,28 +62,39 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
     uint32_t* kind_of = reinterpret_cast<uint32_t*>(lds);
     uint4* coef_of = reinterpret_cast<uint4*>(lds + p.off_coef);
     uint16_t* lo_of = reinterpret_cast<uint16_t*>(lds + p.off_lo);
-    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + p.off_cnt);            // [n_buckets][words]
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + p.off_cnt);            // [n_buckets][words], kCounted only
     uint32_t* hist = reinterpret_cast<uint32_t*>(lds + p.off_hist);          // the three counted parts, one after the other
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_acc);   // e2e, ttft, tpot
-    uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);     // latest finish, within objectives, rejected, failed, p99 bins[3]
+    uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);     // latest finish, within objectives, rejected, windows failed, p99 bins[3], too few counted, the sample's weight
     const uint32_t tid = threadIdx.x, n_threads = blockDim.x, lane = tid & 63u, wv = wave_index(), n_waves = n_threads >> 6;
     const uint32_t R = p.R, M = p.M;
     const uint32_t hist_at[3] = {0u, p.n_bins[0], p.n_bins[0] + p.n_bins[1]};
-    const uint32_t n_hist = hist_at[2] + p.n_bins[2], n_cnt = p.n_buckets * p.words;
+    const uint32_t n_hist = hist_at[2] + p.n_bins[2], n_cnt = kCounted ? p.n_buckets * p.words : 0u;
     for (uint32_t i = tid; i <= M; i += n_threads) kind_of[i] = p.kind[i];
     for (uint32_t i = tid; i < p.n_kinds; i += n_threads) coef_of[i] = p.coef[i];
-    for (uint32_t i = tid; i < p.n_buckets; i += n_threads) lo_of[i] = (uint16_t)p.lo[i];
+    if (kCounted)
+        for (uint32_t i = tid; i < p.n_buckets; i += n_threads) lo_of[i] = (uint16_t)p.lo[i];
 
-    for (uint32_t c = blockIdx.x; c < C; c += gridDim.x) {
+    uint32_t reading = 0;                                                    // 1: the row is read a second time
+    for (uint32_t c = blockIdx.x; c < C;) {
+        const uint16_t* row = assign + (size_t)c * R;
+        uint32_t weight = 0;
+        if (p.weight != nullptr && reading == 0u) weight = p.weight[min((uint32_t)row[(uint32_t)((uint64_t)tid * R / n_threads)], M)];
         for (uint32_t i = tid; i < n_cnt; i += n_threads) cnt[i] = 0u;
         for (uint32_t i = tid; i < n_hist; i += n_threads) hist[i] = 0u;
         if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
-        const uint16_t* row = assign + (size_t)c * R;
+        if (p.weight != nullptr && reading == 0u) {
+            weight = wave_sum_u32(weight);
+            if (lane == 0u) atomicAdd(&acc32[8], weight);
+            __syncthreads();
+            reading = acc32[8] < n_threads * (kStreamWeight + kStreamWeight / 4u) ? 1u : 0u;   // the same word for every thread
+        }
+        const uint32_t least[3] = {p.least[reading][0], p.least[reading][1], p.least[reading][2]};
         const uint32_t a = (uint32_t)(reinterpret_cast<uintptr_t>(row) >> 1) & 1u, n = R + a;   // positions, as in the counting screen
         const uint32_t n_steps = (n + 127u) / 128u;
         unsigned long long s_e2e = 0, s_ttft = 0, s_tpot = 0;
-        uint32_t t_e2e = 0, t_ttft = 0, t_tpot = 0, last_fin = 0, n_ok = 0;  // a wavefront's sums of up to four steps: 8 values below 2^28
+        uint32_t t_e2e = 0, t_ttft = 0, t_tpot = 0, last_fin = 0, n_ok = 0, n_rej = 0;  // a wavefront's sums of up to four steps: 8 values below 2^28
 
         // A lane takes two requests of every 128; the wavefronts take the steps in turn.  The next step's ids and records
         // are requested before the current one is worked on.
@@ -103,7 +121,7 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
         auto score = [&](auto whole_tag, const Step& st, uint32_t s) {
             constexpr bool kWhole = decltype(whole_tag)::value;
             const uint32_t pos = s * 128u + 2u * lane;
-            uint32_t* mine = cnt + (pos >> p.w_log2) * p.words;              // w is even: both requests are in one bucket
+            uint32_t* mine = kCounted ? cnt + (pos >> p.w_log2) * p.words : nullptr;   // w is even: both requests are in one bucket
             const uint32_t id[2] = {(uint32_t)min(st.ids & 0xFFFFu, M), (uint32_t)min(st.ids >> 16, M)};
             const uint32_t kind[2] = {kind_of[id[0]], kind_of[id[1]]};
             const bool in[2] = {kWhole || (pos >= a && pos < n), kWhole || pos + 1u < n};
@@ -118,7 +136,8 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
 #pragma unroll
             for (uint32_t e = 0; e < 2u; ++e) {
                 if (!kWhole && !in[e]) continue;
-                atomicAdd(&mine[id[e] >> 2], 1u << ((id[e] & 3u) * 8u));
+                if (kCounted) atomicAdd(&mine[id[e] >> 2], 1u << ((id[e] & 3u) * 8u));
+                else n_rej += id[e] >= M ? 1u : 0u;
                 const uint32_t arrival = e ? st.rec.z : st.rec.x, lens = e ? st.rec.w : st.rec.y;
                 const uint32_t prompt = lens & 0xFFFFu, len = lens >> 16;
                 uint32_t prefill, tpot;
@@ -137,10 +156,10 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
                 t_e2e += e2e;
                 t_tpot += tpot;
                 if (p.all_within == 0u && id[e] < M) n_ok += (prefill <= p.slo_ttft && tpot <= p.slo_tpot) ? 1u : 0u;
-                if (prefill >= p.least[0] || tpot >= p.least[1] || e2e >= p.least[2]) {
-                    if (prefill >= p.least[0]) atomicAdd(&hist[hist_at[0] + min(hist_bin_u32(prefill) - p.from[0], p.n_bins[0] - 1u)], 1u);
-                    if (tpot >= p.least[1]) atomicAdd(&hist[hist_at[1] + min(hist_bin_u32(tpot) - p.from[1], p.n_bins[1] - 1u)], 1u);
-                    if (e2e >= p.least[2]) atomicAdd(&hist[hist_at[2] + min(hist_bin_u32(e2e) - p.from[2], p.n_bins[2] - 1u)], 1u);
+                if (prefill >= least[0] || tpot >= least[1] || e2e >= least[2]) {
+                    if (prefill >= least[0]) atomicAdd(&hist[hist_at[0] + min(hist_bin_u32(prefill) - p.from[0], p.n_bins[0] - 1u)], 1u);
+                    if (tpot >= least[1]) atomicAdd(&hist[hist_at[1] + min(hist_bin_u32(tpot) - p.from[1], p.n_bins[1] - 1u)], 1u);
+                    if (e2e >= least[2]) atomicAdd(&hist[hist_at[2] + min(hist_bin_u32(e2e) - p.from[2], p.n_bins[2] - 1u)], 1u);
                 }
             }
         };
@@ -164,12 +183,14 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
             s_tpot = wave_sum_u64(s_tpot + t_tpot);
             last_fin = wave_max_u32(last_fin);
             if (p.all_within == 0u) n_ok = wave_sum_u32(n_ok);
+            if (!kCounted) n_rej = wave_sum_u32(n_rej);
             if (lane == 0u) {
                 atomicAdd(&acc64[0], s_e2e);
                 atomicAdd(&acc64[1], s_ttft);
                 atomicAdd(&acc64[2], s_tpot);
                 atomicMax(&acc32[0], last_fin);
                 atomicAdd(&acc32[1], n_ok);
+                if (!kCounted) atomicAdd(&acc32[2], n_rej);
             }
         }
         __syncthreads();
@@ -177,8 +198,8 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
         // The windows: a thread takes one word of the buckets (four replicas) and a share of the buckets, and keeps the
         // window's sum as it moves.  No byte can run over: it is looked at whenever something was added, and a bucket adds
         // at most 128 to a sum of at most 127 that has passed.
-        bool bad = false;
-        {
+        if (kCounted) {
+            bool bad = false;
             const uint32_t shares = max(1u, n_threads / p.words), per = (p.n_buckets + shares - 1u) / shares;
             for (uint32_t job = tid; job < shares * p.words; job += n_threads) {
                 const uint32_t q = job % p.words, b0 = job / p.words * per, b1 = min(b0 + per, p.n_buckets);
@@ -204,9 +225,9 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
                 }
                 if (n_unknown != 0u) atomicAdd(&acc32[2], n_unknown);
             }
+            if (bad) acc32[3] = 1u;
+            __syncthreads();
         }
-        if (bad) acc32[3] = 1u;
-        __syncthreads();
 
         // p99: from the top down, the rejected requests at the penalty's bin
         const uint32_t rejected = acc32[2];
@@ -214,24 +235,26 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
             const uint32_t* counts = hist + hist_at[h];
             uint32_t above = p.penalty_bin >= p.from[h] + p.n_bins[h] ? rejected : 0u, found = kNoKey;
             if (above >= p.need_top) found = p.penalty_bin;
-            for (uint32_t k = 0; k < p.n_bins[h] && found == kNoKey; k += kWave) {
+            const uint32_t n_counted = p.n_counted[reading][h];
+            for (uint32_t k = 0; k < n_counted && found == kNoKey; k += kWave) {
                 const uint32_t down = k + lane, i = p.n_bins[h] - 1u - down;
-                uint32_t v = down < p.n_bins[h] ? counts[i] : 0u;
-                if (down < p.n_bins[h] && p.from[h] + i == p.penalty_bin) v += rejected;
+                uint32_t v = down < n_counted ? counts[i] : 0u;
+                if (down < n_counted && p.from[h] + i == p.penalty_bin) v += rejected;
                 const uint32_t upto = above + wave_inclusive_scan(v, lane);
-                const unsigned long long reached = __ballot(down < p.n_bins[h] && upto >= p.need_top);
+                const unsigned long long reached = __ballot(down < n_counted && upto >= p.need_top);
                 if (reached != 0ull) found = p.from[h] + p.n_bins[h] - 1u - (k + (uint32_t)__ffsll((long long)reached) - 1u);
                 above = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
             }
             if (lane == 0u) {
-                if (found == kNoKey) acc32[3] = 1u;                          // the row has fewer large values than the host expected
+                if (found == kNoKey) acc32[7] = 1u;                          // the row has fewer large values than the host expected
                 else acc32[4u + h] = found;
             }
         }
         __syncthreads();
-        if (tid == 0u) {
+        const bool again = reading == 0u && acc32[3] == 0u && acc32[7] != 0u;
+        if (tid == 0u && !again) {
             ap_metrics mt;
-            if (acc32[3] != 0u) {
+            if (acc32[3] != 0u || acc32[7] != 0u) {
                 __builtin_memset(&mt, 0xFF, sizeof(mt));
                 pending_raise(flags);
             } else {
@@ -248,6 +271,8 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
             out[c] = mt;
         }
         __syncthreads();                                                     // the totals were read
+        reading = again ? 1u : 0u;
+        if (!again) c += gridDim.x;
     }
 }
 

@@ -92,3 +92,97 @@ def test_children_of_a_mixed_cluster():
         g.set_parent(parent, 25)
         got = g.eval_children(first, request, replica)
     assert_same(got, oracle_for(tr).eval_children(parent, first, request, replica), "children")
+
+
+# ------------------------------------------------------------------ light clusters: no more than B requests in service at once
+@pytest.mark.parametrize("R,M,B,gap,kinds", [
+    (1, 5, 4, 1000, 3), (2, 5, 4, 1000, 2), (127, 5, 4, 90000, 3), (128, 20, 12, 9000, 3), (129, 7, 12, 9000, 2),
+    (2051, 33, 24, 4000, 3), (9001, 48, 32, 2500, 3), (4096, 4, 8, 20000, 1), (3000, 256, 16, 6000, 3), (700, 1024, 8, 15000, 3),
+    (70001, 64, 48, 1500, 3)])
+@pytest.mark.parametrize("tabled", [False, True])
+def test_light_clusters_settle_every_row(R, M, B, gap, kinds, tabled):
+    """Crowded on one replica or not, on one kind or not: nobody can wait, so every row is settled where it is read."""
+    tr = _trace(R, M, B, gap, kinds, R + M)
+    rows = _rows(tr, 15 if R < 50000 else 9, R)
+    tables, want = None, oracle_for(tr)
+    if tabled:
+        rng = np.random.default_rng(R)
+        tables = (np.arange(M, dtype=np.uint32) % kinds, rng.integers(0, 9000, (kinds, R)).astype(np.uint32),
+                  rng.integers(0, 30, (kinds, R)).astype(np.uint32))
+        want.set_cost_tables(*tables)
+    with GpuWorkload(tr, tables=tables) as g:
+        for part in (rows, rows[:3], rows[3:]):
+            assert_same(g.eval(part), want.eval_batch(part, nthreads=8), f"R={R} M={M} B={B} kinds={kinds} tabled={tabled}")
+        assert g.counts()[1] == 0
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+@pytest.mark.parametrize("kinds", [1, 3])
+def test_as_many_at_once_as_slots_and_one_more(extra, kinds):
+    """B requests at one instant: even on one replica nobody waits, and nothing has to be counted.  One more may wait."""
+    B, M, R, at = 8, 3, 300, 100
+    tr = _trace(R, M, B, 90000, kinds, 4)
+    arrival = tr.arrival_us.copy()
+    arrival[at:at + B + extra] = arrival[at]
+    arrival[at + B + extra:] += np.uint64(10_000_000)
+    tr = traces.custom_trace(np.maximum.accumulate(arrival), tr.prompt_len, tr.out_len, [KINDS[m % kinds] for m in range(M)], B=B)
+    rows = np.stack([np.full(R, m, dtype=np.uint16) for m in range(M)] + [(np.arange(R) % M).astype(np.uint16)])
+    want = oracle_for(tr).eval_batch(rows, nthreads=4)
+    assert (int(want[0]["sum_ttft_us"]) > int(oracle_for(tr, B=64).eval_batch(rows[:1])[0]["sum_ttft_us"])) == bool(extra)
+    with GpuWorkload(tr) as g:
+        assert_same(g.eval(rows), want, f"extra {extra} kinds {kinds}")
+
+
+@pytest.mark.parametrize("penalty", [0, 1, 5000, 40_000, 10_000_000])
+def test_penalties_where_nobody_can_wait(penalty):
+    """Rejected requests are counted without the proof; rows on the fastest kind are read a second time."""
+    tr = _trace(3000, 30, 24, 9000, 3, 5, penalty_us=penalty, slo_ttft_us=5000, slo_tpot_us=40)
+    rows = np.random.default_rng(6).integers(0, 30, size=(14, 3000)).astype(np.uint16)
+    for c in range(14):
+        if c % 2:
+            rows[c] = rows[c] // 3 * 3 + 1
+        rows[c, 100:100 + 3 * c * c // 4] = 30
+    with GpuWorkload(tr) as g:
+        got = g.eval(rows)
+    assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=8), f"penalty {penalty}")
+
+
+@pytest.mark.parametrize("prefill,tpot", [(0, 0), (0, 5), (5, 0), (1, 1)])
+def test_costs_that_are_all_alike(prefill, tpot):
+    """All values in one bin, the lowest one among them."""
+    tr = _trace(500, 4, 16, 9000, 1, 6)
+    rows = _rows(tr, 9, 3)
+    tables = (np.zeros(4, dtype=np.uint32), np.full((1, 500), prefill, dtype=np.uint32), np.full((1, 500), tpot, dtype=np.uint32))
+    want = oracle_for(tr)
+    want.set_cost_tables(*tables)
+    with GpuWorkload(tr, tables=tables) as g:
+        assert_same(g.eval(rows), want.eval_batch(rows, nthreads=4), f"prefill {prefill} tpot {tpot}")
+
+
+def test_light_clusters_need_no_lists_and_do_not_mind_crowded_rows():
+    """16384 requests at 400 a second on 48 replicas of three kinds: the cost model takes no scratch for lists, and rows on one
+    replica or on the fast kind are not replayed queue by queue (which took 30 and 6 times as long as even rows)."""
+    R, M, C = 16384, 48, 2048
+    tr = _trace(R, M, 32, 2500, 3, 12)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    even = torch.randint(0, M, (C, R), generator=g, device="cuda", dtype=torch.int16)
+    batches = [even, torch.ones_like(even), even // 3 * 3 + 1]
+    out = torch.zeros((C, 8), dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with GpuWorkload(tr) as w:
+        assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+        took = []
+        for rows in batches:
+            best = float("inf")
+            for _ in range(5):
+                start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                start.record()
+                w.eval_device(rows, out)
+                end.record()
+                torch.cuda.synchronize()
+                best = min(best, start.elapsed_time(end))
+            took.append(best)
+            assert_same(to_records(out[:2]), oracle_for(tr).eval_batch(rows[:2].cpu().numpy().view(np.uint16), nthreads=2))
+    assert max(took) < 4.0 * took[0], took
