@@ -152,7 +152,7 @@ __device__ __forceinline__ uint2 lanes_alike(uint32_t id, unsigned long long all
     return make_uint2(lo, hi);
 }
 
-// Streaming kernel (never behind the streamed evaluation, where every request is listed).  One workgroup per candidate at a time;
+// Streaming kernel.  One workgroup per candidate at a time;
 // its wavefronts take the tiles of the row in turn and share nothing but the accumulators (and the histograms), so there is no barrier inside a
 // candidate.
 // Per tile a wavefront classifies its 1024 requests, accumulates the streamed ones, counts the listed ones per
@@ -191,6 +191,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     uint32_t* tile_of = reinterpret_cast<uint32_t*>(mine + p.w_tile);        // [M + 1] the replica's ranges within the tile in hand
     const uint32_t R = p.R, M = p.M;
 
+    if (split_nothing_pending(p)) return;
     if (only_flagged) {                                                             // usually nothing is: leave at once
         bool any = false;
         for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) any = any || (p.part[cb].flags & kFlagNeedHist) != 0u;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     }
 
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
-        if (only_flagged && (p.part[cb].flags & kFlagNeedHist) == 0u) continue;     // the same word for every thread
+        if ((only_flagged && (p.part[cb].flags & kFlagNeedHist) == 0u) || !split_wanted(p, cb)) continue;   // the same for every thread
         __syncthreads();                                                            // the last candidate's totals were read
         if (kHist)
             for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) hist[i] = 0u;

@@ -186,3 +186,27 @@ def test_light_clusters_need_no_lists_and_do_not_mind_crowded_rows():
             took.append(best)
             assert_same(to_records(out[:2]), oracle_for(tr).eval_batch(rows[:2].cpu().numpy().view(np.uint16), nthreads=2))
     assert max(took) < 4.0 * took[0], took
+
+
+@pytest.mark.parametrize("R,C", [(16001, 14), (16000, 600), (70000, 9)])
+@pytest.mark.parametrize("tabled", [False, True])
+def test_a_busy_beginning_is_all_that_is_listed(R, C, tabled):
+    """More than B requests at once only in the first 1500: a row that fails the proof has those listed and the rest scored on
+    arrival, or is handed to the general replay, and the scratch area holds no more than their lists (2.2 GB for all of R = 16001)."""
+    M, B = 20, 16
+    tr = _trace(R, M, B, 12000, 3, 13)
+    rng = np.random.default_rng(2)
+    gap = np.where(np.arange(R) < 1500, 600, 12000)
+    tr = traces.custom_trace(np.cumsum(rng.integers(0, 2 * gap)), tr.prompt_len, tr.out_len, [KINDS[m % 3] for m in range(M)], B=B)
+    rows = _rows(tr, C, R)
+    rows[1], rows[2] = 2, np.where(np.arange(R) < 1490, np.arange(R) % M, 2)
+    tables, want = None, oracle_for(tr)
+    if tabled:
+        tables = (np.arange(M, dtype=np.uint32) % 3, np.stack([a + b * tr.prompt_len for a, b, _, _ in KINDS]).astype(np.uint32),
+                  np.stack([c + d * ((tr.prompt_len + 1023) // 1024) for _, _, c, d in KINDS]).astype(np.uint32))
+        want.set_cost_tables(*tables)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    with GpuWorkload(tr, tables=tables) as g:
+        assert free - torch.cuda.mem_get_info()[0] < 1_400_000_000
+        assert_same(g.eval(rows), want.eval_batch(rows, nthreads=8), f"R={R} C={C} tabled={tabled}")
