@@ -220,6 +220,11 @@ static replay_lists_fn replay_lists_kernel_of(uint32_t B) {
            : B <= 48u ? k_replay_lists<48u, kBins_> : k_replay_lists<64u, kBins_>;
 }
 
+// Small calls go to the fused replay only up to this many replicas (a wavefront works through their queues one after the other: 200
+// requests on 500 replicas, one row, 31 against 27 us), and up to 128 queues per compute unit in all (512 rows of 800 on 128
+// replicas: 55 against 40 us, 256 rows 30 against 38).
+constexpr uint32_t kFusedMaxReplicas = 128;
+
 // The dense path on C rows: screening where it applies, then the exact replay of what is left.
 // marked: only rows whose record carries the pending mark are looked at (screening applies).
 static PendingWord take_pending_word(const ap_workload* w) {
@@ -352,7 +357,7 @@ static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, ui
         }
         if (hipGetLastError() != hipSuccess) return device_error();
     }
-    const bool fused = w->split && !marked && w->split_plan.short_chain && C <= w->n_cu * 2u;
+    const bool fused = w->split && !marked && w->split_plan.short_chain && C <= w->n_cu * 2u && (uint64_t)C * w->params.M <= (uint64_t)w->n_cu * 128u;
     bool split_behind = false;
     if (w->stream && !marked) {
         const ap_status st = launch_stream(w, d_assign, C, d_out, stream, flags);
@@ -797,12 +802,13 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     plan.batch = batch;
     // A small call - few rows, and the fused replay's wavefront per queue has little more to do than a lane of the list replay -
     // is left to the fused replay: one launch instead of three.  It takes 65 ns a request and works on four queues of a row at a
-    // time (12 us + R * 0.016 us a row); the list replay takes 115 ns a request of the longest list while the chip is nearly
-    // empty, and its launches 25 us together.
-    // 64 rows of 256 requests on 4 replicas: 14.4 against 20 us; 65 rows of 16384 on 4, most of them on one: 278 against 1100 us.
-    // The lists count only for tables that are too small for the screen: with windows the longest list says little about the
-    // others, and a crowded trace is reported as listed (ap_eval_counts_get) whatever the number of its rows.
-    plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull);
+    // time (12 us + R * 0.016 us a row that is spread evenly, 12 us + R * 0.065 us one on a single replica); the list replay takes
+    // 115 ns a request of the longest list while the chip is nearly empty, and its launches 25 us together.  Both kinds of row have
+    // to gain: 64 rows of 256 requests on 4 replicas 14.4 against 20 us, 512 rows of 800 on one of 8 replicas 50 against 156; but
+    // 800 on one of 2 replicas that are mostly away, 57 against 32.  With windows the longest list says little about the others:
+    // there even rows have to do without it.
+    plan.short_chain = !w->pipeline && M <= kFusedMaxReplicas && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
+                       65ull * R <= 13000ull + 115ull * longest_list;
     // stream without histograms first when an even spread of the requests over the replicas would reject enough
     plan.expect_lazy = penalty_on_top && expect_rejected / M >= sp.lazy_from;
     applies = true;
