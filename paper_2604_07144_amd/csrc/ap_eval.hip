@@ -144,7 +144,8 @@ struct ap_workload {
     bool screen_packed = false;       // that kernel reads d_pair instead of d_span
     ap_metrics* d_nominal = nullptr;  // record shared by all contention-free candidates
     unsigned char* d_nominal_sums = nullptr;   // k_nominal_metrics: three histograms of 32-bit counts, then its sums and counters
-    uint32_t* d_pending = nullptr;    // [2] "this call has left pending marks", taken in turn by the calls; [2] = candidates replayed
+    uint32_t* d_pending = nullptr;    // [2] "this call has left pending marks", taken in turn by the calls; [2] = candidates replayed;
+                                      //   [3]: those the fused replay scored in place of the lists
     mutable uint32_t turn = 0;        // which of the two the next call uses
     mutable uint64_t n_scored = 0;    // candidates scored since the cost model was set
     bool has_model = false;
@@ -387,8 +388,10 @@ static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, ui
     // After screening, most workgroups only find out that nothing is left for them: as many as can be
     // resident at once look at all the records together.
     const uint32_t grid = std::min(C, pending_only ? w->resident_grid : w->max_grid);
-    hipLaunchKernelGGL(eval_kernel(w->hist16, w->len16, w->tabled), dim3(grid), dim3(kThreads), w->lds_bytes, stream, w->params,
-                       d_assign, d_out, C, pending_only, flags);
+    EvalParams p = w->params;
+    if (fused) p.replayed = w->d_pending + 3;                // in place of the lists: not what ap_eval_counts_get reports
+    hipLaunchKernelGGL(eval_kernel(w->hist16, w->len16, w->tabled), dim3(grid), dim3(kThreads), w->lds_bytes, stream, p, d_assign, d_out, C,
+                       pending_only, flags);
     if (hipGetLastError() != hipSuccess) return device_error();
     return AP_OK;
 }

@@ -114,3 +114,4 @@ def test_small_calls_report_what_larger_ones_do(R, M, C):
     rows[C // 2] = 1
     with GpuWorkload(tr) as g:
         assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R} M={M} C={C}")
+        assert g.counts() == (C, 0)
