@@ -97,7 +97,7 @@ struct SplitParams {
     void* bins;                                   // [batch][n_list_tiles][tile_cap] what every listed request adds to the histograms:
                                                   //   a BinsWord (4 bytes), or two words where the tpot bins span too much
     uint32_t wide_bins;                           // the latter
-    uint32_t least_bin[3], least_us[3];           // no p99 value (ttft, tpot, e2e) can lie below this bin: smaller values are not counted
+    uint32_t least_bin[3], least_us[3];           // no p99 value (ttft, tpot, e2e) can lie below this bin: the list replay leaves smaller ones out
     uint32_t tpot_within;                         // no request's time per token can exceed the objective
     const uint2* tab_pair;                        // tabulated cost model: [T][R] {prefill time, time per token}; the kind
                                                   //   word of a replica then holds its type, SplitQueue::a type * R
@@ -321,10 +321,10 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                             t_tpot += tpot;
                             last_fin = max(last_fin, arrival + e2e);
                             if (p.all_within == 0u) n_ok += (prefill <= p.slo_ttft && tpot <= p.slo_tpot) ? 1u : 0u;
-                            if (kHist) {
-                                if (prefill >= p.least_us[0]) hist_add<kHist16>(hist, 0u, hist_bin_u32(prefill), 1u);
-                                if (tpot >= p.least_us[1]) hist_add<kHist16>(hist, 1u, hist_bin_u32(tpot), 1u);
-                                if (e2e >= p.least_us[2]) hist_add<kHist16>(hist, 2u, hist_bin_u32(e2e), 1u);
+                            if (kHist) {                                            // (a test per value against least_us costs more than it
+                                hist_add<kHist16>(hist, 0u, hist_bin_u32(prefill), 1u);   // saves: 3 rows of 30000 requests 46 against 37 us,
+                                hist_add<kHist16>(hist, 1u, hist_bin_u32(tpot), 1u);      // 2236 rows 261 against 252 in all)
+                                hist_add<kHist16>(hist, 2u, hist_bin_u32(e2e), 1u);
                             }
                         }
                     }
