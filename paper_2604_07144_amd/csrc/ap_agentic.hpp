@@ -25,7 +25,7 @@ namespace {
 // changes:
 //  * the calls in service sit in 64 slots, one per lane (end of the stage, and which call);
 //    the next instant is the minimum over them and the next arrival of a workflow.  Calls beyond 64 in service wait
-//    for their end in an LDS table by call, which is gone through only while there are any;
+//    for their end in an LDS table by call, which is gone through only when one of them ends;
 //  * the calls of a plan are ranked by (key, index) once, before the loop; an instance's queue is a bit mask over ranks in
 //    LDS, so its first waiting call is the first bit set, and joining or leaving a queue is one bit;
 //  * a completion, release or arrival notes which instances it concerns, and only those try to admit or start a call;
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
         wave_sync_lds();
 
         uint32_t ends = kNever, who = 0u;                        // this lane's slot: end of the stage (kNever: free), call | phase << 10
-        uint32_t n_over = 0u;                                    // calls in service without one
+        uint32_t t_over = kNever;                                // the first end among the calls in service without one
         uint32_t room = cap;                                     // lane q: free tokens of decode instance q
         unsigned long long busy = 0ull;                          // prefill instances at work
         unsigned long long try_pre = 0ull, try_dec = 0ull;       // instances something has changed for
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
                     over[k] = end;
                     over_phase[k] = (unsigned char)phase;
                 }
-                ++n_over;
+                t_over = min(t_over, end);
                 wave_sync_lds();
             }
         };
@@ -301,18 +301,20 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
                     due &= due - 1ull;
                     over_now(x & 1023u, x >> 10);
                 }
-                if (n_over != 0u) {
+                if (t_over == t) {                               // one pass: what is due, and the first end among the others
+                    uint32_t rest = kNever;
+                    t_over = kNever;                             // (a call that fails at its release lowers it again, and sets `again`)
                     for (uint32_t k0 = 0; k0 < K; k0 += kWave) {
-                        for (;;) {
-                            const unsigned long long here = __ballot(k0 + lane < K && over[k0 + lane] == t);
-                            if (here == 0ull) break;
+                        const uint32_t end = k0 + lane < K ? over[k0 + lane] : kNever;
+                        rest = min(rest, end == t ? kNever : end);
+                        for (unsigned long long here = __ballot(end == t); here != 0ull; here &= here - 1ull) {
                             const uint32_t k = k0 + (uint32_t)__ffsll((long long)here) - 1u, phase = wave_uniform(over_phase[k]);
                             if (lane == 0u) over[k] = kNever;
-                            --n_over;
                             wave_sync_lds();
                             over_now(k, phase);
                         }
                     }
+                    t_over = min(t_over, wave_all_min(rest));
                 }
                 while (next_arrival <= t) {                      // kNever once all have arrived
                     const uint32_t w = wave_uniform(order[n_arrived]);
@@ -353,10 +355,7 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
                 leave(i, r);
             }
             // ---- 4. the next instant ----
-            uint32_t soonest = ends;
-            if (n_over != 0u)
-                for (uint32_t k = lane; k < K; k += kWave) soonest = min(soonest, over[k]);
-            t = min(wave_all_min(soonest), next_arrival);
+            t = min(min(wave_all_min(ends), t_over), next_arrival);
             if (t == kNever) break;
         }
         wave_sync_lds();

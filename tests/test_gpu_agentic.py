@@ -131,3 +131,23 @@ def test_error_paths():
     assert e.value.status == binding.AP_ERR_INVALID
     binding.ap_agentic_eval(h, 0, 0, 0, 0, 0)                                 # C == 0
     binding.ap_agentic_destroy(h)
+
+
+@pytest.mark.parametrize("decode_us", [7, 400])
+@pytest.mark.parametrize("same_length", [True, False])
+def test_hundreds_in_service_that_end_together(decode_us, same_length):
+    """More calls in service than lanes, many of them ending at one instant, with and without a slot; chains of three in which calls
+    fail at their release, so that an instant is gone through again while such calls are ending."""
+    W = 340
+    K = 3 * W
+    rng = np.random.default_rng(decode_us)
+    lengths = np.full(K, 100, dtype=np.uint32) if same_length else rng.integers(50, 53, K).astype(np.uint32) * 2
+    pred_first = np.concatenate([[0], np.cumsum(np.arange(K) % 3 > 0)]).astype(np.uint32)
+    wl = dict(arrival_us=np.repeat(np.arange(4, dtype=np.uint64) * 300, W // 4), slo_us=np.full(W, 40_000, dtype=np.uint64),
+              wf=np.repeat(np.arange(W, dtype=np.uint32), 3), in_len=lengths, out_len=np.full(K, 10, dtype=np.uint32),
+              pred_first=pred_first, pred=np.array([k - 1 for k in range(K) if k % 3], dtype=np.uint32),
+              pa=np.full(64, 100, dtype=np.uint32), pb=np.zeros(64, dtype=np.uint32), qc=np.full(8, decode_us, dtype=np.uint32),
+              qd=np.zeros(8, dtype=np.uint32), cap=np.full(8, 100_000, dtype=np.uint32), penalty_permille=9000)
+    pre, dec, key = traces.draw_agentic_candidates(5, 10, K, 64, 8, key_range=50, bad_ids=True)
+    pre[:5] = pre[:5] % 64
+    both(wl, pre, dec, key, f"decode {decode_us} same {same_length}")
