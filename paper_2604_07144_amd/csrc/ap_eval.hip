@@ -234,6 +234,29 @@ static PendingWord take_pending_word(const ap_workload* w) {
     return PendingWord{w->d_pending + t, w->d_pending + (t ^ 1u)};
 }
 
+// The counting screen is one launch more in front of the rings, 2 us, which calls of 12 to 30 us do not get back.  It pays
+// from about 2^25 requests (38 against 22 us at 34 million requests on 127 replicas; 30 against 33 us at 26 million on 38)
+// and on long rows, which are a chain of blocks of 512 or 1024 requests for the rings.
+static bool counts_first(const ap_workload* w, uint32_t C) { return w->counts && (w->R >= 32768u || (uint64_t)C * w->R >= (1u << 25)); }
+
+// Wavefronts per row of the counting screen: several while there are fewer rows than the chip holds wavefronts (8192 at eight per
+// SIMD), as long as a wavefront's share stays at least four steps and at least as long as what it has to count again before it.
+static uint32_t count_waves_per_row(const ap_workload* w, uint32_t C) {
+    const CountParams& p = w->count_params;
+    const uint32_t step = p.w_log2 >= 9u ? 512u : 128u, again = (p.ring_mask + 1u) << p.w_log2;
+    uint32_t per_row = 1u;
+    while (per_row < kCountMaxWaves && (uint64_t)C * per_row * 2u <= (uint64_t)w->n_cu * 32u &&
+           w->R / (per_row * 2u) >= std::max(4u * step, again / 2u) &&
+           std::max(4u, per_row * 2u) * p.wave_words * 4u <= kCountLdsBytes)
+        per_row *= 2u;
+    return per_row;
+}
+
+// Calls of few rows that go to the fused replay in place of the lists.
+static bool fused_replay(const ap_workload* w, uint32_t C) {
+    return w->split && w->split_plan.short_chain && C <= w->n_cu * 2u && (uint64_t)C * w->params.M <= (uint64_t)w->n_cu * 128u;
+}
+
 // The counting screen on C rows.
 static ap_status launch_counts(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out, hipStream_t stream,
                                PendingWord flags) {
@@ -243,14 +266,7 @@ static ap_status launch_counts(const ap_workload* w, const uint16_t* d_assign, u
     static const count_fn variants[6] = {k_screen_counts<1u, 2u>, k_screen_counts<1u, 3u>, k_screen_counts<1u, 4u>,
                                          k_screen_counts<4u, 2u>, k_screen_counts<4u, 3u>, k_screen_counts<4u, 4u>};
     const count_fn kernel = variants[p.columns_log2 - 2u + (quad ? 3u : 0u)];
-    // Several wavefronts per row while there are fewer rows than the chip holds wavefronts (8192 at eight per SIMD), as long as
-    // a wavefront's share stays at least four steps and at least as long as what it has to count again before it.
-    const uint32_t step = quad ? 512u : 128u, again = (p.ring_mask + 1u) << p.w_log2;
-    uint32_t per_row = 1u;
-    while (per_row < kCountMaxWaves && (uint64_t)C * per_row * 2u <= (uint64_t)w->n_cu * 32u &&
-           w->R / (per_row * 2u) >= std::max(4u * step, again / 2u) &&
-           std::max(4u, per_row * 2u) * p.wave_words * 4u <= kCountLdsBytes)
-        per_row *= 2u;
+    const uint32_t per_row = count_waves_per_row(w, C);
     p.waves_per_row = per_row;
     const uint32_t waves = std::max(4u, per_row);
     const uint32_t grid = (C + waves / per_row - 1u) / (waves / per_row);
@@ -322,10 +338,7 @@ static ap_status launch_stream(const ap_workload* w, const uint16_t* d_assign, u
 
 static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out,
                               hipStream_t stream, bool marked, PendingWord flags) {
-    // The counting screen is one launch more in front of the rings, 2 us, which calls of 12 to 30 us do not get back.  It pays
-    // from about 2^25 requests (38 against 22 us at 34 million requests on 127 replicas; 30 against 33 us at 26 million on 38)
-    // and on long rows, which are a chain of blocks of 512 or 1024 requests for the rings.
-    if (w->counts && !marked && (w->R >= 32768u || (uint64_t)C * w->R >= (1u << 25))) {
+    if (!marked && counts_first(w, C)) {
         const ap_status st = launch_counts(w, d_assign, C, d_out, stream, flags);
         if (st != AP_OK) return st;
         marked = true;                                       // the rings look at what it has left
@@ -358,7 +371,7 @@ static ap_status launch_dense(const ap_workload* w, const uint16_t* d_assign, ui
         }
         if (hipGetLastError() != hipSuccess) return device_error();
     }
-    const bool fused = w->split && !marked && w->split_plan.short_chain && C <= w->n_cu * 2u && (uint64_t)C * w->params.M <= (uint64_t)w->n_cu * 128u;
+    const bool fused = !marked && fused_replay(w, C);
     bool split_behind = false;
     if (w->stream && !marked) {
         const ap_status st = launch_stream(w, d_assign, C, d_out, stream, flags);
@@ -1542,6 +1555,25 @@ ap_status ap_eval_candidates(const ap_workload* w, const uint16_t* d_assign, uin
     if (!d_assign || !d_out) return AP_ERR_INVALID;
     w->n_scored += C;
     return launch_dense(w, d_assign, C, d_out, static_cast<hipStream_t>(hip_stream), false, take_pending_word(w));
+}
+
+// What a call of C rows goes through, for tests that have to know which kernels they reach (not part of the header):
+//   [0] bucket size of the counting screen in requests (0: not launched), [1] its columns, [2] its wavefronts per row;
+//   [3] wavefronts per row of the slot rings (0: none);
+//   [4] streamed evaluation: 0 none, 1 counts, 2 has nothing to count; [5] bucket size of its counts;
+//   [6] behind that (or first): 0 no lists, 1 every request listed, 2 a listed and a streamed part, 3 the fused replay instead.
+ap_status ap_route_get(const ap_workload* w, uint32_t C, uint32_t out[7]) {
+    if (!w || !out) return AP_ERR_INVALID;
+    if (!w->has_model) return AP_ERR_STATE;
+    const bool counts = counts_first(w, C);
+    out[0] = counts ? 1u << w->count_params.w_log2 : 0u;
+    out[1] = counts ? 1u << w->count_params.columns_log2 : 0u;
+    out[2] = counts ? count_waves_per_row(w, C) : 0u;
+    out[3] = !w->screen ? 0u : w->screen_wide ? kWideWaves : 1u;
+    out[4] = !w->stream ? 0u : w->stream_settles ? 2u : 1u;
+    out[5] = w->stream && !w->stream_settles ? 1u << w->stream_params.w_log2 : 0u;
+    out[6] = fused_replay(w, C) ? 3u : !w->split ? 0u : w->split_plan.params.any_streamed != 0u ? 2u : 1u;
+    return AP_OK;
 }
 
 ap_status ap_eval_counts_get(const ap_workload* w, ap_eval_counts* out) {

@@ -2,6 +2,8 @@
 oracle, compare byte for byte.  (Not a test module.)"""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -52,6 +54,13 @@ class GpuWorkload:
     def counts(self):
         """(candidates scored, candidates that went through the exact replay kernels) since the cost model was set."""
         return binding.ap_eval_counts_get(self.handle)
+
+    def route(self, C):
+        """What a call of C rows goes through: dict of counts (bucket size, columns, wavefronts per row), rings (wavefronts per row),
+        stream (0 none, 1 counts, 2 nothing to count) and its bucket size, lists (0 none, 1 all listed, 2 both parts, 3 fused)."""
+        out = (ctypes.c_uint32 * 7)()
+        assert binding.lib().ap_route_get(ctypes.c_void_p(self.handle), ctypes.c_uint32(C), out) == binding.AP_OK
+        return dict(counts=tuple(out[:3]), rings=out[3], stream=out[4], stream_bucket=out[5], lists=out[6])
 
     def set_parent(self, parent: np.ndarray, max_children: int) -> None:
         binding.ap_parent_set(self.handle, parent, max_children)

@@ -378,6 +378,7 @@ def test_children_beyond_the_bound_that_never_wait_are_settled_by_the_rings(n, M
     want = oracle_for(tr).eval_children(parent, *lists, nthreads=8)
     assert len(set(want["sum_ttft_us"].tolist())) == 1                # the same record for all: nobody waits
     with GpuWorkload(tr) as g:
+        assert g.route(7)["rings"] == (1 if M < 20 else 8)
         g.set_parent(parent, 7)
         got = g.eval_children(*lists)
         counts = g.counts()

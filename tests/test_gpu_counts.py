@@ -9,20 +9,25 @@ torch = pytest.importorskip("torch")
 from paper_2604_07144_amd import traces                    # noqa: E402
 from tests.gpu_harness import GpuWorkload, assert_same, oracle_for, to_records   # noqa: E402
 
-# R, M, B, mean gap (us): requests take 2 .. 22 ms, so a gap of g has about 20000 / g of them in a window
+# R, M, B, mean gap (us), and the form of the counting screen: bucket size and columns (16, 8 or 4 for tables up to 159, 319 and more
+# replicas; buckets of 512 requests or more are read 16 bytes at a time).  Requests take 2 .. 22 ms, so a gap of g has about
+# 20000 / g of them in a window.
+FORMS = [
+    (33001, 45, 32, 400, 128, 16), (33001, 45, 48, 150, 256, 16), (33001, 45, 64, 150, 512, 16), (33001, 128, 64, 150, 1024, 16),
+    (33001, 200, 16, 400, 128, 8), (33001, 200, 24, 150, 256, 8), (33001, 200, 32, 150, 512, 8), (33001, 200, 64, 150, 2048, 8),
+    (33001, 900, 10, 400, 128, 4), (33001, 400, 16, 150, 256, 4), (33001, 400, 24, 150, 512, 4), (33001, 400, 48, 150, 2048, 4),
+    (40960, 128, 64, 150, 1024, 16),       # rows of whole steps
+]
+# the same on shorter rows, which it screens in calls of many
+SHORT_FORMS = [
+    (8191, 45, 32, 400, 128, 16), (8191, 45, 64, 150, 512, 16), (8191, 200, 16, 400, 128, 8), (8191, 200, 48, 150, 1024, 8),
+    (8191, 400, 12, 400, 128, 4), (8191, 400, 32, 150, 1024, 4), (8192, 128, 64, 150, 1024, 16),
+]
+# Identical, always available replicas in calls that are too small for it: rings, streamed evaluation or lists.
 CASES = [
-    (2048, 3, 24, 40000),       # buckets of 16 (eight per step), whole steps
-    (2051, 5, 16, 30000),       # 16 or 32, odd row length
-    (1000, 11, 16, 20000),      # 32 or 64, ragged last step
-    (129, 40, 12, 20000),       # one position into the second step
-    (127, 63, 12, 20000),       # the last table with a lane per replica
-    (130, 64, 12, 20000),       # the first without
-    (5000, 45, 24, 4000),       # buckets of 128
-    (20000, 65, 48, 1000),      # a bucket of several steps, two passes over the replicas
-    (33001, 128, 64, 400),      # 16-byte loads, every alignment of a row
-    (40960, 130, 64, 400),      # rows of whole 512-request steps
-    (9000, 1000, 8, 400),       # the largest tables
-    (1, 4, 8, 1000), (2, 4, 8, 1000), (511, 200, 8, 3000), (513, 200, 64, 3000),
+    (2048, 3, 24, 40000), (2051, 5, 16, 30000), (1000, 11, 16, 20000), (129, 40, 12, 20000), (127, 63, 12, 20000),
+    (130, 64, 12, 20000), (5000, 45, 24, 4000), (20000, 65, 48, 1000), (9000, 1000, 8, 400), (1, 4, 8, 1000), (2, 4, 8, 1000),
+    (511, 200, 8, 3000), (513, 200, 64, 3000),
 ]
 
 
@@ -43,42 +48,71 @@ def _rows(tr, C, seed):
     return rows
 
 
-@pytest.mark.parametrize("R,M,B,gap", CASES)
+@pytest.mark.parametrize("R,M,B,gap,bucket,columns", FORMS)
 @pytest.mark.parametrize("C", [13, 40])
-def test_counted_rows_match_the_oracle(R, M, B, gap, C):
+def test_counted_rows_match_the_oracle(R, M, B, gap, bucket, columns, C):
+    """Few long rows, so several wavefronts share one, each on another 2-byte boundary where R is odd."""
     tr = _trace(R, M, B, gap, R + M)
     rows = _rows(tr, C, R + C)
     with GpuWorkload(tr) as g:
+        assert g.route(C)["counts"][:2] == (bucket, columns) and g.route(C)["counts"][2] > 1
+        got = g.eval(rows)
+    assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R} M={M} B={B} gap={gap} C={C}")
+
+
+@pytest.mark.parametrize("R,M,B,gap,bucket,columns", SHORT_FORMS)
+def test_counted_rows_of_a_large_call_match_the_oracle(R, M, B, gap, bucket, columns):
+    """So many rows that each has one wavefront; 23 different ones over and over."""
+    tr = _trace(R, M, B, gap, R + M)
+    rows = _rows(tr, 23, R)
+    C = 23 * 183
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["counts"] == (bucket, columns, 1)
+        got = to_records(g.eval_device(torch.from_numpy(rows.view(np.int16)).cuda().repeat(183, 1)))
+    assert_same(got, np.tile(oracle_for(tr).eval_batch(rows, nthreads=8), 183), f"R={R} M={M} B={B}")
+
+
+@pytest.mark.parametrize("R,M,B,gap", CASES)
+@pytest.mark.parametrize("C", [13, 40])
+def test_smaller_calls_match_the_oracle(R, M, B, gap, C):
+    tr = _trace(R, M, B, gap, R + M)
+    rows = _rows(tr, C, R + C)
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["counts"] == (0, 0, 0)
         got = g.eval(rows)
     assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R} M={M} B={B} gap={gap} C={C}")
 
 
 @pytest.mark.parametrize("offset", range(1, 8))
-def test_rows_that_start_anywhere(offset):
+@pytest.mark.parametrize("R,M,B,gap", [(33001, 128, 64, 150), (33001, 45, 32, 400), (33002, 400, 24, 150), (5001, 45, 24, 4000)])
+def test_rows_that_start_anywhere(offset, R, M, B, gap):
     """The batch itself on any 2-byte boundary: 16-byte and 4-byte loads begin inside the first unit."""
-    for R, M, B, gap in ((33001, 128, 64, 400), (5001, 45, 24, 4000), (2051, 5, 16, 30000)):
-        tr = _trace(R, M, B, gap, 77)
-        rows = _rows(tr, 9, offset)
-        flat = torch.zeros(rows.size + 8, dtype=torch.int16, device="cuda")
-        flat[offset:offset + rows.size] = torch.from_numpy(rows.reshape(-1).view(np.int16)).cuda()
-        with GpuWorkload(tr) as g:
-            got = to_records(g.eval_device(flat[offset:offset + rows.size].view(rows.shape)))
-        assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=8), f"offset {offset} R={R}")
+    tr = _trace(R, M, B, gap, 77)
+    rows = _rows(tr, 9, offset)
+    flat = torch.zeros(rows.size + 8, dtype=torch.int16, device="cuda")
+    flat[offset:offset + rows.size] = torch.from_numpy(rows.reshape(-1).view(np.int16)).cuda()
+    with GpuWorkload(tr) as g:
+        assert (g.route(9)["counts"][0] > 0) == (R > 32768)
+        got = to_records(g.eval_device(flat[offset:offset + rows.size].view(rows.shape)))
+    assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=8), f"offset {offset} R={R}")
 
 
 @pytest.mark.parametrize("extra", [0, 1])
-def test_exactly_full_and_one_too_many(extra):
-    """B requests at one instant on one replica fill it (nobody waits); one more waits."""
-    B, M, R = 16, 33, 4096
-    tr = _trace(R, M, B, 40000, 3)
+@pytest.mark.parametrize("R,M,B,gap,at", [(33001, 45, 32, 400, 2000), (33001, 128, 64, 150, 1000), (33001, 200, 16, 400, 32900),
+                                          (33001, 400, 24, 150, 511), (4096, 33, 16, 40000, 2000)])
+def test_exactly_full_and_one_too_many(R, M, B, gap, at, extra):
+    """B requests at one instant on a replica that gets no others fill it (nobody waits); one more waits."""
+    tr = _trace(R, M, B, gap, 3)
     arrival = tr.arrival_us.copy()
-    at = 2000
     arrival[at:at + B + extra] = arrival[at]
     tr = traces.custom_trace(np.maximum.accumulate(arrival), tr.prompt_len, tr.out_len, [traces.COEF_STANDARD] * M, B=B)
     rows = np.tile((np.arange(R) % (M - 1)).astype(np.uint16), (4, 1))
     rows[1:, at:at + B + extra] = M - 1
     with GpuWorkload(tr) as g:
+        assert (g.route(4)["counts"][0] > 0) == (R > 32768)
         got = g.eval(rows)
         replayed = g.counts()[1]
-    assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=4), f"extra {extra}")
+    want = oracle_for(tr).eval_batch(rows, nthreads=4)
+    assert_same(got, want, f"extra {extra}")
+    assert (int(want[1]["sum_ttft_us"]) > int(want[0]["sum_ttft_us"])) == bool(extra)
     assert (replayed == 0) == (extra == 0)

@@ -104,8 +104,9 @@ def test_a_workgroup_whose_first_candidate_needs_no_merge(stride):
     assert_same(got, want, f"stride {stride}")
 
 
-@pytest.mark.parametrize("R,M,C", [(256, 4, 1), (256, 4, 512), (256, 4, 513), (200, 128, 256), (200, 128, 257), (200, 129, 3), (800, 2, 40)])
-def test_small_calls_report_what_larger_ones_do(R, M, C):
+@pytest.mark.parametrize("R,M,C,fused", [(256, 4, 1, True), (256, 4, 512, True), (256, 4, 513, False), (200, 128, 256, True),
+                                         (200, 128, 257, False), (200, 129, 3, False), (800, 2, 40, True), (801, 2, 40, False)])
+def test_small_calls_report_what_larger_ones_do(R, M, C, fused):
     """A trace so crowded that every request is listed: no row counts as replayed, whether few rows are scored or many."""
     rng = np.random.default_rng(R + M)
     tr = traces.custom_trace(np.cumsum(rng.integers(0, 3, R)), rng.integers(1, 4000, R), rng.integers(1, 200, R),
@@ -113,5 +114,6 @@ def test_small_calls_report_what_larger_ones_do(R, M, C):
     rows = rng.integers(0, M, size=(C, R)).astype(np.uint16)
     rows[C // 2] = 1
     with GpuWorkload(tr) as g:
+        assert g.route(C)["lists"] == (3 if fused else 1)
         assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R} M={M} C={C}")
         assert g.counts() == (C, 0)

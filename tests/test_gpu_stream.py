@@ -31,16 +31,65 @@ def _rows(tr, C, seed):
     return rows
 
 
-# R, M, B, mean gap (us), kinds: the slowest kind takes up to 35 ms, so a window holds about 35000 / gap requests
+# R, M, B, mean gap (us), kinds: the slowest kind takes up to 35 ms, so a window holds about 35000 / gap requests.
+# With linear costs no more than B are in service at once, and the costs that `tabled` draws need counts here and there.
 CASES = [
-    (256, 4, 8, 50000, 1),         # identical replicas, a table too small for the slot rings: buckets of a few requests
+    (256, 4, 8, 50000, 1),         # identical replicas, a table too small for the slot rings
     (300, 2, 4, 90000, 2), (257, 3, 8, 60000, 3), (1000, 7, 12, 20000, 3),
     (2048, 32, 16, 4000, 3), (2049, 33, 24, 4000, 3), (127, 20, 12, 9000, 3), (128, 20, 12, 9000, 3), (129, 20, 12, 9000, 3),
-    (9001, 48, 32, 1250, 3),       # buckets of whole steps, long rows: many wavefronts per row
-    (3000, 255, 8, 1500, 3), (3000, 256, 8, 1500, 3), (700, 1024, 8, 1500, 3),
+    (9001, 48, 32, 1250, 3),       # long rows: many wavefronts per row
     (70001, 64, 48, 700, 3),       # 65536 requests and more
     (1, 5, 4, 1000, 3), (2, 5, 4, 1000, 3), (3, 5, 4, 1000, 3),
+    (3000, 255, 8, 1500, 3), (3000, 256, 8, 1500, 3),   # more than B at once, and counts that leave no room: listed
 ]
+# More than B at once, and the bucket size that the proof by counting takes.
+COUNTED = [
+    (300, 5, 64, 200, 2, 4), (9001, 5, 64, 400, 3, 8), (2048, 48, 16, 700, 3, 8), (300, 255, 8, 4000, 3, 16), (257, 64, 12, 1250, 2, 16),
+    (9001, 48, 12, 4000, 3, 16), (2049, 255, 12, 200, 2, 32), (2048, 64, 16, 1250, 3, 32), (9001, 7, 64, 200, 2, 32),
+    (257, 1024, 8, 1250, 2, 64), (1000, 130, 16, 200, 2, 64), (9001, 256, 16, 200, 2, 128), (2049, 130, 48, 100, 3, 128),
+    (70001, 20, 64, 300, 3, 128), (70001, 20, 48, 450, 3, 128),
+]
+
+
+def _linear_tables(tr, kinds):
+    """The trace's linear costs as tables."""
+    p = tr.prompt_len.astype(np.int64)
+    return (np.arange(len(tr.coef), dtype=np.uint32) % kinds, np.stack([a + b * p for a, b, _, _ in KINDS[:kinds]]).astype(np.uint32),
+            np.stack([c + d * ((p + 1023) // 1024) for _, _, c, d in KINDS[:kinds]]).astype(np.uint32))
+
+
+@pytest.mark.parametrize("R,M,B,gap,kinds,bucket", COUNTED)
+@pytest.mark.parametrize("tabled", [False, True])
+def test_counted_rows_match_the_oracle(R, M, B, gap, kinds, bucket, tabled):
+    tr = _trace(R, M, B, gap, kinds, R + M)
+    rows = _rows(tr, 14 if R < 50000 else 8, R)
+    tables, want = _linear_tables(tr, kinds) if tabled else None, oracle_for(tr)
+    with GpuWorkload(tr, tables=tables) as g:
+        route = g.route(len(rows))
+        assert (route["rings"], route["stream"], route["stream_bucket"]) == (0, 1, bucket)
+        got = g.eval(rows)
+    assert_same(got, want.eval_batch(rows, nthreads=8), f"R={R} M={M} B={B} gap={gap} kinds={kinds} tabled={tabled}")
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+@pytest.mark.parametrize("R,M,B,gap,kinds", [(9001, 48, 12, 4000, 3), (9001, 256, 16, 200, 2), (70001, 20, 48, 450, 3)])
+@pytest.mark.parametrize("at", [0, 1001, -100])
+def test_exactly_full_and_one_too_many(R, M, B, gap, kinds, at, extra):
+    """B requests at one instant on a replica that gets no others: nobody waits.  One more does."""
+    tr = _trace(R, M, B, gap, kinds, 3)
+    at %= R
+    arrival = tr.arrival_us.copy()
+    arrival[at:at + B + extra] = arrival[at]
+    tr = traces.custom_trace(np.maximum.accumulate(arrival), tr.prompt_len, tr.out_len, [KINDS[m % kinds] for m in range(M)], B=B)
+    rows = np.tile((np.arange(R) % (M - 1)).astype(np.uint16), (4, 1))
+    rows[1:, at:at + B + extra] = M - 1
+    with GpuWorkload(tr) as g:
+        assert g.route(4)["stream"] == 1
+        got = g.eval(rows)
+    want = oracle_for(tr).eval_batch(rows, nthreads=4)
+    waits = int(oracle_for(tr, B=64).eval_batch(rows[1:2])[0]["sum_ttft_us"]) < int(want[1]["sum_ttft_us"])
+    assert_same(got, want, f"extra {extra} at {at}")
+    assert waits == bool(extra)
 
 
 @pytest.mark.parametrize("R,M,B,gap,kinds", CASES)
@@ -62,20 +111,22 @@ def test_streamed_rows_match_the_oracle(R, M, B, gap, kinds, tabled):
 @pytest.mark.parametrize("penalty", [0, 1, 5000, 40_000, 10_000_000])
 @pytest.mark.parametrize("slo", [(500_000, 50_000), (5000, 40)])
 def test_penalties_below_among_and_above_the_latencies(penalty, slo):
-    tr = _trace(3000, 30, 24, 3000, 3, 5, penalty_us=penalty, slo_ttft_us=slo[0], slo_tpot_us=slo[1])
+    tr = _trace(3000, 30, 24, 1000, 3, 5, penalty_us=penalty, slo_ttft_us=slo[0], slo_tpot_us=slo[1])
     rows = np.random.default_rng(6).integers(0, 30, size=(12, 3000)).astype(np.uint16)
     for c in range(12):                                    # 0, 3, 6 ... rejected requests; 31 are needed for the 99th percentile
         rows[c, 100:100 + 3 * c * c // 4] = 30
     with GpuWorkload(tr) as g:
+        assert g.route(12)["stream"] == 1
         got = g.eval(rows)
     assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=8), f"penalty {penalty} slo {slo}")
 
 
 def test_odd_batches_and_a_second_call():
     """The batch itself on a 2-byte boundary, rows of odd length, and a call after one that left pending marks."""
-    tr = _trace(2051, 33, 24, 4000, 3, 9)
+    tr = _trace(2051, 33, 24, 1000, 3, 9)
     want = oracle_for(tr)
     with GpuWorkload(tr) as g:
+        assert g.route(9)["stream"] == 1
         for seed, C in ((1, 9), (2, 30), (3, 5)):
             rows = _rows(tr, C, seed)
             flat = torch.zeros(rows.size + 8, dtype=torch.int16, device="cuda")
@@ -85,10 +136,11 @@ def test_odd_batches_and_a_second_call():
 
 
 def test_children_of_a_mixed_cluster():
-    tr = _trace(4099, 33, 24, 4000, 3, 11)
+    tr = _trace(4099, 33, 24, 1000, 3, 11)
     parent = np.random.default_rng(1).integers(0, 33, 4099).astype(np.uint16)
     first, request, replica = traces.draw_edit_lists(3, 25, 4099, 33, 120.0, replica_range=34)
     with GpuWorkload(tr) as g:
+        assert g.route(25)["stream"] == 1
         g.set_parent(parent, 25)
         got = g.eval_children(first, request, replica)
     assert_same(got, oracle_for(tr).eval_children(parent, first, request, replica), "children")
@@ -111,6 +163,7 @@ def test_light_clusters_settle_every_row(R, M, B, gap, kinds, tabled):
                   rng.integers(0, 30, (kinds, R)).astype(np.uint32))
         want.set_cost_tables(*tables)
     with GpuWorkload(tr, tables=tables) as g:
+        assert g.route(len(rows))["stream"] == 2
         for part in (rows, rows[:3], rows[3:]):
             assert_same(g.eval(part), want.eval_batch(part, nthreads=8), f"R={R} M={M} B={B} kinds={kinds} tabled={tabled}")
         assert g.counts()[1] == 0
@@ -130,6 +183,7 @@ def test_as_many_at_once_as_slots_and_one_more(extra, kinds):
     want = oracle_for(tr).eval_batch(rows, nthreads=4)
     assert (int(want[0]["sum_ttft_us"]) > int(oracle_for(tr, B=64).eval_batch(rows[:1])[0]["sum_ttft_us"])) == bool(extra)
     with GpuWorkload(tr) as g:
+        assert (g.route(4)["stream"] == 2) == (extra == 0)
         assert_same(g.eval(rows), want, f"extra {extra} kinds {kinds}")
 
 
@@ -172,6 +226,7 @@ def test_light_clusters_need_no_lists_and_do_not_mind_crowded_rows():
     torch.cuda.synchronize()
     free = torch.cuda.mem_get_info()[0]
     with GpuWorkload(tr) as w:
+        assert (w.route(C)["stream"], w.route(C)["lists"]) == (2, 0)
         assert free - torch.cuda.mem_get_info()[0] < 64 << 20
         took = []
         for rows in batches:
@@ -193,20 +248,17 @@ def test_light_clusters_need_no_lists_and_do_not_mind_crowded_rows():
 def test_a_busy_beginning_is_all_that_is_listed(R, C, tabled):
     """More than B requests at once only in the first 1500: a row that fails the proof has those listed and the rest scored on
     arrival, or is handed to the general replay, and the scratch area holds no more than their lists (2.2 GB for all of R = 16001)."""
-    M, B = 20, 16
+    M, B = 20, 48
     tr = _trace(R, M, B, 12000, 3, 13)
     rng = np.random.default_rng(2)
-    gap = np.where(np.arange(R) < 1500, 600, 12000)
+    gap = np.where(np.arange(R) < 1500, 450, 12000)
     tr = traces.custom_trace(np.cumsum(rng.integers(0, 2 * gap)), tr.prompt_len, tr.out_len, [KINDS[m % 3] for m in range(M)], B=B)
     rows = _rows(tr, C, R)
     rows[1], rows[2] = 2, np.where(np.arange(R) < 1490, np.arange(R) % M, 2)
-    tables, want = None, oracle_for(tr)
-    if tabled:
-        tables = (np.arange(M, dtype=np.uint32) % 3, np.stack([a + b * tr.prompt_len for a, b, _, _ in KINDS]).astype(np.uint32),
-                  np.stack([c + d * ((tr.prompt_len + 1023) // 1024) for _, _, c, d in KINDS]).astype(np.uint32))
-        want.set_cost_tables(*tables)
+    tables, want = _linear_tables(tr, 3) if tabled else None, oracle_for(tr)
     torch.cuda.synchronize()
     free = torch.cuda.mem_get_info()[0]
     with GpuWorkload(tr, tables=tables) as g:
         assert free - torch.cuda.mem_get_info()[0] < 1_400_000_000
+        assert (g.route(C)["stream"], g.route(C)["lists"]) == (1, 2)
         assert_same(g.eval(rows), want.eval_batch(rows, nthreads=8), f"R={R} C={C} tabled={tabled}")
