@@ -22,9 +22,9 @@ namespace {
 // What it takes is one LDS add per request - no per-request table, no answer from the LDS, nothing shared between
 // wavefronts - so the kernel reads the rows and little else.  Where the add goes decides the pace: one counter per replica
 // sends the 64 lanes of an instruction to random banks (14 LDS cycles each, 0.82 ms on 16384 rows of 131072 requests and
-// 128 replicas).  So a lane picks its bank: four replicas share a word (a byte each), and every word exists once per column,
-// column lane mod n_columns, which leaves an add free of bank conflicts.  When a bucket ends, lane r adds up row r (the four
-// replicas 4 r .. 4 r + 3) over the columns, as whole words.
+// 128 replicas).  So a lane picks its column: four replicas share a word (a byte each), and every word exists once per column,
+// column lane mod n_columns.  Of 64 lanes only those that share a column (4, 8 or 16 of them with 16, 8 or 4 columns) can meet in
+// a bank or a word.  When a bucket ends, lane r adds up row r (the four replicas 4 r .. 4 r + 3) over the columns, as whole words.
 // Nothing is ever cleared: the words are running sums modulo 2^32, and the difference of two of them is
 // n0 + n1 * 2^8 + n2 * 2^16 + n3 * 2^24 modulo 2^32, the four counts of the requests in between, as long as all are below
 // 256.  Should one not be, it reads too small and its neighbour too large, and the bytes add up to less than the requests

@@ -117,7 +117,7 @@ struct SplitPlan {
     uint32_t lds_bytes = 0, lds_bytes_hist = 0;
     unsigned char* tables = nullptr;  // ranges, kinds, coefficients, queues, order
     size_t tables_bytes = 0;
-    size_t o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0, scratch_bytes = 0;   // where its parts lie in the scratch area
+    size_t o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0;   // where its parts lie in the scratch area
     SplitParams params{};
 };
 
@@ -234,9 +234,10 @@ static PendingWord take_pending_word(const ap_workload* w) {
     return PendingWord{w->d_pending + t, w->d_pending + (t ^ 1u)};
 }
 
-// The counting screen is one launch more in front of the rings, 2 us, which calls of 12 to 30 us do not get back.  It pays
-// from about 2^25 requests (38 against 22 us at 34 million requests on 127 replicas; 30 against 33 us at 26 million on 38)
-// and on long rows, which are a chain of blocks of 512 or 1024 requests for the rings.
+// The counting screen is one launch more in front of the rings, 2 us, which calls of 12 to 30 us do not get back.  It pays from
+// about 2^25 requests, and on long rows, which are a chain of blocks of 512 or 1024 requests for the rings.  Even rows, without
+// and with it: of 4096 requests on 45 replicas 19 and 21 us at 2^24 requests, 29 and 28 at 2^25, 49 and 44 at 2^26; of 16384 on
+// 128 replicas 15.1 and 16.5, 24 and 20, 40 and 30; of 32768 on 128, 16.6 and 16.4 at 2^24, 14 and 11 at 2^16.
 static bool counts_first(const ap_workload* w, uint32_t C) { return w->counts && (w->R >= 32768u || (uint64_t)C * w->R >= (1u << 25)); }
 
 // Wavefronts per row of the counting screen: several while there are fewer rows than the chip holds wavefronts (8192 at eight per
@@ -559,8 +560,9 @@ static std::vector<uint32_t> first_in_service(const ap_workload* w, const std::v
 }
 
 // Is a row that is spread evenly over the replicas all but sure to have at most B requests per replica in every one of
-// n_windows windows of `window` requests?  Chernoff's bound on a Poisson count: one chance in 10^7 per row, because a single
-// row that fails makes its call wait for the serial replay of the row's queues.
+// n_windows windows of `window` requests?  Chernoff's bound on a Poisson count: one chance in 10^7 per row.  Behind the streamed
+// evaluation a single row that fails makes its call wait for the serial replay of the row's queues; behind the counting screen
+// it is a pass of the rings over one row, and the line was not tried elsewhere there.
 static bool windows_fit(double window, uint32_t M, uint32_t B, uint32_t n_windows) {
     const double mean = window / M, most = (double)B + 1.0;
     return most > mean && most - mean - most * std::log(most / mean) + std::log((double)M * n_windows) <= -16.0;
@@ -789,7 +791,6 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         w->d_split_scratch = nullptr;
         if (batch == 64u) return AP_OK;                         // no room for the lists: the general replay scores the calls
     }
-    plan.scratch_bytes = total;
     // the tables in one buffer: coefficients at a multiple of 16 bytes, like the queues
     std::vector<uint32_t> words(tab.size() + 4u + 12u * (size_t)M + order.size() + 16u, 0u);
     size_t at = 0;
@@ -947,7 +948,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
         if (worst_service[r] >= (1u << 28)) return AP_OK;
     // With no more than B requests in service at once nobody waits on any row: nothing to count.
     const bool settles = most_in_service <= B;
-    // bucket size: the coarsest that will do and whose counts fit (32 KiB: four workgroups per compute unit)
+    // bucket size: the coarsest that will do and whose counts fit (32 KiB: four workgroups per compute unit; more was not measured)
     const uint32_t words = (M + 4u) / 4u;
     const std::vector<uint32_t> first = settles ? std::vector<uint32_t>() : first_in_service(w, worst_service, 2u, 1u);
     uint32_t w_log2 = 7u, n_buckets = 0;

@@ -95,7 +95,7 @@ struct SplitParams {
     SplitPartial* part;                           // [batch]
     uint32_t* hist;                               // [batch][hist_words] the streamed requests' histograms
     void* bins;                                   // [batch][n_list_tiles][tile_cap] what every listed request adds to the histograms:
-                                                  //   a BinsWord (4 bytes), or two words where the tpot bins span too much
+                                                  //   a bins word as above, or two where the tpot bins span too much
     uint32_t wide_bins;                           // the latter
     uint32_t least_bin[3], least_us[3];           // no p99 value (ttft, tpot, e2e) can lie below this bin: the list replay leaves smaller ones out
     uint32_t tpot_within;                         // no request's time per token can exceed the objective
@@ -152,15 +152,15 @@ __device__ __forceinline__ uint2 lanes_alike(uint32_t id, unsigned long long all
     return make_uint2(lo, hi);
 }
 
-// Streaming kernel.  One workgroup per candidate at a time;
+// Streaming kernel, where something is streamed.  One workgroup per candidate at a time;
 // its wavefronts take the tiles of the row in turn and share nothing but the accumulators (and the histograms), so there is no barrier inside a
 // candidate.
 // Per tile a wavefront classifies its 1024 requests, accumulates the streamed ones, counts the listed ones per
 // replica, queues them in arrival order, ranks them (one ballot per bit of the replica id among 64 queued
 // requests at a time) into per-replica runs that start on multiples of 8 list positions, and writes the runs
 // and their descriptors out.
-// kHistMode: 0 keeps no histograms of the streamed requests (enough when the candidate is settled by penalty, or
-// when nothing is streamed at all), 1 keeps them with 16-bit counts (R < 65536), 2 with 32-bit counts.
+// kHistMode: 0 keeps no histograms of the streamed requests (enough when the candidate is settled by penalty), 1 keeps them
+// with 16-bit counts (R < 65536), 2 with 32-bit counts.
 // only_flagged: look only at candidates that an earlier launch marked kFlagNeedHist.
 // kNarrow: at most 64 replicas, so a queued request (tile index and replica) fits 16 bits, which halves the queue.
 // kTabled: prefill time and time per token are read from the tables (one 8-byte load per request, issued with the
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             sp.last_fin = acc32[0];
             sp.n_ok = acc32[1];
             sp.n_rej = rejected;
-            sp.flags = lazy ? kFlagLazy : (kHist ? 0u : (p.any_streamed != 0u ? kFlagNeedHist : kFlagNoStreamHist));
+            sp.flags = lazy ? kFlagLazy : (kHist ? 0u : kFlagNeedHist);
             p.part[cb] = sp;
         }
         if (kHist && !lazy) {
