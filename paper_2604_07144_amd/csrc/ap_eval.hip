@@ -221,11 +221,6 @@ static replay_lists_fn replay_lists_kernel_of(uint32_t B) {
            : B <= 48u ? k_replay_lists<48u, kBins_> : k_replay_lists<64u, kBins_>;
 }
 
-// Small calls go to the fused replay only up to this many replicas (a wavefront works through their queues one after the other: 200
-// requests on 500 replicas, one row, 31 against 27 us), and up to 128 queues per compute unit in all (512 rows of 800 on 128
-// replicas: 55 against 40 us, 256 rows 30 against 38).
-constexpr uint32_t kFusedMaxReplicas = 128;
-
 // The dense path on C rows: screening where it applies, then the exact replay of what is left.
 // marked: only rows whose record carries the pending mark are looked at (screening applies).
 static PendingWord take_pending_word(const ap_workload* w) {
@@ -253,9 +248,14 @@ static uint32_t count_waves_per_row(const ap_workload* w, uint32_t C) {
     return per_row;
 }
 
-// Calls of few rows that go to the fused replay in place of the lists.
+// Calls of few rows that go to the fused replay in place of the lists: up to two rows per compute unit with up to 64 replicas, one
+// with more (their slots leave room for one workgroup or slow two down: 512 rows of 800 requests on 128 replicas 55 against 40 us,
+// 256 rows 30 against 38).  A wavefront works through the queues of many replicas one after the other, while the launches of the
+// lists cost the same for any number: beyond 128 replicas one row is better off with lists (200 requests on 500 replicas:
+// one row 31 against 27 us, 4 rows 32 against 34; 800 on 500: one row 47 against 41, 4 rows 46 against 55).
 static bool fused_replay(const ap_workload* w, uint32_t C) {
-    return w->split && w->split_plan.short_chain && C <= w->n_cu * 2u && (uint64_t)C * w->params.M <= (uint64_t)w->n_cu * 128u;
+    const uint32_t M = w->params.M;
+    return w->split && w->split_plan.short_chain && C <= (M <= 64u ? 2u : 1u) * w->n_cu && (M <= 128u || C >= 4u);
 }
 
 // The counting screen on C rows.
@@ -841,7 +841,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     // to gain: 64 rows of 256 requests on 4 replicas 14.4 against 20 us, 512 rows of 800 on one of 8 replicas 50 against 156; but
     // 800 on one of 2 replicas that are mostly away, 57 against 32.  With windows the longest list says little about the others:
     // there even rows have to do without it.
-    plan.short_chain = !w->pipeline && M <= kFusedMaxReplicas && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
+    plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
                        65ull * R <= 13000ull + 115ull * longest_list;
     // stream without histograms first when an even spread of the requests over the replicas would reject enough
     plan.expect_lazy = penalty_on_top && expect_rejected / M >= sp.lazy_from;

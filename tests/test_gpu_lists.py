@@ -104,8 +104,9 @@ def test_a_workgroup_whose_first_candidate_needs_no_merge(stride):
     assert_same(got, want, f"stride {stride}")
 
 
-@pytest.mark.parametrize("R,M,C,fused", [(256, 4, 1, True), (256, 4, 512, True), (256, 4, 513, False), (200, 128, 256, True),
-                                         (200, 128, 257, False), (200, 129, 3, False), (800, 2, 40, True), (801, 2, 40, False)])
+@pytest.mark.parametrize("R,M,C,fused", [(256, 4, 1, True), (256, 4, 512, True), (256, 4, 513, False), (200, 65, 256, True),
+                                         (200, 65, 257, False), (200, 128, 3, True), (200, 129, 3, False), (200, 129, 4, True),
+                                         (800, 2, 40, True), (801, 2, 40, False)])
 def test_small_calls_report_what_larger_ones_do(R, M, C, fused):
     """A trace so crowded that every request is listed: no row counts as replayed, whether few rows are scored or many."""
     rng = np.random.default_rng(R + M)
