@@ -843,8 +843,9 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     // there even rows have to do without it.
     plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
                        65ull * R <= 13000ull + 115ull * longest_list;
-    // stream without histograms first when an even spread of the requests over the replicas would reject enough
-    plan.expect_lazy = penalty_on_top && expect_rejected / M >= sp.lazy_from;
+    // stream without histograms first when an even spread of the requests over the replicas would reject enough (never behind the
+    // streamed evaluation, whose replicas do not leave)
+    plan.expect_lazy = !w->stream && penalty_on_top && expect_rejected / M >= sp.lazy_from;
     applies = true;
     return AP_OK;
 }
