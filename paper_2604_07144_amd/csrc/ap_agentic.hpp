@@ -32,9 +32,9 @@ namespace {
 //  * workflows are taken in order of arrival, each with the list of its calls without predecessors.
 // Tables that are the same for all plans (lengths, successors, arrivals) are copied to LDS once per workgroup; the
 // wavefronts of a workgroup share nothing else and never meet at a barrier after that.
-// It is bound by the issue of scalar instructions (245 per call, 156 vector and 24 LDS ones).  Scanning the
-// calls' phases at every instant (a lane per 64 calls, masks per lane) took 2.45 ms for 8192 plans of a 330-call slice,
-// 1.59 ms now.
+// It is bound by the issue of scalar instructions (225 per call, 178 vector and 25 LDS ones).  Scanning the
+// calls' phases at every instant (a lane per 64 calls, masks per lane) took 2.58 ms for 8192 plans of a 330-call slice,
+// 1.64 ms now.
 struct AgenticParams {
     const uint4* blob;            // the tables that go to LDS, laid out as below
     uint32_t blob_bytes;          // a multiple of 16
