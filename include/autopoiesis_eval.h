@@ -116,7 +116,8 @@ ap_status ap_workload_create(const uint64_t *arrival_us, const int32_t *prompt_l
  * otherwise it returns AP_ERR_RANGE and the workload keeps its previous cost model, if any.
  * It also decides which kernels later evaluations run and sizes every device buffer they need:
  * replicas that differ or have windows, crowded traces and very small tables are scored by an
- * evaluation that replays per-replica request lists, whose scratch area (lists for one batch of
+ * evaluation that replays per-replica request lists (unless the replicas stay and nobody can wait,
+ * whatever the assignment), whose scratch area (lists for one batch of
  * candidates, at most 4 GiB) is allocated here; when M*B slot times of one candidate do not fit
  * in LDS next to the histograms, what is left for the general replay goes through a three-kernel
  * path with a scratch area of about 1 GiB, allocated here as well.  A device that cannot provide
