@@ -262,3 +262,46 @@ def test_a_busy_beginning_is_all_that_is_listed(R, C, tabled):
         assert free - torch.cuda.mem_get_info()[0] < 1_400_000_000
         assert (g.route(C)["stream"], g.route(C)["lists"]) == (1, 2)
         assert_same(g.eval(rows), want.eval_batch(rows, nthreads=8), f"R={R} C={C} tabled={tabled}")
+
+
+@pytest.mark.parametrize("gap,settles", [(1000, False), (4000, True)])
+def test_captured_in_a_graph_and_replayed(gap, settles):
+    """Launches only, with counts and without: replays with new rows, eager calls and synchronisations in between."""
+    tr = _trace(3001, 33, 24, gap, 3, 21)
+    want = oracle_for(tr)
+    d_rows = torch.zeros((20, 3001), dtype=torch.int16, device="cuda")
+    d_out = torch.full((20, 8), -1, dtype=torch.int64, device="cuda")
+    with GpuWorkload(tr) as g:
+        assert g.route(20)["stream"] == (2 if settles else 1)
+        g.eval_device(d_rows, d_out)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            g.eval_device(d_rows, d_out)
+        for it in range(4):
+            rows = _rows(tr, 20, it) if it != 2 else np.random.default_rng(it).integers(0, 33, size=(20, 3001)).astype(np.uint16)
+            d_rows.copy_(torch.from_numpy(rows.view(np.int16)).cuda())
+            d_out.fill_(-1)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert_same(to_records(d_out), want.eval_batch(rows, nthreads=8), f"replay {it}")
+            assert_same(g.eval(rows), to_records(d_out), f"eager call after replay {it}")
+
+
+def test_one_workload_between_slot_counts():
+    """The slot count decides whether nothing has to be counted, counts are kept, or everything is listed: back and forth, tables
+    too, on one workload, whose buffers are reused."""
+    from paper_2604_07144_amd import binding
+    tr = _trace(3001, 33, 24, 1000, 3, 22)
+    rows = _rows(tr, 30, 5)
+    with GpuWorkload(tr) as g:
+        for B, stream, tabled in ((24, 1, False), (64, 2, False), (2, 0, False), (64, 2, True), (24, 1, True), (64, 2, False), (24, 1, False)):
+            if tabled:
+                binding.ap_costtable_set(g.handle, _linear_tables(tr, 3)[0], tr.t_on_us, tr.t_off_us, B, tr.slo_ttft_us, tr.slo_tpot_us,
+                                         tr.penalty_us, *_linear_tables(tr, 3)[1:])
+            else:
+                binding.ap_costmodel_set(g.handle, binding.make_replicas(tr.coef, tr.t_on_us, tr.t_off_us), B, tr.slo_ttft_us, tr.slo_tpot_us,
+                                         tr.penalty_us)
+            assert g.route(30)["stream"] == stream
+            assert_same(g.eval(rows), oracle_for(tr, B=B).eval_batch(rows, nthreads=8), f"B={B} tabled={tabled}")
