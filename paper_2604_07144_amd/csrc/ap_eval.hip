@@ -839,10 +839,13 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     // time (12 us + R * 0.016 us a row that is spread evenly, 12 us + R * 0.065 us one on a single replica); the list replay takes
     // 115 ns a request of the longest list while the chip is nearly empty, and its launches 25 us together.  Both kinds of row have
     // to gain: 64 rows of 256 requests on 4 replicas 14.4 against 20 us, 512 rows of 800 on one of 8 replicas 50 against 156; but
-    // 800 on one of 2 replicas that are mostly away, 57 against 32.  With windows the longest list says little about the others:
-    // there even rows have to do without it.
+    // 800 on one of 2 replicas that are mostly away, 57 against 32.  Replicas with a streamed part cost a launch more, 13 us, and
+    // the line lies as much again higher, for lists next to empty at 584 requests: there 97 rows of 577 on 8 replicas that are
+    // mostly always there take 16 against 41 us when they are spread evenly and 38 against 36 when they crowd one (512 rows, 25
+    // against 44 and 49 against 41).  With windows the longest list says little about the others: there even rows have to do
+    // without it in the first term.
     plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
-                       65ull * R <= 13000ull + 115ull * longest_list;
+                       65ull * R <= (any_streamed ? 38000ull : 13000ull) + 115ull * longest_list;
     // stream without histograms first when an even spread of the requests over the replicas would reject enough (never behind the
     // streamed evaluation, whose replicas do not leave)
     plan.expect_lazy = !w->stream && penalty_on_top && expect_rejected / M >= sp.lazy_from;

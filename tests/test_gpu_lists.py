@@ -118,3 +118,17 @@ def test_small_calls_report_what_larger_ones_do(R, M, C, fused):
         assert g.route(C)["lists"] == (3 if fused else 1)
         assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R} M={M} C={C}")
         assert g.counts() == (C, 0)
+
+
+@pytest.mark.parametrize("R,fused", [(200, True), (584, True), (720, False)])
+def test_small_calls_of_replicas_that_come_and_go(R, fused):
+    """Lists next to empty and the rest streamed, on either side of the line up to which the fused replay takes such calls."""
+    rng = np.random.default_rng(R)
+    arrival = np.cumsum(rng.integers(1, 2_000_000, R))
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[m % 3] for m in range(8)], B=8,
+                             t_off_us=[int(arrival[R // 5])] + [traces.UINT64_MAX] * 7)
+    rows = rng.integers(0, 8, size=(97, R)).astype(np.uint16)
+    rows[40], rows[41] = 0, 1
+    with GpuWorkload(tr) as g:
+        assert g.route(97)["lists"] == (3 if fused else 2)
+        assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R}")
