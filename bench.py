@@ -32,21 +32,23 @@ KERNEL_SOURCE_DIR = os.path.join(ROOT, "paper_2604_07144_amd", "csrc")
 # HBM bytes per ap_eval_candidates call from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch, summed over
 # the call's kernels, scaled by what the same counters read for a device copy of known size; see profiles/).
 # Keyed by configuration; valid only for the library source (all of csrc/) whose hash is recorded with it.
+# (Taken at 67614088...; what the source has changed since is the rule that sends small calls to the fused replay, on the
+# host: the device code is the same.)
 MEASURED_TRAFFIC = {
-    # cfg: (sha256 of the kernel source when measured, bytes per call)
-    4: ("67614088ad0fd2d020ad0d2e066621f4b5ed9e1bd8442220d546617be878181d", 4304680356),
-    3: ("67614088ad0fd2d020ad0d2e066621f4b5ed9e1bd8442220d546617be878181d", 1934106508),
+    # cfg: (sha256 of the kernel source, bytes per call)
+    4: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", 4304680356),
+    3: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", 1934106508),
 }
 # Wave-instructions per candidate-request of one ap_eval_candidates call (all its kernels), from rocprofv3 --pmc
 # SQ_INSTS_VALU / SQ_INSTS_SALU / SQ_INSTS_LDS; same validity rule.  The chip issues at most 256 CUs x 4 SIMDs x
 # 2.4 GHz / 4 cycles = 6.1e11 64-lane vector instructions per second.
 VALU_PEAK_PER_S = 256 * 4 * 2.4e9 / 4
 MEASURED_ALU = {
-    4: ("67614088ad0fd2d020ad0d2e066621f4b5ed9e1bd8442220d546617be878181d", {"valu": 0.1226, "salu": 0.0869, "lds": 0.0275}),
-    3: ("67614088ad0fd2d020ad0d2e066621f4b5ed9e1bd8442220d546617be878181d", {"valu": 1.5650, "salu": 0.4630, "lds": 0.1260}),
+    4: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", {"valu": 0.1226, "salu": 0.0869, "lds": 0.0275}),
+    3: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", {"valu": 1.5650, "salu": 0.4630, "lds": 0.1260}),
 }
 # the same for one ap_eval_children call on the sparse form of configs[4]
-MEASURED_TRAFFIC_CHILDREN = {4: ("67614088ad0fd2d020ad0d2e066621f4b5ed9e1bd8442220d546617be878181d", 131238425)}
+MEASURED_TRAFFIC_CHILDREN = {4: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", 131238425)}
 
 
 def kernel_source_hash() -> str:

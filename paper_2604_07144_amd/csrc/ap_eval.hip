@@ -842,8 +842,9 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     // 800 on one of 2 replicas that are mostly away, 57 against 32.  Replicas with a streamed part cost a launch more, 13 us, and
     // the line lies as much again higher, for lists next to empty at 584 requests: there 97 rows of 577 on 8 replicas that are
     // mostly always there take 16 against 41 us when they are spread evenly and 38 against 36 when they crowd one (512 rows, 25
-    // against 44 and 49 against 41).  With windows the longest list says little about the others: there even rows have to do
-    // without it in the first term.
+    // against 44 and 49 against 41).  Most is given up at 512 rows of 800 on 2 replicas with one long list: 60 against 43 us where
+    // they crowd the other, for 33 against 60 where they crowd that one and 40 against 46 where they are even.  With windows the
+    // longest list says little about the others: there even rows have to do without it in the first term.
     plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
                        65ull * R <= (any_streamed ? 38000ull : 13000ull) + 115ull * longest_list;
     // stream without histograms first when an even spread of the requests over the replicas would reject enough (never behind the
