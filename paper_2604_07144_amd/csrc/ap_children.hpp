@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kOccupancyThreads) void k_parent_occupancy(EvalPara
                 my_longest = max(my_longest, service);
             }
         }
-        my_longest = wave_max_u32(my_longest);
+        my_longest = wave_all_max(my_longest);
         if (lane == 0u && my_longest != 0u) atomicMax(&longest, my_longest);
         if (wv == 0u) carry[lane] = latest;
         __syncthreads();
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kOccupancyThreads) void k_parent_occupancy(EvalPara
         while (n_list >= kOccupancyTile) count_tile(kOccupancyTile, !(last_step && n_list == kOccupancyTile));
         if (last_step && n_list > 0u) count_tile(n_list, false);
     }
-    deepest = wave_max_u32(deepest);
+    deepest = wave_all_max(deepest);
     if (lane == 0u) atomicMax(&wg_deepest, deepest);
     __syncthreads();
     if (tid == 0u) {

@@ -89,16 +89,27 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v, uint32_t /*l
     return v;
 }
 
+// The sum over the lanes, as a uniform value, the same way: lane 63 of the scan has it.  (Six exchanges through the LDS crossbar,
+// one after the other, take longer than everything else a wavefront does for a short row.)
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-    for (uint32_t d = 32; d >= 1; d >>= 1) v += (uint32_t)__shfl_xor((int)v, d);
-    return v;
+    return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v, 0u), 63);
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (uint32_t d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d));
-    return v;
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
+    auto from_lane = [&](auto ctrl, auto rows) {
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+        v += ((unsigned long long)(uint32_t)hi << 32) | (uint32_t)lo;
+    };
+    using std::integral_constant;
+    from_lane(integral_constant<int, 0x111>{}, integral_constant<int, 0xF>{});
+    from_lane(integral_constant<int, 0x112>{}, integral_constant<int, 0xF>{});
+    from_lane(integral_constant<int, 0x114>{}, integral_constant<int, 0xF>{});
+    from_lane(integral_constant<int, 0x118>{}, integral_constant<int, 0xF>{});
+    from_lane(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});
+    from_lane(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63);
+    return ((unsigned long long)hi << 32) | lo;
 }
 
 // The maximum over the lanes, as a uniform value, on the vector ALU's cross-lane path: inside each row of 16 lanes, the last
@@ -111,12 +122,6 @@ __device__ __forceinline__ uint32_t wave_all_max(uint32_t v) {
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142 /* row_bcast:15 */, 0xA, 0xF, false));
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143 /* row_bcast:31 */, 0xC, 0xF, false));
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-    for (uint32_t d = 32; d >= 1; d >>= 1) v += (unsigned long long)__shfl_xor((long long)v, d);
-    return v;
 }
 
 // 4096-bin log-linear histogram map for values below 2^32.
@@ -236,7 +241,7 @@ __device__ __forceinline__ void finish_candidate(const EvalParams& p, uint32_t* 
     s_e2e = wave_sum_u64(s_e2e);
     s_ttft = wave_sum_u64(s_ttft);
     s_tpot = wave_sum_u64(s_tpot);
-    last_fin = wave_max_u32(last_fin);
+    last_fin = wave_all_max(last_fin);
     n_ok = wave_sum_u32(n_ok);
     n_rej = wave_sum_u32(n_rej);
     if (lane == 0) {

@@ -203,6 +203,12 @@ struct ap_workload {
     SplitPlan split_plan{};
 };
 
+typedef void (*stream_fn)(StreamParams, const uint16_t*, ap_metrics*, uint32_t, PendingWord);
+static stream_fn stream_kernel(bool settles, bool tabled) {
+    return settles ? (tabled ? k_stream_candidates<true, false> : k_stream_candidates<false, false>)
+                   : (tabled ? k_stream_candidates<true, true> : k_stream_candidates<false, true>);
+}
+
 typedef void (*split_fn)(SplitParams, const uint16_t*, uint32_t, uint32_t, uint32_t, PendingWord);
 static split_fn split_kernel(uint32_t hist_mode, int narrow, bool tabled) {
     static const split_fn variants[12] = {
@@ -331,9 +337,8 @@ static ap_status launch_stream(const ap_workload* w, const uint16_t* d_assign, u
     uint32_t waves = 4u;
     while (waves < kStreamMaxThreads / kWave && (uint64_t)C * waves * 2u <= (uint64_t)w->n_cu * 32u && w->R / 128u >= 8u * waves) waves *= 2u;
     const uint32_t grid = std::min(C, w->n_cu * 64u);
-    const auto kernel = w->stream_settles ? (w->tabled ? k_stream_candidates<true, false> : k_stream_candidates<false, false>)
-                                          : (w->tabled ? k_stream_candidates<true, true> : k_stream_candidates<false, true>);
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * kWave), w->stream_lds_bytes, stream, w->stream_params, d_assign, d_out, C, flags);
+    hipLaunchKernelGGL(stream_kernel(w->stream_settles, w->tabled), dim3(grid), dim3(waves * kWave),
+                       w->stream_lds_bytes + waves * kStreamLargeBytes, stream, w->stream_params, d_assign, d_out, C, flags);
     return hipGetLastError() == hipSuccess ? AP_OK : device_error();
 }
 
@@ -1031,6 +1036,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     sp.off_hist = off; off += align_up(total_bins * 4u, 16u);
     sp.off_acc = off;  off += 64u;
     if (off > 65536u) return AP_OK;
+    sp.off_large = off;                                      // behind them the wavefronts' buffers, as many as a call's workgroups have
     // one buffer: coefficients, kinds, window table, weights
     std::vector<uint32_t> tab(4u * kinds.size() + (M + 1u) + n_buckets + sample_weight.size(), 0u);
     for (size_t k = 0; k < kinds.size() && !tabled; ++k) {
@@ -1068,6 +1074,11 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     sp.all_within = highest[0] < ap_hist_bin(sp.slo_ttft) && highest[1] < ap_hist_bin(sp.slo_tpot) ? 1u : 0u;
     sp.penalty_bin = w->params.penalty_bin;
     sp.penalty = w->params.penalty;
+    constexpr uint32_t large = kStreamMaxThreads / kWave * kStreamLargeBytes;
+    if (off + large > 65536u &&
+        hipFuncSetAttribute(reinterpret_cast<const void*>(stream_kernel(settles, tabled)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            65536 + (int)large) != hipSuccess)
+        return device_error();
     w->stream_params = sp;
     w->stream_lds_bytes = off;
     w->stream = true;

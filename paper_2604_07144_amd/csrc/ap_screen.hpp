@@ -125,7 +125,7 @@ __global__ __launch_bounds__(kThreads) void k_nominal_metrics(EvalParams p, uint
     s_e2e = wave_sum_u64(s_e2e);
     s_ttft = wave_sum_u64(s_ttft);
     s_tpot = wave_sum_u64(s_tpot);
-    last_fin = wave_max_u32(last_fin);
+    last_fin = wave_all_max(last_fin);
     n_ok = wave_sum_u32(n_ok);
     if (lane == 0u) {
         atomicAdd(&g_acc[0], s_e2e);

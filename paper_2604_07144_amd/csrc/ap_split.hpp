@@ -409,7 +409,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
         s_e2e = wave_sum_u64(s_e2e);
         s_ttft = wave_sum_u64(s_ttft);
         s_tpot = wave_sum_u64(s_tpot);
-        last_fin = wave_max_u32(last_fin);
+        last_fin = wave_all_max(last_fin);
         if (p.all_within == 0u) n_ok = wave_sum_u32(n_ok);                          // else counted per wavefront already
         if (lane == 0u) {
             atomicAdd(&acc64[0], s_e2e);

@@ -27,9 +27,14 @@ namespace {
 // atomics per request, time per token on a handful of addresses).  A row that prefers the fast kinds has fewer than need_top
 // values there.  Its values are counted from the bin that enough requests reach on whichever kind (least[1]), where the p99
 // value always is.  On long rows a sample of the row, a request per thread, tells; where there is no sample, or it was wrong, the
-// row is read a second time.  4096 rows of 16384 requests on the fast third of 48 replicas take 132 us (231 without the
-// sample, 1009 when such rows went to the listed evaluation), even rows 144.  Bound by instruction issue: 67 vector and 55 scalar
-// instructions per 64 requests without counts.
+// row is read a second time.  (4096 rows of 16384 requests on the fast third of 48 replicas took 132 us with the sample, 231 without,
+// 1009 when such rows went to the listed evaluation; before the change of the next paragraph.)
+//
+// Bound by instruction issue, 38 vector and 32 scalar instructions per 64 requests without counts, so the common case is kept
+// short: in 128 requests that all exist and name a replica, which one packed compare per lane tells, nothing is tested
+// request by request, the two requests of a lane are added up together, and large values are set aside and counted 64 at a time.
+// Every request by the general form, its large values counted on the spot: 67 and 55 instructions, 136 us for 4096 rows of 16384
+// requests on 48 replicas of three kinds; 91 now.  (Two wavefronts per row instead of four, fewer instructions still, take 10 % longer.)
 struct StreamParams {
     const uint2* req8;            // [R + 1] {arrival, prompt | out << 16}
     const uint32_t* lo;           // [n_buckets] for rows that begin up to one position into their first 4-byte unit
@@ -49,10 +54,22 @@ struct StreamParams {
                                   //   of such requests has just need_top large values
     uint32_t penalty_bin;
     uint64_t penalty;
-    uint32_t off_coef, off_lo, off_cnt, off_hist, off_acc;   // byte offsets into dynamic LDS
+    uint32_t off_coef, off_lo, off_cnt, off_hist, off_acc, off_large;   // byte offsets into dynamic LDS
 };
 constexpr uint32_t kStreamMaxThreads = 1024;
 constexpr uint32_t kStreamWeight = 64;
+constexpr uint32_t kStreamLarge = 256;            // room for 63 requests with a large value that wait to be counted and the 128 of a step
+constexpr uint32_t kStreamLargeBytes = 3u * 4u * kStreamLarge;   // per wavefront
+
+// Two 16-bit ids, each cut down to `most`.
+__device__ __forceinline__ uint32_t both_below(uint32_t ids, uint32_t most) {
+    typedef uint16_t two_ids __attribute__((ext_vector_type(2)));
+    two_ids v, m = {(uint16_t)most, (uint16_t)most};
+    __builtin_memcpy(&v, &ids, 4);
+    v = __builtin_elementwise_min(v, m);
+    __builtin_memcpy(&ids, &v, 4);
+    return ids;
+}
 
 template <bool kTabled, bool kCounted>
 __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(StreamParams p, const uint16_t* __restrict__ assign,
@@ -68,35 +85,16 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_acc);   // e2e, ttft, tpot
     uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);     // latest finish, within objectives, rejected, windows failed, p99 bins[3], too few counted, the sample's weight
     const uint32_t tid = threadIdx.x, n_threads = blockDim.x, lane = tid & 63u, wv = wave_index(), n_waves = n_threads >> 6;
+    uint32_t* large = reinterpret_cast<uint32_t*>(lds + p.off_large + wv * kStreamLargeBytes);   // [3][kStreamLarge]
     const uint32_t R = p.R, M = p.M;
     const uint32_t hist_at[3] = {0u, p.n_bins[0], p.n_bins[0] + p.n_bins[1]};
     const uint32_t n_hist = hist_at[2] + p.n_bins[2], n_cnt = kCounted ? p.n_buckets * p.words : 0u;
-    for (uint32_t i = tid; i <= M; i += n_threads) kind_of[i] = p.kind[i];
-    for (uint32_t i = tid; i < p.n_kinds; i += n_threads) coef_of[i] = p.coef[i];
-    if (kCounted)
-        for (uint32_t i = tid; i < p.n_buckets; i += n_threads) lo_of[i] = (uint16_t)p.lo[i];
-
+    bool staged = false;
     uint32_t reading = 0;                                                    // 1: the row is read a second time
     for (uint32_t c = blockIdx.x; c < C;) {
         const uint16_t* row = assign + (size_t)c * R;
-        uint32_t weight = 0;
-        if (p.weight != nullptr && reading == 0u) weight = p.weight[min((uint32_t)row[(uint32_t)((uint64_t)tid * R / n_threads)], M)];
-        for (uint32_t i = tid; i < n_cnt; i += n_threads) cnt[i] = 0u;
-        for (uint32_t i = tid; i < n_hist; i += n_threads) hist[i] = 0u;
-        if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
-        __syncthreads();
-        if (p.weight != nullptr && reading == 0u) {
-            weight = wave_sum_u32(weight);
-            if (lane == 0u) atomicAdd(&acc32[8], weight);
-            __syncthreads();
-            reading = acc32[8] < n_threads * (kStreamWeight + kStreamWeight / 4u) ? 1u : 0u;   // the same word for every thread
-        }
-        const uint32_t least[3] = {p.least[reading][0], p.least[reading][1], p.least[reading][2]};
         const uint32_t a = (uint32_t)(reinterpret_cast<uintptr_t>(row) >> 1) & 1u, n = R + a;   // positions, as in the counting screen
         const uint32_t n_steps = (n + 127u) / 128u;
-        unsigned long long s_e2e = 0, s_ttft = 0, s_tpot = 0;
-        uint32_t t_e2e = 0, t_ttft = 0, t_tpot = 0, last_fin = 0, n_ok = 0, n_rej = 0;  // a wavefront's sums of up to four steps: 8 values below 2^28
-
         // A lane takes two requests of every 128; the wavefronts take the steps in turn.  The next step's ids and records
         // are requested before the current one is worked on.
         typedef uint32_t two_records __attribute__((ext_vector_type(4), aligned(8)));
@@ -108,9 +106,10 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
         auto fetch = [&](uint32_t s) {
             Step st;
             const uint32_t pos = s * 128u + 2u * lane;
-            if (whole(s)) {
-                st.ids = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(row - a + pos));
-                st.rec = *reinterpret_cast<const two_records*>(p.req8 + (pos - a));
+            if (whole(s)) {                                                  // uniform bases and offsets that stay: no address arithmetic per lane
+                st.ids = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(
+                    reinterpret_cast<const char*>(row + ((size_t)s * 128u - a)) + 4u * lane));
+                st.rec = *reinterpret_cast<const two_records*>(reinterpret_cast<const char*>(p.req8 + ((size_t)s * 128u - a)) + 16u * lane);
             } else {                                                         // positions outside the row: an id no replica has, told apart below
                 const bool in0 = pos >= a && pos < n, in1 = pos + 1u < n;
                 const uint2 r0 = in0 ? p.req8[pos - a] : make_uint2(0u, 0u), r1 = in1 ? p.req8[pos + 1u - a] : make_uint2(0u, 0u);
@@ -119,59 +118,118 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
             }
             return st;
         };
-        auto score = [&](auto whole_tag, const Step& st, uint32_t s) {
-            constexpr bool kWhole = decltype(whole_tag)::value;
+        Step next{};
+        if (wv < n_steps) next = fetch(wv);
+        uint32_t weight = 0;
+        if (p.weight != nullptr && reading == 0u) weight = p.weight[min((uint32_t)row[(uint32_t)((uint64_t)tid * R / n_threads)], M)];
+        if (!staged) {                                                       // behind the row's first loads: a short call waits once
+            for (uint32_t i = tid; i <= M; i += n_threads) kind_of[i] = kTabled ? p.kind[i] : p.off_coef + p.kind[i] * 16u;
+            for (uint32_t i = tid; i < p.n_kinds; i += n_threads) coef_of[i] = p.coef[i];
+            if (kCounted)
+                for (uint32_t i = tid; i < p.n_buckets; i += n_threads) lo_of[i] = (uint16_t)p.lo[i];
+            staged = true;
+        }
+        for (uint32_t i = tid; i < n_cnt; i += n_threads) cnt[i] = 0u;
+        for (uint32_t i = tid; i < n_hist; i += n_threads) hist[i] = 0u;
+        if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
+        __syncthreads();
+        if (p.weight != nullptr && reading == 0u) {
+            weight = wave_sum_u32(weight);
+            if (lane == 0u) atomicAdd(&acc32[8], weight);
+            __syncthreads();
+            reading = acc32[8] < n_threads * (kStreamWeight + kStreamWeight / 4u) ? 1u : 0u;   // the same word for every thread
+        }
+        const uint32_t least[3] = {p.least[reading][0], p.least[reading][1], p.least[reading][2]};
+        unsigned long long s_e2e = 0, s_ttft = 0, s_tpot = 0;
+        uint32_t t_e2e = 0, t_ttft = 0, t_tpot = 0, last_fin = 0, n_ok = 0, n_rej = 0;  // a wavefront's sums of up to four steps: 8 values below 2^28
+
+        // Large values go through a buffer of the wavefront's own and are counted 64 at a time: with one request in twenty large some
+        // lane of nearly every step has one, and counted on the spot each metric's bin costs every lane its instructions.
+        uint32_t n_large = 0, n_counted_large = 0;
+        auto count_large = [&](uint32_t n) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < n) {
+                const uint32_t at = (n_counted_large + lane) & (kStreamLarge - 1u);
+                const uint32_t value[3] = {large[at], large[kStreamLarge + at], large[2u * kStreamLarge + at]};
+#pragma unroll
+                for (uint32_t h = 0; h < 3u; ++h)
+                    if (value[h] >= least[h]) atomicAdd(&hist[hist_at[h] + min(hist_bin_u32(value[h]) - p.from[h], p.n_bins[h] - 1u)], 1u);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            n_counted_large += n;
+        };
+        auto keep_large = [&](unsigned long long all, uint32_t prefill, uint32_t tpot, uint32_t e2e) {
+            if (all == 0ull) return;
+            if (__builtin_amdgcn_inverse_ballot_w64(all)) {
+                const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(all >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)all, n_large)) &
+                                    (kStreamLarge - 1u);
+                large[at] = prefill;
+                large[kStreamLarge + at] = tpot;
+                large[2u * kStreamLarge + at] = e2e;
+            }
+            n_large += (uint32_t)__popcll(all);
+        };
+        // kPlain: all 128 requests exist and name a replica.
+        uint32_t prefill[2], tpot[2], e2e[2];
+        unsigned long long is_large[2];                                      // which lanes' requests
+        // (by LDS address, which begins at 0 with the kinds: through the array's name every access costs an addition of its base)
+        typedef __attribute__((address_space(3))) const uint32_t lds_word;
+        typedef uint32_t four_words __attribute__((ext_vector_type(4)));
+        typedef __attribute__((address_space(3))) const four_words lds_four;
+        lds_word* const kind_at = reinterpret_cast<lds_word*>(0u);
+        auto coef_from = [&](uint32_t at) {
+            const four_words v = *reinterpret_cast<lds_four*>(at);
+            return make_uint4(v.x, v.y, v.z, v.w);
+        };
+        auto score = [&](auto plain_tag, const Step& st, uint32_t s, uint32_t ids) {
+            constexpr bool kPlain = decltype(plain_tag)::value;
             const uint32_t pos = s * 128u + 2u * lane;
             uint32_t* mine = kCounted ? cnt + (pos >> p.w_log2) * p.words : nullptr;   // w is even: both requests are in one bucket
-            const uint32_t id[2] = {(uint32_t)min(st.ids & 0xFFFFu, M), (uint32_t)min(st.ids >> 16, M)};
-            const uint32_t kind[2] = {kind_of[id[0]], kind_of[id[1]]};
-            const bool in[2] = {kWhole || (pos >= a && pos < n), kWhole || pos + 1u < n};
-            uint2 cost[2];
-            if (kTabled) {
+            const uint32_t id[2] = {ids & 0xFFFFu, ids >> 16};
+            const uint32_t kind[2] = {*(kind_at + id[0]), *(kind_at + id[1])};
+            const bool in[2] = {kPlain || (pos >= a && pos < n), kPlain || pos + 1u < n};
 #pragma unroll
-                for (uint32_t e = 0; e < 2u; ++e) {
-                    const uint32_t r = kWhole ? pos + e - a : (in[e] ? pos + e - a : 0u);
-                    cost[e] = p.tab_pair[kind[e] + r];
+            for (uint32_t e = 0; e < 2u; ++e) {
+                const uint32_t lens = e ? st.rec.w : st.rec.y, len = lens >> 16;
+                if (kTabled) {
+                    const uint32_t r = kPlain ? pos + e - a : (in[e] ? pos + e - a : 0u);
+                    const uint2 cost = p.tab_pair[kind[e] + r];
+                    prefill[e] = cost.x;
+                    tpot[e] = cost.y;
+                } else {
+                    const uint32_t prompt = lens & 0xFFFFu;
+                    const uint4 co = coef_from(kind[e]);
+                    prefill[e] = co.x + __umul24(co.y, prompt);              // the host keeps all factors below 2^24
+                    tpot[e] = co.z + __umul24(co.w, (prompt + 1023u) >> 10);
                 }
+                e2e[e] = prefill[e] + __umul24(len, tpot[e]);
             }
 #pragma unroll
             for (uint32_t e = 0; e < 2u; ++e) {
-                if (!kWhole && !in[e]) continue;
-                if (kCounted) atomicAdd(&mine[id[e] >> 2], 1u << ((id[e] & 3u) * 8u));
-                else n_rej += id[e] >= M ? 1u : 0u;
-                const uint32_t arrival = e ? st.rec.z : st.rec.x, lens = e ? st.rec.w : st.rec.y;
-                const uint32_t prompt = lens & 0xFFFFu, len = lens >> 16;
-                uint32_t prefill, tpot;
-                if (kTabled) {
-                    prefill = cost[e].x;
-                    tpot = cost[e].y;
-                } else {
-                    const uint4 co = coef_of[kind[e]];
-                    prefill = co.x + __umul24(co.y, prompt);                 // the host keeps all factors below 2^24
-                    tpot = co.z + __umul24(co.w, (prompt + 1023u) >> 10);
-                }
-                uint32_t e2e = prefill + __umul24(len, tpot);
-                if (id[e] >= M) prefill = tpot = e2e = 0u;                   // rejected: adds nothing here
-                else last_fin = max(last_fin, arrival + e2e);
-                t_ttft += prefill;
-                t_e2e += e2e;
-                t_tpot += tpot;
-                if (p.all_within == 0u && id[e] < M) n_ok += (prefill <= p.slo_ttft && tpot <= p.slo_tpot) ? 1u : 0u;
-                if (prefill >= least[0] || tpot >= least[1] || e2e >= least[2]) {
-                    if (prefill >= least[0]) atomicAdd(&hist[hist_at[0] + min(hist_bin_u32(prefill) - p.from[0], p.n_bins[0] - 1u)], 1u);
-                    if (tpot >= least[1]) atomicAdd(&hist[hist_at[1] + min(hist_bin_u32(tpot) - p.from[1], p.n_bins[1] - 1u)], 1u);
-                    if (e2e >= least[2]) atomicAdd(&hist[hist_at[2] + min(hist_bin_u32(e2e) - p.from[2], p.n_bins[2] - 1u)], 1u);
-                }
+                const bool known = kPlain || (in[e] && id[e] < M);
+                if (kCounted && (kPlain || in[e])) atomicAdd(&mine[id[e] >> 2], 1u << ((id[e] & 3u) * 8u));
+                if (!kCounted && !kPlain) n_rej += in[e] && id[e] >= M ? 1u : 0u;
+                if (!known) prefill[e] = tpot[e] = e2e[e] = 0u;              // rejected: adds nothing here
+                t_ttft += prefill[e];
+                t_e2e += e2e[e];
+                t_tpot += tpot[e];
+                if (p.all_within == 0u) n_ok += (known && prefill[e] <= p.slo_ttft && tpot[e] <= p.slo_tpot) ? 1u : 0u;
+                is_large[e] = __ballot(prefill[e] >= least[0]) | __ballot(tpot[e] >= least[1]) | __ballot(e2e[e] >= least[2]);
+                if (!kPlain) is_large[e] &= __ballot(known);
+                if (!kPlain && known) last_fin = max(last_fin, (e ? st.rec.z : st.rec.x) + e2e[e]);
             }
+            if (kPlain) last_fin = max(last_fin, max(st.rec.x + e2e[0], st.rec.z + e2e[1]));
         };
         if (wv < n_steps) {
-            Step next = fetch(wv);
             uint32_t turn = 0;
             for (uint32_t s = wv; s < n_steps; s += n_waves) {
                 const Step now = next;
                 if (s + n_waves < n_steps) next = fetch(s + n_waves);
-                if (whole(s)) score(std::true_type{}, now, s);
-                else score(std::false_type{}, now, s);
+                if (whole(s) && __ballot(both_below(now.ids, M - 1u) != now.ids) == 0ull) score(std::true_type{}, now, s, now.ids);
+                else score(std::false_type{}, now, s, both_below(now.ids, M));
+#pragma unroll
+                for (uint32_t e = 0; e < 2u; ++e) keep_large(is_large[e], prefill[e], tpot[e], e2e[e]);
+                while (n_large - n_counted_large >= kWave) count_large(kWave);   // leaves 63 at most
                 if ((++turn & 3u) == 0u) {
                     s_e2e += t_e2e;
                     s_ttft += t_ttft;
@@ -179,10 +237,11 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
                     t_e2e = t_ttft = t_tpot = 0u;
                 }
             }
+            if (n_large != n_counted_large) count_large(n_large - n_counted_large);
             s_e2e = wave_sum_u64(s_e2e + t_e2e);
             s_ttft = wave_sum_u64(s_ttft + t_ttft);
             s_tpot = wave_sum_u64(s_tpot + t_tpot);
-            last_fin = wave_max_u32(last_fin);
+            last_fin = wave_all_max(last_fin);
             if (p.all_within == 0u) n_ok = wave_sum_u32(n_ok);
             if (!kCounted) n_rej = wave_sum_u32(n_rej);
             if (lane == 0u) {

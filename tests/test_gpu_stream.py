@@ -305,3 +305,23 @@ def test_one_workload_between_slot_counts():
                                          tr.penalty_us)
             assert g.route(30)["stream"] == stream
             assert_same(g.eval(rows), oracle_for(tr, B=B).eval_batch(rows, nthreads=8), f"B={B} tabled={tabled}")
+
+
+@pytest.mark.parametrize("R,M,B", [(64, 3, 8), (128, 3, 8), (1000, 7, 12), (9001, 7, 12)])
+@pytest.mark.parametrize("few", [False, True])
+def test_steps_full_of_large_values_and_ids_at_the_edge(R, M, B, few):
+    """Equal requests: all values are large, or all but a handful are, so that the buffer of large values is filled by every step;
+    ids M - 1, M and M + 1 in whole steps."""
+    rng = np.random.default_rng(R)
+    prompt, out = np.full(R, 700), np.full(R, 90)
+    if few:
+        prompt[rng.random(R) < 0.02] = 3000
+    arrival = np.cumsum(rng.integers(10_000, 60_000, R)).astype(np.uint64)
+    tr = traces.custom_trace(arrival, prompt, out, [KINDS[m % 2] for m in range(M)], B=B)
+    rows = np.tile((np.arange(R) % M).astype(np.uint16), (5, 1))
+    rows[1], rows[2, R // 2], rows[3, R // 2] = M - 1, M, M + 1
+    rows[4, ::3] = M
+    with GpuWorkload(tr) as g:
+        assert g.route(5)["stream"] != 0
+        got = g.eval(rows)
+    assert_same(got, oracle_for(tr).eval_batch(rows, nthreads=4), f"R={R} few={few}")
