@@ -2010,6 +2010,8 @@ struct ap_agentic {
     uint32_t n_cu = 0;
     uint32_t chunks = 0;              // which kernel
     uint32_t waves = 0;               // wavefronts (candidates) per workgroup
+    uint32_t row_waves = 0, row_lds_bytes = 0;   // k_agentic_rows; 0: it does not apply
+    uint32_t wave_plans = 0, row_plans = 0;      // how many plans a compute unit's LDS holds, by either kernel
     void* d_block = nullptr;          // one allocation behind all the tables
 };
 
@@ -2122,20 +2124,31 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
         std::vector<uint32_t> by_arrival(W);
         for (uint32_t w = 0; w < W; ++w) by_arrival[w] = w;
         std::stable_sort(by_arrival.begin(), by_arrival.end(), [&](uint32_t x, uint32_t y) { return rel[x] < rel[y]; });
-        std::vector<uint16_t> order(by_arrival.begin(), by_arrival.end()), wf16(wf, wf + K), root_first(W + 1u, 0u), root;
-        for (uint32_t k = 0; k < K; ++k)
-            if (n_pred_of[k] == 0u) ++root_first[wf[k] + 1u];
-        for (uint32_t w = 0; w < W; ++w) root_first[w + 1u] = (uint16_t)(root_first[w + 1u] + root_first[w]);
-        root.assign(std::max<uint32_t>(1u, root_first[W]), 0u);
-        std::vector<uint16_t> fill(root_first.begin(), root_first.end() - 1);
+        std::vector<uint16_t> root;                              // calls without predecessors, workflow by workflow in order of arrival
+        std::vector<uint32_t> start(4u * ((size_t)W + 1u), 0u), n_roots(W, 0u), fill(W, 0u);
+        for (uint32_t k = 0; k < K; ++k) n_roots[wf[k]] += n_pred_of[k] == 0u ? 1u : 0u;
+        uint32_t n_root = 0;
+        for (uint32_t i = 0; i < W; ++i) {
+            const uint32_t w = by_arrival[i];
+            start[4u * i] = rel[w];
+            start[4u * i + 1u] = fill[w] = n_root;
+            start[4u * i + 2u] = n_roots[w];
+            start[4u * i + 3u] = w;
+            n_root += n_roots[w];
+        }
+        start[4u * W] = kNever;
+        root.assign(std::max(1u, n_root), 0u);
         for (uint32_t k = 0; k < K; ++k)
             if (n_pred_of[k] == 0u) root[fill[wf[k]]++] = (uint16_t)k;
         std::vector<uint16_t> succ16(succ.begin(), succ.begin() + std::max(1u, succ_first[K]));
         std::vector<unsigned char> left(n_pred_of.begin(), n_pred_of.end());
-        std::vector<uint32_t> lens(2u * (size_t)K);
+        std::vector<uint32_t> info(4u * (size_t)K);
         for (uint32_t k = 0; k < K; ++k) {
-            lens[2u * k] = in_len[k];
-            lens[2u * k + 1u] = out_len[k];
+            info[4u * k] = in_len[k];
+            info[4u * k + 1u] = out_len[k];
+            const uint32_t n = succ_first[k + 1u] - succ_first[k];
+            info[4u * k + 2u] = n == 1u ? succ[succ_first[k]] : succ_first[k];
+            info[4u * k + 3u] = wf[k] | (n << 16);               // both at most 1023
         }
         auto put = [&](const void* src, size_t n) {
             const uint32_t at = (uint32_t)blob.size();
@@ -2143,12 +2156,9 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
             std::memcpy(blob.data() + at, src, n);
             return at;
         };
-        p.o_lens = put(lens.data(), 8u * (size_t)K);
+        p.o_info = put(info.data(), 4u * info.size());
+        p.o_start = put(start.data(), 4u * start.size());
         p.o_arrival = put(rel.data(), 4u * (size_t)W);
-        p.o_succ_first = put(succ_first.data(), 4u * ((size_t)K + 1u));
-        p.o_wf = put(wf16.data(), 2u * (size_t)K);
-        p.o_order = put(order.data(), 2u * (size_t)W);
-        p.o_root_first = put(root_first.data(), 2u * ((size_t)W + 1u));
         p.o_root = put(root.data(), 2u * root.size());
         p.o_n_pred = put(left.data(), left.size());
         p.blob_bytes = (uint32_t)blob.size();
@@ -2205,7 +2215,36 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
         a->waves = kAgenticWaves;
         while (a->waves > 1u && p.blob_bytes + a->waves * p.wave_bytes > (uint32_t)lds_cap) a->waves /= 2u;
         a->lds_bytes = p.blob_bytes + a->waves * p.wave_bytes;
+        a->wave_plans = (uint32_t)lds_cap / a->lds_bytes * a->waves;
         a->n_cu = (uint32_t)n_cu;
+        // a row of lanes per plan: as many plans per compute unit as its LDS takes, in workgroups of up to kAgenticWaves wavefronts
+        off = align_up(std::max(8u * W, 4u * align_up(K, kRowLanes)), 16u);
+        p.g_call = off;    off += align_up(4u * K, 16u);
+        p.g_call_of = off; off += align_up(2u * K, 16u);
+        p.g_left = off;    off += align_up(K, 16u);
+        p.g_comp = off;    off += align_up(4u * W, 16u);
+        p.g_failed = off;  off += align_up((W + 31u) / 32u * 4u, 16u);
+        p.g_queue = off;   off += (P + Q) * ((K + 31u) / 32u) * 4u;
+        p.g_bytes = align_up(off, 16u);
+        bool by_rows = P <= kRowLanes && Q <= kRowLanes && p.o_succ != 0u;   // it multiplies with 24-bit factors
+        for (uint32_t k = 0; k < K; ++k) by_rows = by_rows && in_len[k] < (1u << 24) && out_len[k] < (1u << 24);
+        for (uint32_t i = 0; i < P; ++i) by_rows = by_rows && pb[i] < (1u << 24);
+        for (uint32_t i = 0; i < Q; ++i) by_rows = by_rows && qd[i] < (1u << 24) && (uint64_t)qc[i] + ((uint64_t)qd[i] << 14) < (1u << 24);
+        if (by_rows) {
+            uint32_t most = 0;
+            for (uint32_t waves = kAgenticWaves; waves >= 1u; waves /= 2u) {
+                const uint32_t bytes = p.blob_bytes + waves * (kWave / kRowLanes) * p.g_bytes;
+                const uint32_t plans = bytes <= (uint32_t)lds_cap ? (uint32_t)lds_cap / bytes * waves : 0u;
+                if (plans <= most) continue;
+                most = plans;
+                a->row_waves = waves;
+                a->row_plans = plans * (kWave / kRowLanes);
+                a->row_lds_bytes = bytes;
+            }
+        }
+        if (a->row_waves != 0u && hipFuncSetAttribute(reinterpret_cast<const void*>(&k_agentic_rows), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                      (int)a->row_lds_bytes) != hipSuccess)
+            st = AP_ERR_DEVICE;
         if (a->lds_bytes > (uint32_t)lds_cap) st = AP_ERR_RANGE;
         else if (hipFuncSetAttribute(reinterpret_cast<const void*>(agentic_kernel(a->chunks)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)a->lds_bytes) != hipSuccess)
@@ -2220,11 +2259,26 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
     return AP_OK;
 }
 
+// Four plans per wavefront (k_agentic_rows) where the wavefronts of single plans would crowd the chip or not all be in service at
+// once, as long as all plans of the other form are: that one takes as long for one plan as for all that are resident.  64
+// workflows on 4 + 4 instances, wavefronts of single plans against four: 1024 plans 620 and 900 us, 4608 880 and 1000, 5632 990 and
+// 1000, 6200 1306 and 1003, 8192 1388 and 1011; 8 workflows, 5632 plans 155 and 149 us, 8192 215 and 152.
+static bool agentic_by_rows(const ap_agentic* a, uint32_t C) {
+    return C > a->n_cu * std::min(22u, a->wave_plans) && C <= a->n_cu * a->row_plans;
+}
+
 ap_status ap_agentic_eval(const ap_agentic* a, const uint16_t* d_prefill, const uint16_t* d_decode, const uint32_t* d_key,
                           uint32_t C, ap_agentic_metrics* d_out, void* hip_stream) {
     if (!a) return AP_ERR_INVALID;
     if (C == 0) return AP_OK;
     if (!d_prefill || !d_decode || !d_key || !d_out) return AP_ERR_INVALID;
+    if (agentic_by_rows(a, C)) {
+        const uint32_t plans = a->row_waves * (kWave / kRowLanes);
+        hipLaunchKernelGGL(k_agentic_rows, dim3(std::min((C + plans - 1u) / plans, a->n_cu * 64u)), dim3(a->row_waves * kWave), a->row_lds_bytes,
+                           static_cast<hipStream_t>(hip_stream), a->params, d_prefill, d_decode, d_key, d_out, C);
+        if (hipGetLastError() != hipSuccess) return device_error();
+        return AP_OK;
+    }
     const uint32_t blocks = std::min((C + a->waves - 1u) / a->waves, a->n_cu * 64u);
     hipLaunchKernelGGL(agentic_kernel(a->chunks), dim3(blocks), dim3(a->waves * kWave), a->lds_bytes,
                        static_cast<hipStream_t>(hip_stream), a->params, d_prefill, d_decode, d_key, d_out, C);

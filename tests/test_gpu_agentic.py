@@ -151,3 +151,26 @@ def test_hundreds_in_service_that_end_together(decode_us, same_length):
     pre, dec, key = traces.draw_agentic_candidates(5, 10, K, 64, 8, key_range=50, bad_ids=True)
     pre[:5] = pre[:5] % 64
     both(wl, pre, dec, key, f"decode {decode_us} same {same_length}")
+
+
+@pytest.mark.parametrize("W,P,Q,capacity,rate,bad_ids,C", [
+    (8, 4, 4, 6000, 60.0, False, 6001),           # a last wavefront with one plan
+    (20, 1, 16, 16384, 2000.0, True, 5702),       # all in service at once on one prefill instance, some calls name no instance
+    (20, 16, 1, 1200, 2000.0, True, 5703),        # calls that never fit
+    (64, 16, 16, 60000, 5000.0, True, 5633),      # more calls decode at once than there are slots
+    (3, 2, 3, 3000, 20.0, False, 8192),           # fewer calls than a row has lanes
+    (60, 4, 4, 6000, 60.0, False, 5634),          # keys with many ties
+])
+def test_four_plans_per_wavefront(W, P, Q, capacity, rate, bad_ids, C):
+    """Enough plans that they share wavefronts; the oracle looks at some of them, the first and the last among them."""
+    wl = traces.make_agentic(W, W, P=P, Q=Q, capacity=capacity, rate=rate)
+    if P == 16 and Q == 16:                       # decoding takes long, so that calls pile up
+        wl = dict(wl, qc=np.full(Q, 4000, dtype=np.uint32))
+    K = len(wl["wf"])
+    assert K <= 340
+    pre, dec, key = traces.draw_agentic_candidates(C, C, K, P, Q, key_range=1 << 20 if W < 60 else 9, bad_ids=bad_ids)
+    got = gpu_eval(wl, pre, dec, key)
+    some = np.unique(np.concatenate([np.arange(5), np.arange(5, C - 5, C // 30), np.arange(C - 5, C)]))
+    want = AgenticOracle.from_workload(wl).eval_batch(pre[some], dec[some], key[some])
+    for i, c in enumerate(some):
+        assert got[c].tolist() == want[i].tolist(), (c, got[c], want[i])
