@@ -319,7 +319,7 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         // the list replay: where most candidates are settled by penalty, those go through the variant that leaves no bins, and
         // the wavefronts of the other variant find the few that remain
         if (sp.n_queues != 0u) {
-            const uint32_t groups = sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads);
+            const uint32_t groups = align_up(sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads), sp.even_lists ? kXcds : 1u);
             const bool lean = plan.expect_lazy;
             if (lean) hipLaunchKernelGGL(replay_lean, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, 1u);
             hipLaunchKernelGGL(replay_bins, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, lean ? 2u : 0u);
@@ -713,6 +713,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.n_list_tiles = (longest_list + kTile - 1u) / kTile;
     sp.tile_cap = align_up(std::min(kTile, R) + 7u * std::min(M, std::min(kTile, R)), 8u);
     sp.n_queues = (uint32_t)order.size();
+    sp.even_lists = sp.n_queues == M && queue[order.front()].i_list == queue[order.back()].i_list ? 1u : 0u;
     sp.slo_ttft = w->params.slo_ttft;
     sp.slo_tpot = w->params.slo_tpot;
     // The p99 values are the penalty latency once R - k99 + 1 requests are rejected, if no served latency can

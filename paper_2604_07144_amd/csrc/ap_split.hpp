@@ -110,6 +110,7 @@ struct SplitParams {
     uint32_t any_streamed;                        // some replica has a streamed part
     uint32_t R, M, B, key_bits;
     uint32_t n_tiles, n_list_tiles, tile_cap, n_queues;
+    uint32_t even_lists;                          // every replica has a list, and all are equally long
     uint32_t slo_ttft, slo_tpot;
     uint32_t lazy_from;                           // rejected requests from which the p99 values are the penalty; kNever: never
     uint32_t all_within;                          // no request's prefill or time per token can exceed the objectives
@@ -603,11 +604,21 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // drained and on a light trace.  Together with bins in one word instead of two and none below the bins that a p99 value can
 // reach, 1024 rows of 131072 requests on 128 crowded replicas of 64 slots take 1226 us instead of 1569 (and k_merge_candidates 340
 // instead of 803, before the change described there); on light traces and odd B 1.1 to 1.5 times less.
+// Loads run ahead: a lane's descriptors a stage, its next block of eight entries a block, also into the next tile, and the
+// records of a stage four per thread at a time; a block's last bins are stored behind the wait for the next one.  A register whose
+// load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as one vector
+// and the empty asm where it is waited for.  A pair of steps that no lane needs is left out.  Where all lists are
+// as long as the trace, neighbouring replicas share an XCD, whose L2 then combines their bins and runs.  Together: 1024 rows of
+// 131072 requests on 128 crowded replicas 1190 to 983 us (bound by the bins' 16-byte stores, a third of it, and by memory waits at two
+// wavefronts per SIMD; without medians it takes as long), 3001 rows of 20011 requests on 50 replicas, half of which come and go,
+// 184 to 168 us, and 4096 rows of 32768 on 64 crowded replicas 462 to 445 us.
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
 constexpr uint32_t kListWaves = 4;
 constexpr uint32_t kReplayListThreads = kListWaves * kWave;
+constexpr uint32_t kXcds = 8;                     // workgroups go to them in turn
 constexpr uint32_t kReplayTiles = 2;              // tiles staged at a time: 32 KiB of records per workgroup
+constexpr uint32_t kStageAtOnce = 4;
 constexpr uint32_t kStagedTile = kTile + 1u;      // a tile's records, then the one that padding names
 
 __device__ __forceinline__ uint32_t bin_above(uint32_t v, uint32_t least_us, uint32_t least_bin) {
@@ -620,13 +631,23 @@ __device__ __forceinline__ void add_wide(uint32_t& lo, uint32_t& hi, uint32_t v)
 }
 
 template <uint32_t kSlots, uint32_t kBins_>
-__global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 4 : 5) void k_replay_lists(SplitParams p, uint32_t n_cand, uint32_t which) {
+__global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_replay_lists(SplitParams p, uint32_t n_cand, uint32_t which) {
     __shared__ uint4 recs[kReplayTiles * kStagedTile];                              // {arrival, prefill, decode, tpot}
+    __shared__ uint32_t goes_on[kListWaves];                                        // the wavefront has a lane with something to replay
     if (split_nothing_pending(p)) return;
     const uint32_t tid = threadIdx.x;
     const uint32_t n_blocks = (n_cand + kReplayListThreads - 1u) / kReplayListThreads;
-    const uint32_t m = p.order[blockIdx.x / n_blocks];
-    const uint32_t cb = (blockIdx.x % n_blocks) * kReplayListThreads + tid;
+    // Longest lists first; where all are as long as the trace, replicas next to each other and the same candidates on one XCD: their runs
+    // share cache lines, and so do the bins they leave.
+    uint32_t at_queue = blockIdx.x / n_blocks, at_block = blockIdx.x % n_blocks;
+    if (p.even_lists != 0u) {
+        const uint32_t job = blockIdx.x % kXcds * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+        at_queue = job % p.n_queues;
+        at_block = job / p.n_queues;
+        if (at_block >= n_blocks) return;
+    }
+    const uint32_t m = p.order[at_queue];
+    const uint32_t cb = at_block * kReplayListThreads + tid;
     bool live = cb < n_cand && split_wanted(p, cb);
     const uint32_t flags = live ? p.part[cb].flags : 0u;
     const bool lazy = (flags & kFlagLazy) != 0u;
@@ -653,48 +674,100 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 4 : 5) void k_re
 
     const uint32_t n_t = (q.i_list + kTile - 1u) / kTile;
     uint32_t j0 = 0;
+    const size_t desc_at = (size_t)(live ? cb : 0u) * p.n_list_tiles;
+    auto desc_of = [&](uint32_t j) { return live && j < n_t ? p.desc[(desc_at + j) * (p.M + 1u) + m] : 0u; };
+    auto run_of = [&](uint32_t d, uint32_t& count) {                                // a descriptor that was never written that way lists nothing
+        const uint32_t first = d & 0xFFFFu;
+        count = ((first & 7u) != 0u) | (first + (((d >> 16) + 7u) & ~7u) > p.tile_cap) ? 0u : d >> 16;
+        return first;
+    };
+    typedef uint32_t four_words __attribute__((ext_vector_type(4)));
+    // (block b of a run, or where there is none the tile's first: no branches around the loads)
+    auto block_of = [&](uint32_t d, uint32_t j, uint32_t b) {
+        uint32_t count;
+        const uint32_t first = run_of(d, count);
+        return *reinterpret_cast<const four_words*>(p.lists + (desc_at + min(j, n_t - 1u)) * p.tile_cap + (8u * b < count ? first + 8u * b : 0u));
+    };
+    static_assert(kReplayTiles == 2u, "descriptors of a stage and of the next one");
+    const uint4 padding = make_uint4(kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u);
+    uint32_t d_here[2], d_next[2] = {desc_of(0u), desc_of(1u)};
+    four_words e_next = {};                                                         // the block after the one in hand
+    if (n_t != 0u) e_next = block_of(d_next[0], 0u, 0u);
+    // Bins of the second half of a block are stored once the next block is there: waiting for that block waits for stores as well.
+    uint32_t held[kBins_ == 2u ? 8u : 4u];
+    size_t held_at = 0;
+    bool holds = false, any_held = false;                                           // this lane; the wavefront
+    auto store_bins = [&](const uint32_t* v, size_t at) {
+        if (kBins_ == 2u) {
+            uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + at);
+            dst[0] = make_uint4(v[0], v[1], v[2], v[3]);
+            dst[1] = make_uint4(v[4 % (kBins_ == 2u ? 8 : 4)], v[5 % (kBins_ == 2u ? 8 : 4)], v[6 % (kBins_ == 2u ? 8 : 4)], v[7 % (kBins_ == 2u ? 8 : 4)]);
+        } else {
+            *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + at) = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    };
+    auto store_held = [&] {
+        if (kBins_ == 0u || !any_held) return;
+        if (holds) store_bins(held, held_at);
+        holds = any_held = false;
+    };
     for (; j0 < n_t; j0 += kReplayTiles) {
         const uint32_t r0 = j0 * kTile, n = min(kReplayTiles * kTile, p.R - r0);
-        // also: the last stage's records were read
-        if (__syncthreads_or(live && (s[0] < q.t_off || with_hist) ? 1 : 0) == 0) break;
-        for (uint32_t i = tid; i < n; i += kReplayListThreads) {
-            const uint2 rq = p.req8[r0 + i];
-            const uint32_t prompt = rq.y & 0xFFFFu, out = rq.y >> 16;
-            uint32_t prefill, tpot;
+        if ((tid & 63u) == 0u) goes_on[wave_index()] = 0u;
+        if (__ballot(live && (s[0] < q.t_off || with_hist)) != 0ull && (tid & 63u) == 0u) goes_on[wave_index()] = 1u;
+        __syncthreads();                                                            // also: the last stage's records were read
+        uint32_t any = 0u;
+#pragma unroll
+        for (uint32_t ww = 0; ww < kListWaves; ++ww) any |= goes_on[ww];
+        if (__builtin_amdgcn_readfirstlane((int)any) == 0) break;
+        d_here[0] = d_next[0];
+        d_here[1] = d_next[1];
+        // several records per thread at a time, requested together
+        for (uint32_t i0 = tid; i0 < n; i0 += kStageAtOnce * kReplayListThreads) {
+            uint2 rq[kStageAtOnce], cost[kStageAtOnce];
+#pragma unroll
+            for (uint32_t k = 0; k < kStageAtOnce; ++k) rq[k] = p.req8[r0 + min(i0 + k * kReplayListThreads, n - 1u)];
             if (p.tab_pair != nullptr) {
-                const uint2 cost = p.tab_pair[q.a + r0 + i];
-                prefill = cost.x;
-                tpot = cost.y;
+#pragma unroll
+                for (uint32_t k = 0; k < kStageAtOnce; ++k) cost[k] = p.tab_pair[q.a + r0 + min(i0 + k * kReplayListThreads, n - 1u)];
             } else {
-                prefill = q.a + __umul24(q.b, prompt);                              // the host keeps all factors below 2^24
-                tpot = q.c + __umul24(q.d, (prompt + 1023u) >> 10);
+#pragma unroll
+                for (uint32_t k = 0; k < kStageAtOnce; ++k) {
+                    const uint32_t prompt = rq[k].y & 0xFFFFu;
+                    cost[k] = make_uint2(q.a + __umul24(q.b, prompt),               // the host keeps all factors below 2^24
+                                         q.c + __umul24(q.d, (prompt + 1023u) >> 10));
+                }
             }
-            recs[i + i / kTile] = make_uint4(rq.x, prefill, __umul24(out, tpot), tpot);
+#pragma unroll
+            for (uint32_t k = 0; k < kStageAtOnce; ++k) {
+                const uint32_t i = i0 + k * kReplayListThreads;
+                if (i < n) recs[i + i / kTile] = make_uint4(rq[k].x, cost[k].x, __umul24(rq[k].y >> 16, cost[k].y), cost[k].y);
+            }
         }
         if (tid < kReplayTiles) recs[tid * kStagedTile + kTile] = make_uint4(kNever, 0u, 0u, 0u);
         __syncthreads();
         for (uint32_t j = j0; j < min(j0 + kReplayTiles, n_t); ++j) {
             const uint4* tile_recs = recs + (j - j0) * kStagedTile;
-            const size_t tile_at = (size_t)(live ? cb : 0u) * p.n_list_tiles + j;
-            const uint32_t d = live ? p.desc[tile_at * (p.M + 1u) + m] : 0u;
-            uint32_t count = d >> 16;
-            const uint32_t first = d & 0xFFFFu;
-            if ((first & 7u) != 0u || first + ((count + 7u) & ~7u) > p.tile_cap) count = 0u;   // never written that way
+            const size_t tile_at = desc_at + j;
+            const uint32_t d = j == j0 ? d_here[0] : d_here[1];
+            uint32_t count;
+            const uint32_t first = run_of(d, count);
             n_listed += count;
-            if (__ballot(live && (s[0] < q.t_off || with_hist)) == 0ull) continue;
-            const uint32_t n_steps = wave_all_max(count);
-            const uint4* src = reinterpret_cast<const uint4*>(p.lists + tile_at * p.tile_cap + first);
-            const uint4 padding = make_uint4(kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u);
-            uint4 e_next = padding, e_after = padding;                              // the blocks after the one in hand
-            if (count != 0u) e_next = src[0];
-            if (8u < count) e_after = src[1];
+            // steps of the tile; at least one, so that the next tile's block is requested
+            const uint32_t n_steps = __ballot(live && (s[0] < q.t_off || with_hist)) != 0ull ? max(wave_all_max(count), 1u) : 1u;
             uint4 e = padding;
             for (uint32_t k0 = 0; k0 < n_steps; k0 += 4u) {                         // four requests at a time
                 if ((k0 & 4u) == 0u) {
-                    e = e_next;
-                    e_next = e_after;
-                    e_after = padding;
-                    if (k0 + 16u < count) e_after = src[k0 / 8u + 2u];
+                    const bool last = k0 + 8u >= n_steps;                           // the last block of every lane: on to the next tile's
+                    // waited for here, before the stores and the next requests
+                    asm volatile("" : "+v"(e_next), "+v"(d_next[0]), "+v"(d_next[1]));
+                    store_held();
+                    e = k0 < count ? make_uint4(e_next.x, e_next.y, e_next.z, e_next.w) : padding;
+                    e_next = block_of(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 8u + 1u);
+                    if (k0 == 0u && j == j0) {
+                        d_next[0] = desc_of(j0 + 2u);
+                        d_next[1] = desc_of(j0 + 3u);
+                    }
                 } else {                                                            // the block's second half
                     e.x = e.z;
                     e.y = e.w;
@@ -711,6 +784,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 4 : 5) void k_re
                 else if (kGroups > 2u && __ballot(s[kGroups > 2u ? kSlots - 2u * kGroup + 3u : 0u] > ready) == 0ull) still = kGroups - 2u;
 #pragma unroll
                 for (uint32_t k = 0; k < 4u; ++k) {
+                    if (k >= 2u && k0 + 2u >= n_steps) continue;                    // no lane has a third
                     const uint4 rq = rec[k];
                     const uint32_t start = max(max(rq.x, q.t_on), s[0]);            // s[0] is free if anything holds still
                     const bool served = start < q.t_off;                            // padding never starts
@@ -742,29 +816,37 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 4 : 5) void k_re
                         }
                     }
                 }
-                if (kBins_ != 0u && with_hist && (k0 & ~7u) < count) {              // padding, to the end of the block, reads 0
+                if (kBins_ != 0u) {                                                 // padding, to the end of the block, reads 0
+                    const bool leaves = with_hist && (k0 & ~7u) < count;
                     const size_t at = tile_at * p.tile_cap + first + k0;
-                    if (kBins_ == 2u) {
-                        uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + at);
-                        dst[0] = make_uint4(bins[0], tpot_bins[0], bins[1], tpot_bins[1]);
-                        dst[1] = make_uint4(bins[2], tpot_bins[2], bins[3], tpot_bins[3]);
+                    uint32_t v[kBins_ == 2u ? 8u : 4u];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k) {
+                        if (kBins_ == 2u) v[2u * k % (kBins_ == 2u ? 8u : 4u)] = bins[k], v[(2u * k + 1u) % (kBins_ == 2u ? 8u : 4u)] = tpot_bins[k];
+                        else v[k] = bins[k];
+                    }
+                    if ((k0 & 4u) == 0u) {
+                        if (leaves) store_bins(v, at);
                     } else {
-                        *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + at) = make_uint4(bins[0], bins[1], bins[2], bins[3]);
+#pragma unroll
+                        for (uint32_t k = 0; k < (kBins_ == 2u ? 8u : 4u); ++k) held[k] = v[k];
+                        held_at = at;
+                        holds = leaves;
+                        any_held = true;
                     }
                 }
             }
             // the last block's second half, where no lane has a request in it, is padding too
-            if (kBins_ != 0u && with_hist && count != 0u && n_steps <= (count - 1u) / 8u * 8u + 4u) {
-                const size_t at = tile_at * p.tile_cap + first + (count - 1u) / 8u * 8u + 4u;
-                if (kBins_ == 2u) {
-                    uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + at);
-                    dst[0] = dst[1] = make_uint4(0u, 0u, 0u, 0u);
-                } else {
-                    *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + at) = make_uint4(0u, 0u, 0u, 0u);
-                }
+            if (kBins_ != 0u && ((n_steps - 1u) & 4u) == 0u) {
+                holds = with_hist && count != 0u && n_steps <= (count - 1u) / 8u * 8u + 4u;
+                any_held = true;
+                held_at = tile_at * p.tile_cap + first + (count - 1u) / 8u * 8u + 4u;
+#pragma unroll
+                for (uint32_t k = 0; k < (kBins_ == 2u ? 8u : 4u); ++k) held[k] = 0u;
             }
         }
     }
+    store_held();
     for (; j0 < n_t; ++j0)                                                          // nothing starts any more: only counted
         n_listed += live ? p.desc[((size_t)cb * p.n_list_tiles + j0) * (p.M + 1u) + m] >> 16 : 0u;
     const unsigned long long s_e2e = ((unsigned long long)e2e_hi << 32) | e2e_lo;

@@ -132,3 +132,20 @@ def test_small_calls_of_replicas_that_come_and_go(R, fused):
     with GpuWorkload(tr) as g:
         assert g.route(97)["lists"] == (3 if fused else 2)
         assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"R={R}")
+
+
+@pytest.mark.parametrize("R", [1023, 2048, 2049, 3073, 5121])
+@pytest.mark.parametrize("M,B,C", [(3, 24, 700), (5, 64, 1025), (70, 48, 600)])
+def test_equally_long_lists_over_many_blocks_of_candidates(R, M, B, C):
+    """Every request listed on permanent replicas: odd numbers of tiles, runs that end with a block, lanes without requests, and a number
+    of workgroups that does not divide evenly among the XCDs."""
+    rng = np.random.default_rng(R + M)
+    tr = traces.custom_trace(np.cumsum(rng.integers(0, 40 if M < 70 else 4, R)), rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[0]] * M, B=B)
+    rows = rng.integers(0, M, size=(C, R)).astype(np.uint16)
+    rows[1], rows[2], rows[C - 1] = 0, np.arange(R) // 8 % M, M
+    rows[300:320] = np.sort(rows[300:320], axis=1)
+    some = np.unique(np.concatenate([np.arange(4), np.arange(4, C, 37), np.arange(255, 258), np.arange(300, 304), np.arange(C - 3, C)]))
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["lists"] == 1
+        got = g.eval(rows)
+    assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"R={R} M={M} B={B}")
