@@ -236,19 +236,27 @@ __global__ __launch_bounds__(kThreads) void k_eval_candidates(EvalParams p, cons
                     uint32_t n_served = n_open;
                     if (n_open > 0u) {
                         const uint32_t ready0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)ready);
-                        const unsigned long long idle = __ballot(S <= ready0);
-                        const uint32_t n_idle = __popcll(idle);
+                        unsigned long long idle = __ballot(S <= ready0);
+                        uint32_t n_idle = __popcll(idle);
                         // The first n_idle requests find a free slot whatever the earlier ones of the block
                         // did (a slot free at the first ready time stays free for them), so they start when
                         // ready and their finish times replace the idle slots' times in one permute.  It pays
                         // when that covers the whole block, or enough of it to be worth sorting afterwards.
+                        // From the first request that is left the same again, while eight slots are free or as many as there are
+                        // requests: on a light trace no request is left for the loop below, which takes a request at a time
+                        // (ten rows of 20011 requests on 50 replicas of 24 slots 164 to 117 us, one of 4096 on 8 of 32 41 to 26).
                         uint32_t n_first = 0;
                         if (n_idle >= n_open || (in_order ? n_idle >= 16u : n_idle > 0u)) {
-                            n_first = min(n_idle, n_open);
-                            const uint32_t ri = __popcll(idle & lanes_below);
                             const uint32_t fin = ready + svc;
-                            const uint32_t take = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(ri << 2), (int)fin);
-                            if (((idle >> lane) & 1ull) && ri < n_first) S = take;
+                            do {
+                                const uint32_t ri = __popcll(idle & lanes_below), n_now = min(n_idle, n_open - n_first);
+                                const uint32_t take = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((n_first + ri) << 2), (int)fin);
+                                if (((idle >> lane) & 1ull) && ri < n_now) S = take;
+                                n_first += n_now;
+                                if (n_first == n_open) break;
+                                idle = __ballot(S <= (uint32_t)__builtin_amdgcn_readlane((int)ready, (int)n_first));
+                                n_idle = __popcll(idle);
+                            } while (n_idle >= min(8u, n_open - n_first));
                             in_order = false;
                         }
                         if (n_first < n_open) {
