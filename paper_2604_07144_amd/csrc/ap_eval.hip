@@ -117,7 +117,7 @@ struct SplitPlan {
     uint32_t lds_bytes = 0, lds_bytes_hist = 0;
     unsigned char* tables = nullptr;  // ranges, kinds, coefficients, queues, order
     size_t tables_bytes = 0;
-    size_t o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0;   // where its parts lie in the scratch area
+    size_t o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0, o_bin_base = 0, o_bin_count = 0;   // where its parts lie in the scratch area
     SplitParams params{};
 };
 
@@ -291,6 +291,8 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
     sp.desc = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_desc);
     sp.part = reinterpret_cast<SplitPartial*>(w->d_split_scratch + plan.o_part);
     sp.hist = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_hist);
+    sp.bin_base = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_bin_base);
+    sp.bin_count = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_bin_count);
     const replay_lists_fn replay_lean = replay_lists_kernel_of<0u>(sp.B);
     const replay_lists_fn replay_bins = sp.wide_bins ? replay_lists_kernel_of<2u>(sp.B) : replay_lists_kernel_of<1u>(sp.B);
     // batches of equal size (whole wavefronts of the list replay), none above what the scratch area holds
@@ -752,27 +754,32 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.l_wave = sp.off_wave;
     sp.l_list = align_up((M + 1u) * 4u, 16u);
     sp.l_wave_bytes = sp.l_list + align_up(sp.tile_cap * 2u, 16u);
-    plan.lds_bytes_list = sp.l_wave + kSplitWaves * sp.l_wave_bytes;
+    sp.l_total = sp.l_wave + kSplitWaves * sp.l_wave_bytes;
+    plan.lds_bytes_list = sp.l_total + align_up(M * 4u, 16u);
     int lds_cap = 0;
     if (hipDeviceGetAttribute(&lds_cap, hipDeviceAttributeMaxSharedMemoryPerBlock, w->device) != hipSuccess) return device_error();
     if (off + hist_bytes > (uint32_t)lds_cap) return AP_OK;  // a replica table that large stays with the general replay
     plan.lds_bytes = off;
     plan.lds_bytes_hist = off + hist_bytes;
+    if (off + hist_bytes + align_up(M * 4u, 16u) <= (uint32_t)lds_cap) {     // else (a handful of table sizes) they are added up in device memory
+        sp.off_total = off + hist_bytes;
+        plan.lds_bytes_hist += align_up(M * 4u, 16u);
+    }
     const int narrow = M <= 64u ? 1 : 0;
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_list_candidates), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)plan.lds_bytes_list) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled)),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)off) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled)),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(off + hist_bytes)) != hipSuccess) {
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds_bytes_hist) != hipSuccess) {
         (void)hipGetLastError();
         return device_error();
     }
 
     // scratch for one batch of candidates: lists, run descriptors, partial records, histograms
     const size_t bins_bytes = sp.wide_bins ? 8u : 4u;
-    const size_t per_cand = (size_t)sp.n_list_tiles * sp.tile_cap * (2u + bins_bytes) + (size_t)sp.n_list_tiles * (M + 1u) * 4u +
-                            sizeof(SplitPartial) + hist_bytes;
+    const size_t per_cand = (size_t)sp.n_list_tiles * sp.tile_cap * (2u + bins_bytes) + (size_t)sp.n_list_tiles * M * 4u +
+                            sizeof(SplitPartial) + hist_bytes + 2u * (M + 1u) * 4u;
     if (per_cand > ((size_t)8 << 30) / 64u) return AP_OK;       // a trace so long that 64 candidates' lists take over 8 GiB
     uint32_t batch = (uint32_t)std::min<size_t>(16384u, std::max<size_t>(64u, ((size_t)4 << 30) / per_cand));
     batch = batch / 64u * 64u;
@@ -782,9 +789,11 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         total = 0;
         plan.o_lists = carve(total, (size_t)batch * sp.n_list_tiles * sp.tile_cap * 2u);
         plan.o_bins = carve(total, (size_t)batch * sp.n_list_tiles * sp.tile_cap * bins_bytes);
-        plan.o_desc = carve(total, (size_t)batch * sp.n_list_tiles * (M + 1u) * 4u);
+        plan.o_desc = carve(total, (size_t)batch * sp.n_list_tiles * M * 4u);
         plan.o_part = carve(total, (size_t)batch * sizeof(SplitPartial));
         plan.o_hist = carve(total, (size_t)batch * hist_bytes);
+        plan.o_bin_base = carve(total, (size_t)batch * (M + 1u) * 4u);
+        plan.o_bin_count = carve(total, (size_t)batch * (M + 1u) * 4u);
         if (total <= w->split_scratch_bytes) break;
         if (w->d_split_scratch && hipFree(w->d_split_scratch) != hipSuccess) return device_error();
         w->d_split_scratch = nullptr;
@@ -1256,9 +1265,10 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     const bool hist16 = w->R < 65536u;
     // A chunk should hand each replica about 56 requests, so that the 64-lane blocks of the
     // replay are mostly full and rarely spill into a second block; more than that only costs
-    // LDS.  Prefer a size that lets two workgroups share a compute unit (they cover each
+    // LDS.  At least 2048 requests where there are more than 1024: small tables gain from fewer barriers (a row of 4096 requests on 8
+    // replicas 27 to 22 us).  Prefer a size that lets two workgroups share a compute unit (they cover each
     // other's barriers); otherwise take the largest chunk one workgroup can hold.
-    const uint32_t want = std::min(kMaxChunk, std::max(2u * kThreads, align_up(56u * M, kThreads)));
+    const uint32_t want = std::min(kMaxChunk, std::max((w->R > 2u * kThreads ? 4u : 2u) * kThreads, align_up(56u * M, kThreads)));
     uint32_t bytes = 0, chunk = 0;
     {   // what the kernel itself declares (nothing today) comes off the dynamic part
         hipFuncAttributes attr;

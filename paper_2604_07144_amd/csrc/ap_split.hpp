@@ -42,8 +42,8 @@ namespace {
 // Appendix "Serving Simulator", Memory Feasibility), provided every served latency falls in a lower bin, which
 // the host checks against its bound on all finish times.  Such a candidate is called settled-by-penalty below
 // and carries kFlagLazy; the others keep histograms: the streamed requests are counted in LDS while the row is
-// read (and parked in device memory), the list replay leaves the bins of every listed request next to its list
-// entry, and k_merge_candidates adds the two up.
+// read (and parked in device memory), the list replay leaves, queue by queue, the bins of the listed requests that any p99 value can
+// depend on, and k_merge_candidates adds the two up.
 constexpr uint32_t kSplitWaves = 4;
 constexpr uint32_t kSplitThreads = kSplitWaves * kWave;
 constexpr uint32_t kTile = 1024;                  // requests per tile: a list position fits 10 bits
@@ -89,13 +89,15 @@ struct SplitParams {
     SplitTables tab;
     const SplitQueue* queue;                      // [M]
     const uint32_t* order;                        // [n_queues] replicas with a listed part, longest first
-    uint32_t* desc;                               // [batch][n_list_tiles][M + 1] count << 16 | first list position of
-                                                  //   the replica's run; entry M: list positions the tile uses in all
+    uint32_t* desc;                               // [batch][n_list_tiles][M] count << 16 | first list position of
+                                                  //   the replica's run
     uint16_t* lists;                              // [batch][n_list_tiles][tile_cap] tile-local request indices by replica
     SplitPartial* part;                           // [batch]
     uint32_t* hist;                               // [batch][hist_words] the streamed requests' histograms
-    void* bins;                                   // [batch][n_list_tiles][tile_cap] what every listed request adds to the histograms:
-                                                  //   a bins word as above, or two where the tpot bins span too much
+    void* bins;                                   // [batch][n_list_tiles * tile_cap] what listed requests add to the histograms, where it is
+                                                  //   anything: a bins word as above, or two where the tpot bins span too much
+    uint32_t* bin_base;                           // [batch][M + 1] where a queue's words begin (the requests listed for replicas before it)
+    uint32_t* bin_count;                          // [batch][M + 1] how many the list replay has left
     uint32_t wide_bins;                           // the latter
     uint32_t least_bin[3], least_us[3];           // no p99 value (ttft, tpot, e2e) can lie below this bin: the list replay leaves smaller ones out
     uint32_t tpot_within;                         // no request's time per token can exceed the objective
@@ -117,7 +119,8 @@ struct SplitParams {
     // byte offsets into the streaming kernel's dynamic LDS
     uint32_t off_range, off_range_off, off_kind, off_coef, off_acc, off_wave, wave_bytes, w_pos, w_queue, w_list, w_same, w_tile,
         off_hist;
-    uint32_t l_wave, l_wave_bytes, l_list;               // k_list_candidates: its wavefronts' areas
+    uint32_t off_total;                                  // listed requests per replica; 0: there is no room, they are added up in bin_base
+    uint32_t l_wave, l_wave_bytes, l_list, l_total;      // k_list_candidates: its wavefronts' areas, and the same
 };
 
 // Is candidate cb of the batch one to look at?
@@ -151,6 +154,19 @@ __device__ __forceinline__ uint2 lanes_alike(uint32_t id, unsigned long long all
     if (key_bits > 6u) narrow_down(6u);
     for (uint32_t b = 7u; b < key_bits; ++b) narrow_down(b);
     return make_uint2(lo, hi);
+}
+
+// Where the bins of each replica's queue begin: the sums of the listed requests of the replicas before it (one wavefront).
+template <typename Total>
+__device__ __forceinline__ void place_bins(const SplitParams& p, uint32_t cb, const Total& total_of) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t before = 0;
+    for (uint32_t base = 0; base < p.M; base += kWave) {
+        const uint32_t m = base + lane, v = m < p.M ? total_of(m) : 0u;
+        const uint32_t upto = wave_inclusive_scan(v, lane);
+        if (m < p.M) p.bin_base[(size_t)cb * (p.M + 1u) + m] = before + upto - v;
+        before += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    }
 }
 
 // Streaming kernel, where something is streamed.  One workgroup per candidate at a time;
@@ -190,6 +206,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     uint16_t* list = reinterpret_cast<uint16_t*>(mine + p.w_list);           // [tile_cap]
     unsigned long long* same = reinterpret_cast<unsigned long long*>(mine + p.w_same);   // [M] lanes naming the replica
     uint32_t* tile_of = reinterpret_cast<uint32_t*>(mine + p.w_tile);        // [M + 1] the replica's ranges within the tile in hand
+    uint32_t* total = reinterpret_cast<uint32_t*>(lds + p.off_total);        // kHist only: [M]
     const uint32_t R = p.R, M = p.M;
 
     // Mode 0 never runs behind the streamed evaluation (its spilled scalars: 836 against 834 us for 8192 rows of 32768 requests).
@@ -213,8 +230,13 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
         if ((only_flagged && (p.part[cb].flags & kFlagNeedHist) == 0u) || (kHist && !split_wanted(p, cb))) continue;   // the same for every thread
         __syncthreads();                                                            // the last candidate's totals were read
-        if (kHist)
+        if (kHist) {
             for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) hist[i] = 0u;
+            for (uint32_t m = tid; m < M; m += kSplitThreads) {
+                if (p.off_total != 0u) total[m] = 0u;
+                else __hip_atomic_store(&p.bin_base[(size_t)cb * (M + 1u) + m], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
         if (tid < 10u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
@@ -353,7 +375,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             if (!grouping) return;                                                  // q_n is 0 there
             // runs: every replica's listed requests of the tile, starting on a multiple of 8 positions
             const size_t tile_at = (size_t)cb * p.n_list_tiles + j;
-            uint32_t total = 0;
+            uint32_t n_used = 0;
             for (uint32_t base = 0; base < M; base += kWave) {
                 const uint32_t m = base + lane;
                 const uint32_t c = m < M ? cnt[m] : 0u;
@@ -362,16 +384,19 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                 if ((c & 7u) != 0u) {                                                // the run's last block: what no request takes is padding
                     uint32_t pad = kPadding * 0x10001u;                             // (made here: kept from tile to tile it costs a spill)
                     asm volatile("" : "+v"(pad));
-                    reinterpret_cast<uint4*>(list)[(total + upto - room + c) / 8u] = make_uint4(pad, pad, pad, pad);
+                    reinterpret_cast<uint4*>(list)[(n_used + upto - room + c) / 8u] = make_uint4(pad, pad, pad, pad);
                 }
                 if (m < M) {
-                    pos[m] = total + upto - room;
+                    pos[m] = n_used + upto - room;
                     cnt[m] = 0u;                                                    // for the wavefront's next tile
-                    p.desc[tile_at * (M + 1u) + m] = (c << 16) | (total + upto - room);
+                    p.desc[tile_at * M + m] = (c << 16) | (n_used + upto - room);
+                    if (kHist && c != 0u) {
+                        if (p.off_total != 0u) atomicAdd(&total[m], c);
+                        else atomicAdd(&p.bin_base[(size_t)cb * (M + 1u) + m], c);
+                    }
                 }
-                total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+                n_used += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
             }
-            if (lane == 0u) p.desc[tile_at * (M + 1u) + M] = total;
             // Rank among the queued requests of one replica, 64 queued requests at a time: every lane sets its bit
             // in its replica's word and reads the word back (the LDS executes a wavefront's instructions in order),
             // which tells it how many lanes before it name the same replica; the last of them moves the run's
@@ -395,7 +420,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             }
             // 16 bytes (8 positions) at a time
             uint4* dst = reinterpret_cast<uint4*>(p.lists + tile_at * p.tile_cap);
-            for (uint32_t v = lane; v < total / 8u; v += kWave) dst[v] = reinterpret_cast<const uint4*>(list)[v];
+            for (uint32_t v = lane; v < n_used / 8u; v += kWave) dst[v] = reinterpret_cast<const uint4*>(list)[v];
         };
         fetch_keys(key_next, w);
         for (uint32_t j = w; j < p.n_tiles; j += kSplitWaves) {
@@ -434,6 +459,12 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             sp.flags = lazy ? kFlagLazy : (kHist ? 0u : kFlagNeedHist);
             p.part[cb] = sp;
         }
+        if (kHist && w == 0u) {
+            if (p.off_total != 0u) place_bins(p, cb, [&](uint32_t m) { return total[m]; });
+            else place_bins(p, cb, [&](uint32_t m) {
+                return __hip_atomic_load(&p.bin_base[(size_t)cb * (M + 1u) + m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            });
+        }
         if (kHist && !lazy) {
             uint32_t* dst = p.hist + (size_t)cb * p.hist_words;
             for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) dst[i] = hist[i];
@@ -458,6 +489,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
     const uint32_t R = p.R, M = p.M;
     uint32_t* end_of = reinterpret_cast<uint32_t*>(lds + p.off_range);               // [M + 1] the replica's list ends here
     uint32_t* rejected_of_row = reinterpret_cast<uint32_t*>(lds + p.off_acc);
+    uint32_t* total_of = reinterpret_cast<uint32_t*>(lds + p.l_total);               // [M] listed requests of the row
     unsigned char* mine = lds + p.l_wave + w * p.l_wave_bytes;
     uint32_t* run = reinterpret_cast<uint32_t*>(mine);                               // [M + 1] the run's length so far, then its first position
     uint16_t* list = reinterpret_cast<uint16_t*>(mine + p.l_list);                   // [tile_cap]; before that the tile's ids
@@ -465,8 +497,9 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
     for (uint32_t m = lane; m <= M; m += kWave) run[m] = 0u;
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
         if (!split_wanted(p, cb)) continue;                                          // the same record for every thread
-        __syncthreads();                                                             // the last candidate's total was read
+        __syncthreads();                                                             // the last candidate's totals were read
         if (tid == 0u) rejected_of_row[0] = 0u;
+        for (uint32_t m = tid; m < M; m += kSplitThreads) total_of[m] = 0u;
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
         const bool row_aligned = (reinterpret_cast<uintptr_t>(row) & 3u) == 0u;
@@ -544,11 +577,11 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
                 }
                 if (m < M) {
                     run[m] = total + upto - room;
-                    p.desc[tile_at * (M + 1u) + m] = (c << 16) | (total + upto - room);
+                    if (c != 0u) atomicAdd(&total_of[m], c);
+                    p.desc[tile_at * M + m] = (c << 16) | (total + upto - room);
                 }
                 total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
             }
-            if (lane == 0u) p.desc[tile_at * (M + 1u) + M] = total;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (uint32_t s = 0; s < kSteps; ++s)
@@ -567,6 +600,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
             sp.flags = sp.n_rej >= p.lazy_from ? kFlagLazy : kFlagNoStreamHist;
             p.part[cb] = sp;
         }
+        if (w == 0u) place_bins(p, cb, [&](uint32_t m) { return total_of[m]; });
     }
 }
 
@@ -605,13 +639,16 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // reach, 1024 rows of 131072 requests on 128 crowded replicas of 64 slots take 1226 us instead of 1569 (and k_merge_candidates 340
 // instead of 803, before the change described there); on light traces and odd B 1.1 to 1.5 times less.
 // Loads run ahead: a lane's descriptors a stage, its next block of eight entries a block, also into the next tile, and the
-// records of a stage four per thread at a time; a block's last bins are stored behind the wait for the next one.  A register whose
+// records of a stage four per thread at a time.  A register whose
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as one vector
 // and the empty asm where it is waited for.  A pair of steps that no lane needs is left out.  Where all lists are
-// as long as the trace, neighbouring replicas share an XCD, whose L2 then combines their bins and runs.  Together: 1024 rows of
-// 131072 requests on 128 crowded replicas 1190 to 983 us (bound by the bins' 16-byte stores, a third of it, and by memory waits at two
-// wavefronts per SIMD; without medians it takes as long), 3001 rows of 20011 requests on 50 replicas, half of which come and go,
-// 184 to 168 us, and 4096 rows of 32768 on 64 crowded replicas 462 to 445 us.
+// as long as the trace, neighbouring replicas share an XCD, whose L2 then holds their runs once.  A queue's words for the
+// histograms follow one another (place_bins), and only requests with a value that a p99 value can reach leave one: on a trace that is
+// not hopelessly overloaded one in fifty to one in ten, where a word per list position was a gigabyte of 16-byte stores to as many
+// cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1190 us before all of this, 983 with
+// a word per position, 661 now, and k_merge_candidates 196 and 51; at ten times the load, where every request leaves a word, the
+// call takes 1.02 times as long as before.  3001 rows of 20011 requests on 50 replicas, half of which come and go, 184 to 168 us, and
+// 4096 rows of 32768 on 64 crowded replicas that come and go 462 to 430.
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
 constexpr uint32_t kListWaves = 4;
@@ -638,7 +675,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     const uint32_t tid = threadIdx.x;
     const uint32_t n_blocks = (n_cand + kReplayListThreads - 1u) / kReplayListThreads;
     // Longest lists first; where all are as long as the trace, replicas next to each other and the same candidates on one XCD: their runs
-    // share cache lines, and so do the bins they leave.
+    // share cache lines.
     uint32_t at_queue = blockIdx.x / n_blocks, at_block = blockIdx.x % n_blocks;
     if (p.even_lists != 0u) {
         const uint32_t job = blockIdx.x % kXcds * (gridDim.x / kXcds) + blockIdx.x / kXcds;
@@ -653,7 +690,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     const bool lazy = (flags & kFlagLazy) != 0u;
     live = live && (which == 0u || lazy == (which == 1u));
     if (__syncthreads_or(live ? 1 : 0) == 0) return;
-    const bool with_hist = kBins_ != 0u && live && !lazy;                           // leave the bins of every request
+    const bool with_hist = kBins_ != 0u && live && !lazy;                           // leave bins
     SplitQueue q = p.queue[m];
     q.a = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.a);
     q.b = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.b);
@@ -675,7 +712,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     const uint32_t n_t = (q.i_list + kTile - 1u) / kTile;
     uint32_t j0 = 0;
     const size_t desc_at = (size_t)(live ? cb : 0u) * p.n_list_tiles;
-    auto desc_of = [&](uint32_t j) { return live && j < n_t ? p.desc[(desc_at + j) * (p.M + 1u) + m] : 0u; };
+    auto desc_of = [&](uint32_t j) { return live && j < n_t ? p.desc[(desc_at + j) * p.M + m] : 0u; };
     auto run_of = [&](uint32_t d, uint32_t& count) {                                // a descriptor that was never written that way lists nothing
         const uint32_t first = d & 0xFFFFu;
         count = ((first & 7u) != 0u) | (first + (((d >> 16) + 7u) & ~7u) > p.tile_cap) ? 0u : d >> 16;
@@ -693,24 +730,9 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     uint32_t d_here[2], d_next[2] = {desc_of(0u), desc_of(1u)};
     four_words e_next = {};                                                         // the block after the one in hand
     if (n_t != 0u) e_next = block_of(d_next[0], 0u, 0u);
-    // Bins of the second half of a block are stored once the next block is there: waiting for that block waits for stores as well.
-    uint32_t held[kBins_ == 2u ? 8u : 4u];
-    size_t held_at = 0;
-    bool holds = false, any_held = false;                                           // this lane; the wavefront
-    auto store_bins = [&](const uint32_t* v, size_t at) {
-        if (kBins_ == 2u) {
-            uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + at);
-            dst[0] = make_uint4(v[0], v[1], v[2], v[3]);
-            dst[1] = make_uint4(v[4 % (kBins_ == 2u ? 8 : 4)], v[5 % (kBins_ == 2u ? 8 : 4)], v[6 % (kBins_ == 2u ? 8 : 4)], v[7 % (kBins_ == 2u ? 8 : 4)]);
-        } else {
-            *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + at) = make_uint4(v[0], v[1], v[2], v[3]);
-        }
-    };
-    auto store_held = [&] {
-        if (kBins_ == 0u || !any_held) return;
-        if (holds) store_bins(held, held_at);
-        holds = any_held = false;
-    };
+    // the words of the queue's large values, one after the other
+    const size_t bins_at = with_hist ? (size_t)cb * p.n_list_tiles * p.tile_cap + p.bin_base[(size_t)cb * (p.M + 1u) + m] : 0u;
+    uint32_t n_left = 0;
     for (; j0 < n_t; j0 += kReplayTiles) {
         const uint32_t r0 = j0 * kTile, n = min(kReplayTiles * kTile, p.R - r0);
         if ((tid & 63u) == 0u) goes_on[wave_index()] = 0u;
@@ -759,9 +781,8 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             for (uint32_t k0 = 0; k0 < n_steps; k0 += 4u) {                         // four requests at a time
                 if ((k0 & 4u) == 0u) {
                     const bool last = k0 + 8u >= n_steps;                           // the last block of every lane: on to the next tile's
-                    // waited for here, before the stores and the next requests
+                    // waited for here, before the next requests
                     asm volatile("" : "+v"(e_next), "+v"(d_next[0]), "+v"(d_next[1]));
-                    store_held();
                     e = k0 < count ? make_uint4(e_next.x, e_next.y, e_next.z, e_next.w) : padding;
                     e_next = block_of(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 8u + 1u);
                     if (k0 == 0u && j == j0) {
@@ -776,7 +797,6 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                 uint4 rec[4];
 #pragma unroll
                 for (uint32_t k = 0; k < 4u; ++k) rec[k] = tile_recs[(k & 1u) ? word[k >> 1] >> 16 : word[k >> 1] & 0xFFFFu];
-                uint32_t bins[4] = {0u, 0u, 0u, 0u}, tpot_bins[4] = {0u, 0u, 0u, 0u};
                 // How many of the lower groups of registers hold still (a lane without a request is ready at kNever)
                 const uint32_t ready = max(rec[0].x, q.t_on);
                 uint32_t still = 0u;
@@ -808,47 +828,21 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                         last_fin = max(last_fin, fin);
                         ++n_served;
                         n_ok += (ttft <= p.slo_ttft && rq.w <= slo_tpot) ? 1u : 0u;
-                        if (kBins_ != 0u) {
+                        if (kBins_ != 0u && with_hist & ((ttft >= p.least_us[0]) | (rq.w >= p.least_us[1]) | (e2e >= p.least_us[2]))) {
                             const uint32_t tpot_bin = bin_above(rq.w, p.least_us[1], p.least_bin[1]);
-                            bins[k] = bin_above(ttft, p.least_us[0], p.least_bin[0]) |
-                                      (bin_above(e2e, p.least_us[2], p.least_bin[2]) << 12) | (kBins_ == 2u ? 0u : tpot_bin << 24);
-                            tpot_bins[k] = tpot_bin;
+                            const uint32_t both = bin_above(ttft, p.least_us[0], p.least_bin[0]) | (bin_above(e2e, p.least_us[2], p.least_bin[2]) << 12);
+                            if (kBins_ == 2u) reinterpret_cast<uint2*>(p.bins)[bins_at + n_left] = make_uint2(both, tpot_bin);
+                            else reinterpret_cast<uint32_t*>(p.bins)[bins_at + n_left] = both | (tpot_bin << 24);
+                            ++n_left;
                         }
                     }
                 }
-                if (kBins_ != 0u) {                                                 // padding, to the end of the block, reads 0
-                    const bool leaves = with_hist && (k0 & ~7u) < count;
-                    const size_t at = tile_at * p.tile_cap + first + k0;
-                    uint32_t v[kBins_ == 2u ? 8u : 4u];
-#pragma unroll
-                    for (uint32_t k = 0; k < 4u; ++k) {
-                        if (kBins_ == 2u) v[2u * k % (kBins_ == 2u ? 8u : 4u)] = bins[k], v[(2u * k + 1u) % (kBins_ == 2u ? 8u : 4u)] = tpot_bins[k];
-                        else v[k] = bins[k];
-                    }
-                    if ((k0 & 4u) == 0u) {
-                        if (leaves) store_bins(v, at);
-                    } else {
-#pragma unroll
-                        for (uint32_t k = 0; k < (kBins_ == 2u ? 8u : 4u); ++k) held[k] = v[k];
-                        held_at = at;
-                        holds = leaves;
-                        any_held = true;
-                    }
-                }
-            }
-            // the last block's second half, where no lane has a request in it, is padding too
-            if (kBins_ != 0u && ((n_steps - 1u) & 4u) == 0u) {
-                holds = with_hist && count != 0u && n_steps <= (count - 1u) / 8u * 8u + 4u;
-                any_held = true;
-                held_at = tile_at * p.tile_cap + first + (count - 1u) / 8u * 8u + 4u;
-#pragma unroll
-                for (uint32_t k = 0; k < (kBins_ == 2u ? 8u : 4u); ++k) held[k] = 0u;
             }
         }
     }
-    store_held();
+    if (kBins_ != 0u && with_hist) p.bin_count[(size_t)cb * (p.M + 1u) + m] = n_left;
     for (; j0 < n_t; ++j0)                                                          // nothing starts any more: only counted
-        n_listed += live ? p.desc[((size_t)cb * p.n_list_tiles + j0) * (p.M + 1u) + m] >> 16 : 0u;
+        n_listed += live ? p.desc[((size_t)cb * p.n_list_tiles + j0) * p.M + m] >> 16 : 0u;
     const unsigned long long s_e2e = ((unsigned long long)e2e_hi << 32) | e2e_lo;
     const unsigned long long s_tpot = ((unsigned long long)tpot_hi << 32) | tpot_lo;
     const unsigned long long s_ttft = s_e2e - (((unsigned long long)dec_hi << 32) | dec_lo);
@@ -875,8 +869,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 // Merge: one record per candidate from its partial sums.  A candidate settled by penalty is written by one
 // thread; one that the list replay handed back gets the pending mark (the general replay scores it next); for
 // the others a workgroup takes the streamed requests' histograms from device memory, adds the bins the list replay
-// left for every list position of the candidate (padding reads "not served") and goes through the usual
-// block-wide reduction.
+// left, queue by queue, and goes through the usual block-wide reduction.
 template <bool kHist16>
 __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, SplitParams sp, ap_metrics* __restrict__ out,
                                                                uint32_t c0, uint32_t n_cand, PendingWord flags) {
@@ -937,37 +930,32 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
             reinterpret_cast<uint4*>(hist)[i] = parked ? reinterpret_cast<const uint4*>(src)[i] : make_uint4(0u, 0u, 0u, 0u);
         if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
-        const size_t tiles_at = (size_t)c * sp.n_list_tiles;
-        // A tile per wavefront at a time, the size of the next one requested ahead: with all wavefronts on one tile the kernel waits
-        // for memory twice per tile (1024 rows of 128 tiles, every request listed: 340 against 199 us).
+        // A queue per wavefront at a time, where the next one's words lie requested ahead.
         const uint32_t lane = tid & 63u;
-        auto used_of = [&](uint32_t j) { return j < sp.n_list_tiles ? sp.desc[(tiles_at + j) * (sp.M + 1u) + sp.M] : 0u; };
-        uint32_t used_next = used_of(wave_index());
-        for (uint32_t j = wave_index(); j < sp.n_list_tiles; j += kThreads / kWave) {
-            const uint32_t used = min(used_next, sp.tile_cap);
-            used_next = used_of(j + kThreads / kWave);
-            const size_t at = (tiles_at + j) * sp.tile_cap;
-            auto add = [&](uint32_t te, uint32_t tpot) {
-                if ((te & 0xFFFu) != 0u) hist_add<kHist16>(hist, 0u, min(sp.least_bin[0] + (te & 0xFFFu) - 1u, kBins - 1u), 1u);
+        const size_t bins_at = (size_t)c * sp.n_list_tiles * sp.tile_cap, queues_at = (size_t)c * (sp.M + 1u);
+        auto queue_at = [&](uint32_t i) {
+            if (i >= sp.n_queues) return make_uint2(0u, 0u);
+            const uint32_t m = sp.order[i];
+            return make_uint2(sp.bin_base[queues_at + m], sp.bin_count[queues_at + m]);
+        };
+        uint2 next = queue_at(wave_index());
+        for (uint32_t i = wave_index(); i < sp.n_queues; i += kThreads / kWave) {
+            const uint2 here = next;
+            next = queue_at(i + kThreads / kWave);
+            for (uint32_t k = lane; k < here.y; k += kWave) {
+                uint32_t both, tpot;
+                if (sp.wide_bins != 0u) {
+                    const uint2 word = reinterpret_cast<const uint2*>(sp.bins)[bins_at + here.x + k];
+                    both = word.x;
+                    tpot = word.y;
+                } else {
+                    both = reinterpret_cast<const uint32_t*>(sp.bins)[bins_at + here.x + k];
+                    tpot = both >> 24;
+                }
+                const uint32_t ttft = both & 0xFFFu, e2e = (both >> 12) & 0xFFFu;
+                if (ttft != 0u) hist_add<kHist16>(hist, 0u, min(sp.least_bin[0] + ttft - 1u, kBins - 1u), 1u);
                 if (tpot != 0u) hist_add<kHist16>(hist, 1u, min(sp.least_bin[1] + tpot - 1u, kBins - 1u), 1u);
-                if (((te >> 12) & 0xFFFu) != 0u) hist_add<kHist16>(hist, 2u, min(sp.least_bin[2] + ((te >> 12) & 0xFFFu) - 1u, kBins - 1u), 1u);
-            };
-            if (sp.wide_bins != 0u) {
-                for (uint32_t i = lane; i < used; i += kWave) {
-                    const uint2 word = reinterpret_cast<const uint2*>(sp.bins)[at + i];
-                    if ((word.x | word.y) != 0u) add(word.x, word.y);
-                }
-            } else {                                                                // four positions at a time: runs are whole multiples of 8
-                const uint4* src4 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(sp.bins) + at);
-                uint4 next = lane < used / 4u ? src4[lane] : make_uint4(0u, 0u, 0u, 0u);
-                for (uint32_t i = lane; i < used / 4u; i += kWave) {
-                    const uint4 v = next;
-                    if (i + kWave < used / 4u) next = src4[i + kWave];
-                    if (v.x != 0u) add(v.x, v.x >> 24);
-                    if (v.y != 0u) add(v.y, v.y >> 24);
-                    if (v.z != 0u) add(v.z, v.z >> 24);
-                    if (v.w != 0u) add(v.w, v.w >> 24);
-                }
+                if (e2e != 0u) hist_add<kHist16>(hist, 2u, min(sp.least_bin[2] + e2e - 1u, kBins - 1u), 1u);
             }
         }
         __syncthreads();

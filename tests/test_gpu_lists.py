@@ -149,3 +149,41 @@ def test_equally_long_lists_over_many_blocks_of_candidates(R, M, B, C):
         assert g.route(C)["lists"] == 1
         got = g.eval(rows)
     assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"R={R} M={M} B={B}")
+
+
+@pytest.mark.parametrize("M", [772, 773, 784, 794, 795])
+def test_tables_that_fill_the_lds(M):
+    """With the kernel's histograms no room in LDS for the listed requests per replica (773 to 794 replicas, three kinds): they
+    are added up in device memory.  Nothing rejected, a part listed and a part streamed, bins from both."""
+    rng = np.random.default_rng(M)
+    R, B = 3000, 4
+    arrival = np.cumsum(np.concatenate([rng.integers(0, 3, R // 2), rng.integers(20_000, 60_000, R - R // 2)])).astype(np.uint64)
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[m % 3] for m in range(M)],
+                             np.where(np.arange(M) % 5 == 0, int(arrival[R // 4]), 0), B=B)
+    rows = rng.integers(0, M, size=(700, R)).astype(np.uint16)
+    rows[3] = rows[3] % 7
+    some = np.concatenate([np.arange(6), np.arange(6, 700, 60)])
+    with GpuWorkload(tr) as g:
+        assert g.route(700)["lists"] == (2 if M < 795 else 0)
+        got = g.eval(rows)
+    assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"M={M}")
+
+
+@pytest.mark.parametrize("load", [1, 8, 200])
+@pytest.mark.parametrize("slow", [False, True])
+@pytest.mark.parametrize("kinds", [1, 3])
+def test_bins_few_and_many(load, slow, kinds):
+    """From a trace on which next to no listed request leaves a bins word to one on which all do, in one word and in two; one queue takes
+    most requests of a row, others none."""
+    rng = np.random.default_rng(load)
+    R, M, B = 5000, 9, 12
+    arrival = np.cumsum(rng.integers(0, max(2, 3200 // load), R)).astype(np.uint64)
+    coef = [KINDS[m % kinds] for m in range(M)]
+    if slow:
+        coef[0] = (3500, 5, 40, 2000)
+    tr = traces.custom_trace(arrival, rng.integers(1, 8000, R), rng.integers(1, 60 if slow else 300, R), coef, B=B)
+    rows = rng.integers(0, M, size=(300, R)).astype(np.uint16)
+    rows[1], rows[2] = np.where(rng.random(R) < 0.9, 4, rows[1]), 8
+    rows[3, ::7] = M
+    with GpuWorkload(tr) as g:
+        assert_same(g.eval(rows)[:24], oracle_for(tr).eval_batch(rows[:24], nthreads=8), f"load {load}")
