@@ -733,12 +733,11 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.any_streamed = any_streamed ? 1u : 0u;
     sp.hist_words = wide ? 3u * kBins : 3u * kBins / 2u;
     // LDS of the streaming kernel
-    uint32_t off = 0;
+    uint32_t off = (uint32_t)kinds.size() * 16u;             // the coefficients come first
     const uint32_t hist_bytes = sp.hist_words * 4u;
     sp.off_range = off; off += align_up((M + 1u) * 4u, 16u);
     sp.off_range_off = off; off += wide ? align_up((M + 1u) * 4u, 16u) : 0u;
     sp.off_kind = off;  off += align_up((M + 1u) * 4u, 16u);
-    sp.off_coef = off;  off += (uint32_t)kinds.size() * 16u;
     sp.off_acc = off;   off += 64u;
     sp.off_wave = off;
     uint32_t wb = 0;

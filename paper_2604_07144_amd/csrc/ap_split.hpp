@@ -117,7 +117,7 @@ struct SplitParams {
     uint32_t lazy_from;                           // rejected requests from which the p99 values are the penalty; kNever: never
     uint32_t all_within;                          // no request's prefill or time per token can exceed the objectives
     // byte offsets into the streaming kernel's dynamic LDS
-    uint32_t off_range, off_range_off, off_kind, off_coef, off_acc, off_wave, wave_bytes, w_pos, w_queue, w_list, w_same, w_tile,
+    uint32_t off_range, off_range_off, off_kind, off_acc, off_wave, wave_bytes, w_pos, w_queue, w_list, w_same, w_tile,
         off_hist;
     uint32_t off_total;                                  // listed requests per replica; 0: there is no room, they are added up in bin_base
     uint32_t l_wave, l_wave_bytes, l_list, l_total;      // k_list_candidates: its wavefronts' areas, and the same
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     uint32_t* range_of = reinterpret_cast<uint32_t*>(lds + p.off_range);
     uint32_t* range_off_of = reinterpret_cast<uint32_t*>(lds + p.off_range_off);   // wide only
     uint32_t* kind_of = reinterpret_cast<uint32_t*>(lds + p.off_kind);
-    uint4* coef_of = reinterpret_cast<uint4*>(lds + p.off_coef);
+    uint4* coef_of = reinterpret_cast<uint4*>(lds);
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_acc);
     uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);    // latest finish, within objectives, rejected
     const uint32_t tid = threadIdx.x, lane = tid & 63u, w = wave_index();
@@ -207,6 +207,9 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     unsigned long long* same = reinterpret_cast<unsigned long long*>(mine + p.w_same);   // [M] lanes naming the replica
     uint32_t* tile_of = reinterpret_cast<uint32_t*>(mine + p.w_tile);        // [M + 1] the replica's ranges within the tile in hand
     uint32_t* total = reinterpret_cast<uint32_t*>(lds + p.off_total);        // kHist only: [M]
+    // the coefficients lie at LDS address 0 (read by address: through the array's name every access costs an addition of its base)
+    typedef uint32_t four_words __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) const four_words lds_four;
     const uint32_t R = p.R, M = p.M;
 
     // Mode 0 never runs behind the streamed evaluation (its spilled scalars: 836 against 834 us for 8192 rows of 32768 requests).
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
         const bool row_aligned = (reinterpret_cast<uintptr_t>(row) & 3u) == 0u;      // pairs of ids as one 4-byte load
         unsigned long long s_e2e = 0, s_ttft = 0, s_tpot = 0;
-        uint32_t last_fin = 0, n_ok = 0, n_rej = 0;
+        uint32_t last_fin = 0, n_ok = 0, n_rej = 0, n_streamed = 0;
 
         // A wavefront's tiles.  A lane holds two consecutive requests of every 128 (one 4-byte load of two replica
         // ids, one 16-byte load of two request records).  The ids of the next tile are requested before the current
@@ -302,7 +305,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                     const uint32_t word = tile_of[id[i]];
                     from[i] = word & 0x7FFu;
                     upto[i] = (word >> 11) & 0x7FFu;
-                    kind[i] = kTabled ? (word >> 22) * R : word >> 22;       // tabulated: the type's first table entry
+                    kind[i] = kTabled ? (word >> 22) * R : (word >> 18) & 0x3FF0u;   // tabulated: the type's first table entry; else where the coefficients are
                 }
                 if (kTabled) {
 #pragma unroll
@@ -315,18 +318,16 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                 }
 #pragma unroll
                 for (uint32_t g = 0; g < kHalf; ++g) {
-                    bool listed[2];
+                    unsigned long long listed[2];                                   // which lanes' requests
 #pragma unroll
                     for (uint32_t e = 0; e < 2u; ++e) {
                         const uint32_t i = 2u * g + e;
                         const uint32_t rl = (h * kHalf + g) * 2u * kWave + 2u * lane + e;
-                        const bool in = kWhole || rl < n;
-                        listed[e] = in && rl < from[i];                             // lo <= hi
-                        const bool rejected = in && rl >= upto[i];
-                        const bool streamed = in && !listed[e] && !rejected;
-                        n_rej += (uint32_t)__popcll(__ballot(rejected));
-                        if (p.all_within != 0u) n_ok += (uint32_t)__popcll(__ballot(streamed));   // a wavefront total then
-                        if (streamed) {
+                        const unsigned long long in = kWhole ? ~0ull : __ballot(rl < n);
+                        listed[e] = __ballot(rl < from[i]) & in;                    // lo <= hi
+                        const unsigned long long rejected = __ballot(rl >= upto[i]) & in;
+                        n_rej += (uint32_t)__popcll(rejected);
+                        if (__builtin_amdgcn_inverse_ballot_w64(~(listed[e] | rejected) & in)) {
                             // starts on arrival: ttft = prefill
                             const uint32_t arrival = e ? record[g].z : record[g].x, lens = e ? record[g].w : record[g].y;
                             const uint32_t prompt = lens & 0xFFFFu, out = lens >> 16;
@@ -335,7 +336,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                                 prefill = cost_prefill[i];
                                 tpot = cost_tpot[i];
                             } else {
-                                const uint4 co = coef_of[kind[i]];
+                                const four_words co = *reinterpret_cast<lds_four*>(kind[i]);
                                 prefill = co.x + __umul24(co.y, prompt);            // the host keeps all factors below 2^24
                                 tpot = co.z + __umul24(co.w, (prompt + 1023u) >> 10);
                             }
@@ -353,18 +354,19 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                         }
                     }
                     // queue the listed ones in arrival order: lanes in order, a lane's first request before its second
-                    const unsigned long long lm0 = __ballot(listed[0]), lm1 = __ballot(listed[1]);
+                    const unsigned long long lm0 = listed[0], lm1 = listed[1];
                     if ((lm0 | lm1) == 0ull) continue;
-                    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(lm0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm0, 0u)) +
-                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(lm1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm1, 0u));
+                    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(lm1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm1,
+                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(lm0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm0, q_n))));
                     const uint32_t rl = (h * kHalf + g) * 2u * kWave + 2u * lane;
-                    if (listed[0]) {
+                    const bool first_too = __builtin_amdgcn_inverse_ballot_w64(lm0);
+                    if (first_too) {
                         atomicAdd(&cnt[id[2u * g]], 1u);
-                        queue[q_n + before] = (queued_t)(rl | (id[2u * g] << kIdShift));
+                        queue[before] = (queued_t)(rl | (id[2u * g] << kIdShift));
                     }
-                    if (listed[1]) {
+                    if (__builtin_amdgcn_inverse_ballot_w64(lm1)) {
                         atomicAdd(&cnt[id[2u * g + 1u]], 1u);
-                        queue[q_n + before + (listed[0] ? 1u : 0u)] = (queued_t)((rl + 1u) | (id[2u * g + 1u] << kIdShift));
+                        queue[before + (first_too ? 1u : 0u)] = (queued_t)((rl + 1u) | (id[2u * g + 1u] << kIdShift));
                     }
                     q_n += (uint32_t)__popcll(lm0) + (uint32_t)__popcll(lm1);
                 }
@@ -372,6 +374,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             s_ttft += t_ttft;
             s_e2e += t_e2e;
             s_tpot += t_tpot;
+            n_streamed += n - q_n;                                                  // (the rejected ones are taken off at the end)
             if (!grouping) return;                                                  // q_n is 0 there
             // runs: every replica's listed requests of the tile, starting on a multiple of 8 positions
             const size_t tile_at = (size_t)cb * p.n_list_tiles + j;
@@ -436,7 +439,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
         s_ttft = wave_sum_u64(s_ttft);
         s_tpot = wave_sum_u64(s_tpot);
         last_fin = wave_all_max(last_fin);
-        if (p.all_within == 0u) n_ok = wave_sum_u32(n_ok);                          // else counted per wavefront already
+        n_ok = p.all_within == 0u ? wave_sum_u32(n_ok) : n_streamed - n_rej;        // where all are within the objectives: as many as there are
         if (lane == 0u) {
             atomicAdd(&acc64[0], s_e2e);
             atomicAdd(&acc64[1], s_ttft);
