@@ -2271,10 +2271,10 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
 
 // Four plans per wavefront (k_agentic_rows) where the wavefronts of single plans would crowd the chip or not all be in service at
 // once, as long as all plans of the other form are: that one takes as long for one plan as for all that are resident.  64
-// workflows on 4 + 4 instances, wavefronts of single plans against four: 1024 plans 620 and 900 us, 4608 880 and 1000, 5632 990 and
-// 1000, 6200 1306 and 1003, 8192 1388 and 1011; 8 workflows, 5632 plans 155 and 149 us, 8192 215 and 152.
+// workflows on 4 + 4 instances, wavefronts of single plans against four: 1024 plans 593 and 900 us, 4096 744 and 915, 5632 920 and
+// 1000, 6200 1210 and 1003, 8192 1290 and 1008; 8 workflows, 5632 plans 144 and 149 us, 8192 200 and 152.
 static bool agentic_by_rows(const ap_agentic* a, uint32_t C) {
-    return C > a->n_cu * std::min(22u, a->wave_plans) && C <= a->n_cu * a->row_plans;
+    return C > a->n_cu * std::min(24u, a->wave_plans) && C <= a->n_cu * a->row_plans;
 }
 
 ap_status ap_agentic_eval(const ap_agentic* a, const uint16_t* d_prefill, const uint16_t* d_decode, const uint32_t* d_key,

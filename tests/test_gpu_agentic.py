@@ -154,12 +154,12 @@ def test_hundreds_in_service_that_end_together(decode_us, same_length):
 
 
 @pytest.mark.parametrize("W,P,Q,capacity,rate,bad_ids,C", [
-    (8, 4, 4, 6000, 60.0, False, 6001),           # a last wavefront with one plan
-    (20, 1, 16, 16384, 2000.0, True, 5702),       # all in service at once on one prefill instance, some calls name no instance
-    (20, 16, 1, 1200, 2000.0, True, 5703),        # calls that never fit
-    (64, 16, 16, 60000, 5000.0, True, 5633),      # more calls decode at once than there are slots
+    (8, 4, 4, 6000, 60.0, False, 6201),           # a last wavefront with one plan
+    (20, 1, 16, 16384, 2000.0, True, 6202),       # all in service at once on one prefill instance, some calls name no instance
+    (20, 16, 1, 1200, 2000.0, True, 6203),        # calls that never fit
+    (50, 16, 16, 60000, 5000.0, True, 6145),      # more calls decode at once than there are slots
     (3, 2, 3, 3000, 20.0, False, 8192),           # fewer calls than a row has lanes
-    (60, 4, 4, 6000, 60.0, False, 5634),          # keys with many ties
+    (60, 4, 4, 6000, 60.0, False, 6146),          # keys with many ties
 ])
 def test_four_plans_per_wavefront(W, P, Q, capacity, rate, bad_ids, C):
     """Enough plans that they share wavefronts; the oracle looks at some of them, the first and the last among them."""
