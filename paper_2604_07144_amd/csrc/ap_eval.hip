@@ -220,11 +220,11 @@ static split_fn split_kernel(uint32_t hist_mode, int narrow, bool tabled) {
 }
 
 typedef void (*replay_lists_fn)(SplitParams, uint32_t, uint32_t);
-template <uint32_t kBins_>
+template <uint32_t kBins_, bool kFew>
 static replay_lists_fn replay_lists_kernel_of(uint32_t B) {
-    return B <= 8u ? k_replay_lists<8u, kBins_> : B <= 12u ? k_replay_lists<12u, kBins_> : B <= 16u ? k_replay_lists<16u, kBins_>
-           : B <= 24u ? k_replay_lists<24u, kBins_> : B <= 32u ? k_replay_lists<32u, kBins_>
-           : B <= 48u ? k_replay_lists<48u, kBins_> : k_replay_lists<64u, kBins_>;
+    return B <= 8u ? k_replay_lists<8u, kBins_, kFew> : B <= 12u ? k_replay_lists<12u, kBins_, kFew> : B <= 16u ? k_replay_lists<16u, kBins_, kFew>
+           : B <= 24u ? k_replay_lists<24u, kBins_, kFew> : B <= 32u ? k_replay_lists<32u, kBins_, kFew>
+           : B <= 48u ? k_replay_lists<48u, kBins_, kFew> : k_replay_lists<64u, kBins_, kFew>;
 }
 
 // The dense path on C rows: screening where it applies, then the exact replay of what is left.
@@ -293,8 +293,7 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
     sp.hist = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_hist);
     sp.bin_base = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_bin_base);
     sp.bin_count = reinterpret_cast<uint32_t*>(w->d_split_scratch + plan.o_bin_count);
-    const replay_lists_fn replay_lean = replay_lists_kernel_of<0u>(sp.B);
-    const replay_lists_fn replay_bins = sp.wide_bins ? replay_lists_kernel_of<2u>(sp.B) : replay_lists_kernel_of<1u>(sp.B);
+    const replay_lists_fn replay_lean = replay_lists_kernel_of<0u, false>(sp.B);
     // batches of equal size (whole wavefronts of the list replay), none above what the scratch area holds
     const uint32_t n_batches = (C + plan.batch - 1u) / plan.batch;
     const uint32_t per_batch = std::min(plan.batch, ((C + n_batches - 1u) / n_batches + 63u) / 64u * 64u);
@@ -323,6 +322,9 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         if (sp.n_queues != 0u) {
             const uint32_t groups = align_up(sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads), sp.even_lists ? kXcds : 1u);
             const bool lean = plan.expect_lazy;
+            const bool few = groups <= w->n_cu;
+            const replay_lists_fn replay_bins = sp.wide_bins ? (few ? replay_lists_kernel_of<2u, true>(sp.B) : replay_lists_kernel_of<2u, false>(sp.B))
+                                                             : (few ? replay_lists_kernel_of<1u, true>(sp.B) : replay_lists_kernel_of<1u, false>(sp.B));
             if (lean) hipLaunchKernelGGL(replay_lean, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, 1u);
             hipLaunchKernelGGL(replay_bins, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, lean ? 2u : 0u);
         }

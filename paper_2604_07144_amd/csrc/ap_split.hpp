@@ -96,7 +96,7 @@ struct SplitParams {
     uint32_t* hist;                               // [batch][hist_words] the streamed requests' histograms
     void* bins;                                   // [batch][n_list_tiles * tile_cap] what listed requests add to the histograms, where it is
                                                   //   anything: a bins word as above, or two where the tpot bins span too much
-    uint32_t* bin_base;                           // [batch][M + 1] where a queue's words begin (the requests listed for replicas before it)
+    uint32_t* bin_base;                           // [batch][M + 1] where a queue's words begin (see place_bins)
     uint32_t* bin_count;                          // [batch][M + 1] how many the list replay has left
     uint32_t wide_bins;                           // the latter
     uint32_t least_bin[3], least_us[3];           // no p99 value (ttft, tpot, e2e) can lie below this bin: the list replay leaves smaller ones out
@@ -156,7 +156,8 @@ __device__ __forceinline__ uint2 lanes_alike(uint32_t id, unsigned long long all
     return make_uint2(lo, hi);
 }
 
-// Where the bins of each replica's queue begin: the sums of the listed requests of the replicas before it (one wavefront).
+// Where the bins of each replica's queue begin: the sums of the requests listed for the replicas before it, a tile's counted up to
+// the next multiple of four, which is how the list replay writes (one wavefront).
 template <typename Total>
 __device__ __forceinline__ void place_bins(const SplitParams& p, uint32_t cb, const Total& total_of) {
     const uint32_t lane = threadIdx.x & 63u;
@@ -394,8 +395,8 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                     cnt[m] = 0u;                                                    // for the wavefront's next tile
                     p.desc[tile_at * M + m] = (c << 16) | (n_used + upto - room);
                     if (kHist && c != 0u) {
-                        if (p.off_total != 0u) atomicAdd(&total[m], c);
-                        else atomicAdd(&p.bin_base[(size_t)cb * (M + 1u) + m], c);
+                        if (p.off_total != 0u) atomicAdd(&total[m], (c + 3u) & ~3u);
+                        else atomicAdd(&p.bin_base[(size_t)cb * (M + 1u) + m], (c + 3u) & ~3u);
                     }
                 }
                 n_used += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
@@ -462,7 +463,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             sp.flags = lazy ? kFlagLazy : (kHist ? 0u : kFlagNeedHist);
             p.part[cb] = sp;
         }
-        if (kHist && w == 0u) {
+        if (kHist && !lazy && w == 0u) {
             if (p.off_total != 0u) place_bins(p, cb, [&](uint32_t m) { return total[m]; });
             else place_bins(p, cb, [&](uint32_t m) {
                 return __hip_atomic_load(&p.bin_base[(size_t)cb * (M + 1u) + m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -506,7 +507,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
         const bool row_aligned = (reinterpret_cast<uintptr_t>(row) & 3u) == 0u;
-        uint32_t n_rej = 0;
+        uint32_t n_rej = 0, listed_here = 0;                                         // of replica `lane`
         uint32_t key[kSteps / 2u], key_next[kSteps / 2u];                            // two consecutive ids of every 128
         auto fetch_keys = [&](uint32_t j) {
             const uint32_t r0 = j * kTile;
@@ -580,7 +581,8 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
                 }
                 if (m < M) {
                     run[m] = total + upto - room;
-                    if (c != 0u) atomicAdd(&total_of[m], c);
+                    if (base == 0u) listed_here += (c + 3u) & ~3u;
+                    else if (c != 0u) atomicAdd(&total_of[m], (c + 3u) & ~3u);
                     p.desc[tile_at * M + m] = (c << 16) | (total + upto - room);
                 }
                 total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
@@ -596,6 +598,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         if (lane == 0u) atomicAdd(&rejected_of_row[0], n_rej);                       // a wavefront total
+        if (listed_here != 0u) atomicAdd(&total_of[lane], listed_here);
         __syncthreads();
         if (tid == 0u) {
             SplitPartial sp{};
@@ -603,7 +606,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
             sp.flags = sp.n_rej >= p.lazy_from ? kFlagLazy : kFlagNoStreamHist;
             p.part[cb] = sp;
         }
-        if (w == 0u) place_bins(p, cb, [&](uint32_t m) { return total_of[m]; });
+        if (w == 0u && rejected_of_row[0] < p.lazy_from) place_bins(p, cb, [&](uint32_t m) { return total_of[m]; });
     }
 }
 
@@ -652,7 +655,7 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // a word per position, 661 now, and k_merge_candidates 196 and 51; at ten times the load, where every request leaves a word, the
 // call takes 1.02 times as long as before.  3001 rows of 20011 requests on 50 replicas, half of which come and go, 184 to 168 us, and
 // 4096 rows of 32768 on 64 crowded replicas that come and go 462 to 430.
-// kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
+// kBins: 0 leaves no bins, 1 one word per request, 2 two words.  kFew: no more than a workgroup per compute unit.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
 constexpr uint32_t kListWaves = 4;
 constexpr uint32_t kReplayListThreads = kListWaves * kWave;
@@ -670,7 +673,7 @@ __device__ __forceinline__ void add_wide(uint32_t& lo, uint32_t& hi, uint32_t v)
     asm("v_add_co_u32 %0, vcc, %0, %2\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc" : "+v"(lo), "+v"(hi) : "v"(v) : "vcc");
 }
 
-template <uint32_t kSlots, uint32_t kBins_>
+template <uint32_t kSlots, uint32_t kBins_, bool kFew>
 __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_replay_lists(SplitParams p, uint32_t n_cand, uint32_t which) {
     __shared__ uint4 recs[kReplayTiles * kStagedTile];                              // {arrival, prefill, decode, tpot}
     __shared__ uint32_t goes_on[kListWaves];                                        // the wavefront has a lane with something to replay
@@ -722,18 +725,19 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
         return first;
     };
     typedef uint32_t four_words __attribute__((ext_vector_type(4)));
+    const uint16_t* lists = p.lists + desc_at * p.tile_cap;                         // (the host keeps a candidate's below 2^31 positions)
     // (block b of a run, or where there is none the tile's first: no branches around the loads)
     auto block_of = [&](uint32_t d, uint32_t j, uint32_t b) {
         uint32_t count;
         const uint32_t first = run_of(d, count);
-        return *reinterpret_cast<const four_words*>(p.lists + (desc_at + min(j, n_t - 1u)) * p.tile_cap + (8u * b < count ? first + 8u * b : 0u));
+        return *reinterpret_cast<const four_words*>(lists + (min(j, n_t - 1u) * p.tile_cap + (8u * b < count ? first + 8u * b : 0u)));
     };
     static_assert(kReplayTiles == 2u, "descriptors of a stage and of the next one");
     const uint4 padding = make_uint4(kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u);
     uint32_t d_here[2], d_next[2] = {desc_of(0u), desc_of(1u)};
     four_words e_next = {};                                                         // the block after the one in hand
     if (n_t != 0u) e_next = block_of(d_next[0], 0u, 0u);
-    // the words of the queue's large values, one after the other
+    // the words of the queue's large values, in fours with at least one of them
     const size_t bins_at = with_hist ? (size_t)cb * p.n_list_tiles * p.tile_cap + p.bin_base[(size_t)cb * (p.M + 1u) + m] : 0u;
     uint32_t n_left = 0;
     for (; j0 < n_t; j0 += kReplayTiles) {
@@ -773,13 +777,12 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
         __syncthreads();
         for (uint32_t j = j0; j < min(j0 + kReplayTiles, n_t); ++j) {
             const uint4* tile_recs = recs + (j - j0) * kStagedTile;
-            const size_t tile_at = desc_at + j;
             const uint32_t d = j == j0 ? d_here[0] : d_here[1];
             uint32_t count;
             const uint32_t first = run_of(d, count);
             n_listed += count;
-            // steps of the tile; at least one, so that the next tile's block is requested
-            const uint32_t n_steps = __ballot(live && (s[0] < q.t_off || with_hist)) != 0ull ? max(wave_all_max(count), 1u) : 1u;
+            // steps of the tile; at least one, so that the next tile's block is requested, while there is a lane that still needs it
+            const uint32_t n_steps = __ballot(live && (s[0] < q.t_off || with_hist)) != 0ull ? max(wave_all_max(count), 1u) : 0u;
             uint4 e = padding;
             for (uint32_t k0 = 0; k0 < n_steps; k0 += 4u) {                         // four requests at a time
                 if ((k0 & 4u) == 0u) {
@@ -800,6 +803,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                 uint4 rec[4];
 #pragma unroll
                 for (uint32_t k = 0; k < 4u; ++k) rec[k] = tile_recs[(k & 1u) ? word[k >> 1] >> 16 : word[k >> 1] & 0xFFFFu];
+                uint32_t bins[4] = {0u, 0u, 0u, 0u}, tpot_bins[4] = {0u, 0u, 0u, 0u};
                 // How many of the lower groups of registers hold still (a lane without a request is ready at kNever)
                 const uint32_t ready = max(rec[0].x, q.t_on);
                 uint32_t still = 0u;
@@ -831,14 +835,28 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                         last_fin = max(last_fin, fin);
                         ++n_served;
                         n_ok += (ttft <= p.slo_ttft && rq.w <= slo_tpot) ? 1u : 0u;
-                        if (kBins_ != 0u && with_hist & ((ttft >= p.least_us[0]) | (rq.w >= p.least_us[1]) | (e2e >= p.least_us[2]))) {
-                            const uint32_t tpot_bin = bin_above(rq.w, p.least_us[1], p.least_bin[1]);
-                            const uint32_t both = bin_above(ttft, p.least_us[0], p.least_bin[0]) | (bin_above(e2e, p.least_us[2], p.least_bin[2]) << 12);
-                            if (kBins_ == 2u) reinterpret_cast<uint2*>(p.bins)[bins_at + n_left] = make_uint2(both, tpot_bin);
-                            else reinterpret_cast<uint32_t*>(p.bins)[bins_at + n_left] = both | (tpot_bin << 24);
-                            ++n_left;
+                        if (kBins_ != 0u) {
+                            // (a lone wavefront takes longer over the branch than over the bins: 19 rows of 20480 requests on 5 replicas 1295
+                            // against 1157 us; with a chip full of them they cost more, sweeps of 131072 requests 1080 against 1009)
+                            if (kFew || ((ttft >= p.least_us[0]) | (rq.w >= p.least_us[1]) | (e2e >= p.least_us[2]))) {
+                                const uint32_t tpot_bin = bin_above(rq.w, p.least_us[1], p.least_bin[1]);
+                                bins[k] = bin_above(ttft, p.least_us[0], p.least_bin[0]) | (bin_above(e2e, p.least_us[2], p.least_bin[2]) << 12) |
+                                          (kBins_ == 2u ? 0u : tpot_bin << 24);
+                                tpot_bins[k] = tpot_bin;
+                            }
                         }
                     }
+                }
+                const bool leaves = kBins_ != 0u && with_hist && (bins[0] | bins[1] | bins[2] | bins[3] | (kBins_ == 2u ? tpot_bins[0] | tpot_bins[1] | tpot_bins[2] | tpot_bins[3] : 0u)) != 0u;
+                if (leaves) {
+                    if (kBins_ == 2u) {
+                        uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + bins_at + n_left);
+                        dst[0] = make_uint4(bins[0], tpot_bins[0], bins[1], tpot_bins[1]);
+                        dst[1] = make_uint4(bins[2], tpot_bins[2], bins[3], tpot_bins[3]);
+                    } else {
+                        *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + bins_at + n_left) = make_uint4(bins[0], bins[1], bins[2], bins[3]);
+                    }
+                    n_left += 4u;
                 }
             }
         }
