@@ -649,12 +649,12 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as one vector
 // and the empty asm where it is waited for.  A pair of steps that no lane needs is left out.  Where all lists are
 // as long as the trace, neighbouring replicas share an XCD, whose L2 then holds their runs once.  A queue's words for the
-// histograms follow one another (place_bins), and only requests with a value that a p99 value can reach leave one: on a trace that is
-// not hopelessly overloaded one in fifty to one in ten, where a word per list position was a gigabyte of 16-byte stores to as many
-// cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1190 us before all of this, 983 with
-// a word per position, 661 now, and k_merge_candidates 196 and 51; at ten times the load, where every request leaves a word, the
-// call takes 1.02 times as long as before.  3001 rows of 20011 requests on 50 replicas, half of which come and go, 184 to 168 us, and
-// 4096 rows of 32768 on 64 crowded replicas that come and go 462 to 430.
+// histograms follow one another (place_bins), four requests at a time where one of the four has a value that a p99 value can reach: on a
+// trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list position was a gigabyte of 16-byte
+// stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1190 us before
+// all of this, 983 with a word per position, 690 now, and k_merge_candidates 196 and 55; at ten times the load the whole call 1663 and
+// 1568.  3001 rows of 20011 requests on 50 replicas, half of which come and go, 184 to 165 us, and 4096 rows of 32768 on 64 crowded
+// replicas that come and go 462 to 430.  (Rows of three tiles: 99 to 101 us for 9251 rows of 2993 requests.)
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  kFew: no more than a workgroup per compute unit.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
 constexpr uint32_t kListWaves = 4;
@@ -736,7 +736,6 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     const uint4 padding = make_uint4(kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u);
     uint32_t d_here[2], d_next[2] = {desc_of(0u), desc_of(1u)};
     four_words e_next = {};                                                         // the block after the one in hand
-    if (n_t != 0u) e_next = block_of(d_next[0], 0u, 0u);
     // the words of the queue's large values, in fours with at least one of them
     const size_t bins_at = with_hist ? (size_t)cb * p.n_list_tiles * p.tile_cap + p.bin_base[(size_t)cb * (p.M + 1u) + m] : 0u;
     uint32_t n_left = 0;
@@ -774,6 +773,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             }
         }
         if (tid < kReplayTiles) recs[tid * kStagedTile + kTile] = make_uint4(kNever, 0u, 0u, 0u);
+        if (j0 == 0u) e_next = block_of(d_here[0], 0u, 0u);                         // (behind the records: a short trace waits once)
         __syncthreads();
         for (uint32_t j = j0; j < min(j0 + kReplayTiles, n_t); ++j) {
             const uint4* tile_recs = recs + (j - j0) * kStagedTile;
@@ -781,8 +781,8 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             uint32_t count;
             const uint32_t first = run_of(d, count);
             n_listed += count;
-            // steps of the tile; at least one, so that the next tile's block is requested, while there is a lane that still needs it
-            const uint32_t n_steps = __ballot(live && (s[0] < q.t_off || with_hist)) != 0ull ? max(wave_all_max(count), 1u) : 0u;
+            // steps of the tile; at least one, so that the next tile's block and the next stage's descriptors are requested
+            const uint32_t n_steps = __ballot(live && (s[0] < q.t_off || with_hist)) != 0ull ? max(wave_all_max(count), 1u) : 1u;
             uint4 e = padding;
             for (uint32_t k0 = 0; k0 < n_steps; k0 += 4u) {                         // four requests at a time
                 if ((k0 & 4u) == 0u) {

@@ -187,3 +187,21 @@ def test_bins_few_and_many(load, slow, kinds):
     rows[3, ::7] = M
     with GpuWorkload(tr) as g:
         assert_same(g.eval(rows)[:24], oracle_for(tr).eval_batch(rows[:24], nthreads=8), f"load {load}")
+
+
+@pytest.mark.parametrize("R", [7000, 9217])
+def test_a_wavefront_with_nothing_left_to_start_beside_others(R):
+    """64 rows that crowd a replica until no slot comes free before it leaves, next to rows that do not: their wavefront only counts
+    its requests from then on, stage after stage, while the workgroup's others replay theirs."""
+    rng = np.random.default_rng(R)
+    M, B = 3, 8
+    arrival = np.cumsum(rng.integers(0, 60, R)).astype(np.uint64)
+    t_off = [int(arrival[-1]) - 1, int(arrival[R // 2]), traces.UINT64_MAX]
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[m % 3] for m in range(M)], t_off_us=t_off, B=B)
+    rows = rng.integers(1, M, size=(700, R)).astype(np.uint16)
+    rows[64:][:, ::40] = 0
+    rows[:64] = np.where(rng.random((64, R)) < 0.9, 0, rows[:64])
+    some = np.concatenate([np.arange(0, 64, 5), np.arange(64, 700, 41)])
+    with GpuWorkload(tr) as g:
+        got = g.eval(rows)
+    assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"R={R}")
