@@ -32,23 +32,21 @@ KERNEL_SOURCE_DIR = os.path.join(ROOT, "paper_2604_07144_amd", "csrc")
 # HBM bytes per ap_eval_candidates call from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch, summed over
 # the call's kernels, scaled by what the same counters read for a device copy of known size; see profiles/).
 # Keyed by configuration; valid only for the library source (all of csrc/) whose hash is recorded with it.
-# (Taken at 67614088...; what the source has changed since is the rule that sends small calls to the fused replay, on the
-# host: the device code is the same.)
 MEASURED_TRAFFIC = {
     # cfg: (sha256 of the kernel source, bytes per call)
-    4: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", 4304680356),
-    3: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", 1934106508),
+    4: ("8786e3ac6ed7d9e7547cf75e35c2b4c8593b3291b7b3d26217858b1edf399d6c", 4304555774),
+    3: ("8786e3ac6ed7d9e7547cf75e35c2b4c8593b3291b7b3d26217858b1edf399d6c", 2282372760),
 }
 # Wave-instructions per candidate-request of one ap_eval_candidates call (all its kernels), from rocprofv3 --pmc
 # SQ_INSTS_VALU / SQ_INSTS_SALU / SQ_INSTS_LDS; same validity rule.  The chip issues at most 256 CUs x 4 SIMDs x
 # 2.4 GHz / 4 cycles = 6.1e11 64-lane vector instructions per second.
 VALU_PEAK_PER_S = 256 * 4 * 2.4e9 / 4
 MEASURED_ALU = {
-    4: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", {"valu": 0.1226, "salu": 0.0869, "lds": 0.0275}),
-    3: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", {"valu": 1.5650, "salu": 0.4630, "lds": 0.1260}),
+    4: ("8786e3ac6ed7d9e7547cf75e35c2b4c8593b3291b7b3d26217858b1edf399d6c", {"valu": 0.1224, "salu": 0.0869, "lds": 0.0274}),
+    3: ("8786e3ac6ed7d9e7547cf75e35c2b4c8593b3291b7b3d26217858b1edf399d6c", {"valu": 1.4804, "salu": 0.3988, "lds": 0.1209}),
 }
 # the same for one ap_eval_children call on the sparse form of configs[4]
-MEASURED_TRAFFIC_CHILDREN = {4: ("a73f87853098e8d8b9b90873b27e2a753d988cf379da713d03f58715619f2455", 131238425)}
+MEASURED_TRAFFIC_CHILDREN = {4: ("8786e3ac6ed7d9e7547cf75e35c2b4c8593b3291b7b3d26217858b1edf399d6c", 131178757)}
 
 
 def kernel_source_hash() -> str:

@@ -959,24 +959,46 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
             const uint32_t m = sp.order[i];
             return make_uint2(sp.bin_base[queues_at + m], sp.bin_count[queues_at + m]);
         };
-        uint2 next = queue_at(wave_index());
-        for (uint32_t i = wave_index(); i < sp.n_queues; i += kThreads / kWave) {
-            const uint2 here = next;
-            next = queue_at(i + kThreads / kWave);
-            for (uint32_t k = lane; k < here.y; k += kWave) {
-                uint32_t both, tpot;
-                if (sp.wide_bins != 0u) {
-                    const uint2 word = reinterpret_cast<const uint2*>(sp.bins)[bins_at + here.x + k];
-                    both = word.x;
-                    tpot = word.y;
-                } else {
-                    both = reinterpret_cast<const uint32_t*>(sp.bins)[bins_at + here.x + k];
-                    tpot = both >> 24;
+        auto add = [&](uint32_t both, uint32_t tpot) {
+            const uint32_t ttft = both & 0xFFFu, e2e = (both >> 12) & 0xFFFu;
+            if (ttft != 0u) hist_add<kHist16>(hist, 0u, min(sp.least_bin[0] + ttft - 1u, kBins - 1u), 1u);
+            if (tpot != 0u) hist_add<kHist16>(hist, 1u, min(sp.least_bin[1] + tpot - 1u, kBins - 1u), 1u);
+            if (e2e != 0u) hist_add<kHist16>(hist, 2u, min(sp.least_bin[2] + e2e - 1u, kBins - 1u), 1u);
+        };
+        if (sp.n_queues > 2u * kWave) {              // many queues with few words each: a lane per queue, four words at a time
+            for (uint32_t i = tid; i < sp.n_queues; i += kThreads) {
+                const uint2 here = queue_at(i);
+                for (uint32_t k = 0; k < here.y; k += 4u) {
+                    if (sp.wide_bins != 0u) {
+                        const uint4* src2 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint2*>(sp.bins) + bins_at + here.x + k);
+                        const uint4 v = src2[0], u = src2[1];
+                        add(v.x, v.y);
+                        add(v.z, v.w);
+                        add(u.x, u.y);
+                        add(u.z, u.w);
+                    } else {
+                        const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(sp.bins) + bins_at + here.x + k);
+                        add(v.x, v.x >> 24);
+                        add(v.y, v.y >> 24);
+                        add(v.z, v.z >> 24);
+                        add(v.w, v.w >> 24);
+                    }
                 }
-                const uint32_t ttft = both & 0xFFFu, e2e = (both >> 12) & 0xFFFu;
-                if (ttft != 0u) hist_add<kHist16>(hist, 0u, min(sp.least_bin[0] + ttft - 1u, kBins - 1u), 1u);
-                if (tpot != 0u) hist_add<kHist16>(hist, 1u, min(sp.least_bin[1] + tpot - 1u, kBins - 1u), 1u);
-                if (e2e != 0u) hist_add<kHist16>(hist, 2u, min(sp.least_bin[2] + e2e - 1u, kBins - 1u), 1u);
+            }
+        } else {
+            uint2 next = queue_at(wave_index());
+            for (uint32_t i = wave_index(); i < sp.n_queues; i += kThreads / kWave) {
+                const uint2 here = next;
+                next = queue_at(i + kThreads / kWave);
+                for (uint32_t k = lane; k < here.y; k += kWave) {
+                    if (sp.wide_bins != 0u) {
+                        const uint2 word = reinterpret_cast<const uint2*>(sp.bins)[bins_at + here.x + k];
+                        add(word.x, word.y);
+                    } else {
+                        const uint32_t word = reinterpret_cast<const uint32_t*>(sp.bins)[bins_at + here.x + k];
+                        add(word, word >> 24);
+                    }
+                }
             }
         }
         __syncthreads();
