@@ -203,6 +203,13 @@ struct ap_workload {
     SplitPlan split_plan{};
 };
 
+// Do a kernel's dynamic tables begin at LDS address 0?  k_stream_candidates and k_split_candidates read their first table by address, and
+// whatever a kernel declares itself (__shared__) would come before it.
+static bool tables_at_lds_zero(const void* kernel) {
+    hipFuncAttributes attr;
+    return hipFuncGetAttributes(&attr, kernel) == hipSuccess && attr.sharedSizeBytes == 0u;
+}
+
 typedef void (*stream_fn)(StreamParams, const uint16_t*, ap_metrics*, uint32_t, PendingWord);
 static stream_fn stream_kernel(bool settles, bool tabled) {
     return settles ? (tabled ? k_stream_candidates<true, false> : k_stream_candidates<false, false>)
@@ -767,6 +774,9 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         plan.lds_bytes_hist += align_up(M * 4u, 16u);
     }
     const int narrow = M <= 64u ? 1 : 0;
+    if (!tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled))) ||
+        !tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled))))
+        return device_error();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_list_candidates), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)plan.lds_bytes_list) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled)),
@@ -1085,6 +1095,7 @@ static ap_status plan_stream(ap_workload* w, const ap_replica* replicas, const s
     sp.all_within = highest[0] < ap_hist_bin(sp.slo_ttft) && highest[1] < ap_hist_bin(sp.slo_tpot) ? 1u : 0u;
     sp.penalty_bin = w->params.penalty_bin;
     sp.penalty = w->params.penalty;
+    if (!tables_at_lds_zero(reinterpret_cast<const void*>(stream_kernel(settles, tabled)))) return device_error();
     constexpr uint32_t large = kStreamMaxThreads / kWave * kStreamLargeBytes;
     if (off + large > 65536u &&
         hipFuncSetAttribute(reinterpret_cast<const void*>(stream_kernel(settles, tabled)), hipFuncAttributeMaxDynamicSharedMemorySize,

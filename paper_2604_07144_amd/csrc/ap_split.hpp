@@ -208,7 +208,8 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     unsigned long long* same = reinterpret_cast<unsigned long long*>(mine + p.w_same);   // [M] lanes naming the replica
     uint32_t* tile_of = reinterpret_cast<uint32_t*>(mine + p.w_tile);        // [M + 1] the replica's ranges within the tile in hand
     uint32_t* total = reinterpret_cast<uint32_t*>(lds + p.off_total);        // kHist only: [M]
-    // the coefficients lie at LDS address 0 (read by address: through the array's name every access costs an addition of its base)
+    // The coefficients lie at LDS address 0 (read by address: through the array's name every access costs an addition of its base).  The
+    // kernel must declare no __shared__ variable of its own: the host asks (tables_at_lds_zero).
     typedef uint32_t four_words __attribute__((ext_vector_type(4)));
     typedef __attribute__((address_space(3))) const four_words lds_four;
     const uint32_t R = p.R, M = p.M;

@@ -172,7 +172,8 @@ __global__ __launch_bounds__(kStreamMaxThreads, 6) void k_stream_candidates(Stre
         // kPlain: all 128 requests exist and name a replica.
         uint32_t prefill[2], tpot[2], e2e[2];
         unsigned long long is_large[2];                                      // which lanes' requests
-        // (by LDS address, which begins at 0 with the kinds: through the array's name every access costs an addition of its base)
+        // (by LDS address, which begins at 0 with the kinds: through the array's name every access costs an addition of its base.  The
+        // kernel must declare no __shared__ variable of its own: the host asks, tables_at_lds_zero)
         typedef __attribute__((address_space(3))) const uint32_t lds_word;
         typedef uint32_t four_words __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) const four_words lds_four;

@@ -2,9 +2,12 @@
 symbol the header declares, and its host helpers agree with the oracle's histogram map."""
 import os
 import re
+import shutil
+import struct
 import subprocess
 
 import numpy as np
+import pytest
 
 import oracle
 from paper_2604_07144_amd import binding
@@ -83,6 +86,34 @@ def test_struct_layouts_match_the_header_as_gcc_sees_it(tmp_path):
     assert seen[("ap_decode_instance", "size")] == 12
     from oracle import agentic
     assert agentic.METRICS_DTYPE == binding.AGENTIC_METRICS_DTYPE
+
+
+def static_lds_of_kernels(library, tmp_path):
+    """{kernel: bytes of LDS it declares itself}, from the metadata of the library's gfx950 code object."""
+    readelf = shutil.which("llvm-readelf", path=os.environ.get("PATH", "") + ":/opt/rocm/llvm/bin")
+    if readelf is None:
+        pytest.skip("no llvm-readelf")
+    data = open(library, "rb").read()
+    at = data.index(b"__CLANG_OFFLOAD_BUNDLE__")
+    pos, code = at + 32, None
+    for _ in range(struct.unpack_from("<Q", data, at + 24)[0]):
+        offset, size, n = struct.unpack_from("<QQQ", data, pos)
+        if b"gfx950" in data[pos + 24:pos + 24 + n]:
+            code = data[at + offset:at + offset + size]
+        pos += 24 + n
+    elf = tmp_path / "gfx950.elf"
+    elf.write_bytes(code)
+    notes = subprocess.run([readelf, "--notes", str(elf)], check=True, capture_output=True, text=True).stdout
+    return {re.search(r"\.name:\s+(\S+)", block).group(1): int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", block).group(1))
+            for block in notes.split("  - .agpr_count:")[1:]}
+
+
+def test_kernels_that_read_lds_from_address_zero_declare_none(tmp_path):
+    """The streaming kernels read their first table by LDS address, from 0 on: right only while it is the dynamic part that begins there."""
+    declared = static_lds_of_kernels(binding.LIB_PATH, tmp_path)
+    by_address = [k for k in declared if "k_stream_candidates" in k or "k_split_candidates" in k]
+    assert len(by_address) == 4 + 12
+    assert {k: declared[k] for k in by_address if declared[k] != 0} == {}
 
 
 def test_generators_produce_well_formed_inputs():
