@@ -792,6 +792,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     const size_t per_cand = (size_t)sp.n_list_tiles * sp.tile_cap * (2u + bins_bytes) + (size_t)sp.n_list_tiles * M * 4u +
                             sizeof(SplitPartial) + hist_bytes + 2u * (M + 1u) * 4u;
     if (per_cand > ((size_t)8 << 30) / 64u) return AP_OK;       // a trace so long that 64 candidates' lists take over 8 GiB
+    // (2 of every 6 or 10 bytes are the lists themselves, so those of a batch stay below 2^32 bytes, which the list replay relies on)
     uint32_t batch = (uint32_t)std::min<size_t>(16384u, std::max<size_t>(64u, ((size_t)4 << 30) / per_cand));
     batch = batch / 64u * 64u;
     auto carve = [](size_t& at, size_t bytes) { const size_t here = at; at = (at + bytes + 255u) / 256u * 256u; return here; };

@@ -631,8 +631,7 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // s'[i] = med3(s[i], f, s[i+1]), i.e. min(s[i+1], max(s[i], f)).  A lane without a request in a step (or whose
 // request is rejected) inserts 0, which leaves the registers as they are.
 // Starts do not decrease along a queue, so once a start reaches t_off every later request is rejected too: a tile in which no
-// lane's earliest slot comes free in time is only counted (unless a lane leaves bins), and a workgroup without such a lane
-// stages nothing more.  (4096 rows of 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
+// lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.  (4096 rows of 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
 // kSlots: B rounded up to 8, 12, 16, 24, 32, 48 or 64; registers beyond B hold kNever and stay there.
 //
 // Bound by instruction issue, most of it the medians.  What every lane would evaluate for itself is done once while staging
@@ -722,16 +721,19 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     auto desc_of = [&](uint32_t j) { return live && j < n_t ? p.desc[(desc_at + j) * p.M + m] : 0u; };
     auto run_of = [&](uint32_t d, uint32_t& count) {                                // a descriptor that was never written that way lists nothing
         const uint32_t first = d & 0xFFFFu;
-        count = ((first & 7u) != 0u) | (first + (((d >> 16) + 7u) & ~7u) > p.tile_cap) ? 0u : d >> 16;
+        count = (((first & 7u) != 0u) | (first + (((d >> 16) + 7u) & ~7u) > p.tile_cap)) ? 0u : d >> 16;
         return first;
     };
     typedef uint32_t four_words __attribute__((ext_vector_type(4)));
-    const uint16_t* lists = p.lists + desc_at * p.tile_cap;                         // (the host keeps a candidate's below 2^31 positions)
-    // (block b of a run, or where there is none the tile's first: no branches around the loads)
+    // Block b of a run.  A lane without one reads where all such lanes do, the area's first 16 bytes, so that there is no branch around
+    // the load and next to no traffic: where each read its own tile's first block, one that no lane needed, 8388 rows of 8000 requests
+    // that crowd 50 of 300 replicas took 605 us in here, 351 before anything was read ahead, 359 now.
+    const uint32_t lists_at = 2u * p.tile_cap * (uint32_t)desc_at;                  // bytes: plan_split keeps a batch's lists below 2^32
     auto block_of = [&](uint32_t d, uint32_t j, uint32_t b) {
         uint32_t count;
         const uint32_t first = run_of(d, count);
-        return *reinterpret_cast<const four_words*>(lists + (min(j, n_t - 1u) * p.tile_cap + (8u * b < count ? first + 8u * b : 0u)));
+        const uint32_t at = 8u * b < count ? lists_at + 2u * (j * p.tile_cap + first + 8u * b) : 0u;
+        return *reinterpret_cast<const four_words*>(reinterpret_cast<const char*>(p.lists) + at);
     };
     static_assert(kReplayTiles == 2u, "descriptors of a stage and of the next one");
     const uint4 padding = make_uint4(kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u, kPadding * 0x10001u);
@@ -743,7 +745,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     for (; j0 < n_t; j0 += kReplayTiles) {
         const uint32_t r0 = j0 * kTile, n = min(kReplayTiles * kTile, p.R - r0);
         if ((tid & 63u) == 0u) goes_on[wave_index()] = 0u;
-        if (__ballot(live && (s[0] < q.t_off || with_hist)) != 0ull && (tid & 63u) == 0u) goes_on[wave_index()] = 1u;
+        if (__ballot(live && s[0] < q.t_off) != 0ull && (tid & 63u) == 0u) goes_on[wave_index()] = 1u;
         __syncthreads();                                                            // also: the last stage's records were read
         uint32_t any = 0u;
 #pragma unroll
@@ -780,10 +782,11 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             const uint4* tile_recs = recs + (j - j0) * kStagedTile;
             const uint32_t d = j == j0 ? d_here[0] : d_here[1];
             uint32_t count;
-            const uint32_t first = run_of(d, count);
+            (void)run_of(d, count);
             n_listed += count;
-            // steps of the tile; at least one, so that the next tile's block and the next stage's descriptors are requested
-            const uint32_t n_steps = __ballot(live && (s[0] < q.t_off || with_hist)) != 0ull ? max(wave_all_max(count), 1u) : 1u;
+            // Steps of the tile; where nothing can start there is one all the same, in which only the next tile's block and the next
+            // stage's descriptors are requested.
+            const uint32_t most = __ballot(live && s[0] < q.t_off) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
             uint4 e = padding;
             for (uint32_t k0 = 0; k0 < n_steps; k0 += 4u) {                         // four requests at a time
                 if ((k0 & 4u) == 0u) {
@@ -800,6 +803,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                     e.x = e.z;
                     e.y = e.w;
                 }
+                if (most == 0u) continue;
                 const uint32_t word[2] = {e.x, e.y};
                 uint4 rec[4];
 #pragma unroll

@@ -205,3 +205,42 @@ def test_a_wavefront_with_nothing_left_to_start_beside_others(R):
     with GpuWorkload(tr) as g:
         got = g.eval(rows)
     assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"R={R}")
+
+
+@pytest.mark.parametrize("R", [1024, 5000, 8193])
+@pytest.mark.parametrize("B", [12, 64])
+def test_queues_that_few_rows_use(R, B):
+    """More blocks of candidates than compute units, and most wavefronts of the list replay find tiles, or whole queues, without a
+    request among blocks that have some: rows on a few of the replicas, on one for a stretch of the trace, on all."""
+    rng = np.random.default_rng(R + B)
+    M, C = 130, 700
+    arrival = np.cumsum(rng.integers(0, 8, R)).astype(np.uint64)
+    t_off = np.where(np.arange(M) % 3 == 1, int(arrival[2 * R // 3]), U64MAX).astype(np.uint64)
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[m % 3] for m in range(M)], t_off_us=t_off, B=B)
+    rows = rng.integers(0, 9, size=(C, R)).astype(np.uint16)
+    rows[70] = np.arange(R) * M // R
+    rows[71], rows[C - 1] = M - 1, rng.integers(0, M, R)
+    rows[640:650, 3000:] = M
+    some = np.unique(np.concatenate([np.arange(0, C, 60), np.arange(69, 73), np.arange(638, 652, 3), [C - 1]]))
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["lists"] != 3
+        got = g.eval(rows)
+    assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"R={R} B={B}")
+
+
+@pytest.mark.parametrize("C", [40, 700])
+def test_a_queue_that_closes_early_in_rows_that_need_histograms(C):
+    """A crowded replica leaves in the first third of the trace, and so few requests name it that the p99 values come from the
+    histograms: its wavefronts have bins to leave at first and nothing to start after that, tile after tile."""
+    rng = np.random.default_rng(C)
+    R, M, B = 9000, 5, 8
+    arrival = np.cumsum(rng.integers(0, 400, R)).astype(np.uint64)
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[m % 3] for m in range(M)],
+                             t_off_us=[int(arrival[R // 3])] + [U64MAX] * (M - 1), B=B)
+    rows = rng.integers(1, M, size=(C, R)).astype(np.uint16)
+    rows[:, R // 4:R // 4 + 60] = 0
+    rows[1::2, R // 3 + 100:R // 3 + 120] = 0
+    want = oracle_for(tr).eval_batch(rows[:40], nthreads=8)
+    assert (want["n_rejected"] > 0).any() and (want["n_rejected"] < R // 100).all()
+    with GpuWorkload(tr) as g:
+        assert_same(g.eval(rows)[:40], want, f"C={C}")
