@@ -288,6 +288,9 @@ static ap_status launch_counts(const ap_workload* w, const uint16_t* d_assign, u
     return hipGetLastError() == hipSuccess ? AP_OK : device_error();
 }
 
+// Histograms and accumulators, and behind them two words per queue.
+static uint32_t merge_lds_bytes(const ap_workload* w, const SplitParams& sp) { return w->reduce_lds_bytes + 8u * sp.n_queues; }
+
 // The listed / streamed evaluation, a batch of candidates at a time; what it hands back carries the pending mark.
 // pending: only candidates that carry the pending mark already (behind the streamed evaluation).
 static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const uint16_t* d_assign, uint32_t C, ap_metrics* d_out,
@@ -336,7 +339,7 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
             hipLaunchKernelGGL(replay_bins, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, lean ? 2u : 0u);
         }
         hipLaunchKernelGGL(sp.wide ? k_merge_candidates<false> : k_merge_candidates<true>, dim3(std::min(n, w->n_cu * 8u)),
-                           dim3(kThreads), w->reduce_lds_bytes, stream, w->reduce_eval, sp, d_out, c0, n, flags);
+                           dim3(kThreads), merge_lds_bytes(w, sp), stream, w->reduce_eval, sp, d_out, c0, n, flags);
     }
     return hipGetLastError() == hipSuccess ? AP_OK : device_error();
 }
@@ -724,6 +727,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.n_list_tiles = (longest_list + kTile - 1u) / kTile;
     sp.tile_cap = align_up(std::min(kTile, R) + 7u * std::min(M, std::min(kTile, R)), 8u);
     sp.n_queues = (uint32_t)order.size();
+    for (sp.queue_span = 1u; sp.queue_span * 2u <= sp.n_queues;) sp.queue_span *= 2u;
     sp.even_lists = sp.n_queues == M && queue[order.front()].i_list == queue[order.back()].i_list ? 1u : 0u;
     sp.slo_ttft = w->params.slo_ttft;
     sp.slo_tpot = w->params.slo_tpot;
@@ -845,7 +849,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     if (hipMemcpy(plan.tables, words.data(), 4u * words.size(), hipMemcpyHostToDevice) != hipSuccess ||
         hipFuncSetAttribute(wide ? reinterpret_cast<const void*>(&k_merge_candidates<false>)
                                  : reinterpret_cast<const void*>(&k_merge_candidates<true>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)w->reduce_lds_bytes) != hipSuccess) {
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)merge_lds_bytes(w, sp)) != hipSuccess) {
         (void)hipGetLastError();
         return device_error();
     }

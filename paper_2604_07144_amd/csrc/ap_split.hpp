@@ -112,6 +112,7 @@ struct SplitParams {
     uint32_t any_streamed;                        // some replica has a streamed part
     uint32_t R, M, B, key_bits;
     uint32_t n_tiles, n_list_tiles, tile_cap, n_queues;
+    uint32_t queue_span;                          // the largest power of two up to n_queues
     uint32_t even_lists;                          // every replica has a list, and all are equally long
     uint32_t slo_ttft, slo_tpot;
     uint32_t lazy_from;                           // rejected requests from which the p99 values are the penalty; kNever: never
@@ -895,7 +896,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 // Merge: one record per candidate from its partial sums.  A candidate settled by penalty is written by one
 // thread; one that the list replay handed back gets the pending mark (the general replay scores it next); for
 // the others a workgroup takes the streamed requests' histograms from device memory, adds the bins the list replay
-// left, queue by queue, and goes through the usual block-wide reduction.
+// left and goes through the usual block-wide reduction.
 template <bool kHist16>
 __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, SplitParams sp, ap_metrics* __restrict__ out,
                                                                uint32_t c0, uint32_t n_cand, PendingWord flags) {
@@ -904,6 +905,8 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_misc);
     uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_misc + 24);
     uint32_t* wtot = reinterpret_cast<uint32_t*>(lds + p.off_misc + 64);
+    uint32_t* n_before = wtot + 3u * kWaves;                                         // [n_queues], and then
+    uint32_t* at_of = n_before + sp.n_queues;                                        // [n_queues]
     const uint32_t tid = threadIdx.x;
     if (split_nothing_pending(sp)) return;
     // One workgroup per candidate that needs its histograms; the others are one thread's work each, so a
@@ -956,54 +959,54 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
             reinterpret_cast<uint4*>(hist)[i] = parked ? reinterpret_cast<const uint4*>(src)[i] : make_uint4(0u, 0u, 0u, 0u);
         if (tid < 16u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
-        // A queue per wavefront at a time, where the next one's words lie requested ahead.
-        const uint32_t lane = tid & 63u;
+        // The words of all queues as one sequence, four at a time and a four per thread, however they are spread over the queues:
+        // n_before[i] fours lie before queue i's, and the sequence's f-th four is the candidate's (f + at_of[i])-th.  (With a queue per
+        // wavefront, or per lane where there are many, one long queue kept the workgroup waiting: 559 rows of 60000 requests that crowd 42
+        // of 256 replicas 383 us, 131 before bins were compact, 80 now; 11184 of 3000 on one of 8, 472, 261 and 135; one row of 16384 on
+        // 2 replicas, 57, 26 and 19.)
         const size_t bins_at = (size_t)c * sp.n_list_tiles * sp.tile_cap, queues_at = (size_t)c * (sp.M + 1u);
-        auto queue_at = [&](uint32_t i) {
-            if (i >= sp.n_queues) return make_uint2(0u, 0u);
-            const uint32_t m = sp.order[i];
-            return make_uint2(sp.bin_base[queues_at + m], sp.bin_count[queues_at + m]);
-        };
+        uint32_t n_fours = 0;
+        for (uint32_t base = 0; base < sp.n_queues; base += kThreads) {
+            const uint32_t i = base + tid, m = i < sp.n_queues ? sp.order[i] : 0u;
+            const uint32_t n = i < sp.n_queues ? sp.bin_count[queues_at + m] / 4u : 0u, first = sp.bin_base[queues_at + m] / 4u;
+            const uint32_t upto = wave_inclusive_scan(n, tid & 63u);
+            if ((tid & 63u) == 63u) wtot[wave_index()] = upto;
+            __syncthreads();
+            uint32_t before = n_fours + upto - n;
+#pragma unroll
+            for (uint32_t ww = 0; ww < kWaves; ++ww) {
+                before += ww < wave_index() ? wtot[ww] : 0u;
+                n_fours += wtot[ww];
+            }
+            if (i < sp.n_queues) {
+                n_before[i] = before;
+                at_of[i] = first - before;
+            }
+            __syncthreads();
+        }
         auto add = [&](uint32_t both, uint32_t tpot) {
             const uint32_t ttft = both & 0xFFFu, e2e = (both >> 12) & 0xFFFu;
             if (ttft != 0u) hist_add<kHist16>(hist, 0u, min(sp.least_bin[0] + ttft - 1u, kBins - 1u), 1u);
             if (tpot != 0u) hist_add<kHist16>(hist, 1u, min(sp.least_bin[1] + tpot - 1u, kBins - 1u), 1u);
             if (e2e != 0u) hist_add<kHist16>(hist, 2u, min(sp.least_bin[2] + e2e - 1u, kBins - 1u), 1u);
         };
-        if (sp.n_queues > 2u * kWave) {              // many queues with few words each: a lane per queue, four words at a time
-            for (uint32_t i = tid; i < sp.n_queues; i += kThreads) {
-                const uint2 here = queue_at(i);
-                for (uint32_t k = 0; k < here.y; k += 4u) {
-                    if (sp.wide_bins != 0u) {
-                        const uint4* src2 = reinterpret_cast<const uint4*>(reinterpret_cast<const uint2*>(sp.bins) + bins_at + here.x + k);
-                        const uint4 v = src2[0], u = src2[1];
-                        add(v.x, v.y);
-                        add(v.z, v.w);
-                        add(u.x, u.y);
-                        add(u.z, u.w);
-                    } else {
-                        const uint4 v = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint32_t*>(sp.bins) + bins_at + here.x + k);
-                        add(v.x, v.x >> 24);
-                        add(v.y, v.y >> 24);
-                        add(v.z, v.z >> 24);
-                        add(v.w, v.w >> 24);
-                    }
-                }
-            }
-        } else {
-            uint2 next = queue_at(wave_index());
-            for (uint32_t i = wave_index(); i < sp.n_queues; i += kThreads / kWave) {
-                const uint2 here = next;
-                next = queue_at(i + kThreads / kWave);
-                for (uint32_t k = lane; k < here.y; k += kWave) {
-                    if (sp.wide_bins != 0u) {
-                        const uint2 word = reinterpret_cast<const uint2*>(sp.bins)[bins_at + here.x + k];
-                        add(word.x, word.y);
-                    } else {
-                        const uint32_t word = reinterpret_cast<const uint32_t*>(sp.bins)[bins_at + here.x + k];
-                        add(word, word >> 24);
-                    }
-                }
+        for (uint32_t f = tid; f < n_fours; f += kThreads) {
+            uint32_t i = 0;                                                         // the last queue that begins at or before it
+            for (uint32_t step = sp.queue_span; step != 0u; step /= 2u)
+                if (i + step < sp.n_queues && n_before[i + step] <= f) i += step;
+            const size_t at = bins_at / 4u + (uint32_t)(f + at_of[i]);
+            if (sp.wide_bins != 0u) {
+                const uint4 v = reinterpret_cast<const uint4*>(sp.bins)[2u * at], u = reinterpret_cast<const uint4*>(sp.bins)[2u * at + 1u];
+                add(v.x, v.y);
+                add(v.z, v.w);
+                add(u.x, u.y);
+                add(u.z, u.w);
+            } else {
+                const uint4 v = reinterpret_cast<const uint4*>(sp.bins)[at];
+                add(v.x, v.x >> 24);
+                add(v.y, v.y >> 24);
+                add(v.z, v.z >> 24);
+                add(v.w, v.w >> 24);
             }
         }
         __syncthreads();

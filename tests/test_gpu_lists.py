@@ -244,3 +244,26 @@ def test_a_queue_that_closes_early_in_rows_that_need_histograms(C):
     assert (want["n_rejected"] > 0).any() and (want["n_rejected"] < R // 100).all()
     with GpuWorkload(tr) as g:
         assert_same(g.eval(rows)[:40], want, f"C={C}")
+
+
+@pytest.mark.parametrize("M,R", [(1, 3000), (2, 2500), (63, 4000), (64, 4000), (129, 5000), (300, 5000), (513, 3000), (790, 3000), (520, 66000)])
+@pytest.mark.parametrize("slow", [False, True])
+def test_bins_of_one_long_queue_among_short_ones(M, R, slow):
+    """What the merge adds up lies in one queue, in a few, in all of them or in the last, with empty queues before, between and behind;
+    one word per request and two, histograms of both widths, more queues than the workgroup has threads."""
+    rng = np.random.default_rng(M + R)
+    arrival = np.cumsum(rng.integers(0, 3, R)).astype(np.uint64)
+    coef = [(3500, 5, 40, 2000) if slow and m == M // 2 else KINDS[m % 3] for m in range(M)]
+    longest = 200 if not slow else 60 if R < 60000 else 9                       # all requests one after the other stay below 2^32 us
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, longest, R), coef, B=8)
+    rows = rng.integers(0, M, size=(9, R)).astype(np.uint16)
+    rows[0], rows[1], rows[2] = M // 2, M - 1, 0
+    rows[3] = np.where(rng.random(R) < 0.95, M // 3, rows[3])
+    rows[4] = rows[4] // 7 * 7
+    rows[5] = np.minimum(M - 1, M // 2 + rows[5] % 3)
+    C = 530
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["lists"] in (1, 2)
+        got = g.eval(np.resize(rows, (C, R)) if R < 60000 else rows)
+    assert_same(got[:9], oracle_for(tr).eval_batch(rows, nthreads=8), f"M={M} R={R} slow={slow}")
+    assert (got == got[np.arange(len(got)) % 9]).all()
