@@ -727,7 +727,6 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.n_list_tiles = (longest_list + kTile - 1u) / kTile;
     sp.tile_cap = align_up(std::min(kTile, R) + 7u * std::min(M, std::min(kTile, R)), 8u);
     sp.n_queues = (uint32_t)order.size();
-    for (sp.queue_span = 1u; sp.queue_span * 2u <= sp.n_queues;) sp.queue_span *= 2u;
     sp.even_lists = sp.n_queues == M && queue[order.front()].i_list == queue[order.back()].i_list ? 1u : 0u;
     sp.slo_ttft = w->params.slo_ttft;
     sp.slo_tpot = w->params.slo_tpot;

@@ -112,7 +112,6 @@ struct SplitParams {
     uint32_t any_streamed;                        // some replica has a streamed part
     uint32_t R, M, B, key_bits;
     uint32_t n_tiles, n_list_tiles, tile_cap, n_queues;
-    uint32_t queue_span;                          // the largest power of two up to n_queues
     uint32_t even_lists;                          // every replica has a list, and all are equally long
     uint32_t slo_ttft, slo_tpot;
     uint32_t lazy_from;                           // rejected requests from which the p99 values are the penalty; kNever: never
@@ -992,7 +991,7 @@ __global__ __launch_bounds__(kThreads) void k_merge_candidates(EvalParams p, Spl
         };
         for (uint32_t f = tid; f < n_fours; f += kThreads) {
             uint32_t i = 0;                                                         // the last queue that begins at or before it
-            for (uint32_t step = sp.queue_span; step != 0u; step /= 2u)
+            for (uint32_t step = 1u << (31u - (uint32_t)__clz((int)sp.n_queues)); step != 0u; step /= 2u)
                 if (i + step < sp.n_queues && n_before[i + step] <= f) i += step;
             const size_t at = bins_at / 4u + (uint32_t)(f + at_of[i]);
             if (sp.wide_bins != 0u) {
