@@ -267,3 +267,22 @@ def test_bins_of_one_long_queue_among_short_ones(M, R, slow):
         got = g.eval(np.resize(rows, (C, R)) if R < 60000 else rows)
     assert_same(got[:9], oracle_for(tr).eval_batch(rows, nthreads=8), f"M={M} R={R} slow={slow}")
     assert (got == got[np.arange(len(got)) % 9]).all()
+
+
+@pytest.mark.parametrize("B", [8, 16, 24, 48, 64])
+@pytest.mark.parametrize("count", [1, 2, 3, 4, 7, 8, 9, 15, 16, 17, 31, 32, 33, 1023, 1024])
+def test_runs_that_end_anywhere_in_a_block(B, count):
+    """A replica's run of a tile has exactly `count` requests, another's the rest: sixteen entries are read ahead, four replayed at a time,
+    in every row alike, so that no other lane makes a wavefront go on; odd numbers of tiles."""
+    rng = np.random.default_rng(B + count)
+    R = 3 * 1024 + min(count, 500)
+    tr = traces.custom_trace(np.cumsum(rng.integers(0, 40, R)), rng.integers(1, 4000, R), rng.integers(1, 200, R), [KINDS[0]] * 3, B=B)
+    row = np.ones(R, dtype=np.uint16)
+    for t in range(0, R, 1024):
+        n = min(1024, R - t)
+        row[t + rng.permutation(n)[:count]] = 0
+    rows = np.repeat(row[None], 70, axis=0)
+    with GpuWorkload(tr) as g:
+        assert g.route(70)["lists"] == 1
+        got = g.eval(rows)
+    assert_same(got, np.repeat(oracle_for(tr).eval_batch(rows[:1]), 70), f"B={B} count={count}")
