@@ -162,7 +162,7 @@ struct ap_workload {
     bool screen_wide = false;         // eight wavefronts per candidate (large replica tables)
     uint32_t screen_wide_lds_bytes = 0;
     uint32_t max_grid = 0;
-    uint32_t resident_grid = 0;       // workgroups of the replay kernel that fit on the device at once
+    uint32_t resident_grid = 0;       // workgroups of the replay kernel behind a screen: a multiple of what the device holds at once
     uint32_t n_cu = 0;
     // three-kernel replay: request records, scratch for one batch of candidates, launch parameters
     uint4* d_req = nullptr;           // [R] {arrival, prompt_len, out_len, 0}
@@ -1286,11 +1286,14 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     // other's barriers); otherwise take the largest chunk one workgroup can hold.
     const uint32_t want = std::min(kMaxChunk, std::max((w->R > 2u * kThreads ? 4u : 2u) * kThreads, align_up(56u * M, kThreads)));
     uint32_t bytes = 0, chunk = 0;
+    uint32_t by_registers = 1;                               // workgroups of the kernel that a compute unit's registers hold
     {   // what the kernel itself declares (nothing today) comes off the dynamic part
         hipFuncAttributes attr;
         if (hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(eval_kernel(hist16, w->len16, tabled))) != hipSuccess)
             return device_error();
         lds_cap -= (int)std::min<size_t>(attr.sharedSizeBytes, (size_t)lds_cap);
+        const uint32_t waves_per_simd = std::min(8u, 512u / std::max(8u, align_up((uint32_t)std::max(attr.numRegs, 1), 8u)));
+        by_registers = std::max(1u, waves_per_simd * 4u / kWaves);
     }
     for (uint32_t budget : {(uint32_t)lds_cap / 2u, (uint32_t)lds_cap}) {
         const uint32_t smallest = budget == (uint32_t)lds_cap ? kThreads : std::max(kThreads, want / 2u);
@@ -1386,7 +1389,13 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     w->hist16 = hist16;
     w->n_cu = (uint32_t)n_cu;
     w->max_grid = (uint32_t)n_cu * 64u;    // few candidates per workgroup: the hardware balances uneven finish times
-    w->resident_grid = (uint32_t)n_cu * std::max(1u, std::min(4u, bytes ? (uint32_t)lds_cap / bytes : 1u));
+    // Behind a screen: a workgroup looks at C / resident_grid records, all at once, and replays those of them that are marked.  Twice what
+    // a compute unit holds (two by registers), so that marked rows spread better, and never a number in between: by LDS alone
+    // three fit with the chunk above, and the third of every three ran beside an empty place.  8192 rows of 4096 requests, all on one of
+    // 16 replicas, 3240 us with two or four workgroups per compute unit, 4060 with three; where every other row is marked 2 take 147 us
+    // and 4 take 124 (3000 rows of 3000 requests on 4 of 8 replicas).
+    const uint32_t by_lds = bytes ? (uint32_t)lds_cap / bytes : 1u, at_once = std::max(1u, std::min(by_lds, by_registers));
+    w->resident_grid = (uint32_t)n_cu * (at_once == 1u ? 1u : 2u * at_once);
 
     // ---- three-kernel replay: scratch for one batch of candidates -------------------------
     w->reduce_eval = p;

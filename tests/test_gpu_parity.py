@@ -448,3 +448,23 @@ def test_saturated_variants_reduced(cfg):
     got = both(tr, rows, tr.spec.name + " x100")
     nominal = oracle_for(tr, B=64).eval_batch(rows[:1])            # sanity: the variant does queue
     assert int(got["sum_ttft_us"][0]) >= int(nominal["sum_ttft_us"][0])
+
+
+@pytest.mark.parametrize("R", [1500, 4097])
+@pytest.mark.parametrize("every", [1, 3, 64])
+def test_more_marked_rows_than_the_replay_has_workgroups(R, every):
+    """Identical replicas: rows that crowd one of them fail the rings, and a workgroup of the replay goes through several of its records,
+    marked ones among others."""
+    rng = np.random.default_rng(R + every)
+    M, B, C = 8, 32, 2600
+    tr = traces.custom_trace(np.cumsum(rng.integers(0, 9000, R)), rng.integers(1, 4000, R), rng.integers(1, 400, R),
+                             [traces.COEF_STANDARD] * M, B=B)
+    rows = rng.integers(0, M, size=(C, R)).astype(np.uint16)
+    rows[::every] = 3
+    rows[::every, ::5] = rng.integers(0, M, size=(len(rows[::every]), len(range(0, R, 5))))
+    some = np.unique(np.concatenate([np.arange(6), np.arange(0, C, 130), np.arange(1020, 1030), np.arange(C - 4, C)]))
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["rings"] > 0
+        got = g.eval(rows)
+        assert g.counts()[1] >= len(rows[::every]) // 2
+    assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"R={R} every={every}")
