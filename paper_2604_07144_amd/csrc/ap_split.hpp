@@ -783,8 +783,8 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             }
         }
         if (tid < kReplayTiles) recs[tid * kStagedTile + kTile] = make_uint4(kNever, 0u, 0u, 0u);
-        if (j0 == 0u) request_block(d_here[0], 0u, 0u);                             // (behind the records: a short trace waits once)
         __syncthreads();
+        if (j0 == 0u) request_block(d_here[0], 0u, 0u);
         for (uint32_t j = j0; j < min(j0 + kReplayTiles, n_t); ++j) {
             const uint4* tile_recs = recs + (j - j0) * kStagedTile;
             const uint32_t d = j == j0 ? d_here[0] : d_here[1];
@@ -804,7 +804,8 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                     asm volatile("" : "+v"(e_next[0]), "+v"(e_next[1]), "+v"(d_next[0]), "+v"(d_next[1]));
 #pragma unroll
                     for (uint32_t i = 0; i < 8u; ++i) e[i] = k0 + (i < 4u ? 0u : 8u) < count ? e_next[i / 4u][i % 4u] : kPadding * 0x10001u;
-                    request_block(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 16u + 1u);
+                    if (!last || j + 1u < n_t) request_block(                       // (short traces have no next tile: 106 to 92 us for 512 x 800 on 755)
+                        !last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 16u + 1u);
                     if (k0 == 0u && j == j0) {
                         d_next[0] = desc_of(j0 + 2u);
                         d_next[1] = desc_of(j0 + 3u);
