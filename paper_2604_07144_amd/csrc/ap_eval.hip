@@ -330,9 +330,11 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         // the list replay: where most candidates are settled by penalty, those go through the variant that leaves no bins, and
         // the wavefronts of the other variant find the few that remain
         if (sp.n_queues != 0u) {
-            const uint32_t groups = align_up(sp.n_queues * ((n + kReplayListThreads - 1u) / kReplayListThreads), sp.even_lists ? kXcds : 1u);
+            const uint32_t blocks = (n + kReplayListThreads - 1u) / kReplayListThreads;
+            const uint32_t groups = sp.even_lists != 0u ? align_up((sp.n_queues + kNeighbours - 1u) / kNeighbours * blocks, kXcds) * kNeighbours
+                                                        : sp.n_queues * blocks;
             const bool lean = plan.expect_lazy;
-            const bool few = groups <= w->n_cu;
+            const bool few = sp.n_queues * blocks <= w->n_cu;
             const replay_lists_fn replay_bins = sp.wide_bins ? (few ? replay_lists_kernel_of<2u, true>(sp.B) : replay_lists_kernel_of<2u, false>(sp.B))
                                                              : (few ? replay_lists_kernel_of<1u, true>(sp.B) : replay_lists_kernel_of<1u, false>(sp.B));
             if (lean) hipLaunchKernelGGL(replay_lean, dim3(groups), dim3(kReplayListThreads), 0, stream, sp, n, 1u);

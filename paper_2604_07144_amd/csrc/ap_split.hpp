@@ -664,6 +664,7 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 constexpr uint32_t kListWaves = 4;
 constexpr uint32_t kReplayListThreads = kListWaves * kWave;
 constexpr uint32_t kXcds = 8;                     // workgroups go to them in turn
+constexpr uint32_t kNeighbours = 4;               // replicas whose workgroups for the same candidates share an XCD
 constexpr uint32_t kReplayTiles = 2;              // tiles staged at a time: 32 KiB of records per workgroup
 constexpr uint32_t kStageAtOnce = 4;
 constexpr uint32_t kStagedTile = kTile + 1u;      // a tile's records, then the one that padding names
@@ -684,14 +685,17 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     if (split_nothing_pending(p)) return;
     const uint32_t tid = threadIdx.x;
     const uint32_t n_blocks = (n_cand + kReplayListThreads - 1u) / kReplayListThreads;
-    // Longest lists first; where all are as long as the trace, replicas next to each other and the same candidates on one XCD: their runs
-    // share cache lines.
+    // Longest lists first; where all are as long as the trace, kNeighbours replicas next to each other and the same candidates on one XCD:
+    // their runs share cache lines.  Such units go round the XCDs, the blocks of candidates of the same replicas one after the other, so
+    // that the long queues of rows that crowd neighbouring replicas are spread over the XCDs and over the compute units of each (a
+    // contiguous eighth of all workgroups per XCD put them side by side: 1500 rows of 30000 requests that crowd 50 of 300 replicas 624
+    // against 454 us, calls of 11184 of 3000 on one of 8, 1134 against 923; even rows, and units of 4, 8 and 16, alike to 1 %).
     uint32_t at_queue = blockIdx.x / n_blocks, at_block = blockIdx.x % n_blocks;
     if (p.even_lists != 0u) {
-        const uint32_t job = blockIdx.x % kXcds * (gridDim.x / kXcds) + blockIdx.x / kXcds;
-        at_queue = job % p.n_queues;
-        at_block = job / p.n_queues;
-        if (at_block >= n_blocks) return;
+        const uint32_t in_xcd = blockIdx.x / kXcds, unit = in_xcd / kNeighbours * kXcds + blockIdx.x % kXcds;
+        at_queue = unit / n_blocks * kNeighbours + in_xcd % kNeighbours;
+        at_block = unit % n_blocks;
+        if (at_queue >= p.n_queues) return;
     }
     const uint32_t m = p.order[at_queue];
     const uint32_t cb = at_block * kReplayListThreads + tid;

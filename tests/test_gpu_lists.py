@@ -286,3 +286,25 @@ def test_runs_that_end_anywhere_in_a_block(B, count):
         assert g.route(70)["lists"] == 1
         got = g.eval(rows)
     assert_same(got, np.repeat(oracle_for(tr).eval_batch(rows[:1]), 70), f"B={B} count={count}")
+
+
+@pytest.mark.parametrize("M,B,C", [(129, 16, 700), (64, 64, 1100), (66, 24, 1537), (31, 48, 2305), (257, 8, 520)])
+@pytest.mark.parametrize("slow", [False, True])
+def test_equally_long_lists_with_more_workgroups_than_compute_units(M, B, C, slow):
+    """As many blocks of candidates times replicas as put the list replay beyond a workgroup per compute unit, with bins in one word and in
+    two: every queue of every block is replayed once, in whatever order the workgroups take them, also where replicas, blocks or
+    both do not divide evenly; and rows that crowd neighbouring replicas."""
+    rng = np.random.default_rng(M + C)
+    R = 2049
+    assert M * ((C + 255) // 256) > torch.cuda.get_device_properties(0).multi_processor_count
+    arrival = np.cumsum(rng.integers(0, 3, R)).astype(np.uint64)
+    coef = [(3500, 5, 40, 2000) if slow else KINDS[0]] * M
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 60 if slow else 200, R), coef, B=B)
+    rows = rng.integers(0, M, size=(C, R)).astype(np.uint16)
+    rows[::7] %= max(1, M // 6)
+    rows[1], rows[2], rows[C - 1] = 0, np.arange(R) // 8 % M, M - 1
+    some = np.unique(np.concatenate([np.arange(4), np.arange(4, C, 97), np.arange(255, 258), np.arange(0, C, 133), np.arange(C - 3, C)]))
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["lists"] == 1
+        got = g.eval(rows)
+    assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"M={M} B={B} C={C} slow={slow}")
