@@ -450,7 +450,6 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
 // by itself takes 890 us for plans of 320 calls, two per SIMD 1010 us, and there they are bound by instruction issue (8192
 // plans: 1140 us against 1620 by k_agentic_eval, measured in turn).  Which kernel takes a call: agentic_by_rows.
 constexpr uint32_t kRowLanes = 16;
-constexpr uint32_t kRowPlans = kAgenticThreads / kRowLanes;
 constexpr uint32_t kRowSlots = 4;                 // decoding calls per lane
 
 template <uint32_t kBy>

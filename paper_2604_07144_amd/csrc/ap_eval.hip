@@ -203,6 +203,11 @@ struct ap_workload {
     SplitPlan split_plan{};
 };
 
+// Wavefronts of a kernel that the registers of a SIMD hold at once.
+static uint32_t waves_by_registers(const hipFuncAttributes& attr) {
+    return std::min(8u, 512u / align_up((uint32_t)std::max(attr.numRegs, 1), 8u));
+}
+
 // Do a kernel's dynamic tables begin at LDS address 0?  k_stream_candidates and k_split_candidates read their first table by address, and
 // whatever a kernel declares itself (__shared__) would come before it.
 static bool tables_at_lds_zero(const void* kernel) {
@@ -1294,8 +1299,7 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
         if (hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(eval_kernel(hist16, w->len16, tabled))) != hipSuccess)
             return device_error();
         lds_cap -= (int)std::min<size_t>(attr.sharedSizeBytes, (size_t)lds_cap);
-        const uint32_t waves_per_simd = std::min(8u, 512u / std::max(8u, align_up((uint32_t)std::max(attr.numRegs, 1), 8u)));
-        by_registers = std::max(1u, waves_per_simd * 4u / kWaves);
+        by_registers = std::max(1u, waves_by_registers(attr) * 4u / kWaves);
     }
     for (uint32_t budget : {(uint32_t)lds_cap / 2u, (uint32_t)lds_cap}) {
         const uint32_t smallest = budget == (uint32_t)lds_cap ? kThreads : std::max(kThreads, want / 2u);
@@ -2049,7 +2053,7 @@ struct ap_agentic {
     uint32_t chunks = 0;              // which kernel
     uint32_t waves = 0;               // wavefronts (candidates) per workgroup
     uint32_t row_waves = 0, row_lds_bytes = 0;   // k_agentic_rows; 0: it does not apply
-    uint32_t wave_plans = 0, row_plans = 0;      // how many plans a compute unit's LDS holds, by either kernel
+    uint32_t wave_plans = 0, row_plans = 0;      // how many plans a compute unit's LDS holds, by either kernel (the latter: its registers too)
     void* d_block = nullptr;          // one allocation behind all the tables
 };
 
@@ -2280,9 +2284,14 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
                 a->row_lds_bytes = bytes;
             }
         }
-        if (a->row_waves != 0u && hipFuncSetAttribute(reinterpret_cast<const void*>(&k_agentic_rows), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                      (int)a->row_lds_bytes) != hipSuccess)
-            st = AP_ERR_DEVICE;
+        if (a->row_waves != 0u) {
+            hipFuncAttributes attr;
+            if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_agentic_rows), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)a->row_lds_bytes) != hipSuccess ||
+                hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(&k_agentic_rows)) != hipSuccess)
+                st = AP_ERR_DEVICE;
+            else a->row_plans = std::min(a->row_plans, waves_by_registers(attr) * 4u * (kWave / kRowLanes));
+        }
         if (a->lds_bytes > (uint32_t)lds_cap) st = AP_ERR_RANGE;
         else if (hipFuncSetAttribute(reinterpret_cast<const void*>(agentic_kernel(a->chunks)), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)a->lds_bytes) != hipSuccess)
@@ -2298,11 +2307,27 @@ ap_status ap_agentic_create(const uint64_t* arrival_us, const uint64_t* slo_us, 
 }
 
 // Four plans per wavefront (k_agentic_rows) where the wavefronts of single plans would crowd the chip or not all be in service at
-// once, as long as all plans of the other form are: that one takes as long for one plan as for all that are resident.  64
-// workflows on 4 + 4 instances, wavefronts of single plans against four: 1024 plans 593 and 900 us, 4096 744 and 915, 5632 920 and
-// 1000, 6200 1210 and 1003, 8192 1290 and 1008; 8 workflows, 5632 plans 144 and 149 us, 8192 200 and 152.
+// once: those take as long for one plan as for all that are resident, and 0.036 of what a round of k_agentic_rows takes for each further
+// plan of a compute unit.  In us, single plans against four, for plans of 317 calls on 4 + 4 instances, of which a compute unit holds 32:
+// 1024 plans 659 and 1004, 6144 1030 and 1107, 6656 1382 and 1106, 8192 1458 and 1105.  More plans than that are several
+// rounds.  A round that is not half full takes nearly as long as a full one: 8704 plans 1540 and 1971, 10240 1653 and 1985, 12288 1909 and
+// 1982 (1917 and 1680 on 1 + 1 instances, 2155 and 1986 on 8 + 8), 14336 2256 and 2206, 16384 2476 and 2206, 20480 3050 and 2980, 32768
+// 4691 and 4329.  Where a compute unit holds 48 (161 calls) no fill matters: 14336 plans 1134 and 792, 32768 2363 and 1468; 44 calls, 64 by
+// registers: 8704 plans 207 and 172, 98304 1684 and 1049.  Where it holds 24 or fewer a second round never pays (362 calls: 5632 plans
+// 1543 and 1310, 6656 1623 and 2281, 32768 5913 and 7185; 627 calls, 16: 4096 plans 2681 and 2140, 8192 4232 and 4278), and none does where
+// it holds no more than single plans (486 calls: 4096 plans 1286 and 1604).
 static bool agentic_by_rows(const ap_agentic* a, uint32_t C) {
-    return C > a->n_cu * std::min(24u, a->wave_plans) && C <= a->n_cu * a->row_plans;
+    const uint32_t at_once = a->n_cu * a->row_plans;
+    if (C <= a->n_cu * std::min(24u, a->wave_plans) || at_once == 0u) return false;
+    if (C <= at_once || a->row_plans >= 48u) return true;
+    return a->row_plans >= 32u && (C % at_once == 0u || C % at_once >= at_once / 2u);
+}
+
+// Which kernel C plans go through, for tests (not part of the header): 1 k_agentic_rows, 0 k_agentic_eval.
+ap_status ap_agentic_route_get(const ap_agentic* a, uint32_t C, uint32_t* out) {
+    if (!a || !out) return AP_ERR_INVALID;
+    *out = agentic_by_rows(a, C) ? 1u : 0u;
+    return AP_OK;
 }
 
 ap_status ap_agentic_eval(const ap_agentic* a, const uint16_t* d_prefill, const uint16_t* d_decode, const uint32_t* d_key,

@@ -1,5 +1,7 @@
 """GPU parity for candidate plans of agentic workflows (``ap_agentic_*``), through the C ABI, against the
 serial CPU oracle: integer work, so every field of every record must be equal."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -174,3 +176,33 @@ def test_four_plans_per_wavefront(W, P, Q, capacity, rate, bad_ids, C):
     want = AgenticOracle.from_workload(wl).eval_batch(pre[some], dec[some], key[some])
     for i, c in enumerate(some):
         assert got[c].tolist() == want[i].tolist(), (c, got[c], want[i])
+
+
+@pytest.mark.parametrize("W,P,Q,C,rows", [
+    (64, 4, 4, 6144, 0), (64, 4, 4, 6145, 1), (64, 4, 4, 8192, 1),        # a compute unit holds 32 plans of about 320 calls
+    (64, 4, 4, 8193, 0), (64, 4, 4, 12287, 0), (64, 4, 4, 12289, 1),      # a second round that is not half full, and one that is
+    (64, 4, 4, 16384, 1), (64, 4, 4, 16385, 0),
+    (8, 4, 4, 33001, 1),                                                  # many plans of few calls: several rounds
+    (128, 4, 4, 3072, 0), (128, 4, 4, 4001, 1), (128, 4, 4, 4097, 0),     # twenty words of a queue's mask, ranks beyond 600
+    (150, 1, 1, 2600, 1),                                                 # twenty-five
+    (200, 4, 4, 4096, 0),                                                 # tables so large that single plans are never worse
+])
+def test_which_kernel_takes_a_call(W, P, Q, C, rows):
+    """On either side of each line of the rule, the kernel that takes the call and its records (the first plans, the last and some)."""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines go by the number of compute units")
+    wl = traces.make_agentic(3, W, P=P, Q=Q, capacity=6000, rate=60.0)
+    K = len(wl["wf"])
+    handle = binding.ap_agentic_create(*(wl[f] for f in FIELDS))
+    try:
+        out = ctypes.c_uint32()
+        assert binding.lib().ap_agentic_route_get(ctypes.c_void_p(handle), ctypes.c_uint32(C), ctypes.byref(out)) == binding.AP_OK
+        assert out.value == rows, (K, out.value)
+    finally:
+        binding.ap_agentic_destroy(handle)
+    drawn = traces.draw_agentic_candidates(W, 500, K, P, Q, key_range=[1 << 20, 50][C % 2], bad_ids=True)
+    pre, dec, key = (np.resize(a, (C, K)) for a in drawn)
+    got = gpu_eval(wl, pre, dec, key)
+    want = AgenticOracle.from_workload(wl).eval_batch(*(a[:40] for a in drawn))
+    assert got[:40].tolist() == want.tolist()
+    assert got.tolist() == np.resize(got[:500], C).tolist()
