@@ -29,14 +29,13 @@ namespace {
 //  * the calls of a plan are ranked by (key, index) once, before the loop; an instance's queue is a bit mask over ranks in
 //    LDS, so its first waiting call is the first bit set, and joining or leaving a queue is one bit;
 //  * a completion, release or arrival notes which instances it concerns, and only those try to admit or start a call; lane i keeps the
-//    first waiting call of instance i with what it takes, so that whether it goes needs no look into the tables (646 to 593 us for
-//    a plan of 320 calls by itself, three LDS round trips for each attempt before);
+//    first waiting call of instance i with what it takes, so that whether it goes needs no look into the tables (8 % less for
+//    plans of 320 calls by themselves, three LDS round trips for each attempt before);
 //  * workflows are taken in order of arrival, each with the list of its calls without predecessors.
 // Tables that are the same for all plans (lengths, successors, arrivals) are copied to LDS once per workgroup; the
 // wavefronts of a workgroup share nothing else and never meet at a barrier after that.
-// It is bound by the issue of scalar instructions (225 per call, 178 vector and 25 LDS ones).  Scanning the
-// calls' phases at every instant (a lane per 64 calls, masks per lane) took 2.58 ms for 8192 plans of a 330-call slice,
-// 1.64 ms now.
+// It is bound by instruction issue (per call 214 vector instructions, 196 scalar and 19 LDS ones): 8192 plans of a 330-call slice take
+// 1.51 ms, 2.58 when the calls' phases were scanned at every instant (a lane per 64 calls, masks per lane).
 struct AgenticParams {
     const uint4* blob;            // the tables that go to LDS, laid out as below
     uint32_t blob_bytes;          // a multiple of 16
@@ -437,7 +436,7 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
 
 // ---- four plans per wavefront -----------------------------------------------------------------
 // The same event loop for up to 16 instances of either kind, a row of 16 lanes per plan.  With a wavefront per plan every step of
-// the loop is scalar work (225 scalar and 178 vector instructions per call of a plan, both issued at most once per SIMD and
+// the loop is scalar work (196 scalar and 214 vector instructions per call of a plan, both issued at most once per SIMD and
 // four cycles); here a step is vector work that four plans share, each at its own instant:
 //  * lane i of a row owns prefill instance i and decode instance i: what runs on the former, the free tokens of the latter, the
 //    first waiting call of both queues with what it takes (so a decision needs registers only), and which words of the queue's mask
@@ -446,9 +445,10 @@ __global__ __launch_bounds__(kAgenticThreads) void k_agentic_eval(AgenticParams 
 //  * one ended call or one arrival per plan and pass: a minimum over the row (rotations on the vector ALU's cross-lane path) says
 //    which, and tells every lane of the row.
 // Rows are at different instants, and all go through what one of them needs; values that concern a plan are the same in
-// its 16 lanes.  A pass is some 220 vector instructions, 60 scalar ones and six LDS round trips one after the other, so a wavefront
-// by itself takes 890 us for plans of 320 calls, two per SIMD 1010 us, and there they are bound by instruction issue (8192
-// plans: 1140 us against 1620 by k_agentic_eval, measured in turn).  Which kernel takes a call: agentic_by_rows.
+// its 16 lanes.  A pass is some 220 vector instructions, 60 scalar ones and six LDS round trips one after the other (per call of a plan 166
+// vector instructions, 43 scalar and 11 LDS ones), so a wavefront by itself takes 1.00 ms for plans of 317 calls, two per SIMD 1.11, and
+// there they are bound by instruction issue.  8192 plans of 330 calls 1.16 ms, 1.51 by k_agentic_eval, measured in turn.  Which kernel
+// takes a call: agentic_by_rows.
 constexpr uint32_t kRowLanes = 16;
 constexpr uint32_t kRowSlots = 4;                 // decoding calls per lane
 

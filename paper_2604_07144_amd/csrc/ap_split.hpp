@@ -631,7 +631,8 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // s'[i] = med3(s[i], f, s[i+1]), i.e. min(s[i+1], max(s[i], f)).  A lane without a request in a step (or whose
 // request is rejected) inserts 0, which leaves the registers as they are.
 // Starts do not decrease along a queue, so once a start reaches t_off every later request is rejected too: a tile in which no
-// lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.  (4096 rows of 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
+// lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.  (4096 rows of
+// 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
 // kSlots: B rounded up to 8, 12, 16, 24, 32, 48 or 64; registers beyond B hold kNever and stay there.
 //
 // Bound by instruction issue, most of it the medians.  What every lane would evaluate for itself is done once while staging
@@ -651,16 +652,21 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // a request there, a line from HBM and the stores before it more than eight of those (400 rows of 16384 requests on one of 2 replicas of
 // 8 slots 3801 us before anything ran ahead, 3842 with blocks of eight, 3356 with sixteen; one row on both of 2, 1807, 1906 and 1757;
 // 100 rows of 131072 on 21 of 128 replicas of 64 slots 3680, 3340 and 3280).  With more than 48 slots a pair of steps that
-// no lane needs is left out; up to there the branch costs more (crowds of one queue 6 % at 8 and 16 slots, 4 % at 24 to 48).  Where all lists are
-// as long as the trace, neighbouring replicas share an XCD, whose L2 then holds their runs once.  A queue's words for the
-// histograms follow one another (place_bins), four requests at a time where one of the four has a value that a p99 value can reach: on a
-// trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list position was a gigabyte of 16-byte
-// stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1190 us before
-// all of this, 983 with a word per position, 690 now, and k_merge_candidates 196 and 55; at ten times the load the whole call 1663 and
-// 1568.  3001 rows of 20011 requests on 50 replicas, half of which come and go, 184 to 165 us, and 4096 rows of 32768 on 64 crowded
-// replicas that come and go 462 to 430.  (Rows of three tiles: 99 to 101 us for 9251 rows of 2993 requests.)
-// kBins: 0 leaves no bins, 1 one word per request, 2 two words.  kFew: no more than a workgroup per compute unit.  which: 0 every candidate, 1 only those settled by penalty,
+// no lane needs is left out; up to there the branch costs more (crowds of one queue 6 % at 8 and 16 slots, 4 % at 24 to 48).
+// Where all lists are as long as the trace, a few neighbouring replicas share an XCD, whose L2 then holds their runs once.
+// A queue's words for the histograms follow one another (place_bins), four requests at a time where one of the four has a value
+// that a p99 value can reach: on a trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list position was a gigabyte of 16-byte
+// stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1203 us before
+// all of this, 983 with a word per position, 705 now, and k_merge_candidates 198 and 31.  3001 rows of 20011 requests on 50 replicas,
+// half of which come and go, 186 to 166 us, and 4096 rows of 32768 on 64 crowded replicas that come and go 467 to 422.
+// kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
+// kFew: no more than a workgroup per compute unit; bins are then taken of every request, without a test whether any of them counts.  A
+// wavefront that has its SIMD to itself loses more over that branch than over the bins, and gains by it where the chip is full.  With bins
+// of every request and with the test, calls of 8192 requests on 64 replicas of 8 slots, rows that crowd 10 of them: 64 workgroups 261
+// and 288 us, 256 292 and 320, 512 339 and 367, 1024 557 and 572; even rows 100 and 104, 133 and 136, 191 and 191, 403 and 406;
+// 16384 on 24 of 16 slots, even, 64 279 and 282, 512 629 and 625; 559 rows of 60000 on 256 (768 workgroups) 489 and 468; 1024 of 131072
+// on 128 (512) 1080 and 1009.  The line is at the compute units: beyond it even rows, which are the larger calls, begin to lose.
 constexpr uint32_t kListWaves = 4;
 constexpr uint32_t kReplayListThreads = kListWaves * kWave;
 constexpr uint32_t kXcds = 8;                     // workgroups go to them in turn
@@ -808,8 +814,9 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                     asm volatile("" : "+v"(e_next[0]), "+v"(e_next[1]), "+v"(d_next[0]), "+v"(d_next[1]));
 #pragma unroll
                     for (uint32_t i = 0; i < 8u; ++i) e[i] = k0 + (i < 4u ? 0u : 8u) < count ? e_next[i / 4u][i % 4u] : kPadding * 0x10001u;
-                    if (!last || j + 1u < n_t) request_block(                       // (short traces have no next tile: 106 to 92 us for 512 x 800 on 755)
-                        !last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 16u + 1u);
+                    // (short traces have no next tile: 106 to 92 us for 512 rows of 800 requests on 755 replicas)
+                    if (!last || j + 1u < n_t)
+                        request_block(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 16u + 1u);
                     if (k0 == 0u && j == j0) {
                         d_next[0] = desc_of(j0 + 2u);
                         d_next[1] = desc_of(j0 + 3u);
@@ -856,8 +863,6 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                         ++n_served;
                         n_ok += (ttft <= p.slo_ttft && rq.w <= slo_tpot) ? 1u : 0u;
                         if (kBins_ != 0u) {
-                            // (a lone wavefront takes longer over the branch than over the bins: 19 rows of 20480 requests on 5 replicas 1295
-                            // against 1157 us; with a chip full of them they cost more, sweeps of 131072 requests 1080 against 1009)
                             if (kFew || ((ttft >= p.least_us[0]) | (rq.w >= p.least_us[1]) | (e2e >= p.least_us[2]))) {
                                 const uint32_t tpot_bin = bin_above(rq.w, p.least_us[1], p.least_bin[1]);
                                 bins[k] = bin_above(ttft, p.least_us[0], p.least_bin[0]) | (bin_above(e2e, p.least_us[2], p.least_bin[2]) << 12) |
