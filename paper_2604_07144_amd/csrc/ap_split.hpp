@@ -645,18 +645,20 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // drained and on a light trace.  Together with bins in one word instead of two and none below the bins that a p99 value can
 // reach, 1024 rows of 131072 requests on 128 crowded replicas of 64 slots take 1226 us instead of 1569 (and k_merge_candidates 340
 // instead of 803, before the change described there); on light traces and odd B 1.1 to 1.5 times less.
-// Loads run ahead: a lane's descriptors a stage, its next block of sixteen entries a block, also into the next tile, and the
+// Loads run ahead: a lane's descriptors a stage, its next block of entries a block, also into the next tile, and the
 // records of a stage four per thread at a time.  A register whose
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as vectors
 // and the empty asm where they are waited for.  Blocks of eight come too late for queues of few slots: a wavefront by itself takes 200 ns
 // a request there, a line from HBM and the stores before it more than eight of those (400 rows of 16384 requests on one of 2 replicas of
 // 8 slots 3801 us before anything ran ahead, 3842 with blocks of eight, 3356 with sixteen; one row on both of 2, 1807, 1906 and 1757;
-// 100 rows of 131072 on 21 of 128 replicas of 64 slots 3680, 3340 and 3280).  With more than 48 slots a pair of steps that
+// 100 rows of 131072 on 21 of 128 replicas of 64 slots 3680, 3340 and 3280).  Only without bins and with more than 48 slots it is eight:
+// sixteen take 139 registers, which leave room for three wavefronts per SIMD instead of four (8192 rows of 32768 requests on 64
+// replicas that come and go 807 against 799 us).  With more than 48 slots a pair of steps that
 // no lane needs is left out; up to there the branch costs more (crowds of one queue 6 % at 8 and 16 slots, 4 % at 24 to 48).
 // Where all lists are as long as the trace, a few neighbouring replicas share an XCD, whose L2 then holds their runs once.
 // A queue's words for the histograms follow one another (place_bins), four requests at a time where one of the four has a value
-// that a p99 value can reach: on a trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list position was a gigabyte of 16-byte
-// stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1203 us before
+// that a p99 value can reach: on a trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list
+// position was a gigabyte of 16-byte stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1203 us before
 // all of this, 983 with a word per position, 705 now, and k_merge_candidates 198 and 31.  3001 rows of 20011 requests on 50 replicas,
 // half of which come and go, 186 to 166 us, and 4096 rows of 32768 on 64 crowded replicas that come and go 467 to 422.
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
@@ -724,6 +726,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 
     constexpr uint32_t kGroup = kSlots > 48u ? 32u : 16u, kGroups = (kSlots + kGroup - 1u) / kGroup;   // groups of registers, counted from the top
     constexpr bool kPairs = kSlots > 48u;                                           // two steps are worth a branch
+    constexpr uint32_t kHalves = kSlots > 48u && kBins_ == 0u ? 1u : 2u, kBlock = 8u * kHalves;   // entries ahead
     uint32_t s[kSlots];
 #pragma unroll
     for (uint32_t i = 0; i < kSlots; ++i) s[i] = i < p.B ? 0u : kNever;
@@ -740,17 +743,17 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
         return first;
     };
     typedef uint32_t four_words __attribute__((ext_vector_type(4)));
-    // The sixteen entries from 16 b on of a run.  A lane without them reads where all such lanes do, the area's first bytes, so that there
+    // The kBlock entries from kBlock * b on of a run.  A lane without them reads where all such lanes do, the area's first bytes, so that there
     // is no branch around the loads and next to no traffic: where each read its own tile's first block, one that no lane needed, 8388 rows
     // of 8000 requests that crowd 50 of 300 replicas took 605 us in here, 351 before anything was read ahead, 359 with this.
     const uint32_t lists_at = 2u * p.tile_cap * (uint32_t)desc_at;                  // bytes: plan_split keeps a batch's lists below 2^32
-    four_words e_next[2] = {};                                                      // the block after the one in hand
+    four_words e_next[kHalves] = {};                                                      // the block after the one in hand
     auto request_block = [&](uint32_t d, uint32_t j, uint32_t b) {
         uint32_t count;
-        const uint32_t first = run_of(d, count), run_at = lists_at + 2u * (j * p.tile_cap + first + 16u * b);
+        const uint32_t first = run_of(d, count), run_at = lists_at + 2u * (j * p.tile_cap + first + kBlock * b);
 #pragma unroll
-        for (uint32_t h = 0; h < 2u; ++h) {
-            const uint32_t at = 16u * b + 8u * h < count ? run_at + 16u * h : 0u;
+        for (uint32_t h = 0; h < kHalves; ++h) {
+            const uint32_t at = kBlock * b + 8u * h < count ? run_at + 16u * h : 0u;
             e_next[h] = *reinterpret_cast<const four_words*>(reinterpret_cast<const char*>(p.lists) + at);
         }
     };
@@ -804,26 +807,28 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             // Steps of the tile; where nothing can start there is one all the same, in which only the next tile's block and the next
             // stage's descriptors are requested.
             const uint32_t most = __ballot(live && s[0] < q.t_off) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
-            uint32_t e[8];                                                          // two entries each, the next ones first
+            uint32_t e[4u * kHalves];                                               // two entries each, the next ones first
 #pragma unroll
-            for (uint32_t i = 0; i < 8u; ++i) e[i] = kPadding * 0x10001u;
+            for (uint32_t i = 0; i < 4u * kHalves; ++i) e[i] = kPadding * 0x10001u;
             for (uint32_t k0 = 0; k0 < n_steps; k0 += 4u) {                         // four requests at a time
-                if ((k0 & 12u) == 0u) {
-                    const bool last = k0 + 16u >= n_steps;                          // the last block of every lane: on to the next tile's
+                if (k0 % kBlock == 0u) {
+                    const bool last = k0 + kBlock >= n_steps;                       // the last block of every lane: on to the next tile's
                     // waited for here, before the next requests
-                    asm volatile("" : "+v"(e_next[0]), "+v"(e_next[1]), "+v"(d_next[0]), "+v"(d_next[1]));
 #pragma unroll
-                    for (uint32_t i = 0; i < 8u; ++i) e[i] = k0 + (i < 4u ? 0u : 8u) < count ? e_next[i / 4u][i % 4u] : kPadding * 0x10001u;
+                    for (uint32_t h = 0; h < kHalves; ++h) asm volatile("" : "+v"(e_next[h]));
+                    asm volatile("" : "+v"(d_next[0]), "+v"(d_next[1]));
+#pragma unroll
+                    for (uint32_t i = 0; i < 4u * kHalves; ++i) e[i] = k0 + (i < 4u ? 0u : 8u) < count ? e_next[i / 4u][i % 4u] : kPadding * 0x10001u;
                     // (short traces have no next tile: 106 to 92 us for 512 rows of 800 requests on 755 replicas)
-                    if (!last || j + 1u < n_t)
-                        request_block(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / 16u + 1u);
+                    if (kHalves == 1u || !last || j + 1u < n_t)
+                        request_block(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / kBlock + 1u);
                     if (k0 == 0u && j == j0) {
                         d_next[0] = desc_of(j0 + 2u);
                         d_next[1] = desc_of(j0 + 3u);
                     }
                 } else {
 #pragma unroll
-                    for (uint32_t i = 0; i < 6u; ++i) e[i] = e[i + 2u];
+                    for (uint32_t i = 0; i + 2u < 4u * kHalves; ++i) e[i] = e[i + 2u];
                 }
                 if (most == 0u) continue;
                 const uint32_t word[2] = {e[0], e[1]};
