@@ -1395,13 +1395,13 @@ static ap_status set_cost_model_checked(ap_workload* w, const ap_replica* replic
     w->hist16 = hist16;
     w->n_cu = (uint32_t)n_cu;
     w->max_grid = (uint32_t)n_cu * 64u;    // few candidates per workgroup: the hardware balances uneven finish times
-    // Behind a screen: a workgroup looks at C / resident_grid records, all at once, and replays those of them that are marked.  Twice what
-    // a compute unit holds (two by registers), so that marked rows spread better, and never a number in between: by LDS alone
-    // three fit with the chunk above, and the third of every three ran beside an empty place.  8192 rows of 4096 requests, all on one of
-    // 16 replicas, 3240 us with two or four workgroups per compute unit, 4060 with three; where every other row is marked 2 take 147 us
-    // and 4 take 124 (3000 rows of 3000 requests on 4 of 8 replicas).
-    const uint32_t by_lds = bytes ? (uint32_t)lds_cap / bytes : 1u, at_once = std::max(1u, std::min(by_lds, by_registers));
-    w->resident_grid = (uint32_t)n_cu * (at_once == 1u ? 1u : 2u * at_once);
+    // Behind a screen: a workgroup looks at C / resident_grid records, all at once, and replays those of them that are marked.  As many as LDS
+    // holds, four at most per compute unit, rounded up to a multiple of what registers and LDS hold together (two): three, which LDS
+    // alone allows with the chunk above, left the third of every three beside an empty place.  8192 rows of 4096 requests, all on one of
+    // 16 replicas, 3240 us with two or four workgroups per compute unit, 4060 with three; where some rows are marked two take 147 us and
+    // four 124 (3000 rows of 3000 requests on 4 of 8 replicas); where none is, 512 more that leave at once cost half a microsecond.
+    const uint32_t by_lds = std::min(4u, bytes ? (uint32_t)lds_cap / bytes : 1u), at_once = std::max(1u, std::min(by_lds, by_registers));
+    w->resident_grid = (uint32_t)n_cu * ((std::max(1u, by_lds) + at_once - 1u) / at_once * at_once);
 
     // ---- three-kernel replay: scratch for one batch of candidates -------------------------
     w->reduce_eval = p;

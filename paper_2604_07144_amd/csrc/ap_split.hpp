@@ -659,8 +659,8 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // A queue's words for the histograms follow one another (place_bins), four requests at a time where one of the four has a value
 // that a p99 value can reach: on a trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list
 // position was a gigabyte of 16-byte stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1203 us before
-// all of this, 983 with a word per position, 705 now, and k_merge_candidates 198 and 31.  3001 rows of 20011 requests on 50 replicas,
-// half of which come and go, 186 to 166 us, and 4096 rows of 32768 on 64 crowded replicas that come and go 467 to 422.
+// all of this, 983 with a word per position, 693 now, and k_merge_candidates 198 and 31.  3001 rows of 20011 requests on 50 replicas,
+// half of which come and go, 186 to 166 us, and 4096 rows of 32768 on 64 crowded replicas that come and go 467 to 450.
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
 // kFew: no more than a workgroup per compute unit; bins are then taken of every request, without a test whether any of them counts.  A
