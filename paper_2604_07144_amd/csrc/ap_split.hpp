@@ -626,25 +626,28 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // with the most requests of the tile sets the pace.  Staging several tiles at a time for several wavefronts is
 // what keeps the share of idle lane-steps down: the counts of a stage differ less, relative to their mean, than
 // those of a single tile.
-// A lane keeps its B slot-free times sorted in registers (s[0] the earliest); a request starts at
-// max(ready, s[0]), and its finish time f replaces s[0] by one median per register:
+// A lane keeps its B slot-free times in registers, as two ascending sequences: the front, kFront of them, and the rest.  A request
+// starts at max(ready, s[0]), and its finish time f replaces s[0] in the front by one median per register:
 // s'[i] = med3(s[i], f, s[i+1]), i.e. min(s[i+1], max(s[i], f)).  A lane without a request in a step (or whose
 // request is rejected) inserts 0, which leaves the registers as they are.
+// Is s[0] the earliest slot?  Slots that are free when a request is ready are as good as each other, then and later, whatever time
+// they hold.  So four requests may take theirs from the front if s[3] <= max(earliest of the rest, ready time of the first): of
+// s[0..3] one is still there at each of the four.  Where that does not hold in some lane, all lanes merge the two sequences
+// (Batcher's network) and the front is the kFront earliest again, which is good for kFront requests at least, and for any
+// number while slots are free: as a queue fills up, after its backlog has drained, on a light trace.
 // Starts do not decrease along a queue, so once a start reaches t_off every later request is rejected too: a tile in which no
 // lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.  (4096 rows of
 // 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
 // kSlots: B rounded up to 8, 12, 16, 24, 32, 48 or 64; registers beyond B hold kNever and stay there.
 //
-// Bound by instruction issue, most of it the medians.  What every lane would evaluate for itself is done once while staging
+// Bound by instruction issue.  What every lane would evaluate for itself is done once while staging
 // (the request's prefill and decode time on this replica, from coefficients or tables), records are read from LDS four at a
-// time before they are needed, a tile's steps are counted once (the longest run sets the pace).  And registers that hold
-// free slots need no medians: slots that are free when a request is ready stay free for later ones, whatever time they
-// hold (a group is 16 registers, or 32 of 64: more groups cost a test and a branch each), so if the lowest
-// four of the upper K registers are free for the first of four requests - in every lane - all four start when they
-// are ready and only those K registers move.  That is so while a queue fills up, after its backlog has
-// drained and on a light trace.  Together with bins in one word instead of two and none below the bins that a p99 value can
-// reach, 1024 rows of 131072 requests on 128 crowded replicas of 64 slots take 1226 us instead of 1569 (and k_merge_candidates 340
-// instead of 803, before the change described there); on light traces and odd B 1.1 to 1.5 times less.
+// time before they are needed, a tile's steps are counted once (the longest run sets the pace).  Of 64 slots a front of 16 takes 16
+// operations a request and a merge about 300 and its register moves, at most once in 16: half of the 64 medians over one sorted sequence, and a
+// quarter while slots are free (fronts of 8 and 32 are 38 and 42).  With 16, 24 and 32 slots it is a front of 8, below that the front is all.
+// Replay kernels with one sorted sequence, whose lower registers held still where slots were free, and now: 8192 rows of 32768 requests on 64
+// replicas of 64 slots that come and go 380 and 300 us, 4096 of them crowded 430 and 310; 1024 of 131072 on 128 crowded 665 and 550; calls of
+// 4096 rows of 16384 on 48 that come and go, half their slots in use: 16 slots 233 to 229 us, 24 265 to 249, 32 280 to 260, 48 320 to 275, 64 345 to 280.
 // Loads run ahead: a lane's descriptors a stage, its next block of entries a block, also into the next tile, and the
 // records of a stage four per thread at a time.  A register whose
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as vectors
@@ -684,6 +687,33 @@ __device__ __forceinline__ uint32_t bin_above(uint32_t v, uint32_t least_us, uin
 // hi:lo += v in two instructions (the compiler's 64-bit add takes a register for the upper half of v as well)
 __device__ __forceinline__ void add_wide(uint32_t& lo, uint32_t& hi, uint32_t v) {
     asm("v_add_co_u32 %0, vcc, %0, %2\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc" : "+v"(lo), "+v"(hi) : "v"(v) : "vcc");
+}
+
+// Merge of two ascending sequences by Batcher's odd-even network (K. E. Batcher, Sorting networks and their applications, 1968), in place:
+// the kM elements s[kAt], s[kAt + kStride], .. and the kN behind them (kM a power of two, kN >= kM).  A single element goes in by a
+// median per place.  The asm keeps the order of the exchanges, and with it the registers to the elements and one more: left to the
+// compiler's schedule, 64 elements take 35 registers more, written so 14.
+template <uint32_t kSlots, uint32_t kAt, uint32_t kStride, uint32_t kM, uint32_t kN>
+__device__ __forceinline__ void merge_sorted(uint32_t (&s)[kSlots]) {
+    if constexpr (kM == 1u) {
+        const uint32_t v = s[kAt];
+        asm volatile("v_min_u32 %0, %1, %2" : "=&v"(s[kAt]) : "v"(v), "v"(s[kAt + kStride]));
+#pragma unroll
+        for (uint32_t i = 1; i < kN; ++i)
+            median3(s[kAt + i * kStride], v, s[kAt + (i + 1u) * kStride]);
+        raise(s[kAt + kN * kStride], v);
+    } else {
+        merge_sorted<kSlots, kAt, 2u * kStride, kM / 2u, (kN + 1u) / 2u>(s);
+        merge_sorted<kSlots, kAt + kStride, 2u * kStride, kM / 2u, kN / 2u>(s);
+#pragma unroll
+        for (uint32_t i = 1; i + 1u < kM + kN; i += 2u) {
+            uint32_t& a = s[kAt + i * kStride];
+            uint32_t& b = s[kAt + (i + 1u) * kStride];
+            uint32_t low;
+            asm volatile("v_min_u32 %0, %1, %2\n\tv_max_u32 %2, %1, %2" : "=&v"(low), "+v"(a), "+v"(b));
+            a = low;
+        }
+    }
 }
 
 template <uint32_t kSlots, uint32_t kBins_, bool kFew>
@@ -726,12 +756,14 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     // one compare per request unless both objectives can be missed
     const uint32_t slo_tpot = p.tpot_within != 0u ? kNever : p.slo_tpot;
 
-    constexpr uint32_t kGroup = kSlots > 48u ? 32u : 16u, kGroups = (kSlots + kGroup - 1u) / kGroup;   // groups of registers, counted from the top
+    constexpr uint32_t kFront = kSlots >= 48u ? 16u : kSlots >= 16u ? 8u : kSlots;  // a power of two where there is a rest
     constexpr bool kPairs = kSlots > 48u;                                           // two steps are worth a branch
     constexpr uint32_t kHalves = kSlots > 48u && kBins_ == 0u ? 1u : 2u, kBlock = 8u * kHalves;   // entries ahead
     uint32_t s[kSlots];
 #pragma unroll
     for (uint32_t i = 0; i < kSlots; ++i) s[i] = i < p.B ? 0u : kNever;
+    static_assert(kFront == kSlots || (kFront >= 4u && (kFront & (kFront - 1u)) == 0u && 2u * kFront <= kSlots), "four at a time; merge_sorted");
+    auto earliest = [&]() { return kFront < kSlots ? min(s[0], s[kFront < kSlots ? kFront : 0u]) : s[0]; };
     uint32_t e2e_lo = 0, e2e_hi = 0, dec_lo = 0, dec_hi = 0, tpot_lo = 0, tpot_hi = 0;
     uint32_t last_fin = 0, n_ok = 0, n_served = 0, n_listed = 0;
 
@@ -767,7 +799,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     for (; j0 < n_t; j0 += kReplayTiles) {
         const uint32_t r0 = j0 * kTile, n = min(kReplayTiles * kTile, p.R - r0);
         if ((tid & 63u) == 0u) goes_on[wave_index()] = 0u;
-        if (__ballot(live && s[0] < q.t_off) != 0ull && (tid & 63u) == 0u) goes_on[wave_index()] = 1u;
+        if (__ballot(live && earliest() < q.t_off) != 0ull && (tid & 63u) == 0u) goes_on[wave_index()] = 1u;
         __syncthreads();                                                            // also: the last stage's records were read
         uint32_t any = 0u;
 #pragma unroll
@@ -808,7 +840,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             n_listed += count;
             // Steps of the tile; where nothing can start there is one all the same, in which only the next tile's block and the next
             // stage's descriptors are requested.
-            const uint32_t most = __ballot(live && s[0] < q.t_off) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
+            const uint32_t most = __ballot(live && earliest() < q.t_off) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
             uint32_t e[4u * kHalves];                                               // two entries each, the next ones first
 #pragma unroll
             for (uint32_t i = 0; i < 4u * kHalves; ++i) e[i] = kPadding * 0x10001u;
@@ -838,28 +870,21 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 #pragma unroll
                 for (uint32_t k = 0; k < 4u; ++k) rec[k] = tile_recs[(k & 1u) ? word[k >> 1] >> 16 : word[k >> 1] & 0xFFFFu];
                 uint32_t bins[4] = {0u, 0u, 0u, 0u}, tpot_bins[4] = {0u, 0u, 0u, 0u};
-                // How many of the lower groups of registers hold still (a lane without a request is ready at kNever)
-                const uint32_t ready = max(rec[0].x, q.t_on);
-                uint32_t still = 0u;
-                if (kGroups > 1u && __ballot(s[kGroups > 1u ? kSlots - kGroup + 3u : 0u] > ready) == 0ull) still = kGroups - 1u;
-                else if (kGroups > 2u && __ballot(s[kGroups > 2u ? kSlots - 2u * kGroup + 3u : 0u] > ready) == 0ull) still = kGroups - 2u;
+                // do the next four starts come from the front in every lane? (a lane without a request is ready at kNever)
+                if (kFront < kSlots && __ballot(s[kFront < kSlots ? 3u : 0u] > max(s[kFront < kSlots ? kFront : 0u], max(rec[0].x, q.t_on))) != 0ull)
+                    merge_sorted<kSlots, 0u, 1u, kFront, kSlots - kFront>(s);
 #pragma unroll
                 for (uint32_t k = 0; k < 4u; ++k) {
                     if (kPairs && k >= 2u && k0 + 2u >= n_steps) continue;          // no lane has a third
                     const uint4 rq = rec[k];
-                    const uint32_t start = max(max(rq.x, q.t_on), s[0]);            // s[0] is free if anything holds still
+                    const uint32_t start = max(max(rq.x, q.t_on), s[0]);            // 
                     const bool served = start < q.t_off;                            // padding never starts
                     const uint32_t fin = start + rq.y + rq.z;
                     const uint32_t f = served ? fin : 0u;
 #pragma unroll
-                    for (uint32_t g = 0; g < kGroups; ++g) {
-                        if (g + 1u < kGroups && g < still) continue;
-                        const uint32_t low = g == 0u ? 0u : kSlots - kGroup * (kGroups - g), high = kSlots - kGroup * (kGroups - 1u - g);
-#pragma unroll
-                        for (uint32_t i = low; i < high; ++i) {
-                            if (i + 1u < kSlots) median3(s[i], f, s[i + 1u < kSlots ? i + 1u : i]);
-                            else raise(s[i], f);
-                        }
+                    for (uint32_t i = 0; i < kFront; ++i) {
+                        if (i + 1u < kFront) median3(s[i], f, s[i + 1u < kFront ? i + 1u : i]);
+                        else raise(s[i], f);
                     }
                     if (served) {
                         const uint32_t e2e = fin - rq.x, ttft = e2e - rq.z;

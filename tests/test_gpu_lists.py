@@ -308,3 +308,27 @@ def test_equally_long_lists_with_more_workgroups_than_compute_units(M, B, C, slo
         assert g.route(C)["lists"] == 1
         got = g.eval(rows)
     assert_same(got[some], oracle_for(tr).eval_batch(rows[some], nthreads=8), f"M={M} B={B} C={C} slow={slow}")
+
+
+@pytest.mark.parametrize("B", [13, 16, 17, 23, 24, 25, 31, 32, 33, 47, 48, 49, 63, 64])
+@pytest.mark.parametrize("kind", ["equal", "wide", "mostly short", "closing"])
+def test_slots_taken_from_the_front(B, kind):
+    """The slot times a lane keeps in order are merged with the others when one of the next four starts may not be among them.  A backlog
+    that all becomes ready at once, then a trickle, then a burst, with service times that are all alike, that span five orders, or of
+    which most end before the slots taken first come free again, so that they are taken from the front over and over; and replicas that
+    leave while some lanes still start requests."""
+    rng = np.random.default_rng(B)
+    R, M, C = 2600, 3, 130
+    gap = np.repeat([0, 900, 0, 20_000, 25, 0], [500, 600, 300, 200, 700, 300])
+    arrival = np.cumsum(gap + rng.integers(0, 2, R))
+    out = {"equal": np.full(R, 40), "wide": np.exp(rng.uniform(0, 11, R)).astype(int) + 1,
+           "mostly short": np.where(rng.random(R) < 0.1, 20_000, 1 + rng.integers(0, 3, R)), "closing": rng.integers(1, 400, R)}[kind]
+    t_on = [int(arrival[450]), 0, int(arrival[900])]
+    t_off = [U64MAX] * 3 if kind != "closing" else [int(arrival[450]) + 60_000, int(arrival[1300]), int(arrival[-1]) + 1]
+    tr = traces.custom_trace(arrival, rng.integers(1, 60, R), out, [(5, 1, 3, 2), (0, 0, 1, 1), (2000, 3, 25, 5)], t_on, t_off, B=B)
+    rows = rng.integers(0, M, size=(C, R)).astype(np.uint16)
+    rows[1], rows[2], rows[3] = 0, 1, 2
+    rows[64:80] %= 2
+    with GpuWorkload(tr) as g:
+        assert g.route(C)["lists"] in (1, 2)
+        assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"B={B} {kind}")
