@@ -742,7 +742,17 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     const bool penalty_on_top = w->params.penalty_bin > ap_hist_bin(latest_finish_bound);
     sp.lazy_from = penalty_on_top ? R - w->params.k99 + 1u : kNever;
     sp.all_within = (longest_prefill <= w->params.slo_ttft && longest_tpot <= w->params.slo_tpot) ? 1u : 0u;
-    sp.tpot_within = longest_tpot <= w->params.slo_tpot ? 1u : 0u;
+    // A request that waits beyond its ready time finds all B slots taken by earlier ones, so it waits no longer than all service together
+    // takes B slots.
+    uint64_t all_service = 0, longest_service = 0, latest_on = 0;
+    for (uint32_t r = 0; r < R; ++r) {
+        all_service += worst_service[r];
+        longest_service = std::max<uint64_t>(longest_service, worst_service[r]);
+    }
+    for (const DevReplica& d : dev)
+        if (d.t_on < d.t_off) latest_on = std::max<uint64_t>(latest_on, d.t_on);
+    sp.step_facts = (longest_tpot <= w->params.slo_tpot ? kTpotWithin : 0u) |
+                    (latest_on + all_service / B + longest_service < (1u << 30) ? kSumsFit : 0u);
     for (uint32_t h = 0; h < 3u; ++h) {
         sp.least_bin[h] = std::min(least_bin[h], w->params.penalty_bin);
         sp.least_us[h] = (uint32_t)std::min<uint64_t>(ap_hist_lower(sp.least_bin[h]), kNever);

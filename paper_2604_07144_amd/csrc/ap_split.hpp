@@ -50,8 +50,12 @@ constexpr uint32_t kTile = 1024;                  // requests per tile: a list p
 constexpr uint32_t kFlagNeedHist = 1u;            // streamed without histograms, but they are needed: stream again
 constexpr uint32_t kFlagFallback = 2u;            // the listed part left too many slots taken: general replay
 constexpr uint32_t kFlagLazy = 4u;                // the p99 values are the penalty latency
+constexpr uint32_t kTpotWithin = 1u;              // no request's time per token can exceed the objective
+constexpr uint32_t kSumsFit = 2u;                 // four latencies (e2e) add up to less than 2^32
 constexpr uint32_t kFlagNoStreamHist = 8u;        // histograms needed, and no request of the candidate was streamed
-constexpr uint32_t kPadding = kTile;              // list entry of a run's padding: names a record that never starts
+// A list entry is 16 times the request's index in its tile: the list replay reads 16-byte records.
+constexpr uint32_t kEntryShift = 4;
+constexpr uint32_t kPadding = kTile << kEntryShift;   // the entry of a run's padding: names a record that never starts
 // Bins word of a listed request: for each metric 0 (not served, or below least_bin), or bin - least_bin + 1.  Finish times are
 // below 2^32, so bins are below 3328: 12 bits for ttft and for e2e, and 8 for tpot where its bins span no more than 255 from
 // least_bin on.  Two words otherwise: ttft and e2e in the first, tpot in the second.
@@ -91,7 +95,7 @@ struct SplitParams {
     const uint32_t* order;                        // [n_queues] replicas with a listed part, longest first
     uint32_t* desc;                               // [batch][n_list_tiles][M] count << 16 | first list position of
                                                   //   the replica's run
-    uint16_t* lists;                              // [batch][n_list_tiles][tile_cap] tile-local request indices by replica
+    uint16_t* lists;                              // [batch][n_list_tiles][tile_cap] entries of tile-local request indices by replica
     SplitPartial* part;                           // [batch]
     uint32_t* hist;                               // [batch][hist_words] the streamed requests' histograms
     void* bins;                                   // [batch][n_list_tiles * tile_cap] what listed requests add to the histograms, where it is
@@ -100,7 +104,7 @@ struct SplitParams {
     uint32_t* bin_count;                          // [batch][M + 1] how many the list replay has left
     uint32_t wide_bins;                           // the latter
     uint32_t least_bin[3], least_us[3];           // no p99 value (ttft, tpot, e2e) can lie below this bin: the list replay leaves smaller ones out
-    uint32_t tpot_within;                         // no request's time per token can exceed the objective
+    uint32_t step_facts;                          // of the list replay: kTpotWithin, kSumsFit
     const uint2* tab_pair;                        // tabulated cost model: [T][R] {prefill time, time per token}; the kind
                                                   //   word of a replica then holds its type, SplitQueue::a type * R
     // Set when the listed evaluation runs behind the streamed one (ap_stream.hpp): only candidates whose record in `pending`
@@ -416,7 +420,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
                     const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
                     const uint32_t n_peers = (uint32_t)__popcll(peers);
                     const uint32_t at = pos[k];
-                    list[at + rank] = (uint16_t)(pair & (kTile - 1u));
+                    list[at + rank] = (uint16_t)((pair << kEntryShift) & ((kTile - 1u) << kEntryShift));
                     if (rank + 1u == n_peers) {
                         pos[k] = at + n_peers;
                         same[k] = 0ull;
@@ -591,7 +595,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
             for (uint32_t s = 0; s < kSteps; ++s)
-                if (at[s] < M) list[run[at[s]] + before[s]] = (uint16_t)(s * kWave + lane);
+                if (at[s] < M) list[run[at[s]] + before[s]] = (uint16_t)((s * kWave + lane) << kEntryShift);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             for (uint32_t m = lane; m < M; m += kWave) run[m] = 0u;                  // for the wavefront's next tile
             uint4* dst = reinterpret_cast<uint4*>(p.lists + tile_at * p.tile_cap);
@@ -628,8 +632,10 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // those of a single tile.
 // A lane keeps its B slot-free times in registers, as two ascending sequences: the front, kFront of them, and the rest.  A request
 // starts at max(ready, s[0]), and its finish time f replaces s[0] in the front by one median per register:
-// s'[i] = med3(s[i], f, s[i+1]), i.e. min(s[i+1], max(s[i], f)).  A lane without a request in a step (or whose
-// request is rejected) inserts 0, which leaves the registers as they are.
+// s'[i] = med3(s[i], f, s[i+1]), i.e. min(s[i+1], max(s[i], f)).  A lane without a request in a step has a record that inserts 0,
+// which leaves the registers as they are, and adds one microsecond to the sum of latencies, taken off in the end: nothing in a step asks
+// whether a request was served.  Requests that would start too late are given that record before their step; lanes look for them
+// only when one of four starts may be that late, once or twice in a queue.
 // Is s[0] the earliest slot?  Slots that are free when a request is ready are as good as each other, then and later, whatever time
 // they hold.  So four requests may take theirs from the front if s[3] <= max(earliest of the rest, ready time of the first): of
 // s[0..3] one is still there at each of the four.  Where that does not hold in some lane, all lanes merge the two sequences
@@ -648,6 +654,8 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // Replay kernels with one sorted sequence, whose lower registers held still where slots were free, and now: 8192 rows of 32768 requests on 64
 // replicas of 64 slots that come and go 380 and 300 us, 4096 of them crowded 430 and 310; 1024 of 131072 on 128 crowded 665 and 550; calls of
 // 4096 rows of 16384 on 48 that come and go, half their slots in use: 16 slots 233 to 229 us, 24 265 to 249, 32 280 to 260, 48 320 to 275, 64 345 to 280.
+// Of the rest of a step, 36 operations were 22 when sums of four came in place of a 64-bit sum each, the latest finish from the slot times,
+// and served or not from the record: the same three kernels 300, 310 and 550 to 292, 296 and 540 us.
 // Loads run ahead: a lane's descriptors a stage, its next block of entries a block, also into the next tile, and the
 // records of a stage four per thread at a time.  A register whose
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as vectors
@@ -718,7 +726,7 @@ __device__ __forceinline__ void merge_sorted(uint32_t (&s)[kSlots]) {
 
 template <uint32_t kSlots, uint32_t kBins_, bool kFew>
 __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_replay_lists(SplitParams p, uint32_t n_cand, uint32_t which) {
-    __shared__ uint4 recs[kReplayTiles * kStagedTile];                              // {arrival, prefill, decode, tpot}
+    __shared__ uint4 recs[kReplayTiles * kStagedTile];                              // {arrival, prefill + decode, decode, tpot}
     __shared__ uint32_t goes_on[kListWaves];                                        // the wavefront has a lane with something to replay
     if (split_nothing_pending(p)) return;
     const uint32_t tid = threadIdx.x;
@@ -753,8 +761,6 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     q.t_on = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.t_on);
     q.t_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.t_off);
     q.i_list = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.i_list);
-    // one compare per request unless both objectives can be missed
-    const uint32_t slo_tpot = p.tpot_within != 0u ? kNever : p.slo_tpot;
 
     constexpr uint32_t kFront = kSlots >= 48u ? 16u : kSlots >= 16u ? 8u : kSlots;  // a power of two where there is a rest
     constexpr bool kPairs = kSlots > 48u;                                           // two steps are worth a branch
@@ -765,7 +771,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     static_assert(kFront == kSlots || (kFront >= 4u && (kFront & (kFront - 1u)) == 0u && 2u * kFront <= kSlots), "four at a time; merge_sorted");
     auto earliest = [&]() { return kFront < kSlots ? min(s[0], s[kFront < kSlots ? kFront : 0u]) : s[0]; };
     uint32_t e2e_lo = 0, e2e_hi = 0, dec_lo = 0, dec_hi = 0, tpot_lo = 0, tpot_hi = 0;
-    uint32_t last_fin = 0, n_ok = 0, n_served = 0, n_listed = 0;
+    uint32_t n_ok = 0, n_rej = 0, n_over = 0, n_run = 0, n_here = 0;       // steps, and requests among them
 
     const uint32_t n_t = (q.i_list + kTile - 1u) / kTile;
     uint32_t j0 = 0;
@@ -777,6 +783,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
         return first;
     };
     typedef uint32_t four_words __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) const four_words lds_four;
     // The kBlock entries from kBlock * b on of a run.  A lane without them reads where all such lanes do, the area's first bytes, so that there
     // is no branch around the loads and next to no traffic: where each read its own tile's first block, one that no lane needed, 8388 rows
     // of 8000 requests that crowd 50 of 300 replicas took 605 us in here, 351 before anything was read ahead, 359 with this.
@@ -826,21 +833,29 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 #pragma unroll
             for (uint32_t k = 0; k < kStageAtOnce; ++k) {
                 const uint32_t i = i0 + k * kReplayListThreads;
-                if (i < n) recs[i + i / kTile] = make_uint4(rq[k].x, cost[k].x, __umul24(rq[k].y >> 16, cost[k].y), cost[k].y);
+                if (i < n) {
+                    const uint32_t decode = __umul24(rq[k].y >> 16, cost[k].y);
+                    recs[i + i / kTile] = make_uint4(rq[k].x, cost[k].x + decode, decode, cost[k].y);
+                }
             }
         }
-        if (tid < kReplayTiles) recs[tid * kStagedTile + kTile] = make_uint4(kNever, 0u, 0u, 0u);
+        if (tid < kReplayTiles) recs[tid * kStagedTile + kTile] = make_uint4(kNever, 1u, 0u, 0u);
         __syncthreads();
         if (j0 == 0u) request_block(d_here[0], 0u, 0u);
         for (uint32_t j = j0; j < min(j0 + kReplayTiles, n_t); ++j) {
-            const uint4* tile_recs = recs + (j - j0) * kStagedTile;
-            const uint32_t d = j == j0 ? d_here[0] : d_here[1];
+            const uint32_t records_at = lds_address(recs) + (j - j0) * kStagedTile * 16u;
+            uint32_t d = j == j0 ? d_here[0] : d_here[1];
             uint32_t count;
             (void)run_of(d, count);
-            n_listed += count;
+            const bool open = live && earliest() < q.t_off;                         // else nothing starts any more: its run is left alone
+            n_over += open ? 0u : count;
+            d = open ? d : 0u;
+            count = open ? count : 0u;
+            n_here += count;
+            const uint32_t closes = open ? q.t_off : kNever;
             // Steps of the tile; where nothing can start there is one all the same, in which only the next tile's block and the next
             // stage's descriptors are requested.
-            const uint32_t most = __ballot(live && earliest() < q.t_off) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
+            const uint32_t most = __ballot(open) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
             uint32_t e[4u * kHalves];                                               // two entries each, the next ones first
 #pragma unroll
             for (uint32_t i = 0; i < 4u * kHalves; ++i) e[i] = kPadding * 0x10001u;
@@ -866,65 +881,102 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                 }
                 if (most == 0u) continue;
                 const uint32_t word[2] = {e[0], e[1]};
-                uint4 rec[4];
+                four_words rec[4];
 #pragma unroll
-                for (uint32_t k = 0; k < 4u; ++k) rec[k] = tile_recs[(k & 1u) ? word[k >> 1] >> 16 : word[k >> 1] & 0xFFFFu];
-                uint32_t bins[4] = {0u, 0u, 0u, 0u}, tpot_bins[4] = {0u, 0u, 0u, 0u};
+                for (uint32_t k = 0; k < 4u; ++k)
+                    rec[k] = *reinterpret_cast<lds_four*>(records_at + ((k & 1u) ? word[k >> 1] >> 16 : word[k >> 1] & 0xFFFFu));
                 // do the next four starts come from the front in every lane? (a lane without a request is ready at kNever)
                 if (kFront < kSlots && __ballot(s[kFront < kSlots ? 3u : 0u] > max(s[kFront < kSlots ? kFront : 0u], max(rec[0].x, q.t_on))) != 0ull)
                     merge_sorted<kSlots, 0u, 1u, kFront, kSlots - kFront>(s);
+                const bool short_four = kPairs && k0 + 2u >= n_steps;               // no lane has a third
+                // No start is later than s[3], or ready time.  Where some lane's four may start too late, those of them that do are made
+                // padding first: which they are comes from the four earliest slots.
+                if (__ballot(s[kSlots > 3u ? 3u : 0u] >= closes) != 0ull) {
+                    uint32_t early[4];
+#pragma unroll
+                    for (uint32_t i = 0; i < 4u; ++i) early[i] = s[i];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k) {
+                        const uint32_t start = max(max(rec[k].x, q.t_on), early[0]);
+                        const bool served = start < q.t_off;
+                        const uint32_t f = served ? start + rec[k].y : 0u;
+#pragma unroll
+                        for (uint32_t i = 0; i < 3u; ++i) median3(early[i], f, early[i + 1u]);
+                        raise(early[3], f);
+                        n_rej += !served && rec[k].x != kNever ? 1u : 0u;
+                        rec[k].x = served ? rec[k].x : kNever;
+                        rec[k].y = served ? rec[k].y : 1u;
+                        rec[k].z = served ? rec[k].z : 0u;
+                        rec[k].w = served ? rec[k].w : 0u;
+                    }
+                }
+                uint32_t e2e[4] = {1u, 1u, 1u, 1u}, ttft[4];
 #pragma unroll
                 for (uint32_t k = 0; k < 4u; ++k) {
-                    if (kPairs && k >= 2u && k0 + 2u >= n_steps) continue;          // no lane has a third
-                    const uint4 rq = rec[k];
-                    const uint32_t start = max(max(rq.x, q.t_on), s[0]);            // 
-                    const bool served = start < q.t_off;                            // padding never starts
-                    const uint32_t fin = start + rq.y + rq.z;
-                    const uint32_t f = served ? fin : 0u;
+                    if (k >= 2u && short_four) continue;
+                    const uint32_t f = max(max(rec[k].x, q.t_on), s[0]) + rec[k].y; // padding: kNever + 1
 #pragma unroll
                     for (uint32_t i = 0; i < kFront; ++i) {
                         if (i + 1u < kFront) median3(s[i], f, s[i + 1u < kFront ? i + 1u : i]);
                         else raise(s[i], f);
                     }
-                    if (served) {
-                        const uint32_t e2e = fin - rq.x, ttft = e2e - rq.z;
-                        add_wide(e2e_lo, e2e_hi, e2e);
-                        add_wide(dec_lo, dec_hi, rq.z);
-                        add_wide(tpot_lo, tpot_hi, rq.w);
-                        last_fin = max(last_fin, fin);
-                        ++n_served;
-                        n_ok += (ttft <= p.slo_ttft && rq.w <= slo_tpot) ? 1u : 0u;
-                        if (kBins_ != 0u) {
-                            if (kFew || ((ttft >= p.least_us[0]) | (rq.w >= p.least_us[1]) | (e2e >= p.least_us[2]))) {
-                                const uint32_t tpot_bin = bin_above(rq.w, p.least_us[1], p.least_bin[1]);
-                                bins[k] = bin_above(ttft, p.least_us[0], p.least_bin[0]) | (bin_above(e2e, p.least_us[2], p.least_bin[2]) << 12) |
-                                          (kBins_ == 2u ? 0u : tpot_bin << 24);
-                                tpot_bins[k] = tpot_bin;
-                            }
-                        }
+                    e2e[k] = f - rec[k].x;                                          // padding: 1
+                }
+                n_run += 4u;
+                add_wide(dec_lo, dec_hi, rec[0].z + rec[1].z + rec[2].z + rec[3].z);   // each below 2^28
+                add_wide(tpot_lo, tpot_hi, rec[0].w + rec[1].w + rec[2].w + rec[3].w);
+#pragma unroll
+                for (uint32_t k = 0; k < 4u; ++k) ttft[k] = e2e[k] - rec[k].z;
+                if (p.step_facts == (kTpotWithin | kSumsFit)) {
+                    add_wide(e2e_lo, e2e_hi, e2e[0] + e2e[1] + e2e[2] + e2e[3]);
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k) n_ok += ttft[k] <= p.slo_ttft ? 1u : 0u;
+                } else {
+#pragma unroll
+                    for (uint32_t k = 0; k < 4u; ++k) {
+                        add_wide(e2e_lo, e2e_hi, e2e[k]);
+                        n_ok += (ttft[k] <= p.slo_ttft && rec[k].w <= p.slo_tpot) ? 1u : 0u;
                     }
                 }
-                const bool leaves = kBins_ != 0u && with_hist && (bins[0] | bins[1] | bins[2] | bins[3] | (kBins_ == 2u ? tpot_bins[0] | tpot_bins[1] | tpot_bins[2] | tpot_bins[3] : 0u)) != 0u;
-                if (leaves) {
-                    if (kBins_ == 2u) {
-                        uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + bins_at + n_left);
-                        dst[0] = make_uint4(bins[0], tpot_bins[0], bins[1], tpot_bins[1]);
-                        dst[1] = make_uint4(bins[2], tpot_bins[2], bins[3], tpot_bins[3]);
-                    } else {
-                        *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + bins_at + n_left) = make_uint4(bins[0], bins[1], bins[2], bins[3]);
+                if constexpr (kBins_ != 0u) {
+                    const bool any_large = (max(max(ttft[0], ttft[1]), max(ttft[2], ttft[3])) >= p.least_us[0]) |
+                                           (max(max(rec[0].w, rec[1].w), max(rec[2].w, rec[3].w)) >= p.least_us[1]) |
+                                           (max(max(e2e[0], e2e[1]), max(e2e[2], e2e[3])) >= p.least_us[2]);
+                    if ((kFew || any_large) && with_hist) {
+                        uint32_t bins[4], tpot_bins[4];
+#pragma unroll
+                        for (uint32_t k = 0; k < 4u; ++k) {
+                            tpot_bins[k] = rec[k].x == kNever ? 0u : bin_above(rec[k].w, p.least_us[1], p.least_bin[1]);
+                            bins[k] = rec[k].x == kNever ? 0u : bin_above(ttft[k], p.least_us[0], p.least_bin[0]) | (bin_above(e2e[k], p.least_us[2], p.least_bin[2]) << 12) |
+                                                                (kBins_ == 2u ? 0u : tpot_bins[k] << 24);
+                        }
+                        if ((bins[0] | bins[1] | bins[2] | bins[3] | (kBins_ == 2u ? tpot_bins[0] | tpot_bins[1] | tpot_bins[2] | tpot_bins[3] : 0u)) != 0u) {
+                            if (kBins_ == 2u) {
+                                uint4* dst = reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(p.bins) + bins_at + n_left);
+                                dst[0] = make_uint4(bins[0], tpot_bins[0], bins[1], tpot_bins[1]);
+                                dst[1] = make_uint4(bins[2], tpot_bins[2], bins[3], tpot_bins[3]);
+                            } else {
+                                *reinterpret_cast<uint4*>(reinterpret_cast<uint32_t*>(p.bins) + bins_at + n_left) = make_uint4(bins[0], bins[1], bins[2], bins[3]);
+                            }
+                            n_left += 4u;
+                        }
                     }
-                    n_left += 4u;
                 }
             }
         }
     }
     if (kBins_ != 0u && with_hist) p.bin_count[(size_t)cb * (p.M + 1u) + m] = n_left;
     for (; j0 < n_t; ++j0)                                                          // nothing starts any more: only counted
-        n_listed += live ? p.desc[((size_t)cb * p.n_list_tiles + j0) * p.M + m] >> 16 : 0u;
-    const unsigned long long s_e2e = ((unsigned long long)e2e_hi << 32) | e2e_lo;
+        n_over += live ? p.desc[((size_t)cb * p.n_list_tiles + j0) * p.M + m] >> 16 : 0u;
+    // steps without a request that was served: each has left a latency of one microsecond, and was within the objectives if that is
+    const uint32_t n_padding = n_run - (n_here - n_rej);
+    if (p.slo_ttft >= 1u) n_ok -= n_padding;
+    const unsigned long long s_e2e = (((unsigned long long)e2e_hi << 32) | e2e_lo) - n_padding;
     const unsigned long long s_tpot = ((unsigned long long)tpot_hi << 32) | tpot_lo;
     const unsigned long long s_ttft = s_e2e - (((unsigned long long)dec_hi << 32) | dec_lo);
-    const uint32_t n_rej = n_listed - n_served;                                     // the replica was gone before they could start
+    uint32_t last_fin = 0;                                                          // a slot's time is replaced by a later one only: the latest stays
+#pragma unroll
+    for (uint32_t i = 0; i < kSlots; ++i) last_fin = max(last_fin, s[i] == kNever ? 0u : s[i]);
     if (!live) return;
     // does the listed part leave the streamed part the room the host counted on?
     uint32_t flag = 0u;
@@ -940,7 +992,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     if (s_tpot) atomicAdd(&sp->s_tpot, s_tpot);
     if (last_fin) atomicMax(&sp->last_fin, last_fin);
     if (n_ok) atomicAdd(&sp->n_ok, n_ok);
-    if (n_rej) atomicAdd(&sp->n_rej, n_rej);
+    if (n_rej + n_over) atomicAdd(&sp->n_rej, n_rej + n_over);
     if (flag) atomicOr(&sp->flags, flag);
 }
 
