@@ -111,7 +111,7 @@ struct RoofBuffers {
 // One plan of the listed / streamed evaluation.
 struct SplitPlan {
     bool short_chain = false;         // calls of few rows are left to the fused replay
-    uint32_t lds_bytes_list = 0;      // k_list_candidates
+    uint32_t list_waves_most = 0;     // k_list_candidates: wavefronts of a workgroup that LDS has room for
     bool expect_lazy = false;         // stream without histograms first
     uint32_t batch = 0;               // candidates per batch (what the scratch area holds)
     uint32_t lds_bytes = 0, lds_bytes_hist = 0;
@@ -324,7 +324,12 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         const int narrow = sp.M <= 64u ? 1 : 0;
         const bool plain_first = plan.expect_lazy;
         if (sp.any_streamed == 0u)
-            hipLaunchKernelGGL(k_list_candidates, dim3(grid), dim3(kSplitThreads), plan.lds_bytes_list, stream, sp, d_assign, c0, n, flags);
+        {
+            // A workgroup per row: four wavefronts, up to eight where rows leave the chip less than four per SIMD.  With more wavefronts than
+            // that the LDS is what they wait for: 1024 rows of 131072 requests on 128 replicas 172 us with four wavefronts a row, 179 with six.
+            const uint32_t waves = std::max(kSplitWaves, std::min(std::min(plan.list_waves_most, sp.n_tiles), w->n_cu * 16u / n));
+            hipLaunchKernelGGL(k_list_candidates, dim3(grid), dim3(waves * kWave), sp.l_wave + waves * sp.l_wave_bytes, stream, sp, d_assign, c0, n, flags);
+        }
         else if (plain_first)
             hipLaunchKernelGGL(split_kernel(0u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads), plan.lds_bytes, stream,
                                sp, d_assign, c0, n, 0u, flags);
@@ -779,14 +784,14 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.wave_bytes = wb;
     off += kSplitWaves * wb;
     sp.off_hist = off;
-    sp.l_wave = sp.off_wave;
+    sp.l_total = sp.off_wave;
+    sp.l_wave = sp.l_total + align_up(M * 4u, 16u);
     sp.l_list = align_up((M + 1u) * 4u, 16u);
-    sp.l_wave_bytes = sp.l_list + align_up(sp.tile_cap * 2u, 16u);
-    sp.l_total = sp.l_wave + kSplitWaves * sp.l_wave_bytes;
-    plan.lds_bytes_list = sp.l_total + align_up(M * 4u, 16u);
+    sp.l_wave_bytes = sp.l_list + align_up(sp.tile_cap * 2u, 16u) + 32u;    // eight entries more on either side
     int lds_cap = 0;
     if (hipDeviceGetAttribute(&lds_cap, hipDeviceAttributeMaxSharedMemoryPerBlock, w->device) != hipSuccess) return device_error();
-    if (off + hist_bytes > (uint32_t)lds_cap) return AP_OK;  // a replica table that large stays with the general replay
+    plan.list_waves_most = std::min(kBuildMaxWaves, ((uint32_t)lds_cap - std::min((uint32_t)lds_cap, sp.l_wave)) / sp.l_wave_bytes);
+    if (off + hist_bytes > (uint32_t)lds_cap || plan.list_waves_most < kSplitWaves) return AP_OK;  // a replica table that large stays with the general replay
     plan.lds_bytes = off;
     plan.lds_bytes_hist = off + hist_bytes;
     if (off + hist_bytes + align_up(M * 4u, 16u) <= (uint32_t)lds_cap) {     // else (a handful of table sizes) they are added up in device memory
@@ -798,7 +803,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         !tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled))))
         return device_error();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_list_candidates), hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)plan.lds_bytes_list) != hipSuccess ||
+                            (int)(sp.l_wave + plan.list_waves_most * sp.l_wave_bytes)) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled)),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)off) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled)),

@@ -5,6 +5,7 @@
 #include <type_traits>
 
 #include "ap_common.hpp"
+#include "ap_runs.hpp"
 #include "ap_screen.hpp"
 
 namespace {
@@ -46,6 +47,7 @@ namespace {
 // depend on, and k_merge_candidates adds the two up.
 constexpr uint32_t kSplitWaves = 4;
 constexpr uint32_t kSplitThreads = kSplitWaves * kWave;
+constexpr uint32_t kBuildMaxWaves = 8;            // of a workgroup of k_list_candidates
 constexpr uint32_t kTile = 1024;                  // requests per tile: a list position fits 10 bits
 constexpr uint32_t kFlagNeedHist = 1u;            // streamed without histograms, but they are needed: stream again
 constexpr uint32_t kFlagFallback = 2u;            // the listed part left too many slots taken: general replay
@@ -124,7 +126,7 @@ struct SplitParams {
     uint32_t off_range, off_range_off, off_kind, off_acc, off_wave, wave_bytes, w_pos, w_queue, w_list, w_same, w_tile,
         off_hist;
     uint32_t off_total;                                  // listed requests per replica; 0: there is no room, they are added up in bin_base
-    uint32_t l_wave, l_wave_bytes, l_list, l_total;      // k_list_candidates: its wavefronts' areas, and the same
+    uint32_t l_wave, l_wave_bytes, l_list, l_total;      // k_list_candidates: its wavefronts' areas (last), and the same
 };
 
 // Is candidate cb of the batch one to look at?
@@ -141,23 +143,12 @@ __global__ __launch_bounds__(kThreads) void k_pair_tables(const uint32_t* __rest
         pair[i] = make_uint2(prefill[i], tpot[i]);
 }
 
-// The lanes among those in `all` that name the same replica as this one (meaningless in the others): one ballot per bit of the
-// replica id, and four instructions each, kept apart from the next bit's (merged, they are more).  key_bits: bits of an id below M.
-__device__ __forceinline__ uint2 lanes_alike(uint32_t id, unsigned long long all, uint32_t key_bits) {
-    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
-    auto narrow_down = [&](uint32_t b) {
-        uint32_t ours = (uint32_t)((int32_t)(id << (31u - b)) >> 31);
-        asm("" : "+v"(ours));
-        const unsigned long long set = __ballot(ours != 0u);
-        lo &= ~(ours ^ (uint32_t)set);
-        hi &= ~(ours ^ (uint32_t)(set >> 32));
-        asm("" : "+v"(lo), "+v"(hi));
-    };
-#pragma unroll
-    for (uint32_t b = 0; b < 6u; ++b) narrow_down(b);                                // (a bit that no id has takes nothing away)
-    if (key_bits > 6u) narrow_down(6u);
-    for (uint32_t b = 7u; b < key_bits; ++b) narrow_down(b);
-    return make_uint2(lo, hi);
+// Ranks by LDS additions.  A wavefront's LDS instructions execute in order; of the lanes of one addition that name the same word, lower
+// ones have been seen to come first, always, but nothing promises it.  So every lane looks, once a tile's entries are in their runs, at
+// the entry before its own, and a tile in which one is larger has its runs sorted.  (A random read of 64 entries is 5 LDS cycles; ranks
+// that need no such look, from ballots, are 30 vector instructions.)
+__device__ __forceinline__ void sort_runs(uint16_t* list, const uint32_t* first_of, const uint32_t* desc, uint32_t M) {
+    for (uint32_t m = threadIdx.x & 63u; m < M; m += kWave) sort_run(list + first_of[m], desc[m] >> 16);
 }
 
 // Where the bins of each replica's queue begin: the sums of the requests listed for the replicas before it, a tile's counted up to
@@ -481,19 +472,19 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     }
 }
 
-// Lists where nothing is streamed: every request is listed, or its replica is gone.  No record, cost or queue is needed then,
-// so a tile's ids go through LDS once (into the order of arrival, 64 at a time) and stay in registers, together with the
-// position of the request in its replica's run: the run's length so far plus the rank among the 64, from one ballot per bit of
-// the replica id.  Bound by LDS accesses and instruction issue about equally.  k_split_candidates does the same with a queue
-// of listed requests and its ranks from LDS words, twice as many LDS accesses and 64-bit atomics among them: 455 against 271 us for
-// 1024 rows of 131072 requests on 128 replicas, 241 against 221 us for 4096 rows of 32768 on 64.
-__global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParams p, const uint16_t* __restrict__ assign, uint32_t c0,
+// Lists where nothing is streamed: every request is listed, or its replica is gone.  No record, cost or queue is needed then, so a
+// tile's ids stay in registers, a lane's request of every 64, together with what an LDS addition to the length of its replica's run returned:
+// the request's place in the run (see sort_runs).
+// Bound by LDS accesses, about 30 cycles for 64 requests: the addition, the run's beginning, the entry's store and the look at the entry
+// before it, all at random banks.  1024 rows of 131072 requests on 128 replicas 172 us (61 vector instructions for 64 requests and 287 us
+// with places from one ballot per bit of the replica id), 4096 rows of 32768 on 64 that come and go 137 (222).
+__global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(SplitParams p, const uint16_t* __restrict__ assign, uint32_t c0,
                                                                       uint32_t n_cand, PendingWord flags) {
     extern __shared__ __align__(16) unsigned char lds[];
     pending_clear_next(flags);
     if (split_nothing_pending(p)) return;
     constexpr uint32_t kSteps = kTile / kWave;
-    const uint32_t tid = threadIdx.x, w = wave_index();
+    const uint32_t tid = threadIdx.x, w = wave_index(), n_waves = blockDim.x >> 6;
     uint32_t lane = tid & 63u;
     const uint32_t R = p.R, M = p.M;
     uint32_t* end_of = reinterpret_cast<uint32_t*>(lds + p.off_range);               // [M + 1] the replica's list ends here
@@ -501,77 +492,60 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
     uint32_t* total_of = reinterpret_cast<uint32_t*>(lds + p.l_total);               // [M] listed requests of the row
     unsigned char* mine = lds + p.l_wave + w * p.l_wave_bytes;
     uint32_t* run = reinterpret_cast<uint32_t*>(mine);                               // [M + 1] the run's length so far, then its first position
-    uint16_t* list = reinterpret_cast<uint16_t*>(mine + p.l_list);                   // [tile_cap]; before that the tile's ids
-    for (uint32_t i = tid; i <= M; i += kSplitThreads) end_of[i] = p.wide != 0u ? p.tab.range[i] : p.tab.range[i] & 0xFFFFu;
-    for (uint32_t m = lane; m <= M; m += kWave) run[m] = 0u;
+    uint16_t* list = reinterpret_cast<uint16_t*>(mine + p.l_list) + 8u;              // [-8 .. tile_cap + 8)
+    for (uint32_t i = tid; i <= M; i += blockDim.x) end_of[i] = p.wide != 0u ? p.tab.range[i] : p.tab.range[i] & 0xFFFFu;
+    uint32_t least_end = kNever;
+    for (uint32_t m = lane; m < M; m += kWave) least_end = min(least_end, p.wide != 0u ? p.tab.range[m] : p.tab.range[m] & 0xFFFFu);
+    least_end = kNever - wave_all_max(kNever - least_end);
+    for (uint32_t m = lane; m <= M; m += kWave) run[m] = m < M ? 0u : p.tile_cap + 1u;   // entry M: behind the list, and behind one place more
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
         if (!split_wanted(p, cb)) continue;                                          // the same record for every thread
         __syncthreads();                                                             // the last candidate's totals were read
         if (tid == 0u) rejected_of_row[0] = 0u;
-        for (uint32_t m = tid; m < M; m += kSplitThreads) total_of[m] = 0u;
+        for (uint32_t m = tid; m < M; m += blockDim.x) total_of[m] = 0u;
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
-        const bool row_aligned = (reinterpret_cast<uintptr_t>(row) & 3u) == 0u;
-        uint32_t n_rej = 0, listed_here = 0;                                         // of replica `lane`
-        uint32_t key[kSteps / 2u], key_next[kSteps / 2u];                            // two consecutive ids of every 128
-        auto fetch_keys = [&](uint32_t j) {
-            const uint32_t r0 = j * kTile;
-            const uint32_t n = r0 < R ? min(kTile, R - r0) : 0u;
-            if (n == kTile && row_aligned) {
+        uint32_t n_seen = 0, n_listed = 0, listed_here = 0;                          // the last: of replica `lane`
+        uint32_t at[kSteps], at_next[kSteps];                                        // the replica
+        auto fetch_ids = [&](uint32_t j) {
+            if (j * kTile + kTile <= R) {
+                const uint16_t* ids = row + j * kTile + lane;
 #pragma unroll
-                for (uint32_t g = 0; g < kSteps / 2u; ++g)
-                    key_next[g] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(row + r0 + g * 2u * kWave + 2u * lane));
+                for (uint32_t s = 0; s < kSteps; ++s) at_next[s] = __builtin_nontemporal_load(ids + s * kWave);
             } else {
 #pragma unroll
-                for (uint32_t g = 0; g < kSteps / 2u; ++g) {
-                    const uint32_t rl = g * 2u * kWave + 2u * lane;
-                    const uint32_t lo = rl < n ? (uint32_t)__builtin_nontemporal_load(row + r0 + rl) : 0u;
-                    const uint32_t hi = rl + 1u < n ? (uint32_t)__builtin_nontemporal_load(row + r0 + rl + 1u) : 0u;
-                    key_next[g] = lo | (hi << 16);
+                for (uint32_t s = 0; s < kSteps; ++s) {
+                    const uint32_t r = j * kTile + s * kWave + lane;
+                    at_next[s] = r < R ? (uint32_t)__builtin_nontemporal_load(row + r) : M;
                 }
             }
         };
-        fetch_keys(w);
-        for (uint32_t j = w; j < p.n_tiles; j += kSplitWaves) {
-            const uint32_t r0 = j * kTile, n = min(kTile, R - r0);
+        fetch_ids(w);
+        for (uint32_t j = w; j < p.n_tiles; j += n_waves) {
+            const uint32_t r0 = j * kTile;
+            n_seen += min(kTile, R - r0);
             asm volatile("" : "+v"(lane));                                           // positions are made here, not kept in registers
 #pragma unroll
-            for (uint32_t g = 0; g < kSteps / 2u; ++g) key[g] = key_next[g];
-            fetch_keys(j + kSplitWaves);
+            for (uint32_t s = 0; s < kSteps; ++s) at[s] = min(at_next[s], M);
+            fetch_ids(j + n_waves);
+            uint32_t place[kSteps];                                                  // in the run
+            if (r0 + kTile <= least_end) {                                           // all but unknown replicas': the next look-ups say nothing
 #pragma unroll
-            for (uint32_t g = 0; g < kSteps / 2u; ++g) {                             // (a position past n is within the list's room)
-                const uint32_t rl = g * 2u * kWave + 2u * lane;
-                if (rl < n) reinterpret_cast<uint32_t*>(list)[rl / 2u] = key[g];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            uint32_t at[kSteps];                                                     // the replica; M: not listed
+                for (uint32_t s = 0; s < kSteps; ++s) place[s] = at[s] < M ? kNever : 0u;
+            } else {
 #pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) {
-                const uint32_t rl = s * kWave + lane;
-                at[s] = rl < n ? min((uint32_t)list[rl], M) : M;
+                for (uint32_t s = 0; s < kSteps; ++s) place[s] = end_of[at[s]];      // entry M is 0
             }
 #pragma unroll
             for (uint32_t s = 0; s < kSteps; ++s) {
-                const uint32_t rl = s * kWave + lane;
-                const bool listed = r0 + rl < end_of[at[s]];                         // entry M is 0
-                n_rej += (uint32_t)__popcll(__ballot(rl < n && !listed));
-                if (!listed) at[s] = M;
-                asm("" : "+v"(at[s]));
+                const bool listed = r0 + s * kWave + lane < place[s];                // and below R
+                n_listed += (uint32_t)__popcll(__ballot(listed));
+                place[s] = 0u;
+                if (listed) place[s] = atomicAdd(&run[at[s]], 1u);
+                at[s] = listed ? at[s] : M;
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (j >= p.n_list_tiles) continue;                                       // nothing is listed: no tile of the lists either
-            // The run lengths are read and moved on without a wait in between: a wavefront's LDS accesses execute in order, and the
-            // last lane of each replica adds what it knows without the length.
-            uint32_t before[kSteps];
-#pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) {
-                const bool listed = at[s] < M;
-                const uint2 peers = lanes_alike(at[s], __ballot(listed), p.key_bits);
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi(peers.y, __builtin_amdgcn_mbcnt_lo(peers.x, 0u));
-                const uint32_t n_peers = (uint32_t)__popc(peers.x) + (uint32_t)__popc(peers.y);
-                before[s] = run[at[s]] + rank;
-                if (listed && rank + 1u == n_peers) atomicAdd(&run[at[s]], n_peers);
-            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             const size_t tile_at = (size_t)cb * p.n_list_tiles + j;
             uint32_t total = 0;
             for (uint32_t base = 0; base < M; base += kWave) {
@@ -593,16 +567,30 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_list_candidates(SplitParam
                 total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            // (what is not listed goes to one place behind the runs)
+#pragma unroll
+            for (uint32_t s = 0; s < kSteps; ++s) at[s] = run[at[s]];
+#pragma unroll
+            for (uint32_t s = 0; s < kSteps; ++s) {
+                at[s] += place[s];
+                list[at[s]] = (uint16_t)((s * kWave + lane) << kEntryShift);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint32_t before[kSteps];
+#pragma unroll
+            for (uint32_t s = 0; s < kSteps; ++s) before[s] = list[at[s] - 1u];      // (of the first in a run, or of what is not listed, not looked at)
+            unsigned long long disorder = 0ull;
 #pragma unroll
             for (uint32_t s = 0; s < kSteps; ++s)
-                if (at[s] < M) list[run[at[s]] + before[s]] = (uint16_t)((s * kWave + lane) << kEntryShift);
+                disorder |= __ballot(before[s] > (s * kWave + lane) << kEntryShift) & __ballot(place[s] != 0u);
+            if (disorder != 0ull) sort_runs(list, run, p.desc + tile_at * M, M);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             for (uint32_t m = lane; m < M; m += kWave) run[m] = 0u;                  // for the wavefront's next tile
             uint4* dst = reinterpret_cast<uint4*>(p.lists + tile_at * p.tile_cap);
             for (uint32_t v = lane; v < total / 8u; v += kWave) dst[v] = reinterpret_cast<const uint4*>(list)[v];
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        if (lane == 0u) atomicAdd(&rejected_of_row[0], n_rej);                       // a wavefront total
+        if (lane == 0u) atomicAdd(&rejected_of_row[0], n_seen - n_listed);           // wavefront totals
         if (listed_here != 0u) atomicAdd(&total_of[lane], listed_here);
         __syncthreads();
         if (tid == 0u) {

@@ -1,5 +1,6 @@
 """Host-side checks of the C-ABI library that need no GPU: it loads, exports every
 symbol the header declares, and its host helpers agree with the oracle's histogram map."""
+import ctypes
 import os
 import re
 import shutil
@@ -140,3 +141,19 @@ def test_generators_produce_well_formed_inputs():
     assert (np.diff(wl["arrival_us"].astype(np.int64)) >= 0).all() and wl["slo_us"].min() >= 1
     pre, dec, key = traces.draw_agentic_candidates(5, 3, K, 4, 4)
     assert pre.shape == dec.shape == key.shape == (3, K) and int(pre.max()) < 4 and int(dec.max()) < 4 and (key[1] == 0).all()
+
+
+@pytest.mark.parametrize("n", [0, 1, 2, 3, 8, 64, 1024])
+def test_a_run_out_of_order_is_put_in_order(n, tmp_path):
+    """What the list kernels do with a run whose entries did not come in the order of their lanes: the same code, on the host."""
+    src, so = tmp_path / "runs.cpp", tmp_path / "runs.so"
+    src.write_text('#include "ap_runs.hpp"\nextern "C" void order(uint16_t* list, uint32_t n) { sort_run(list, n); }\n')
+    subprocess.run([shutil.which("g++"), "-O1", "-shared", "-fPIC", "-I", os.path.join(ROOT, "paper_2604_07144_amd", "csrc"), str(src), "-o", str(so)],
+                   check=True)
+    order = ctypes.CDLL(str(so)).order
+    rng = np.random.default_rng(n)
+    entries = (rng.choice(1024, size=n, replace=False) << 4).astype(np.uint16)
+    for given in (entries, np.sort(entries), np.sort(entries)[::-1].copy()):
+        around = np.concatenate([[7], given, [3]]).astype(np.uint16)              # a neighbour on either side stays
+        order(ctypes.c_void_p(around[1:].ctypes.data), ctypes.c_uint32(n))
+        assert around.tolist() == [7, *sorted(entries.tolist()), 3]
