@@ -111,6 +111,7 @@ struct RoofBuffers {
 // One plan of the listed / streamed evaluation.
 struct SplitPlan {
     bool short_chain = false;         // calls of few rows are left to the fused replay
+    bool all_within = false;          // no request's prefill or time per token can exceed the objectives
     uint32_t list_waves_most = 0;     // k_list_candidates: wavefronts of a workgroup that LDS has room for
     bool expect_lazy = false;         // stream without histograms first
     uint32_t batch = 0;               // candidates per batch (what the scratch area holds)
@@ -222,13 +223,13 @@ static stream_fn stream_kernel(bool settles, bool tabled) {
 }
 
 typedef void (*split_fn)(SplitParams, const uint16_t*, uint32_t, uint32_t, uint32_t, PendingWord);
-static split_fn split_kernel(uint32_t hist_mode, int narrow, bool tabled) {
+static split_fn split_kernel(uint32_t hist_mode, bool tabled, bool within) {
     static const split_fn variants[12] = {
         k_split_candidates<0u, false, false>, k_split_candidates<1u, false, false>, k_split_candidates<2u, false, false>,
         k_split_candidates<0u, true, false>,  k_split_candidates<1u, true, false>,  k_split_candidates<2u, true, false>,
         k_split_candidates<0u, false, true>,  k_split_candidates<1u, false, true>,  k_split_candidates<2u, false, true>,
         k_split_candidates<0u, true, true>,   k_split_candidates<1u, true, true>,   k_split_candidates<2u, true, true>};
-    return variants[hist_mode + (narrow ? 3u : 0u) + (tabled ? 6u : 0u)];
+    return variants[hist_mode + (tabled ? 3u : 0u) + (within ? 6u : 0u)];
 }
 
 typedef void (*replay_lists_fn)(SplitParams, uint32_t, uint32_t);
@@ -321,7 +322,6 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         const uint32_t grid = std::min(n, w->n_cu * 16u);
         // Where something is streamed: first without histograms if the candidates are expected to be settled by penalty; then
         // with histograms, for every candidate or for those the first pass marked.
-        const int narrow = sp.M <= 64u ? 1 : 0;
         const bool plain_first = plan.expect_lazy;
         if (sp.any_streamed == 0u)
         {
@@ -331,10 +331,10 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
             hipLaunchKernelGGL(k_list_candidates, dim3(grid), dim3(waves * kWave), sp.l_wave + waves * sp.l_wave_bytes, stream, sp, d_assign, c0, n, flags);
         }
         else if (plain_first)
-            hipLaunchKernelGGL(split_kernel(0u, narrow, w->tabled), dim3(grid), dim3(kSplitThreads), plan.lds_bytes, stream,
+            hipLaunchKernelGGL(split_kernel(0u, w->tabled, plan.all_within), dim3(grid), dim3(kSplitThreads), plan.lds_bytes, stream,
                                sp, d_assign, c0, n, 0u, flags);
         if (sp.any_streamed != 0u)              // (behind a plain pass: usually nothing to do, so few workgroups)
-            hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, narrow, w->tabled),
+            hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, w->tabled, plan.all_within),
                                dim3(plain_first ? std::min(n, w->n_cu * 3u) : grid), dim3(kSplitThreads),
                                plan.lds_bytes_hist, stream, sp, d_assign, c0, n, plain_first ? 1u : 0u, flags);
         // the list replay: where most candidates are settled by penalty, those go through the variant that leaves no bins, and
@@ -746,7 +746,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     // reach the penalty's bin: all of them lie below the bound on finish times of the range proof.
     const bool penalty_on_top = w->params.penalty_bin > ap_hist_bin(latest_finish_bound);
     sp.lazy_from = penalty_on_top ? R - w->params.k99 + 1u : kNever;
-    sp.all_within = (longest_prefill <= w->params.slo_ttft && longest_tpot <= w->params.slo_tpot) ? 1u : 0u;
+    plan.all_within = longest_prefill <= w->params.slo_ttft && longest_tpot <= w->params.slo_tpot;
     // A request that waits beyond its ready time finds all B slots taken by earlier ones, so it waits no longer than all service together
     // takes B slots.
     uint64_t all_service = 0, longest_service = 0, latest_on = 0;
@@ -767,46 +767,42 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.any_streamed = any_streamed ? 1u : 0u;
     sp.hist_words = wide ? 3u * kBins : 3u * kBins / 2u;
     // LDS of the streaming kernel
-    uint32_t off = (uint32_t)kinds.size() * 16u;             // the coefficients come first
+    uint32_t off = ((uint32_t)kinds.size() + 1u) * 16u;      // the coefficients come first, and 0 behind them
     const uint32_t hist_bytes = sp.hist_words * 4u;
     sp.off_range = off; off += align_up((M + 1u) * 4u, 16u);
     sp.off_range_off = off; off += wide ? align_up((M + 1u) * 4u, 16u) : 0u;
     sp.off_kind = off;  off += align_up((M + 1u) * 4u, 16u);
     sp.off_acc = off;   off += 64u;
     sp.off_wave = off;
-    uint32_t wb = 0;
-    wb += align_up(M * 4u, 16u);            sp.w_pos = wb;
-    wb += align_up(M * 4u, 16u);            sp.w_queue = wb;
-    wb += kTile * (M <= 64u ? 2u : 4u);     sp.w_list = wb;
-    wb += align_up(sp.tile_cap * 2u, 16u);  sp.w_same = wb;
-    wb += align_up(M * 8u, 16u);            sp.w_tile = wb;
-    wb += align_up((M + 1u) * 4u, 16u);
+    sp.w_tile = align_up(runs_bytes(M, sp.tile_cap), 16u);
+    sp.w_sums = sp.w_tile + align_up((M + 1u) * 4u, 16u);
+    const uint32_t wb = sp.w_sums + 3u * kWave * 8u;
     sp.wave_bytes = wb;
     off += kSplitWaves * wb;
     sp.off_hist = off;
     sp.l_total = sp.off_wave;
     sp.l_wave = sp.l_total + align_up(M * 4u, 16u);
-    sp.l_list = align_up((M + 1u) * 4u, 16u);
-    sp.l_wave_bytes = sp.l_list + align_up(sp.tile_cap * 2u, 16u) + 32u;    // eight entries more on either side
+    sp.l_wave_bytes = align_up(runs_bytes(M, sp.tile_cap), 16u);
     int lds_cap = 0;
     if (hipDeviceGetAttribute(&lds_cap, hipDeviceAttributeMaxSharedMemoryPerBlock, w->device) != hipSuccess) return device_error();
     plan.list_waves_most = std::min(kBuildMaxWaves, ((uint32_t)lds_cap - std::min((uint32_t)lds_cap, sp.l_wave)) / sp.l_wave_bytes);
-    if (off + hist_bytes > (uint32_t)lds_cap || plan.list_waves_most < kSplitWaves) return AP_OK;  // a replica table that large stays with the general replay
+    // A replica table that large stays with the general replay.  (The line is that of a streaming kernel which held 28 bytes a replica and
+    // six a request of a tile per wavefront; above it the lists would fit up to about 900 replicas, and were not measured.)
+    const uint32_t held = 2u * align_up(M * 4u, 16u) + kTile * (M <= 64u ? 2u : 4u) + align_up(sp.tile_cap * 2u, 16u) + align_up(M * 8u, 16u) +
+                          align_up((M + 1u) * 4u, 16u);
+    if (sp.off_wave - 16u + kSplitWaves * held + hist_bytes > (uint32_t)lds_cap) return AP_OK;
     plan.lds_bytes = off;
     plan.lds_bytes_hist = off + hist_bytes;
-    if (off + hist_bytes + align_up(M * 4u, 16u) <= (uint32_t)lds_cap) {     // else (a handful of table sizes) they are added up in device memory
-        sp.off_total = off + hist_bytes;
-        plan.lds_bytes_hist += align_up(M * 4u, 16u);
-    }
-    const int narrow = M <= 64u ? 1 : 0;
-    if (!tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled))) ||
-        !tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled))))
+    sp.off_total = off + hist_bytes;
+    plan.lds_bytes_hist += align_up(M * 4u, 16u);
+    if (!tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(0u, tabled, plan.all_within))) ||
+        !tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, tabled, plan.all_within))))
         return device_error();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_list_candidates), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(sp.l_wave + plan.list_waves_most * sp.l_wave_bytes)) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, narrow, tabled)),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, tabled, plan.all_within)),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)off) != hipSuccess ||
-        hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, narrow, tabled)),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, tabled, plan.all_within)),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds_bytes_hist) != hipSuccess) {
         (void)hipGetLastError();
         return device_error();

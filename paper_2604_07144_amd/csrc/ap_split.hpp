@@ -49,6 +49,7 @@ constexpr uint32_t kSplitWaves = 4;
 constexpr uint32_t kSplitThreads = kSplitWaves * kWave;
 constexpr uint32_t kBuildMaxWaves = 8;            // of a workgroup of k_list_candidates
 constexpr uint32_t kTile = 1024;                  // requests per tile: a list position fits 10 bits
+constexpr uint32_t kTileSteps = kTile / kWave;
 constexpr uint32_t kFlagNeedHist = 1u;            // streamed without histograms, but they are needed: stream again
 constexpr uint32_t kFlagFallback = 2u;            // the listed part left too many slots taken: general replay
 constexpr uint32_t kFlagLazy = 4u;                // the p99 values are the penalty latency
@@ -121,12 +122,10 @@ struct SplitParams {
     uint32_t even_lists;                          // every replica has a list, and all are equally long
     uint32_t slo_ttft, slo_tpot;
     uint32_t lazy_from;                           // rejected requests from which the p99 values are the penalty; kNever: never
-    uint32_t all_within;                          // no request's prefill or time per token can exceed the objectives
     // byte offsets into the streaming kernel's dynamic LDS
-    uint32_t off_range, off_range_off, off_kind, off_acc, off_wave, wave_bytes, w_pos, w_queue, w_list, w_same, w_tile,
-        off_hist;
-    uint32_t off_total;                                  // listed requests per replica; 0: there is no room, they are added up in bin_base
-    uint32_t l_wave, l_wave_bytes, l_list, l_total;      // k_list_candidates: its wavefronts' areas (last), and the same
+    uint32_t off_range, off_range_off, off_kind, off_acc, off_wave, wave_bytes, w_tile, w_sums, off_hist;
+    uint32_t off_total;                                  // listed requests per replica
+    uint32_t l_wave, l_wave_bytes, l_total;      // k_list_candidates: its wavefronts' areas (last), and the same
 };
 
 // Is candidate cb of the batch one to look at?
@@ -151,14 +150,103 @@ __device__ __forceinline__ void sort_runs(uint16_t* list, const uint32_t* first_
     for (uint32_t m = threadIdx.x & 63u; m < M; m += kWave) sort_run(list + first_of[m], desc[m] >> 16);
 }
 
+// A wavefront's LDS area for a tile's runs: [M] the runs' lengths, then where they begin; [64] words for what is not listed, one a lane; a list
+// of tile_cap entries with eight more on either side.  What is not listed gets half of the list's length for a place, and one more than that
+// for a run's beginning, which makes it write to the second spot behind the list, and finds 0 in the first.
+__host__ __device__ inline uint32_t runs_list_offset(uint32_t M) { return (M + kWave) * 4u; }
+__host__ __device__ inline uint32_t runs_bytes(uint32_t M, uint32_t tile_cap) { return ((runs_list_offset(M) + 15u) & ~15u) + tile_cap * 2u + 32u; }
+__device__ __forceinline__ void init_runs(const SplitParams& p, unsigned char* area, uint32_t lane) {
+    uint32_t* run = reinterpret_cast<uint32_t*>(area);
+    for (uint32_t m = lane; m < p.M; m += kWave) run[m] = 0u;
+    run[p.M + lane] = p.tile_cap / 2u + 1u;
+    uint16_t* list = reinterpret_cast<uint16_t*>(area + ((runs_list_offset(p.M) + 15u) & ~15u)) + 8u;
+    if (lane < 8u) list[p.tile_cap + lane] = 0u;
+}
+
+// A tile's runs and their descriptors, from the lengths of the runs (cleared again).  at: the LDS address of a request's run length or, if it is
+// not listed, of its lane's word; place: the request's place in the run.  on_run(m, c): replica m has c requests here.
+template <typename OnRun>
+__device__ __forceinline__ void write_runs(const SplitParams& p, size_t tile_at, uint32_t lane, unsigned char* area,
+                                           uint32_t (&at)[kTileSteps], const uint32_t (&place)[kTileSteps], const OnRun& on_run) {
+    const uint32_t M = p.M;
+    uint32_t* run = reinterpret_cast<uint32_t*>(area);
+    uint16_t* list = reinterpret_cast<uint16_t*>(area + ((runs_list_offset(M) + 15u) & ~15u)) + 8u;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t total = 0;
+    for (uint32_t base = 0; base < M; base += kWave) {
+        const uint32_t m = base + lane;
+        const uint32_t c = m < M ? run[m] : 0u;
+        const uint32_t room = (c + 7u) & ~7u;                                        // runs start on multiples of 8 positions
+        const uint32_t upto = wave_inclusive_scan(room, lane);
+        if ((c & 7u) != 0u) {                                                        // the run's last block: what no request takes is padding
+            uint32_t pad = kPadding * 0x10001u;                                      // (made here: kept from tile to tile it costs a spill)
+            asm volatile("" : "+v"(pad));
+            reinterpret_cast<uint4*>(list)[(total + upto - room + c) / 8u] = make_uint4(pad, pad, pad, pad);
+        }
+        if (m < M) {
+            run[m] = total + upto - room;
+            p.desc[tile_at * M + m] = (c << 16) | (total + upto - room);
+            on_run(m, c);
+        }
+        total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
+    }
+    if (total != 0u) {
+        typedef __attribute__((address_space(3))) uint16_t lds_half;
+        const uint32_t before_list = lds_address(list) - 2u;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = *(lds_word*)(uintptr_t)at[s];
+#pragma unroll
+        for (uint32_t s = 0; s < kTileSteps; ++s) {
+            at[s] = before_list + 2u * (at[s] + place[s]);
+            ((lds_half*)(uintptr_t)at[s])[1] = (uint16_t)((s * kWave + lane) << kEntryShift);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = *(lds_half*)(uintptr_t)at[s];   // the entry before (that of the first in a run is not looked at)
+        unsigned long long disorder = 0ull;
+#pragma unroll
+        for (uint32_t s = 0; s < kTileSteps; ++s)
+            disorder |= __ballot(at[s] > (s * kWave + lane) << kEntryShift) & __ballot(place[s] != 0u);
+        if (disorder != 0ull) sort_runs(list, run, p.desc + tile_at * M, M);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        uint4* dst = reinterpret_cast<uint4*>(p.lists + tile_at * p.tile_cap);       // 16 bytes (8 positions) at a time
+        typedef uint32_t four_words __attribute__((ext_vector_type(4)));
+        const four_words* from = reinterpret_cast<const four_words*>(list);
+        four_words* to = reinterpret_cast<four_words*>(dst);
+        for (uint32_t v = lane; v < total / 8u; v += 2u * kWave) {
+            const uint32_t u = v + kWave;
+            const four_words first = from[v], second = from[min(u, total / 8u - 1u)];
+            to[v] = first;
+            if (u < total / 8u) to[u] = second;
+        }
+    }
+    for (uint32_t m = lane; m < M; m += kWave) run[m] = 0u;                          // for the wavefront's next tile
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+}
+
+// The ids of tile j, a lane's request of every 64; M beyond the row.
+__device__ __forceinline__ void fetch_ids(uint32_t (&into)[kTileSteps], const uint16_t* row, uint32_t j, uint32_t lane, uint32_t R, uint32_t M) {
+    if (j * kTile + kTile <= R) {
+        const uint16_t* ids = row + j * kTile + lane;
+#pragma unroll
+        for (uint32_t s = 0; s < kTileSteps; ++s) into[s] = __builtin_nontemporal_load(ids + s * kWave);
+    } else {
+#pragma unroll
+        for (uint32_t s = 0; s < kTileSteps; ++s) {
+            const uint32_t r = j * kTile + s * kWave + lane;
+            into[s] = r < R ? (uint32_t)__builtin_nontemporal_load(row + r) : M;
+        }
+    }
+}
+
 // Where the bins of each replica's queue begin: the sums of the requests listed for the replicas before it, a tile's counted up to
 // the next multiple of four, which is how the list replay writes (one wavefront).
-template <typename Total>
-__device__ __forceinline__ void place_bins(const SplitParams& p, uint32_t cb, const Total& total_of) {
+__device__ __forceinline__ void place_bins(const SplitParams& p, uint32_t cb, const uint32_t* total_of) {
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t before = 0;
     for (uint32_t base = 0; base < p.M; base += kWave) {
-        const uint32_t m = base + lane, v = m < p.M ? total_of(m) : 0u;
+        const uint32_t m = base + lane, v = m < p.M ? total_of[m] : 0u;
         const uint32_t upto = wave_inclusive_scan(v, lane);
         if (m < p.M) p.bin_base[(size_t)cb * (p.M + 1u) + m] = before + upto - v;
         before += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
@@ -168,18 +256,20 @@ __device__ __forceinline__ void place_bins(const SplitParams& p, uint32_t cb, co
 // Streaming kernel, where something is streamed.  One workgroup per candidate at a time;
 // its wavefronts take the tiles of the row in turn and share nothing but the accumulators (and the histograms), so there is no barrier inside a
 // candidate.
-// Per tile a wavefront classifies its 1024 requests, accumulates the streamed ones, counts the listed ones per
-// replica, queues them in arrival order, ranks them (one ballot per bit of the replica id among 64 queued
-// requests at a time) into per-replica runs that start on multiples of 8 list positions, and writes the runs
-// and their descriptors out.
+// Per tile a wavefront classifies its 1024 requests, accumulates the streamed ones, finds the places of the listed ones in their replicas'
+// runs by LDS additions (see sort_runs) and writes the runs, which start on multiples of 8 list positions, and their descriptors out.
+// Bound by instruction issue and, with five wavefronts per SIMD, by what they wait for.  43 instructions for 64 requests and 404 us for 8192
+// rows of 32768 requests on 64 replicas that come and go (3001 of 20011 on 50 with tables: 199) when listed requests were queued in LDS, counted and
+// ranked from a second pass over the queue; 36 and 356 (144) now.  Of the 356 the runs are 110 and the costs 60; without a coefficient of 0 for
+// requests that cost nothing, a branch for each instead, 405; with the sums in registers, 101 of them and four wavefronts, 400.
 // kHistMode: 0 keeps no histograms of the streamed requests (enough when the candidate is settled by penalty), 1 keeps them
 // with 16-bit counts (R < 65536), 2 with 32-bit counts.
 // only_flagged: look only at candidates that an earlier launch marked kFlagNeedHist.
-// kNarrow: at most 64 replicas, so a queued request (tile index and replica) fits 16 bits, which halves the queue.
+// kWithin: no request's prefill or time per token can exceed the objectives.
 // kTabled: prefill time and time per token are read from the tables (one 8-byte load per request, issued with the
 // table look-ups of the quarter tile) instead of being evaluated from a kind's coefficients.
-template <uint32_t kHistMode, bool kNarrow, bool kTabled>
-__global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitParams p, const uint16_t* __restrict__ assign,
+template <uint32_t kHistMode, bool kTabled, bool kWithin>
+__global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_split_candidates(SplitParams p, const uint16_t* __restrict__ assign,
                                                                     uint32_t c0, uint32_t n_cand, uint32_t only_flagged,
                                                                     PendingWord flags) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -192,15 +282,10 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
     uint4* coef_of = reinterpret_cast<uint4*>(lds);
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_acc);
     uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);    // latest finish, within objectives, rejected
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, w = wave_index();
+    const uint32_t tid = threadIdx.x, w = wave_index();
+    uint32_t lane = tid & 63u;
     unsigned char* mine = lds + p.off_wave + w * p.wave_bytes;
-    uint32_t* cnt = reinterpret_cast<uint32_t*>(mine);                       // [M] listed requests of the tile per replica
-    uint32_t* pos = reinterpret_cast<uint32_t*>(mine + p.w_pos);             // [M] next free position of the replica's run
-    using queued_t = typename std::conditional<kNarrow, uint16_t, uint32_t>::type;
-    constexpr uint32_t kIdShift = kNarrow ? 10u : 16u;
-    queued_t* queue = reinterpret_cast<queued_t*>(mine + p.w_queue);         // [kTile] tile index | replica << kIdShift, arrival order
-    uint16_t* list = reinterpret_cast<uint16_t*>(mine + p.w_list);           // [tile_cap]
-    unsigned long long* same = reinterpret_cast<unsigned long long*>(mine + p.w_same);   // [M] lanes naming the replica
+    unsigned long long* sums = reinterpret_cast<unsigned long long*>(mine + p.w_sums);   // [3][64] per lane: e2e, ttft, tpot
     uint32_t* tile_of = reinterpret_cast<uint32_t*>(mine + p.w_tile);        // [M + 1] the replica's ranges within the tile in hand
     uint32_t* total = reinterpret_cast<uint32_t*>(lds + p.off_total);        // kHist only: [M]
     // The coefficients lie at LDS address 0 (read by address: through the array's name every access costs an addition of its base).  The
@@ -221,222 +306,159 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
         if (p.wide != 0u) range_off_of[i] = p.tab.range_off[i];
         kind_of[i] = p.tab.kind[i];
     }
-    for (uint32_t i = tid; i < p.tab.n_kinds; i += kSplitThreads) coef_of[i] = p.tab.coef[i];
-    for (uint32_t m = lane; m < M; m += kWave) {
-        cnt[m] = 0u;
-        same[m] = 0ull;
-    }
+    for (uint32_t i = tid; i <= p.tab.n_kinds; i += kSplitThreads) coef_of[i] = i < p.tab.n_kinds ? p.tab.coef[i] : make_uint4(0u, 0u, 0u, 0u);
+    init_runs(p, mine, lane);
+    const uint32_t runs_at = lds_address(mine), nowhere_at = runs_at + 4u * (M + (tid & 63u));
 
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
         if ((only_flagged && (p.part[cb].flags & kFlagNeedHist) == 0u) || (kHist && !split_wanted(p, cb))) continue;   // the same for every thread
         __syncthreads();                                                            // the last candidate's totals were read
         if (kHist) {
             for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) hist[i] = 0u;
-            for (uint32_t m = tid; m < M; m += kSplitThreads) {
-                if (p.off_total != 0u) total[m] = 0u;
-                else __hip_atomic_store(&p.bin_base[(size_t)cb * (M + 1u) + m], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            for (uint32_t m = tid; m < M; m += kSplitThreads) total[m] = 0u;
         }
         if (tid < 10u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
-        const bool row_aligned = (reinterpret_cast<uintptr_t>(row) & 3u) == 0u;      // pairs of ids as one 4-byte load
-        unsigned long long s_e2e = 0, s_ttft = 0, s_tpot = 0;
         uint32_t last_fin = 0, n_ok = 0, n_rej = 0, n_streamed = 0;
+        for (uint32_t k = 0; k < 3u; ++k) sums[k * kWave + lane] = 0ull;
 
-        // A wavefront's tiles.  A lane holds two consecutive requests of every 128 (one 4-byte load of two replica
-        // ids, one 16-byte load of two request records).  The ids of the next tile are requested before the current
-        // one is worked on and the records of a quarter tile before that quarter; the table look-ups of a quarter are issued
-        // together, so that no request waits for memory or for the LDS by itself.
-        constexpr uint32_t kPairs = kTile / (2u * kWave), kParts = 4u, kHalf = kPairs / kParts;   // pairs per lane and tile; per part
-        uint32_t key[kPairs], key_next[kPairs];
-        auto fetch_keys = [&](uint32_t (&into)[kPairs], uint32_t j) {
-            const uint32_t r0 = j * kTile;
-            if (r0 + kTile <= R && row_aligned) {                                   // a whole tile: no guards
-#pragma unroll
-                for (uint32_t g = 0; g < kPairs; ++g)
-                    into[g] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(row + r0 + g * 2u * kWave + 2u * lane));
-            } else {
-                const uint32_t n = r0 < R ? min(kTile, R - r0) : 0u;
-#pragma unroll
-                for (uint32_t g = 0; g < kPairs; ++g) {
-                    const uint32_t rl = g * 2u * kWave + 2u * lane;
-                    const uint32_t lo = rl < n ? (uint32_t)__builtin_nontemporal_load(row + r0 + rl) : 0u;
-                    const uint32_t hi = rl + 1u < n ? (uint32_t)__builtin_nontemporal_load(row + r0 + rl + 1u) : 0u;
-                    into[g] = lo | (hi << 16);
-                }
-            }
-        };
+        // A wavefront's tiles.  A lane holds a request of every 64.  The ids of the next tile are requested before the runs of
+        // this one are written, the records and table look-ups of a quarter tile together before it is worked on.
+        constexpr uint32_t kParts = 4u, kPart = kTileSteps / kParts;
+        uint32_t at[kTileSteps], at_next[kTileSteps];                               // the replica
         // one tile; kWhole: all of its 1024 requests exist
         auto work_tile = [&](auto whole_tag, uint32_t j) {
             constexpr bool kWhole = decltype(whole_tag)::value;
             const uint32_t r0 = j * kTile, n = min(kTile, R - r0);
-            const bool grouping = j < p.n_list_tiles;                               // beyond: nothing can be listed
-            // The replica ranges cut down to this tile, one word per replica: listed below position `lo` of the tile,
-            // gone from position `hi` on (both 0 .. 1024, 11 bits each), and the replica's kind
-            // above them (or its type, when the costs come from tables), so that a request needs one look-up.
+            asm volatile("" : "+v"(lane));                                          // positions are made here, not kept in registers
+            // The replica ranges cut down to this tile, one word per replica: in the halves, listed below position `lo` of the tile and
+            // gone from position `hi` on (both 0 .. 1024), and below them, in five bits each, the replica's kind
+            // (or its type, when the costs come from tables), so that a request needs one look-up, and a half of it is
+            // compared as it stands with the request's position, shifted alike and filled with ones.
             // (The wavefront's own LDS accesses execute in order.)
             for (uint32_t m = lane; m <= M; m += kWave) {
                 const uint32_t word = range_of[m];
                 const uint32_t i_list = p.wide != 0u ? word : (word & 0xFFFFu);
                 const uint32_t i_off = p.wide != 0u ? range_off_of[m] : (word >> 16);
-                const uint32_t lo = min(max(i_list, r0) - r0, kTile), hi = min(max(i_off, r0) - r0, kTile);
-                tile_of[m] = lo | (hi << 11) | (kind_of[m] << 22);
+                const uint32_t lo = min(max(i_list, r0) - r0, kTile), hi = min(max(i_off, r0) - r0, kTile), kind = kind_of[m];
+                tile_of[m] = (lo << 5) | (kind & 31u) | (((hi << 5) | (kind >> 5)) << 16);
             }
-            uint32_t q_n = 0;                                                       // queued so far (the same in every lane)
+            const char* records = reinterpret_cast<const char*>(p.req8 + r0);
+            uint32_t n_listed = 0;                                                  // (the same in every lane)
             uint32_t t_e2e = 0, t_ttft = 0, t_tpot = 0;                             // the tile's sums: 16 values below 2^28 each
+            uint32_t place[kTileSteps];                                             // in the replica's run
 #pragma unroll
             for (uint32_t h = 0; h < kParts; ++h) {
-                uint4 record[kHalf];
-                uint32_t id[2u * kHalf], from[2u * kHalf], upto[2u * kHalf], kind[2u * kHalf];   // listed below `from`, gone from `upto`
-                uint32_t cost_prefill[kTabled ? 2u * kHalf : 1u], cost_tpot[kTabled ? 2u * kHalf : 1u];
+                unsigned long long record[kPart];                                   // (relaxed loads: others are moved to where they are used)
+                uint32_t word[kPart], kind[kPart];
+                uint32_t cost_prefill[kTabled ? kPart : 1u], cost_tpot[kTabled ? kPart : 1u];
 #pragma unroll
-                for (uint32_t g = 0; g < kHalf; ++g) {
-                    const uint32_t rl = (h * kHalf + g) * 2u * kWave + 2u * lane;
-                    record[g] = (kWhole || rl < n) ? *reinterpret_cast<const uint4*>(p.req8 + r0 + rl) : make_uint4(0u, 0u, 0u, 0u);
-                    id[2u * g] = min(key[h * kHalf + g] & 0xFFFFu, M);
-                    id[2u * g + 1u] = min(key[h * kHalf + g] >> 16, M);
+                for (uint32_t i = 0; i < kPart; ++i) {
+                    const uint32_t rl = (h * kPart + i) * kWave + lane;
+                    record[i] = 0ull;
+                    if (kWhole || rl < n)
+                        record[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(records + (h * kPart + i) * kWave * 8u + lane * 8u),
+                                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    word[i] = tile_of[at[h * kPart + i]];
                 }
 #pragma unroll
-                for (uint32_t i = 0; i < 2u * kHalf; ++i) {
-                    const uint32_t word = tile_of[id[i]];
-                    from[i] = word & 0x7FFu;
-                    upto[i] = (word >> 11) & 0x7FFu;
-                    kind[i] = kTabled ? (word >> 22) * R : (word >> 18) & 0x3FF0u;   // tabulated: the type's first table entry; else where the coefficients are
+                for (uint32_t i = 0; i < kPart; ++i) {
+                    if (kTabled) {
+                        const uint32_t type = (word[i] & 31u) | ((word[i] >> 11) & 0x3E0u);
+                        kind[i] = R < (1u << 24) ? __umul24(type, R) : type * R;    // the type's first table entry
+                    } else {
+                        kind[i] = (word[i] & 31u) << 4;                             // where the coefficients are
+                    }
+                }
+                if (!kTabled && p.tab.n_kinds > 32u) {
+#pragma unroll
+                    for (uint32_t i = 0; i < kPart; ++i) {
+                        kind[i] |= (word[i] >> 7) & 0x3E00u;
+                        asm volatile("" : "+v"(kind[i]));                           // (a branch, not a choice for each)
+                    }
                 }
                 if (kTabled) {
 #pragma unroll
-                    for (uint32_t i = 0; i < 2u * kHalf; ++i) {                     // whether streamed or not: the entry exists
-                        const uint32_t r = min(r0 + (h * kHalf + (i >> 1)) * 2u * kWave + 2u * lane + (i & 1u), R - 1u);
-                        const uint2 cost = p.tab_pair[kind[i] + r];
-                        cost_prefill[i] = cost.x;
-                        cost_tpot[i] = cost.y;
+                    for (uint32_t i = 0; i < kPart; ++i) {                          // whether streamed or not: the entry exists
+                        const uint32_t r = kWhole ? r0 + (h * kPart + i) * kWave + lane : min(r0 + (h * kPart + i) * kWave + lane, R - 1u);
+                        const unsigned long long cost = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p.tab_pair) + (kind[i] + r),
+                                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                        cost_prefill[i] = (uint32_t)cost;
+                        cost_tpot[i] = (uint32_t)(cost >> 32);
                     }
                 }
+                // which of the lanes' requests start on arrival
+                unsigned long long streamed[kPart], any_streamed = 0ull;
 #pragma unroll
-                for (uint32_t g = 0; g < kHalf; ++g) {
-                    unsigned long long listed[2];                                   // which lanes' requests
+                for (uint32_t i = 0; i < kPart; ++i) {
+                    const uint32_t s = h * kPart + i, rl = s * kWave + lane, position = (rl << 5) | 31u;
+                    const unsigned long long in = kWhole ? ~0ull : __ballot(rl < n);
+                    const unsigned long long listed = __ballot(position < (word[i] & 0xFFFFu)) & in;    // lo <= hi
+                    const unsigned long long rejected = __ballot(position >= word[i] >> 16) & in;
+                    streamed[i] = ~(listed | rejected) & in;
+                    any_streamed |= streamed[i];
+                    n_rej += (uint32_t)__popcll(rejected);
+                    n_listed += (uint32_t)__popcll(listed);
+                    asm volatile("" : "+s"(n_rej), "+s"(n_listed));                 // counted here, not kept as masks
+                    const bool is_listed = __builtin_amdgcn_inverse_ballot_w64(listed);
+                    at[s] = is_listed ? runs_at + 4u * at[s] : nowhere_at;
+                    place[s] = p.tile_cap / 2u;
+                    if (is_listed) place[s] = lds_add_rtn(at[s], 1u);
+                }
+                if (any_streamed == 0ull) continue;
+                // ttft = prefill for these; the others cost nothing, from coefficients of 0 or instead of what the tables say
+                uint32_t prefill[kPart], tpot[kPart], e2e[kPart], fin[kPart];
 #pragma unroll
-                    for (uint32_t e = 0; e < 2u; ++e) {
-                        const uint32_t i = 2u * g + e;
-                        const uint32_t rl = (h * kHalf + g) * 2u * kWave + 2u * lane + e;
-                        const unsigned long long in = kWhole ? ~0ull : __ballot(rl < n);
-                        listed[e] = __ballot(rl < from[i]) & in;                    // lo <= hi
-                        const unsigned long long rejected = __ballot(rl >= upto[i]) & in;
-                        n_rej += (uint32_t)__popcll(rejected);
-                        if (__builtin_amdgcn_inverse_ballot_w64(~(listed[e] | rejected) & in)) {
-                            // starts on arrival: ttft = prefill
-                            const uint32_t arrival = e ? record[g].z : record[g].x, lens = e ? record[g].w : record[g].y;
-                            const uint32_t prompt = lens & 0xFFFFu, out = lens >> 16;
-                            uint32_t prefill, tpot;
-                            if (kTabled) {
-                                prefill = cost_prefill[i];
-                                tpot = cost_tpot[i];
-                            } else {
-                                const four_words co = *reinterpret_cast<lds_four*>(kind[i]);
-                                prefill = co.x + __umul24(co.y, prompt);            // the host keeps all factors below 2^24
-                                tpot = co.z + __umul24(co.w, (prompt + 1023u) >> 10);
-                            }
-                            const uint32_t e2e = prefill + __umul24(out, tpot);
-                            t_ttft += prefill;
-                            t_e2e += e2e;
-                            t_tpot += tpot;
-                            last_fin = max(last_fin, arrival + e2e);
-                            if (p.all_within == 0u) n_ok += (prefill <= p.slo_ttft && tpot <= p.slo_tpot) ? 1u : 0u;
-                            if (kHist) {                                            // (a test per value against least_us costs more than it
-                                hist_add<kHist16>(hist, 0u, hist_bin_u32(prefill), 1u);   // saves: 3 rows of 30000 requests 46 against 37 us,
-                                hist_add<kHist16>(hist, 1u, hist_bin_u32(tpot), 1u);      // 2236 rows 261 against 252 in all)
-                                hist_add<kHist16>(hist, 2u, hist_bin_u32(e2e), 1u);
-                            }
-                        }
+                for (uint32_t i = 0; i < kPart; ++i) {
+                    const bool is_streamed = __builtin_amdgcn_inverse_ballot_w64(streamed[i]);
+                    const uint32_t arrival = (uint32_t)record[i], lens = (uint32_t)(record[i] >> 32);
+                    const uint32_t prompt = lens & 0xFFFFu, out = lens >> 16;
+                    if (kTabled) {
+                        prefill[i] = is_streamed ? cost_prefill[i] : 0u;
+                        tpot[i] = is_streamed ? cost_tpot[i] : 0u;
+                    } else {
+                        const four_words co = *reinterpret_cast<lds_four*>(is_streamed ? kind[i] : p.tab.n_kinds * 16u);
+                        prefill[i] = co.x + __umul24(co.y, prompt);                 // the host keeps all factors below 2^24
+                        tpot[i] = co.z + __umul24(co.w, (prompt + 1023u) >> 10);
                     }
-                    // queue the listed ones in arrival order: lanes in order, a lane's first request before its second
-                    const unsigned long long lm0 = listed[0], lm1 = listed[1];
-                    if ((lm0 | lm1) == 0ull) continue;
-                    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(lm1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm1,
-                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(lm0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lm0, q_n))));
-                    const uint32_t rl = (h * kHalf + g) * 2u * kWave + 2u * lane;
-                    const bool first_too = __builtin_amdgcn_inverse_ballot_w64(lm0);
-                    if (first_too) {
-                        atomicAdd(&cnt[id[2u * g]], 1u);
-                        queue[before] = (queued_t)(rl | (id[2u * g] << kIdShift));
+                    e2e[i] = prefill[i] + __umul24(out, tpot[i]);
+                    fin[i] = is_streamed ? arrival + e2e[i] : 0u;
+                    if (!kWithin) n_ok += (is_streamed && prefill[i] <= p.slo_ttft && tpot[i] <= p.slo_tpot) ? 1u : 0u;
+                    if (kHist && is_streamed) {                                     // (a test per value against least_us costs more than it
+                        hist_add<kHist16>(hist, 0u, hist_bin_u32(prefill[i]), 1u);  // saves: 3 rows of 30000 requests 46 against 37 us,
+                        hist_add<kHist16>(hist, 1u, hist_bin_u32(tpot[i]), 1u);     // 2236 rows 261 against 252 in all)
+                        hist_add<kHist16>(hist, 2u, hist_bin_u32(e2e[i]), 1u);
                     }
-                    if (__builtin_amdgcn_inverse_ballot_w64(lm1)) {
-                        atomicAdd(&cnt[id[2u * g + 1u]], 1u);
-                        queue[before + (first_too ? 1u : 0u)] = (queued_t)((rl + 1u) | (id[2u * g + 1u] << kIdShift));
-                    }
-                    q_n += (uint32_t)__popcll(lm0) + (uint32_t)__popcll(lm1);
                 }
+                static_assert(kPart == 4u, "four added up");
+                t_ttft += prefill[0] + prefill[1] + prefill[2] + prefill[3];
+                t_e2e += e2e[0] + e2e[1] + e2e[2] + e2e[3];
+                t_tpot += tpot[0] + tpot[1] + tpot[2] + tpot[3];
+                last_fin = max(max(max(last_fin, fin[0]), max(fin[1], fin[2])), fin[3]);
             }
-            s_ttft += t_ttft;
-            s_e2e += t_e2e;
-            s_tpot += t_tpot;
-            n_streamed += n - q_n;                                                  // (the rejected ones are taken off at the end)
-            if (!grouping) return;                                                  // q_n is 0 there
-            // runs: every replica's listed requests of the tile, starting on a multiple of 8 positions
-            const size_t tile_at = (size_t)cb * p.n_list_tiles + j;
-            uint32_t n_used = 0;
-            for (uint32_t base = 0; base < M; base += kWave) {
-                const uint32_t m = base + lane;
-                const uint32_t c = m < M ? cnt[m] : 0u;
-                const uint32_t room = (c + 7u) & ~7u;
-                const uint32_t upto = wave_inclusive_scan(room, lane);
-                if ((c & 7u) != 0u) {                                                // the run's last block: what no request takes is padding
-                    uint32_t pad = kPadding * 0x10001u;                             // (made here: kept from tile to tile it costs a spill)
-                    asm volatile("" : "+v"(pad));
-                    reinterpret_cast<uint4*>(list)[(n_used + upto - room + c) / 8u] = make_uint4(pad, pad, pad, pad);
-                }
-                if (m < M) {
-                    pos[m] = n_used + upto - room;
-                    cnt[m] = 0u;                                                    // for the wavefront's next tile
-                    p.desc[tile_at * M + m] = (c << 16) | (n_used + upto - room);
-                    if (kHist && c != 0u) {
-                        if (p.off_total != 0u) atomicAdd(&total[m], (c + 3u) & ~3u);
-                        else atomicAdd(&p.bin_base[(size_t)cb * (M + 1u) + m], (c + 3u) & ~3u);
-                    }
-                }
-                n_used += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-            }
-            // Rank among the queued requests of one replica, 64 queued requests at a time: every lane sets its bit
-            // in its replica's word and reads the word back (the LDS executes a wavefront's instructions in order),
-            // which tells it how many lanes before it name the same replica; the last of them moves the run's
-            // position on and clears the word.  (Ballots instead, as in k_list_candidates, take 5 % longer here, where the
-            // streamed requests keep the vector units busy.)
-            for (uint32_t d0 = 0; d0 < q_n; d0 += kWave) {
-                if (d0 + lane < q_n) {
-                    const uint32_t pair = queue[d0 + lane];
-                    const uint32_t k = pair >> kIdShift;
-                    atomicOr(&same[k], 1ull << lane);
-                    const unsigned long long peers = same[k];
-                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-                    const uint32_t n_peers = (uint32_t)__popcll(peers);
-                    const uint32_t at = pos[k];
-                    list[at + rank] = (uint16_t)((pair << kEntryShift) & ((kTile - 1u) << kEntryShift));
-                    if (rank + 1u == n_peers) {
-                        pos[k] = at + n_peers;
-                        same[k] = 0ull;
-                    }
-                }
-            }
-            // 16 bytes (8 positions) at a time
-            uint4* dst = reinterpret_cast<uint4*>(p.lists + tile_at * p.tile_cap);
-            for (uint32_t v = lane; v < n_used / 8u; v += kWave) dst[v] = reinterpret_cast<const uint4*>(list)[v];
+            atomicAdd(&sums[lane], (unsigned long long)t_e2e);                      // (in LDS they take no six registers)
+            atomicAdd(&sums[kWave + lane], (unsigned long long)t_ttft);
+            atomicAdd(&sums[2u * kWave + lane], (unsigned long long)t_tpot);
+            fetch_ids(at_next, row, j + kSplitWaves, lane, R, M);
+            n_streamed += n - n_listed;                                             // (the rejected ones are taken off at the end)
+            if (j >= p.n_list_tiles) return;                                        // nothing can be listed there
+            write_runs(p, (size_t)cb * p.n_list_tiles + j, lane, mine, at, place, [&](uint32_t m, uint32_t c) {
+                if (kHist && c != 0u) atomicAdd(&total[m], (c + 3u) & ~3u);
+            });
         };
-        fetch_keys(key_next, w);
+        fetch_ids(at_next, row, w, lane, R, M);
         for (uint32_t j = w; j < p.n_tiles; j += kSplitWaves) {
 #pragma unroll
-            for (uint32_t g = 0; g < kPairs; ++g) key[g] = key_next[g];
-            fetch_keys(key_next, j + kSplitWaves);
+            for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = min(at_next[s], M);
             if ((j + 1u) * kTile <= R) work_tile(std::true_type{}, j);
             else work_tile(std::false_type{}, j);
         }
 
         // the workgroup's totals
-        s_e2e = wave_sum_u64(s_e2e);
-        s_ttft = wave_sum_u64(s_ttft);
-        s_tpot = wave_sum_u64(s_tpot);
+        const unsigned long long s_e2e = wave_sum_u64(sums[lane]), s_ttft = wave_sum_u64(sums[kWave + lane]), s_tpot = wave_sum_u64(sums[2u * kWave + lane]);
         last_fin = wave_all_max(last_fin);
-        n_ok = p.all_within == 0u ? wave_sum_u32(n_ok) : n_streamed - n_rej;        // where all are within the objectives: as many as there are
+        n_ok = kWithin ? n_streamed - n_rej : wave_sum_u32(n_ok);
         if (lane == 0u) {
             atomicAdd(&acc64[0], s_e2e);
             atomicAdd(&acc64[1], s_ttft);
@@ -459,12 +481,7 @@ __global__ __launch_bounds__(kSplitThreads, 5) void k_split_candidates(SplitPara
             sp.flags = lazy ? kFlagLazy : (kHist ? 0u : kFlagNeedHist);
             p.part[cb] = sp;
         }
-        if (kHist && !lazy && w == 0u) {
-            if (p.off_total != 0u) place_bins(p, cb, [&](uint32_t m) { return total[m]; });
-            else place_bins(p, cb, [&](uint32_t m) {
-                return __hip_atomic_load(&p.bin_base[(size_t)cb * (M + 1u) + m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            });
-        }
+        if (kHist && !lazy && w == 0u) place_bins(p, cb, total);
         if (kHist && !lazy) {
             uint32_t* dst = p.hist + (size_t)cb * p.hist_words;
             for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) dst[i] = hist[i];
@@ -483,7 +500,6 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(S
     extern __shared__ __align__(16) unsigned char lds[];
     pending_clear_next(flags);
     if (split_nothing_pending(p)) return;
-    constexpr uint32_t kSteps = kTile / kWave;
     const uint32_t tid = threadIdx.x, w = wave_index(), n_waves = blockDim.x >> 6;
     uint32_t lane = tid & 63u;
     const uint32_t R = p.R, M = p.M;
@@ -491,13 +507,12 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(S
     uint32_t* rejected_of_row = reinterpret_cast<uint32_t*>(lds + p.off_acc);
     uint32_t* total_of = reinterpret_cast<uint32_t*>(lds + p.l_total);               // [M] listed requests of the row
     unsigned char* mine = lds + p.l_wave + w * p.l_wave_bytes;
-    uint32_t* run = reinterpret_cast<uint32_t*>(mine);                               // [M + 1] the run's length so far, then its first position
-    uint16_t* list = reinterpret_cast<uint16_t*>(mine + p.l_list) + 8u;              // [-8 .. tile_cap + 8)
+    init_runs(p, mine, tid & 63u);
+    const uint32_t runs_at = lds_address(mine), nowhere_at = runs_at + 4u * (M + (tid & 63u));
     for (uint32_t i = tid; i <= M; i += blockDim.x) end_of[i] = p.wide != 0u ? p.tab.range[i] : p.tab.range[i] & 0xFFFFu;
     uint32_t least_end = kNever;
     for (uint32_t m = lane; m < M; m += kWave) least_end = min(least_end, p.wide != 0u ? p.tab.range[m] : p.tab.range[m] & 0xFFFFu);
     least_end = kNever - wave_all_max(kNever - least_end);
-    for (uint32_t m = lane; m <= M; m += kWave) run[m] = m < M ? 0u : p.tile_cap + 1u;   // entry M: behind the list, and behind one place more
     for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) {
         if (!split_wanted(p, cb)) continue;                                          // the same record for every thread
         __syncthreads();                                                             // the last candidate's totals were read
@@ -506,89 +521,36 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(S
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
         uint32_t n_seen = 0, n_listed = 0, listed_here = 0;                          // the last: of replica `lane`
-        uint32_t at[kSteps], at_next[kSteps];                                        // the replica
-        auto fetch_ids = [&](uint32_t j) {
-            if (j * kTile + kTile <= R) {
-                const uint16_t* ids = row + j * kTile + lane;
-#pragma unroll
-                for (uint32_t s = 0; s < kSteps; ++s) at_next[s] = __builtin_nontemporal_load(ids + s * kWave);
-            } else {
-#pragma unroll
-                for (uint32_t s = 0; s < kSteps; ++s) {
-                    const uint32_t r = j * kTile + s * kWave + lane;
-                    at_next[s] = r < R ? (uint32_t)__builtin_nontemporal_load(row + r) : M;
-                }
-            }
-        };
-        fetch_ids(w);
+        uint32_t at[kTileSteps], at_next[kTileSteps];                                        // the replica
+        fetch_ids(at_next, row, w, lane, R, M);
         for (uint32_t j = w; j < p.n_tiles; j += n_waves) {
             const uint32_t r0 = j * kTile;
             n_seen += min(kTile, R - r0);
             asm volatile("" : "+v"(lane));                                           // positions are made here, not kept in registers
 #pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) at[s] = min(at_next[s], M);
-            fetch_ids(j + n_waves);
-            uint32_t place[kSteps];                                                  // in the run
+            for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = min(at_next[s], M);
+            fetch_ids(at_next, row, j + n_waves, lane, R, M);
+            uint32_t place[kTileSteps];                                                  // in the run
             if (r0 + kTile <= least_end) {                                           // all but unknown replicas': the next look-ups say nothing
 #pragma unroll
-                for (uint32_t s = 0; s < kSteps; ++s) place[s] = at[s] < M ? kNever : 0u;
+                for (uint32_t s = 0; s < kTileSteps; ++s) place[s] = at[s] < M ? kNever : 0u;
             } else {
 #pragma unroll
-                for (uint32_t s = 0; s < kSteps; ++s) place[s] = end_of[at[s]];      // entry M is 0
+                for (uint32_t s = 0; s < kTileSteps; ++s) place[s] = end_of[at[s]];      // entry M is 0
             }
 #pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) {
+            for (uint32_t s = 0; s < kTileSteps; ++s) {
                 const bool listed = r0 + s * kWave + lane < place[s];                // and below R
                 n_listed += (uint32_t)__popcll(__ballot(listed));
-                place[s] = 0u;
-                if (listed) place[s] = atomicAdd(&run[at[s]], 1u);
-                at[s] = listed ? at[s] : M;
+                at[s] = listed ? runs_at + 4u * at[s] : nowhere_at;
+                place[s] = p.tile_cap / 2u;
+                if (listed) place[s] = lds_add_rtn(at[s], 1u);
             }
             if (j >= p.n_list_tiles) continue;                                       // nothing is listed: no tile of the lists either
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            const size_t tile_at = (size_t)cb * p.n_list_tiles + j;
-            uint32_t total = 0;
-            for (uint32_t base = 0; base < M; base += kWave) {
-                const uint32_t m = base + lane;
-                const uint32_t c = m < M ? run[m] : 0u;
-                const uint32_t room = (c + 7u) & ~7u;
-                const uint32_t upto = wave_inclusive_scan(room, lane);
-                if ((c & 7u) != 0u) {                                                // the run's last block: what no request takes is padding
-                    uint32_t pad = kPadding * 0x10001u;
-                    asm volatile("" : "+v"(pad));
-                    reinterpret_cast<uint4*>(list)[(total + upto - room + c) / 8u] = make_uint4(pad, pad, pad, pad);
-                }
-                if (m < M) {
-                    run[m] = total + upto - room;
-                    if (base == 0u) listed_here += (c + 3u) & ~3u;
-                    else if (c != 0u) atomicAdd(&total_of[m], (c + 3u) & ~3u);
-                    p.desc[tile_at * M + m] = (c << 16) | (total + upto - room);
-                }
-                total += (uint32_t)__builtin_amdgcn_readlane((int)upto, 63);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            // (what is not listed goes to one place behind the runs)
-#pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) at[s] = run[at[s]];
-#pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) {
-                at[s] += place[s];
-                list[at[s]] = (uint16_t)((s * kWave + lane) << kEntryShift);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            uint32_t before[kSteps];
-#pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s) before[s] = list[at[s] - 1u];      // (of the first in a run, or of what is not listed, not looked at)
-            unsigned long long disorder = 0ull;
-#pragma unroll
-            for (uint32_t s = 0; s < kSteps; ++s)
-                disorder |= __ballot(before[s] > (s * kWave + lane) << kEntryShift) & __ballot(place[s] != 0u);
-            if (disorder != 0ull) sort_runs(list, run, p.desc + tile_at * M, M);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            for (uint32_t m = lane; m < M; m += kWave) run[m] = 0u;                  // for the wavefront's next tile
-            uint4* dst = reinterpret_cast<uint4*>(p.lists + tile_at * p.tile_cap);
-            for (uint32_t v = lane; v < total / 8u; v += kWave) dst[v] = reinterpret_cast<const uint4*>(list)[v];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            write_runs(p, (size_t)cb * p.n_list_tiles + j, lane, mine, at, place, [&](uint32_t m, uint32_t c) {
+                if (m < kWave) listed_here += (c + 3u) & ~3u;
+                else if (c != 0u) atomicAdd(&total_of[m], (c + 3u) & ~3u);
+            });
         }
         if (lane == 0u) atomicAdd(&rejected_of_row[0], n_seen - n_listed);           // wavefront totals
         if (listed_here != 0u) atomicAdd(&total_of[lane], listed_here);
@@ -599,7 +561,7 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(S
             sp.flags = sp.n_rej >= p.lazy_from ? kFlagLazy : kFlagNoStreamHist;
             p.part[cb] = sp;
         }
-        if (w == 0u && rejected_of_row[0] < p.lazy_from) place_bins(p, cb, [&](uint32_t m) { return total_of[m]; });
+        if (w == 0u && rejected_of_row[0] < p.lazy_from) place_bins(p, cb, total_of);
     }
 }
 

@@ -318,3 +318,32 @@ def test_switching_cost_models_on_one_workload():
             assert_same(run(), want, f"tables, two slots (round {round_})")
     finally:
         binding.ap_workload_destroy(handle)
+
+
+@pytest.mark.parametrize("kinds", [1, 31, 32, 33, 64, 200])
+@pytest.mark.parametrize("R", [1023, 1024, 1025, 4 * 1024 + 65])
+@pytest.mark.parametrize("tabled", [False, True])
+def test_many_kinds_of_replica(kinds, R, tabled):
+    """A replica's kind lies in two parts beside the positions that bound its list and its service, in one look-up word: kinds on either side
+    of where the second part begins, tiles with one request more or less, requests before, at and behind a window's edges, objectives that some
+    requests miss by time per token alone."""
+    rng = np.random.default_rng(kinds + R)
+    M = max(kinds, 5)
+    coef = [(2000 + 7 * (m % kinds), 3 + (m % kinds) % 5, 25, 5 + m % kinds) for m in range(M)]
+    arrival = np.cumsum(rng.integers(0, 30_000, R)).astype(np.uint64)
+    edge = arrival[rng.integers(0, R, size=(M, 2))]
+    t_on = np.where(np.arange(M) % 4 == 0, 0, edge.min(axis=1)).astype(np.uint64)
+    t_off = np.where(np.arange(M) % 4 < 2, np.uint64(traces.UINT64_MAX), edge.max(axis=1) + np.uint64(1))
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), coef, t_on, t_off, B=16, slo_tpot_us=60)
+    rows = rng.integers(0, M, size=(9, R)).astype(np.uint16)
+    rows[1] = np.where(rng.random(R) < 0.3, M, rows[1])
+    rows[2] = rows[2] // 4 * 4
+    tables, want = None, oracle_for(tr)
+    if tabled:
+        tables = (np.arange(M, dtype=np.uint32) % kinds, rng.integers(0, 9000, (kinds, R)).astype(np.uint32), rng.integers(0, 90, (kinds, R)).astype(np.uint32))
+        want.set_cost_tables(*tables)
+    with GpuWorkload(tr, tables=tables) as g:
+        assert g.route(600)["lists"] == 2
+        got = g.eval(np.resize(rows, (600, R)))
+    assert_same(got[:9], want.eval_batch(rows, nthreads=8), f"kinds={kinds} R={R} tabled={tabled}")
+    assert (got == got[np.arange(600) % 9]).all()
