@@ -347,3 +347,28 @@ def test_many_kinds_of_replica(kinds, R, tabled):
         got = g.eval(np.resize(rows, (600, R)))
     assert_same(got[:9], want.eval_batch(rows, nthreads=8), f"kinds={kinds} R={R} tabled={tabled}")
     assert (got == got[np.arange(600) % 9]).all()
+
+
+@pytest.mark.parametrize("quiet,lists", [(40, 1), (600, 2)])
+@pytest.mark.parametrize("tabled", [False, True])
+def test_a_quiet_end_too_short_to_be_streamed(quiet, lists, tabled):
+    """A trace that is too busy to stream anything but its last requests: listed with the others where they are few, streamed where they
+    are not, behind a backlog that leaves slots taken in some rows and replicas that come and go."""
+    rng = np.random.default_rng(quiet)
+    R, M, B = 3000, 12, 8
+    gap = np.where(np.arange(R) < R - quiet, 300, 150_000)
+    arrival = np.cumsum(rng.integers(0, 2 * gap)).astype(np.uint64)
+    t_on = np.where(np.arange(M) % 3 == 0, int(arrival[R // 3]), 0).astype(np.uint64)
+    t_off = np.where(np.arange(M) % 4 == 1, int(arrival[R - quiet // 2]), traces.UINT64_MAX).astype(np.uint64)
+    tr = traces.custom_trace(arrival, rng.integers(1, 4000, R), rng.integers(1, 200, R), [(2000, 3, 25, 5), (1200, 2, 15, 3)] * (M // 2), t_on, t_off, B=B)
+    rows = rng.integers(0, M, size=(40, R)).astype(np.uint16)
+    rows[1], rows[2] = 1, M
+    rows[3, R - quiet:] = 4
+    tables, want = None, oracle_for(tr)
+    if tabled:
+        tables = (np.arange(M, dtype=np.uint32) % 2, rng.integers(0, 9000, (2, R)).astype(np.uint32), rng.integers(0, 60, (2, R)).astype(np.uint32))
+        want.set_cost_tables(*tables)
+    with GpuWorkload(tr, tables=tables) as g:
+        assert g.route(600)["lists"] == lists
+        got = g.eval(np.resize(rows, (600, R)))
+    assert_same(got[:40], want.eval_batch(rows, nthreads=8), f"quiet={quiet} tabled={tabled}")
