@@ -112,10 +112,11 @@ struct RoofBuffers {
 struct SplitPlan {
     bool short_chain = false;         // calls of few rows are left to the fused replay
     bool all_within = false;          // no request's prefill or time per token can exceed the objectives
-    uint32_t list_waves_most = 0;     // k_list_candidates: wavefronts of a workgroup that LDS has room for
+    uint32_t list_waves_most = 0, split_waves_most[2] = {};   // wavefronts of a workgroup that LDS has room for: k_list_candidates, k_split_candidates
+                                      //   without and with histograms
+    uint32_t off_wave[2] = {};        // where the latter's areas begin
     bool expect_lazy = false;         // stream without histograms first
     uint32_t batch = 0;               // candidates per batch (what the scratch area holds)
-    uint32_t lds_bytes = 0, lds_bytes_hist = 0;
     unsigned char* tables = nullptr;  // ranges, kinds, coefficients, queues, order
     size_t tables_bytes = 0;
     size_t o_lists = 0, o_bins = 0, o_desc = 0, o_part = 0, o_hist = 0, o_bin_base = 0, o_bin_count = 0;   // where its parts lie in the scratch area
@@ -323,20 +324,24 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         // Where something is streamed: first without histograms if the candidates are expected to be settled by penalty; then
         // with histograms, for every candidate or for those the first pass marked.
         const bool plain_first = plan.expect_lazy;
-        if (sp.any_streamed == 0u)
-        {
-            // A workgroup per row: four wavefronts, up to eight where rows leave the chip less than four per SIMD.  With more wavefronts than
-            // that the LDS is what they wait for: 1024 rows of 131072 requests on 128 replicas 172 us with four wavefronts a row, 179 with six.
-            const uint32_t waves = std::max(kSplitWaves, std::min(std::min(plan.list_waves_most, sp.n_tiles), w->n_cu * 16u / n));
+        // A workgroup per row: four wavefronts, or eight where rows leave the chip less than two per SIMD (300 rows of 20001 requests on 61
+        // replicas 1.2 to 1.3 times less).  Not more beyond: LDS is what they wait for, and a row's tiles take as many turns
+        // with five wavefronts as with four (1024 rows of 131072 on 128, 172 us with four, 179 with six; 700 rows of 16384 on 64, 52 and 63 with five).
+        auto waves_of = [&](uint32_t most) { return n <= 2u * w->n_cu ? std::max(kBuildMinWaves, std::min(most, sp.n_tiles)) : kBuildMinWaves; };
+        auto launch_split_kernel = [&](uint32_t hist_mode, uint32_t blocks, uint32_t only_flagged) {
+            const uint32_t h = hist_mode != 0u ? 1u : 0u, waves = waves_of(plan.split_waves_most[h]);
+            sp.off_wave = plan.off_wave[h];
+            hipLaunchKernelGGL(split_kernel(hist_mode, w->tabled, plan.all_within), dim3(blocks), dim3(waves * kWave),
+                               sp.off_wave + waves * sp.wave_bytes, stream, sp, d_assign, c0, n, only_flagged, flags);
+        };
+        if (sp.any_streamed == 0u) {
+            const uint32_t waves = waves_of(plan.list_waves_most);
             hipLaunchKernelGGL(k_list_candidates, dim3(grid), dim3(waves * kWave), sp.l_wave + waves * sp.l_wave_bytes, stream, sp, d_assign, c0, n, flags);
+        } else {
+            if (plain_first) launch_split_kernel(0u, grid, 0u);
+            // (behind a plain pass: usually nothing to do, so few workgroups)
+            launch_split_kernel(sp.wide ? 2u : 1u, plain_first ? std::min(n, w->n_cu * 3u) : grid, plain_first ? 1u : 0u);
         }
-        else if (plain_first)
-            hipLaunchKernelGGL(split_kernel(0u, w->tabled, plan.all_within), dim3(grid), dim3(kSplitThreads), plan.lds_bytes, stream,
-                               sp, d_assign, c0, n, 0u, flags);
-        if (sp.any_streamed != 0u)              // (behind a plain pass: usually nothing to do, so few workgroups)
-            hipLaunchKernelGGL(split_kernel(sp.wide ? 2u : 1u, w->tabled, plan.all_within),
-                               dim3(plain_first ? std::min(n, w->n_cu * 3u) : grid), dim3(kSplitThreads),
-                               plan.lds_bytes_hist, stream, sp, d_assign, c0, n, plain_first ? 1u : 0u, flags);
         // the list replay: where most candidates are settled by penalty, those go through the variant that leaves no bins, and
         // the wavefronts of the other variant find the few that remain
         if (sp.n_queues != 0u) {
@@ -789,37 +794,38 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.off_range_off = off; off += wide ? align_up((M + 1u) * 4u, 16u) : 0u;
     sp.off_kind = off;  off += align_up((M + 1u) * 4u, 16u);
     sp.off_acc = off;   off += 64u;
-    sp.off_wave = off;
-    sp.w_tile = align_up(runs_bytes(M, sp.tile_cap), 16u);
-    sp.w_sums = sp.w_tile + align_up((M + 1u) * 4u, 16u);
-    const uint32_t wb = sp.w_sums + 3u * kWave * 8u;
-    sp.wave_bytes = wb;
-    off += kSplitWaves * wb;
-    sp.off_hist = off;
-    sp.l_total = sp.off_wave;
+    const uint32_t before_waves = off;
+    sp.l_total = off;
     sp.l_wave = sp.l_total + align_up(M * 4u, 16u);
     sp.l_wave_bytes = align_up(runs_bytes(M, sp.tile_cap), 16u);
+    // the wavefronts' areas come last, behind the histograms and totals where there are some
+    sp.off_hist = off;
+    sp.off_total = off + hist_bytes;
+    sp.w_tile = sp.l_wave_bytes;
+    sp.w_sums = sp.w_tile + align_up((M + 1u) * 4u, 16u);
+    sp.wave_bytes = sp.w_sums + 3u * kWave * 8u;
+    plan.off_wave[0] = off;
+    plan.off_wave[1] = sp.off_total + align_up(M * 4u, 16u);
     int lds_cap = 0;
     if (hipDeviceGetAttribute(&lds_cap, hipDeviceAttributeMaxSharedMemoryPerBlock, w->device) != hipSuccess) return device_error();
-    plan.list_waves_most = std::min(kBuildMaxWaves, ((uint32_t)lds_cap - std::min((uint32_t)lds_cap, sp.l_wave)) / sp.l_wave_bytes);
+    auto waves_most = [&](uint32_t fixed, uint32_t per_wave) { return std::min(kBuildMaxWaves, ((uint32_t)lds_cap - std::min((uint32_t)lds_cap, fixed)) / per_wave); };
+    plan.list_waves_most = waves_most(sp.l_wave, sp.l_wave_bytes);
+    for (uint32_t h = 0; h < 2u; ++h) plan.split_waves_most[h] = waves_most(plan.off_wave[h], sp.wave_bytes);
     // A replica table that large stays with the general replay.  (The line is that of a streaming kernel which held 28 bytes a replica and
     // six a request of a tile per wavefront; above it the lists would fit up to about 900 replicas, and were not measured.)
     const uint32_t held = 2u * align_up(M * 4u, 16u) + kTile * (M <= 64u ? 2u : 4u) + align_up(sp.tile_cap * 2u, 16u) + align_up(M * 8u, 16u) +
                           align_up((M + 1u) * 4u, 16u);
-    if (sp.off_wave - 16u + kSplitWaves * held + hist_bytes > (uint32_t)lds_cap) return AP_OK;
-    plan.lds_bytes = off;
-    plan.lds_bytes_hist = off + hist_bytes;
-    sp.off_total = off + hist_bytes;
-    plan.lds_bytes_hist += align_up(M * 4u, 16u);
+    if (before_waves - 16u + kBuildMinWaves * held + hist_bytes > (uint32_t)lds_cap ||
+        std::min(plan.list_waves_most, std::min(plan.split_waves_most[0], plan.split_waves_most[1])) < kBuildMinWaves) return AP_OK;
     if (!tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(0u, tabled, plan.all_within))) ||
         !tables_at_lds_zero(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, tabled, plan.all_within))))
         return device_error();
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_list_candidates), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(sp.l_wave + plan.list_waves_most * sp.l_wave_bytes)) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(0u, tabled, plan.all_within)),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)off) != hipSuccess ||
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(plan.off_wave[0] + plan.split_waves_most[0] * sp.wave_bytes)) != hipSuccess ||
         hipFuncSetAttribute(reinterpret_cast<const void*>(split_kernel(wide ? 2u : 1u, tabled, plan.all_within)),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)plan.lds_bytes_hist) != hipSuccess) {
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(plan.off_wave[1] + plan.split_waves_most[1] * sp.wave_bytes)) != hipSuccess) {
         (void)hipGetLastError();
         return device_error();
     }

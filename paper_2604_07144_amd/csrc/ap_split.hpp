@@ -45,9 +45,7 @@ namespace {
 // and carries kFlagLazy; the others keep histograms: the streamed requests are counted in LDS while the row is
 // read (and parked in device memory), the list replay leaves, queue by queue, the bins of the listed requests that any p99 value can
 // depend on, and k_merge_candidates adds the two up.
-constexpr uint32_t kSplitWaves = 4;
-constexpr uint32_t kSplitThreads = kSplitWaves * kWave;
-constexpr uint32_t kBuildMaxWaves = 8;            // of a workgroup of k_list_candidates
+constexpr uint32_t kBuildMinWaves = 4, kBuildMaxWaves = 8;   // of a workgroup of the kernels that build the lists
 constexpr uint32_t kTile = 1024;                  // requests per tile: a list position fits 10 bits
 constexpr uint32_t kTileSteps = kTile / kWave;
 constexpr uint32_t kFlagNeedHist = 1u;            // streamed without histograms, but they are needed: stream again
@@ -269,7 +267,7 @@ __device__ __forceinline__ void place_bins(const SplitParams& p, uint32_t cb, co
 // kTabled: prefill time and time per token are read from the tables (one 8-byte load per request, issued with the
 // table look-ups of the quarter tile) instead of being evaluated from a kind's coefficients.
 template <uint32_t kHistMode, bool kTabled, bool kWithin>
-__global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_split_candidates(SplitParams p, const uint16_t* __restrict__ assign,
+__global__ __launch_bounds__(kBuildMaxWaves * kWave, kHistMode == 0u ? 5 : 4) void k_split_candidates(SplitParams p, const uint16_t* __restrict__ assign,
                                                                     uint32_t c0, uint32_t n_cand, uint32_t only_flagged,
                                                                     PendingWord flags) {
     extern __shared__ __align__(16) unsigned char lds[];
@@ -282,7 +280,7 @@ __global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_spli
     uint4* coef_of = reinterpret_cast<uint4*>(lds);
     unsigned long long* acc64 = reinterpret_cast<unsigned long long*>(lds + p.off_acc);
     uint32_t* acc32 = reinterpret_cast<uint32_t*>(lds + p.off_acc + 24);    // latest finish, within objectives, rejected
-    const uint32_t tid = threadIdx.x, w = wave_index();
+    const uint32_t tid = threadIdx.x, w = wave_index(), n_waves = blockDim.x >> 6;
     uint32_t lane = tid & 63u;
     unsigned char* mine = lds + p.off_wave + w * p.wave_bytes;
     unsigned long long* sums = reinterpret_cast<unsigned long long*>(mine + p.w_sums);   // [3][64] per lane: e2e, ttft, tpot
@@ -301,12 +299,12 @@ __global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_spli
         for (uint32_t cb = blockIdx.x; cb < n_cand; cb += gridDim.x) any = any || (p.part[cb].flags & kFlagNeedHist) != 0u;
         if (!any) return;                                                           // the same words for every thread
     }
-    for (uint32_t i = tid; i <= M; i += kSplitThreads) {
+    for (uint32_t i = tid; i <= M; i += blockDim.x) {
         range_of[i] = p.tab.range[i];
         if (p.wide != 0u) range_off_of[i] = p.tab.range_off[i];
         kind_of[i] = p.tab.kind[i];
     }
-    for (uint32_t i = tid; i <= p.tab.n_kinds; i += kSplitThreads) coef_of[i] = i < p.tab.n_kinds ? p.tab.coef[i] : make_uint4(0u, 0u, 0u, 0u);
+    for (uint32_t i = tid; i <= p.tab.n_kinds; i += blockDim.x) coef_of[i] = i < p.tab.n_kinds ? p.tab.coef[i] : make_uint4(0u, 0u, 0u, 0u);
     init_runs(p, mine, lane);
     const uint32_t runs_at = lds_address(mine), nowhere_at = runs_at + 4u * (M + (tid & 63u));
 
@@ -314,8 +312,8 @@ __global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_spli
         if ((only_flagged && (p.part[cb].flags & kFlagNeedHist) == 0u) || (kHist && !split_wanted(p, cb))) continue;   // the same for every thread
         __syncthreads();                                                            // the last candidate's totals were read
         if (kHist) {
-            for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) hist[i] = 0u;
-            for (uint32_t m = tid; m < M; m += kSplitThreads) total[m] = 0u;
+            for (uint32_t i = tid; i < p.hist_words; i += blockDim.x) hist[i] = 0u;
+            for (uint32_t m = tid; m < M; m += blockDim.x) total[m] = 0u;
         }
         if (tid < 10u) reinterpret_cast<uint32_t*>(acc64)[tid] = 0u;
         __syncthreads();
@@ -440,7 +438,7 @@ __global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_spli
             atomicAdd(&sums[lane], (unsigned long long)t_e2e);                      // (in LDS they take no six registers)
             atomicAdd(&sums[kWave + lane], (unsigned long long)t_ttft);
             atomicAdd(&sums[2u * kWave + lane], (unsigned long long)t_tpot);
-            fetch_ids(at_next, row, j + kSplitWaves, lane, R, M);
+            fetch_ids(at_next, row, j + n_waves, lane, R, M);
             n_streamed += n - n_listed;                                             // (the rejected ones are taken off at the end)
             if (j >= p.n_list_tiles) return;                                        // nothing can be listed there
             write_runs(p, (size_t)cb * p.n_list_tiles + j, lane, mine, at, place, [&](uint32_t m, uint32_t c) {
@@ -448,7 +446,7 @@ __global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_spli
             });
         };
         fetch_ids(at_next, row, w, lane, R, M);
-        for (uint32_t j = w; j < p.n_tiles; j += kSplitWaves) {
+        for (uint32_t j = w; j < p.n_tiles; j += n_waves) {
 #pragma unroll
             for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = min(at_next[s], M);
             if ((j + 1u) * kTile <= R) work_tile(std::true_type{}, j);
@@ -484,7 +482,7 @@ __global__ __launch_bounds__(kSplitThreads, kHistMode == 0u ? 5 : 4) void k_spli
         if (kHist && !lazy && w == 0u) place_bins(p, cb, total);
         if (kHist && !lazy) {
             uint32_t* dst = p.hist + (size_t)cb * p.hist_words;
-            for (uint32_t i = tid; i < p.hist_words; i += kSplitThreads) dst[i] = hist[i];
+            for (uint32_t i = tid; i < p.hist_words; i += blockDim.x) dst[i] = hist[i];
         }
     }
 }
@@ -842,6 +840,10 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                 // No start is later than s[3], or ready time.  Where some lane's four may start too late, those of them that do are made
                 // padding first: which they are comes from the four earliest slots.
                 if (__ballot(s[kSlots > 3u ? 3u : 0u] >= closes) != 0ull) {
+                    if (__ballot(open && earliest() < q.t_off) == 0ull) {           // nothing starts any more
+                        n_rej += count - min(count, k0);
+                        break;
+                    }
                     uint32_t early[4];
 #pragma unroll
                     for (uint32_t i = 0; i < 4u; ++i) early[i] = s[i];
