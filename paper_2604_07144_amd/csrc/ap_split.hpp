@@ -603,16 +603,16 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // replicas of 64 slots that come and go 380 and 300 us, 4096 of them crowded 430 and 310; 1024 of 131072 on 128 crowded 665 and 550; calls of
 // 4096 rows of 16384 on 48 that come and go, half their slots in use: 16 slots 233 to 229 us, 24 265 to 249, 32 280 to 260, 48 320 to 275, 64 345 to 280.
 // Of the rest of a step, 36 operations were 22 when sums of four came in place of a 64-bit sum each, the latest finish from the slot times,
-// and served or not from the record: the same three kernels 300, 310 and 550 to 292, 296 and 540 us.
+// and served or not from the record: the same three kernels 300, 310 and 550 to 292, 296 and 540 us.  A wavefront of which no
+// queue has a slot that comes free in time leaves the tile (512 rows of 800 that crowd one of 500 replicas of 8 slots 62 to 8 us).
 // Loads run ahead: a lane's descriptors a stage, its next block of entries a block, also into the next tile, and the
 // records of a stage four per thread at a time.  A register whose
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as vectors
 // and the empty asm where they are waited for.  Blocks of eight come too late for queues of few slots: a wavefront by itself takes 200 ns
 // a request there, a line from HBM and the stores before it more than eight of those (400 rows of 16384 requests on one of 2 replicas of
 // 8 slots 3801 us before anything ran ahead, 3842 with blocks of eight, 3356 with sixteen; one row on both of 2, 1807, 1906 and 1757;
-// 100 rows of 131072 on 21 of 128 replicas of 64 slots 3680, 3340 and 3280).  Only without bins and with more than 48 slots it is eight:
-// sixteen take 139 registers, which leave room for three wavefronts per SIMD instead of four (8192 rows of 32768 requests on 64
-// replicas that come and go 807 against 799 us).  With more than 48 slots a pair of steps that
+// 100 rows of 131072 on 21 of 128 replicas of 64 slots 3680, 3340 and 3280; eight also where registers then left room for a wavefront more,
+// 8192 rows of 32768 on 64 that come and go 293 and now 289 in here).  With more than 48 slots a pair of steps that
 // no lane needs is left out; up to there the branch costs more (crowds of one queue 6 % at 8 and 16 slots, 4 % at 24 to 48).
 // Where all lists are as long as the trace, a few neighbouring replicas share an XCD, whose L2 then holds their runs once.
 // A queue's words for the histograms follow one another (place_bins), four requests at a time where one of the four has a value
@@ -640,9 +640,10 @@ __device__ __forceinline__ uint32_t bin_above(uint32_t v, uint32_t least_us, uin
     return v >= least_us ? hist_bin_u32(v) - least_bin + 1u : 0u;
 }
 
-// hi:lo += v in two instructions (the compiler's 64-bit add takes a register for the upper half of v as well)
+// hi:lo += v in two instructions (the compiler's 64-bit add takes a register for the upper half of v as well), the two wait states that
+// the compiler keeps between a vector instruction that writes vcc and one that reads it among them
 __device__ __forceinline__ void add_wide(uint32_t& lo, uint32_t& hi, uint32_t v) {
-    asm("v_add_co_u32 %0, vcc, %0, %2\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc" : "+v"(lo), "+v"(hi) : "v"(v) : "vcc");
+    asm("v_add_co_u32 %0, vcc, %0, %2\n\ts_nop 1\n\tv_addc_co_u32 %1, vcc, 0, %1, vcc" : "+v"(lo), "+v"(hi) : "v"(v) : "vcc");
 }
 
 // Merge of two ascending sequences by Batcher's odd-even network (K. E. Batcher, Sorting networks and their applications, 1968), in place:
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 
     constexpr uint32_t kFront = kSlots >= 48u ? 16u : kSlots >= 16u ? 8u : kSlots;  // a power of two where there is a rest
     constexpr bool kPairs = kSlots > 48u;                                           // two steps are worth a branch
-    constexpr uint32_t kHalves = kSlots > 48u && kBins_ == 0u ? 1u : 2u, kBlock = 8u * kHalves;   // entries ahead
+    constexpr uint32_t kHalves = 2u, kBlock = 8u * kHalves;                         // entries ahead
     uint32_t s[kSlots];
 #pragma unroll
     for (uint32_t i = 0; i < kSlots; ++i) s[i] = i < p.B ? 0u : kNever;
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
 #pragma unroll
                     for (uint32_t i = 0; i < 4u * kHalves; ++i) e[i] = k0 + (i < 4u ? 0u : 8u) < count ? e_next[i / 4u][i % 4u] : kPadding * 0x10001u;
                     // (short traces have no next tile: 106 to 92 us for 512 rows of 800 requests on 755 replicas)
-                    if (kHalves == 1u || !last || j + 1u < n_t)
+                    if (!last || j + 1u < n_t)
                         request_block(!last ? d : j == j0 ? d_here[1] : d_next[0], last ? j + 1u : j, last ? 0u : k0 / kBlock + 1u);
                     if (k0 == 0u && j == j0) {
                         d_next[0] = desc_of(j0 + 2u);
