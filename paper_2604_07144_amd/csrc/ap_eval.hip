@@ -755,7 +755,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return queue[x].i_list > queue[y].i_list; });
 
     SplitParams sp{};
-    sp.R = R; sp.M = M; sp.B = B; sp.key_bits = w->params.key_bits;
+    sp.R = R; sp.M = M; sp.B = B;
     sp.n_tiles = (R + kTile - 1u) / kTile;
     sp.n_list_tiles = (longest_list + kTile - 1u) / kTile;
     sp.tile_cap = align_up(std::min(kTile, R) + 7u * std::min(M, std::min(kTile, R)), 8u);

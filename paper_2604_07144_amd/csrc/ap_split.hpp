@@ -51,9 +51,9 @@ constexpr uint32_t kTileSteps = kTile / kWave;
 constexpr uint32_t kFlagNeedHist = 1u;            // streamed without histograms, but they are needed: stream again
 constexpr uint32_t kFlagFallback = 2u;            // the listed part left too many slots taken: general replay
 constexpr uint32_t kFlagLazy = 4u;                // the p99 values are the penalty latency
+constexpr uint32_t kFlagNoStreamHist = 8u;        // histograms needed, and no request of the candidate was streamed
 constexpr uint32_t kTpotWithin = 1u;              // no request's time per token can exceed the objective
 constexpr uint32_t kSumsFit = 2u;                 // four latencies (e2e) add up to less than 2^32
-constexpr uint32_t kFlagNoStreamHist = 8u;        // histograms needed, and no request of the candidate was streamed
 // A list entry is 16 times the request's index in its tile: the list replay reads 16-byte records.
 constexpr uint32_t kEntryShift = 4;
 constexpr uint32_t kPadding = kTile << kEntryShift;   // the entry of a run's padding: names a record that never starts
@@ -115,7 +115,7 @@ struct SplitParams {
     uint32_t hist_words;                          // 3 * kBins / 2 (16-bit counts, R < 65536) or 3 * kBins
     uint32_t wide;                                // R >= 65536: two range words per replica
     uint32_t any_streamed;                        // some replica has a streamed part
-    uint32_t R, M, B, key_bits;
+    uint32_t R, M, B;
     uint32_t n_tiles, n_list_tiles, tile_cap, n_queues;
     uint32_t even_lists;                          // every replica has a list, and all are equally long
     uint32_t slo_ttft, slo_tpot;
