@@ -688,7 +688,6 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     uint32_t longest_list = 0;
     uint64_t expect_rejected = 0;
     bool any_streamed = false;
-    uint64_t n_streamed = 0;
     std::vector<uint32_t> i_list_of(M), i_off_of(M), kind_index(M);
     for (uint32_t m = 0; m < M; ++m) {
         const DevReplica& d = dev[m];
@@ -715,17 +714,32 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
             i_list = (uint32_t)(std::lower_bound(arr, arr + R, (uint32_t)std::min<uint64_t>(t_target, kNever)) - arr);
         }
         i_list = std::min(std::max(i_list, i_calm), i_off);
-        n_streamed += i_off - i_list;
         i_list_of[m] = i_list;
         i_off_of[m] = i_off;
         kind_index[m] = (uint32_t)ki;
     }
+    const uint32_t hist_words = wide ? 3u * kBins : 3u * kBins / 2u, hist_bytes = hist_words * 4u;
+    const uint32_t tile_cap = align_up(std::min(kTile, R) + 7u * std::min(M, std::min(kTile, R)), 8u);
+    const uint32_t least_tpot_bin = std::min(least_bin[1], w->params.penalty_bin);
+    const bool wide_bins = ap_hist_bin(longest_tpot) >= least_tpot_bin + kTpotSpan;
+    // scratch of a candidate: lists, run descriptors, a partial record, histograms.  A trace so long that 64 candidates' lists take over
+    // 8 GiB stays with the general replay.
+    auto bytes_per_candidate = [&](uint32_t longest) {
+        const size_t tiles = (longest + kTile - 1u) / kTile;
+        return tiles * tile_cap * (2u + (wide_bins ? 8u : 4u)) + tiles * M * 4u + sizeof(SplitPartial) + hist_bytes + 2u * (M + 1u) * 4u;
+    };
+    const size_t most_per_candidate = ((size_t)8 << 30) / 64u;
     // Where next to nothing would be streamed, list that too: k_list_candidates takes half of k_split_candidates' time, and no row is handed back
     // for what its listed part leaves taken.  Calls of a busy beginning and a quiet end, streamed and listed: the last 2 % quiet, 3355 rows
     // 739 and 657 us (20000 requests on 50 replicas), with tables 802 (rows handed back) and 566, 200 rows 228 and 214; 5 % 718 and 653, 200 rows
     // 223 and 215; 10 % 691 and 646, 200 rows 210 and 214; 20 % 643 and 645, 200 rows 191 and 212; 30 % 580 and 660, 174 and 210.  The line
-    // is where a call of few rows loses nothing either.
-    const bool list_all = n_streamed * 14u < (uint64_t)R * M;
+    // is where a call of few rows loses nothing either, and it is asked of every replica by itself: a row that crowds one waits for its list,
+    // request after request.  With the line on the trace as a whole, 64 rows of 32768 requests on 4 replicas that stay while 60 are never there
+    // took 2.2 ms (54 us with these streamed), 7.5 ms on one of them (64 us); even rows of 63 replicas that come at the end and one that stays
+    // would gain by it, 457 against 519 us.
+    bool list_all = true;
+    for (uint32_t m = 0; m < M; ++m) list_all = list_all && (i_off_of[m] - i_list_of[m]) * 14ull <= i_off_of[m];
+    list_all = list_all && bytes_per_candidate(*std::max_element(i_off_of.begin(), i_off_of.end())) <= most_per_candidate;
     for (uint32_t m = 0; m < M; ++m) {
         const DevReplica& d = dev[m];
         const uint32_t i_list = list_all ? i_off_of[m] : i_list_of[m], i_off = i_off_of[m], ki = kind_index[m];
@@ -758,7 +772,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     sp.R = R; sp.M = M; sp.B = B;
     sp.n_tiles = (R + kTile - 1u) / kTile;
     sp.n_list_tiles = (longest_list + kTile - 1u) / kTile;
-    sp.tile_cap = align_up(std::min(kTile, R) + 7u * std::min(M, std::min(kTile, R)), 8u);
+    sp.tile_cap = tile_cap;
     sp.n_queues = (uint32_t)order.size();
     sp.even_lists = sp.n_queues == M && queue[order.front()].i_list == queue[order.back()].i_list ? 1u : 0u;
     sp.slo_ttft = w->params.slo_ttft;
@@ -783,13 +797,12 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         sp.least_bin[h] = std::min(least_bin[h], w->params.penalty_bin);
         sp.least_us[h] = (uint32_t)std::min<uint64_t>(ap_hist_lower(sp.least_bin[h]), kNever);
     }
-    sp.wide_bins = ap_hist_bin(longest_tpot) >= sp.least_bin[1] + kTpotSpan ? 1u : 0u;
+    sp.wide_bins = wide_bins ? 1u : 0u;
     sp.wide = wide ? 1u : 0u;
     sp.any_streamed = any_streamed ? 1u : 0u;
-    sp.hist_words = wide ? 3u * kBins : 3u * kBins / 2u;
+    sp.hist_words = hist_words;
     // LDS of the streaming kernel
     uint32_t off = ((uint32_t)kinds.size() + 1u) * 16u;      // the coefficients come first, and 0 behind them
-    const uint32_t hist_bytes = sp.hist_words * 4u;
     sp.off_range = off; off += align_up((M + 1u) * 4u, 16u);
     sp.off_range_off = off; off += wide ? align_up((M + 1u) * 4u, 16u) : 0u;
     sp.off_kind = off;  off += align_up((M + 1u) * 4u, 16u);
@@ -830,11 +843,8 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         return device_error();
     }
 
-    // scratch for one batch of candidates: lists, run descriptors, partial records, histograms
-    const size_t bins_bytes = sp.wide_bins ? 8u : 4u;
-    const size_t per_cand = (size_t)sp.n_list_tiles * sp.tile_cap * (2u + bins_bytes) + (size_t)sp.n_list_tiles * M * 4u +
-                            sizeof(SplitPartial) + hist_bytes + 2u * (M + 1u) * 4u;
-    if (per_cand > ((size_t)8 << 30) / 64u) return AP_OK;       // a trace so long that 64 candidates' lists take over 8 GiB
+    const size_t bins_bytes = wide_bins ? 8u : 4u, per_cand = bytes_per_candidate(longest_list);
+    if (per_cand > most_per_candidate) return AP_OK;
     // (2 of every 6 or 10 bytes are the lists themselves, so those of a batch stay below 2^32 bytes, which the list replay relies on)
     uint32_t batch = (uint32_t)std::min<size_t>(16384u, std::max<size_t>(64u, ((size_t)4 << 30) / per_cand));
     batch = batch / 64u * 64u;

@@ -372,3 +372,32 @@ def test_a_quiet_end_too_short_to_be_streamed(quiet, lists, tabled):
         assert g.route(600)["lists"] == lists
         got = g.eval(np.resize(rows, (600, R)))
     assert_same(got[:40], want.eval_batch(rows, nthreads=8), f"quiet={quiet} tabled={tabled}")
+
+
+@pytest.mark.parametrize("kind,lists", [("empty", 2), ("closed early", 2), ("others late", 2), ("short windows", 2), ("quiet end", 1)])
+def test_streamed_parts_that_are_lists_of_their_own(kind, lists):
+    """Streamed parts are listed too only where that makes no replica's list much longer: not where most replicas are away, or have lists for
+    reasons of their own, while a few are there all the time and nobody waits on them (a row that crowds one of those would be replayed
+    request after request)."""
+    rng = np.random.default_rng(len(kind))
+    R, M, B, stay = 3000, 40, 16, 2
+    gap = np.full(R, 2000) if kind != "quiet end" else np.where(np.arange(R) < R - 60, 60, 60_000)
+    arrival = np.cumsum(rng.integers(0, 2 * gap)).astype(np.uint64)
+    last = int(arrival[-1])
+    t_on, t_off = np.zeros(M, np.uint64), np.full(M, traces.UINT64_MAX, np.uint64)
+    if kind == "empty":
+        t_off[stay:] = 0
+    elif kind == "closed early":
+        t_off[stay:] = arrival[rng.integers(1, 30, M - stay)]
+    elif kind == "others late":
+        t_on[stay:] = last - 2000
+    elif kind == "short windows":
+        t_on = arrival[rng.integers(0, R - 150, M)]
+        t_off = t_on + np.uint64(300_000)
+    tr = traces.custom_trace(arrival, rng.integers(1, 800, R), rng.integers(1, 100, R), [(2000, 3, 25, 5), (1200, 2, 15, 3)] * (M // 2), t_on, t_off, B=B)
+    rows = rng.integers(0, M, size=(20, R)).astype(np.uint16)
+    rows[1], rows[2] = 0, 1
+    rows[3:9] %= stay
+    with GpuWorkload(tr) as g:
+        assert g.route(600)["lists"] == lists
+        assert_same(g.eval(np.resize(rows, (600, R)))[:20], oracle_for(tr).eval_batch(rows, nthreads=8), kind)
