@@ -236,7 +236,7 @@ static split_fn split_kernel(uint32_t hist_mode, bool tabled, bool within) {
 typedef void (*replay_lists_fn)(SplitParams, uint32_t, uint32_t);
 template <uint32_t kBins_, bool kFew>
 static replay_lists_fn replay_lists_kernel_of(uint32_t B) {
-    return B <= 8u ? k_replay_lists<8u, kBins_, kFew> : B <= 12u ? k_replay_lists<12u, kBins_, kFew> : B <= 16u ? k_replay_lists<16u, kBins_, kFew>
+    return B < 4u ? k_replay_lists<4u, kBins_, kFew> : B <= 8u ? k_replay_lists<8u, kBins_, kFew> : B <= 12u ? k_replay_lists<12u, kBins_, kFew> : B <= 16u ? k_replay_lists<16u, kBins_, kFew>
            : B <= 24u ? k_replay_lists<24u, kBins_, kFew> : B <= 32u ? k_replay_lists<32u, kBins_, kFew>
            : B <= 48u ? k_replay_lists<48u, kBins_, kFew> : k_replay_lists<64u, kBins_, kFew>;
 }
@@ -674,8 +674,8 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     if (longest_tpot >= (1u << 24)) return AP_OK;
     for (uint32_t m = 0; m < M && tabled; ++m)
         if (rep_type[m] >= 1024u) return AP_OK;              // the type rides in ten bits of a tile word
-    for (uint32_t r = 0; r < R; ++r)
-        if (worst_service[r] >= (1u << 28)) return AP_OK;
+    const uint32_t longest_service = *std::max_element(worst_service.begin(), worst_service.end());
+    if (longest_service >= (1u << 28)) return AP_OK;
     std::vector<uint32_t> tab(3u * (AP_MAX_REPLICAS + 1u) + 4u * kinds.size(), 0u);   // range words, kind words, coefficients
     std::vector<SplitQueue> queue(M);
     std::vector<uint32_t> order;
@@ -752,6 +752,7 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
         q.i_list = i_list;
         q.t_split = i_list < i_off ? arr[i_list] : kNever;
         q.allow_busy = i_list < i_off ? B - std::min(B, depth_from[i_list]) : 0u;
+        q.late_from = d.t_off == kNever ? kNever : d.t_off - std::min(d.t_off, 3u * longest_service);
         queue[m] = q;
         longest_list = std::max(longest_list, i_list);
         expect_rejected += R - i_off;
@@ -784,11 +785,8 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     plan.all_within = longest_prefill <= w->params.slo_ttft && longest_tpot <= w->params.slo_tpot;
     // A request that waits beyond its ready time finds all B slots taken by earlier ones, so it waits no longer than all service together
     // takes B slots.
-    uint64_t all_service = 0, longest_service = 0, latest_on = 0;
-    for (uint32_t r = 0; r < R; ++r) {
-        all_service += worst_service[r];
-        longest_service = std::max<uint64_t>(longest_service, worst_service[r]);
-    }
+    uint64_t all_service = 0, latest_on = 0;
+    for (uint32_t r = 0; r < R; ++r) all_service += worst_service[r];
     for (const DevReplica& d : dev)
         if (d.t_on < d.t_off) latest_on = std::max<uint64_t>(latest_on, d.t_on);
     sp.step_facts = (longest_tpot <= w->params.slo_tpot ? kTpotWithin : 0u) |

@@ -80,7 +80,8 @@ struct SplitQueue {                               // per replica, for the list r
     uint32_t i_list;
     uint32_t t_split;                             // arrival of request i_list; kNever: nothing is streamed
     uint32_t allow_busy;                          // slots that may still be taken beyond t_split
-    uint32_t pad0, pad1, pad2;
+    uint32_t late_from;                           // t_off less three of the longest services; kNever: the replica stays
+    uint32_t pad0, pad1;
 };
 
 struct SplitPartial {                             // per candidate of a batch, 64 bytes
@@ -583,7 +584,7 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // s'[i] = med3(s[i], f, s[i+1]), i.e. min(s[i+1], max(s[i], f)).  A lane without a request in a step has a record that inserts 0,
 // which leaves the registers as they are, and adds one microsecond to the sum of latencies, taken off in the end: nothing in a step asks
 // whether a request was served.  Requests that would start too late are given that record before their step; lanes look for them
-// only when one of four starts may be that late, once or twice in a queue.
+// only when one of four starts may be that late: where a queue closes, and then until the tile ends, for the other lanes too.
 // Is s[0] the earliest slot?  Slots that are free when a request is ready are as good as each other, then and later, whatever time
 // they hold.  So four requests may take theirs from the front if s[3] <= max(earliest of the rest, ready time of the first): of
 // s[0..3] one is still there at each of the four.  Where that does not hold in some lane, all lanes merge the two sequences
@@ -592,7 +593,9 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // Starts do not decrease along a queue, so once a start reaches t_off every later request is rejected too: a tile in which no
 // lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.  (4096 rows of
 // 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
-// kSlots: B rounded up to 8, 12, 16, 24, 32, 48 or 64; registers beyond B hold kNever and stay there.
+// kSlots: B rounded up to 8, 12, 16, 24, 32, 48 or 64, and 4 below four; registers beyond B hold kNever and stay there.  Below four slots a
+// start may be later than all of them were four requests before, and the bound is another (see below): with s[3], which is none there, the
+// look was taken at every step, 300 rows of 16384 requests that crowd 8 of 48 replicas 676 us, 562 now (stay, any load), 368 and 255 (leave).
 //
 // Bound by instruction issue.  What every lane would evaluate for itself is done once while staging
 // (the request's prefill and decode time on this replica, from coefficients or tables), records are read from LDS four at a
@@ -710,7 +713,9 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
     q.t_on = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.t_on);
     q.t_off = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.t_off);
     q.i_list = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.i_list);
+    q.late_from = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.late_from);
 
+    constexpr bool kBelowFour = kSlots == 4u;                                       // slots
     constexpr uint32_t kFront = kSlots >= 48u ? 16u : kSlots >= 16u ? 8u : kSlots;  // a power of two where there is a rest
     constexpr bool kPairs = kSlots > 48u;                                           // two steps are worth a branch
     constexpr uint32_t kHalves = 2u, kBlock = 8u * kHalves;                         // entries ahead
@@ -801,7 +806,11 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             d = open ? d : 0u;
             count = open ? count : 0u;
             n_here += count;
-            const uint32_t closes = open ? q.t_off : kNever;
+            uint32_t closes = open ? q.t_off : kNever;
+            if constexpr (kBelowFour) {
+                const uint32_t latest = max(recs[(j - j0) * kStagedTile + min(kTile, p.R - j * kTile) - 1u].x, q.t_on);   // of the tile's ready times
+                closes = !open ? kNever : latest < q.late_from ? q.late_from : 0u;
+            }
             // Steps of the tile; where nothing can start there is one all the same, in which only the next tile's block and the next
             // stage's descriptors are requested.
             const uint32_t most = __ballot(open) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
@@ -838,9 +847,10 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                 if (kFront < kSlots && __ballot(s[kFront < kSlots ? 3u : 0u] > max(s[kFront < kSlots ? kFront : 0u], max(rec[0].x, q.t_on))) != 0ull)
                     merge_sorted<kSlots, 0u, 1u, kFront, kSlots - kFront>(s);
                 const bool short_four = kPairs && k0 + 2u >= n_steps;               // no lane has a third
-                // No start is later than s[3], or ready time.  Where some lane's four may start too late, those of them that do are made
+                // No start is later than s[3], or ready time; with fewer than four slots, where s[3] is none, than the later of s[0] and the
+                // ready times and three services on top.  Where some lane's four may start too late, those of them that do are made
                 // padding first: which they are comes from the four earliest slots.
-                if (__ballot(s[kSlots > 3u ? 3u : 0u] >= closes) != 0ull) {
+                if (__ballot(s[kBelowFour ? 0u : 3u] >= closes) != 0ull) {
                     if (__ballot(open && earliest() < q.t_off) == 0ull) {           // nothing starts any more
                         n_rej += count - min(count, k0);
                         break;

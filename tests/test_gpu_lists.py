@@ -332,3 +332,35 @@ def test_slots_taken_from_the_front(B, kind):
     with GpuWorkload(tr) as g:
         assert g.route(C)["lists"] in (1, 2)
         assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=8), f"B={B} {kind}")
+
+
+@pytest.mark.parametrize("B", [1, 2, 3, 4])
+@pytest.mark.parametrize("kind", ["crowded", "last before", "long first", "stay"])
+def test_starts_that_come_too_late_with_few_slots(B, kind):
+    """With fewer than four slots a start may be later than every slot time of four requests before: each of the four may wait for the one
+    before it.  Replicas that leave while a crowd waits, right after a request becomes ready, after three of the longest services in a row
+    that fit exactly or by a microsecond not, and replicas that stay."""
+    rng = np.random.default_rng(B)
+    R, M, C = 2500, 5, 70
+    long = 2000 + 3 * 40 + 25 * 400 + 5 * 400                            # the longest service: 40 tokens in, 400 out
+    prompt, out = rng.integers(1, 40, R), rng.integers(1, 40, R)
+    arrival = np.cumsum(rng.integers(0, {"crowded": 300, "stay": 300, "last before": 60_000, "long first": 400}[kind], R)).astype(np.uint64)
+    prompt[::97], out[::97] = 40, 400
+    if kind == "long first":
+        prompt[1200:1300], out[1200:1300] = 40, 400
+    at = int(arrival[1250])
+    t_on = np.array([0, 0, int(arrival[1100]), 0, 0], np.uint64)
+    t_off = {"crowded": [int(arrival[2000]), int(arrival[2400]) + 9_000_000, at + 400_000, 30_000_000, U64MAX],
+             "last before": [at + 1, at + long, at + 3 * long, at + 3 * long + 1, at + 3 * long - 1],
+             "long first": [at + 1, at + long, int(arrival[1100]) + 3 * long, int(arrival[1100]) + 3 * long + 1, at + 40 * long],
+             "stay": [U64MAX] * 5}[kind]
+    tr = traces.custom_trace(arrival, prompt, out, [(2000, 3, 25, 5)] * 3 + [(1200, 2, 15, 3)] * 2, t_on, np.array(t_off, np.uint64), B=B, penalty_us=10**9)
+    rows = rng.integers(0, M, size=(C, R)).astype(np.uint16)
+    for m in range(M):
+        rows[m] = m
+        rows[8 + m, 1150:] = m
+    with GpuWorkload(tr) as g:
+        assert g.route(600)["lists"] in (1, 2)
+        got = g.eval(np.resize(rows, (600, R)))
+    assert_same(got[:C], oracle_for(tr).eval_batch(rows, nthreads=8), f"B={B} {kind}")
+    assert (got == got[np.arange(600) % C]).all()
