@@ -48,6 +48,7 @@ namespace {
 constexpr uint32_t kBuildMinWaves = 4, kBuildMaxWaves = 8;   // of a workgroup of the kernels that build the lists
 constexpr uint32_t kTile = 1024;                  // requests per tile: a list position fits 10 bits
 constexpr uint32_t kTileSteps = kTile / kWave;
+constexpr uint32_t kCrowd = 16;                   // of a tile's first 64 requests on one replica (k_list_candidates)
 constexpr uint32_t kFlagNeedHist = 1u;            // streamed without histograms, but they are needed: stream again
 constexpr uint32_t kFlagFallback = 2u;            // the listed part left too many slots taken: general replay
 constexpr uint32_t kFlagLazy = 4u;                // the p99 values are the penalty latency
@@ -488,9 +489,18 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, kHistMode == 0u ? 5 : 4) vo
     }
 }
 
+// `before`, and the lanes of `lanes` below this one.
+__device__ __forceinline__ uint32_t lanes_before(unsigned long long lanes, uint32_t before) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, before));
+}
+
 // Lists where nothing is streamed: every request is listed, or its replica is gone.  No record, cost or queue is needed then, so a
 // tile's ids stay in registers, a lane's request of every 64, together with what an LDS addition to the length of its replica's run returned:
 // the request's place in the run (see sort_runs).
+// Lanes that add to one word are served one after the other, so a tile that crowds a replica has the places on it, and on one more, counted
+// by ballots instead: 2048 rows of 32768 requests on one of 64 replicas 254 to 78 us (122 with ballots alone), on two 157 to 79 (122), on three
+// 126 to 111, four 110 to 107; from six on few tiles reach kCrowd, and even rows take 74 either way.  (Both forms behind a test in one loop cost
+// even rows 109: registers.)
 // Bound by LDS accesses, about 30 cycles for 64 requests: the addition, the run's beginning, the entry's store and the look at the entry
 // before it, all at random banks.  1024 rows of 131072 requests on 128 replicas 172 us (61 vector instructions for 64 requests and 287 us
 // with places from one ballot per bit of the replica id), 4096 rows of 32768 on 64 that come and go 137 (222).
@@ -520,36 +530,76 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(S
         __syncthreads();
         const uint16_t* row = assign + (size_t)(c0 + cb) * R;
         uint32_t n_seen = 0, n_listed = 0, listed_here = 0;                          // the last: of replica `lane`
-        uint32_t at[kTileSteps], at_next[kTileSteps];                                        // the replica
+        uint32_t at_next[kTileSteps];                                                // the replica
+        // Tiles from j on while they are crowded, or while they are not: kCrowd or more of the first 64 requests name one replica.
+        auto work_tiles = [&](auto crowded_tag, uint32_t j) {
+            constexpr bool kCrowded = decltype(crowded_tag)::value;
+            for (; j < p.n_tiles; j += n_waves) {
+                // the replica that the tile's first lane with one names
+                const unsigned long long known = __ballot(at_next[0] < M);
+                const uint32_t some = known != 0ull ? (uint32_t)__builtin_amdgcn_readlane((int)at_next[0], __builtin_ctzll(known)) : kNever;
+                const unsigned long long of_some = __ballot(at_next[0] == some);
+                if (((uint32_t)__popcll(of_some) >= kCrowd) != kCrowded) break;
+                const uint32_t r0 = j * kTile;
+                n_seen += min(kTile, R - r0);
+                asm volatile("" : "+v"(lane));                                       // positions are made here, not kept in registers
+                uint32_t at[kTileSteps];
+#pragma unroll
+                for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = min(at_next[s], M);
+                fetch_ids(at_next, row, j + n_waves, lane, R, M);
+                uint32_t place[kTileSteps];                                          // in the run
+                if (r0 + kTile <= least_end) {                                       // all but unknown replicas': the next look-ups say nothing
+#pragma unroll
+                    for (uint32_t s = 0; s < kTileSteps; ++s) place[s] = at[s] < M ? kNever : 0u;
+                } else {
+#pragma unroll
+                    for (uint32_t s = 0; s < kTileSteps; ++s) place[s] = end_of[at[s]];  // entry M is 0
+                }
+                if constexpr (!kCrowded) {
+#pragma unroll
+                    for (uint32_t s = 0; s < kTileSteps; ++s) {
+                        const bool listed = r0 + s * kWave + lane < place[s];        // and below R
+                        n_listed += (uint32_t)__popcll(__ballot(listed));
+                        at[s] = listed ? runs_at + 4u * at[s] : nowhere_at;
+                        place[s] = p.tile_cap / 2u;
+                        if (listed) place[s] = lds_add_rtn(at[s], 1u);
+                    }
+                } else {
+                    // that replica's places, and those of the first one beside it, are counted by ballots
+                    const unsigned long long others = known & ~of_some;
+                    const uint32_t other = others != 0ull ? (uint32_t)__builtin_amdgcn_readlane((int)at[0], __builtin_ctzll(others)) : kNever;
+                    uint32_t n_some = 0, n_other = 0;
+#pragma unroll
+                    for (uint32_t s = 0; s < kTileSteps; ++s) {
+                        const unsigned long long listed = __ballot(r0 + s * kWave + lane < place[s]);
+                        const unsigned long long lanes_some = __ballot(at[s] == some) & listed, lanes_other = __ballot(at[s] == other) & listed;
+                        at[s] = __builtin_amdgcn_inverse_ballot_w64(listed) ? runs_at + 4u * at[s] : nowhere_at;
+                        place[s] = __builtin_amdgcn_inverse_ballot_w64(lanes_some) ? lanes_before(lanes_some, n_some) : p.tile_cap / 2u;
+                        place[s] = __builtin_amdgcn_inverse_ballot_w64(lanes_other) ? lanes_before(lanes_other, n_other) : place[s];
+                        if (__builtin_amdgcn_inverse_ballot_w64(listed & ~(lanes_some | lanes_other))) place[s] = lds_add_rtn(at[s], 1u);
+                        n_listed += (uint32_t)__popcll(listed);
+                        n_some += (uint32_t)__popcll(lanes_some);
+                        n_other += (uint32_t)__popcll(lanes_other);
+                        __builtin_amdgcn_sched_barrier(0);                           // counted here, not kept as masks
+                    }
+                    if (lane == 0u) {
+                        uint32_t* run = reinterpret_cast<uint32_t*>(mine);
+                        run[some] = n_some;
+                        if (other != kNever) run[other] = n_other;
+                    }
+                }
+                if (j >= p.n_list_tiles) continue;                                   // nothing is listed: no tile of the lists either
+                write_runs(p, (size_t)cb * p.n_list_tiles + j, lane, mine, at, place, [&](uint32_t m, uint32_t c) {
+                    if (m < kWave) listed_here += (c + 3u) & ~3u;
+                    else if (c != 0u) atomicAdd(&total_of[m], (c + 3u) & ~3u);
+                });
+            }
+            return j;
+        };
         fetch_ids(at_next, row, w, lane, R, M);
-        for (uint32_t j = w; j < p.n_tiles; j += n_waves) {
-            const uint32_t r0 = j * kTile;
-            n_seen += min(kTile, R - r0);
-            asm volatile("" : "+v"(lane));                                           // positions are made here, not kept in registers
-#pragma unroll
-            for (uint32_t s = 0; s < kTileSteps; ++s) at[s] = min(at_next[s], M);
-            fetch_ids(at_next, row, j + n_waves, lane, R, M);
-            uint32_t place[kTileSteps];                                                  // in the run
-            if (r0 + kTile <= least_end) {                                           // all but unknown replicas': the next look-ups say nothing
-#pragma unroll
-                for (uint32_t s = 0; s < kTileSteps; ++s) place[s] = at[s] < M ? kNever : 0u;
-            } else {
-#pragma unroll
-                for (uint32_t s = 0; s < kTileSteps; ++s) place[s] = end_of[at[s]];      // entry M is 0
-            }
-#pragma unroll
-            for (uint32_t s = 0; s < kTileSteps; ++s) {
-                const bool listed = r0 + s * kWave + lane < place[s];                // and below R
-                n_listed += (uint32_t)__popcll(__ballot(listed));
-                at[s] = listed ? runs_at + 4u * at[s] : nowhere_at;
-                place[s] = p.tile_cap / 2u;
-                if (listed) place[s] = lds_add_rtn(at[s], 1u);
-            }
-            if (j >= p.n_list_tiles) continue;                                       // nothing is listed: no tile of the lists either
-            write_runs(p, (size_t)cb * p.n_list_tiles + j, lane, mine, at, place, [&](uint32_t m, uint32_t c) {
-                if (m < kWave) listed_here += (c + 3u) & ~3u;
-                else if (c != 0u) atomicAdd(&total_of[m], (c + 3u) & ~3u);
-            });
+        for (uint32_t j = w; j < p.n_tiles;) {
+            j = work_tiles(std::false_type{}, j);
+            if (j < p.n_tiles) j = work_tiles(std::true_type{}, j);
         }
         if (lane == 0u) atomicAdd(&rejected_of_row[0], n_seen - n_listed);           // wavefront totals
         if (listed_here != 0u) atomicAdd(&total_of[lane], listed_here);

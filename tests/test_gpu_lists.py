@@ -364,3 +364,32 @@ def test_starts_that_come_too_late_with_few_slots(B, kind):
         got = g.eval(np.resize(rows, (600, R)))
     assert_same(got[:C], oracle_for(tr).eval_batch(rows, nthreads=8), f"B={B} {kind}")
     assert (got == got[np.arange(600) % C]).all()
+
+
+@pytest.mark.parametrize("M,R", [(1, 1030), (2, 2048), (40, 1000), (64, 4 * 1024 + 65), (130, 9 * 1024 + 1)])
+def test_tiles_that_crowd_a_replica(M, R):
+    """A tile whose first requests name one replica often enough has its places, and those of one more replica, counted another way: rows on
+    one to five replicas, on one replica and now and then another, with unknown ids in front and in between, tiles that crowd in turn with
+    tiles that do not, and replicas that are gone by a tile or in its middle."""
+    rng = np.random.default_rng(M + R)
+    B = 6
+    arrival = np.cumsum(rng.integers(0, 200, R)).astype(np.uint64)
+    t_off = np.where(np.arange(M) % 3 == 2, arrival[rng.integers(R // 3, R, M)], traces.UINT64_MAX).astype(np.uint64)
+    tr = traces.custom_trace(arrival, rng.integers(1, 800, R), rng.integers(1, 100, R), [(2000, 3, 25, 5)] * M, None, t_off, B=B)
+    rows = rng.integers(0, M, size=(40, R)).astype(np.uint16)
+    for c in range(20):
+        some = rng.choice(M, size=min(M, 1 + c % 5), replace=False)
+        rows[c] = rng.choice(some, size=R)
+        if c >= 5:                                                       # a share of others, unknown ones among them
+            rows[c] = np.where(rng.random(R) < (0.02, 0.3, 0.7)[c % 3], rng.integers(0, M + 2, R), rows[c])
+    rows[20:28] = np.where(np.arange(R) // 1024 % 2 == 0, rows[0:8], rows[20:28])
+    rows[22, ::1024] = rows[23, :64] = M
+    rows[24:28, 32:64] = rows[28:32, 32:64]
+    with GpuWorkload(tr) as g:
+        assert g.route(600)["lists"] == 1
+        got = g.eval(np.resize(rows, (600, R)))
+        odd = g.eval(rows[:7])                                           # few rows: eight wavefronts each
+    want = oracle_for(tr).eval_batch(rows, nthreads=8)
+    assert_same(got[:40], want, f"M={M} R={R}")
+    assert (got == got[np.arange(600) % 40]).all()
+    assert_same(odd, want[:7], f"M={M} R={R}, few rows")
