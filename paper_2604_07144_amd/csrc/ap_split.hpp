@@ -863,7 +863,8 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
             }
             // Steps of the tile; where nothing can start there is one all the same, in which only the next tile's block and the next
             // stage's descriptors are requested.
-            const uint32_t most = __ballot(open) != 0ull ? wave_all_max(count) : 0u, n_steps = max(most, 1u);
+            const uint32_t most = __ballot(open) != 0ull ? wave_all_max(count) : 0u;
+            uint32_t n_steps = max(most, 1u);
             uint32_t e[4u * kHalves];                                               // two entries each, the next ones first
 #pragma unroll
             for (uint32_t i = 0; i < 4u * kHalves; ++i) e[i] = kPadding * 0x10001u;
@@ -901,9 +902,11 @@ __global__ __launch_bounds__(kReplayListThreads, kSlots > 32u ? 3 : 5) void k_re
                 // ready times and three services on top.  Where some lane's four may start too late, those of them that do are made
                 // padding first: which they are comes from the four earliest slots.
                 if (__ballot(s[kBelowFour ? 0u : 3u] >= closes) != 0ull) {
-                    if (__ballot(open && earliest() < q.t_off) == 0ull) {           // nothing starts any more
-                        n_rej += count - min(count, k0);
-                        break;
+                    // (A way out of the loop here costs every step three branches: 1024 rows of 131072 requests, all on one replica, 37.3 ms
+                    // instead of 36.4, even rows 1106 us instead of 1080.)
+                    if (__ballot(open && earliest() < q.t_off) == 0ull) {           // nothing starts any more: these four are the last
+                        n_rej += count - min(count, k0 + 4u);
+                        n_steps = k0;
                     }
                     uint32_t early[4];
 #pragma unroll
