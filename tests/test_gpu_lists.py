@@ -393,3 +393,42 @@ def test_tiles_that_crowd_a_replica(M, R):
     assert_same(got[:40], want, f"M={M} R={R}")
     assert (got == got[np.arange(600) % 40]).all()
     assert_same(odd, want[:7], f"M={M} R={R}, few rows")
+
+
+@pytest.mark.parametrize("bins", [False, True])
+@pytest.mark.parametrize("kind", ["comes up late", "one slot", "two slots", "late, two slots"])
+@pytest.mark.parametrize("beyond", [-1, 0, 1, 100_000_000, 700_000_000])
+def test_latencies_on_either_side_of_a_quarter_of_the_range(kind, beyond, bins):
+    """Four latencies are added up in 32 bits where the host's bound on a latency - the latest window's beginning, all service over the
+    slots and one service more - is below 2^30 us, and one by one where it is not: bounds one below it, at it, one above and far above, by a
+    replica that comes up behind a backlog, by an overload of one or two slots, and by both, with latencies next to the bound.  bins: with and
+    without rejected requests that settle the p99 values."""
+    rng = np.random.default_rng(abs(beyond))
+    R, M = 2304, 3
+    bound = (1 << 30) + beyond                                           # what the host compares with 2^30
+    B = {"comes up late": 8, "one slot": 1, "two slots": 2, "late, two slots": 2}[kind]
+    arrival = np.arange(R, dtype=np.uint64)
+    on_replica = {"comes up late": bound - 2_000_000, "one slot": 0, "two slots": 0, "late, two slots": bound // 2}[kind]
+    tpot, out = 10, 20
+    service = (bound - on_replica) * B // (R + B)                        # of each request, and a microsecond more for some of them
+    extra = np.zeros(R, int)
+    while on_replica + (service * R + int(extra.sum())) // B + service + int(extra.max()) < bound:
+        extra[int(extra.argmin())] += 1
+    assert on_replica + (service * R + int(extra.sum())) // B + service + int(extra.max()) == bound
+    t_on = np.array([0, 0, on_replica], np.uint64)
+    t_off = np.array([U64MAX, 5_000_000 if not bins else U64MAX, U64MAX], np.uint64)
+    tr = traces.custom_trace(arrival, 1 + extra, np.full(R, out), [(service - tpot * out - 1, 1, tpot, 0)] * M, t_on, t_off, B=B,
+                             penalty_us=(1 << 32) - 1 if bins else 1 << 40)
+    rows = rng.integers(0, M, size=(70, R)).astype(np.uint16)
+    rows[0] = rows[1] = 2
+    rows[1, ::3] = M
+    rows[2, :40] = 1
+    rows[3] = 0
+    want = oracle_for(tr).eval_batch(rows, nthreads=8)
+    if beyond > 1:
+        assert int(want["p99_e2e_us"][0]) > (1 << 30)                    # one request in a hundred: four in a row do not fit 32 bits
+    with GpuWorkload(tr) as g:
+        assert g.route(600)["lists"] in (1, 2)
+        got = g.eval(np.resize(rows, (600, R)))
+    assert_same(got[:70], want, f"{kind} {beyond}")
+    assert (got == got[np.arange(600) % 70]).all()
