@@ -269,10 +269,10 @@ static uint32_t count_waves_per_row(const ap_workload* w, uint32_t C) {
 }
 
 // Calls of few rows that go to the fused replay in place of the lists: up to two rows per compute unit with up to 64 replicas, one
-// with more (their slots leave room for one workgroup or slow two down: 512 rows of 800 requests on 128 replicas 55 against 40 us,
-// 256 rows 30 against 38).  A wavefront works through the queues of many replicas one after the other, while the launches of the
-// lists cost the same for any number: beyond 128 replicas one row is better off with lists (200 requests on 500 replicas:
-// one row 31 against 27 us, 4 rows 32 against 34; 800 on 500: one row 47 against 41, 4 rows 46 against 55).
+// with more, whose slots leave room for one workgroup or slow two down (even rows of 800 requests on replicas that come and go, lists and
+// fused replay: 512 rows on 64 replicas 36 and 29 us, on 128 34 and 37, 256 rows there 32 and 30).  A wavefront works through the queues of
+// many replicas one after the other, while the launches of the lists cost the same for any number: beyond 128 replicas one row is better
+// off with lists (200 requests on 500 replicas: one row 27 and 30, 4 rows 32 and 31; 800 on 500: 39 and 46, 52 and 46).
 static bool fused_replay(const ap_workload* w, uint32_t C) {
     const uint32_t M = w->params.M;
     return w->split && w->split_plan.short_chain && C <= (M <= 64u ? 2u : 1u) * w->n_cu && (M <= 128u || C >= 4u);
@@ -325,7 +325,7 @@ static ap_status launch_split(const ap_workload* w, const SplitPlan& plan, const
         // with histograms, for every candidate or for those the first pass marked.
         const bool plain_first = plan.expect_lazy;
         // A workgroup per row: four wavefronts, or eight where rows leave the chip less than two per SIMD (300 rows of 20001 requests on 61
-        // replicas 1.2 to 1.3 times less).  Not more beyond: LDS is what they wait for, and a row's tiles take as many turns
+        // replicas 1.2 to 1.3 times less time).  Not more beyond: LDS is what they wait for, and a row's tiles take as many turns
         // with five wavefronts as with four (1024 rows of 131072 on 128, 172 us with four, 179 with six; 700 rows of 16384 on 64, 52 and 63 with five).
         auto waves_of = [&](uint32_t most) { return n <= 2u * w->n_cu ? std::max(kBuildMinWaves, std::min(most, sp.n_tiles)) : kBuildMinWaves; };
         auto launch_split_kernel = [&](uint32_t hist_mode, uint32_t blocks, uint32_t only_flagged) {
@@ -730,13 +730,17 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     };
     const size_t most_per_candidate = ((size_t)8 << 30) / 64u;
     // Where next to nothing would be streamed, list that too: k_list_candidates takes half of k_split_candidates' time, and no row is handed back
-    // for what its listed part leaves taken.  Calls of a busy beginning and a quiet end, streamed and listed: the last 2 % quiet, 3355 rows
-    // 739 and 657 us (20000 requests on 50 replicas), with tables 802 (rows handed back) and 566, 200 rows 228 and 214; 5 % 718 and 653, 200 rows
-    // 223 and 215; 10 % 691 and 646, 200 rows 210 and 214; 20 % 643 and 645, 200 rows 191 and 212; 30 % 580 and 660, 174 and 210.  The line
-    // is where a call of few rows loses nothing either, and it is asked of every replica by itself: a row that crowds one waits for its list,
-    // request after request.  With the line on the trace as a whole, 64 rows of 32768 requests on 4 replicas that stay while 60 are never there
-    // took 2.2 ms (54 us with these streamed), 7.5 ms on one of them (64 us); even rows of 63 replicas that come at the end and one that stays
-    // would gain by it, 457 against 519 us.
+    // for what its listed part leaves taken.  Calls of a busy beginning and a quiet end, streamed and listed, half of the replicas coming late:
+    //   quiet   1677 rows of 20000, 50 replicas   200 rows    4096 of 4000 on 12   200 rows    559 of 60000 on 200   200 rows
+    //    2 %    430 and 388 us                    223 and 215   318 and 207        121 and 116   678 and 590         344 and 334
+    //    6 %    413 and 386                       216 and 215   490 and 204        166 and 116   660 and 590         335 and 335
+    //   10 %    399 and 388                       208 and 214   476 and 204        165 and 116   635 and 585         325 and 335
+    //   15 %    385 and 384                       198 and 214   529 and 206        166 and 115   607 and 590         311 and 334
+    // (4000 on 12: streamed, rows are handed back).  The line, a fourteenth, is where 200 rows begin to lose; three lose 3 % there, and rows that
+    // crowd a replica, which then wait for its quiet end as well, up to the share itself (200 rows of 4000 on one of 12, 6 % quiet, 727 and 763).
+    // It is asked of every replica by itself: a row that crowds one waits for its list, request after request.  With the line on the trace as a
+    // whole, 64 rows of 32768 requests on 4 replicas that stay while 60 are never there took 2.2 ms (54 us with these streamed), 7.5 ms on one of
+    // them (64 us); even rows of 63 replicas that come at the end and one that stays would gain by it, 457 against 519 us.
     bool list_all = true;
     for (uint32_t m = 0; m < M; ++m) list_all = list_all && (i_off_of[m] - i_list_of[m]) * 14ull <= i_off_of[m];
     list_all = list_all && bytes_per_candidate(*std::max_element(i_off_of.begin(), i_off_of.end())) <= most_per_candidate;
@@ -822,8 +826,12 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     auto waves_most = [&](uint32_t fixed, uint32_t per_wave) { return std::min(kBuildMaxWaves, ((uint32_t)lds_cap - std::min((uint32_t)lds_cap, fixed)) / per_wave); };
     plan.list_waves_most = waves_most(sp.l_wave, sp.l_wave_bytes);
     for (uint32_t h = 0; h < 2u; ++h) plan.split_waves_most[h] = waves_most(plan.off_wave[h], sp.wave_bytes);
-    // A replica table that large stays with the general replay.  (The line is that of a streaming kernel which held 28 bytes a replica and
-    // six a request of a tile per wavefront; above it the lists would fit up to about 900 replicas, and were not measured.)
+    // A replica table that large stays with the general replay.  The line is 28 bytes a replica, two a list position and two or four a request
+    // of a tile for each of four wavefronts, and 8 or 12 a replica besides: 794 replicas with 16-bit counts, 607 with 32-bit ones (three kinds,
+    // traces of a tile or more; 160 KB).  The kernels hold less: they would fit all 1024 and 951.  Above it, general replay and lists: 1000 even
+    // rows of 16384 requests on 800 replicas of 8 slots that come and go 1255 and 459 us, that stay under load 1676 and 608, of 70000 on 700
+    // 4646 and 1133 (4 slots, staying, 7146 and 2095); but rows on one replica that stays 2778 and 3569, 64 of them 696 and 3397, one of 70000 on
+    // one of 700 2922 and 14700.  The lists lose as much below the line; it is kept until both kinds of row are worth having.
     const uint32_t held = 2u * align_up(M * 4u, 16u) + kTile * (M <= 64u ? 2u : 4u) + align_up(sp.tile_cap * 2u, 16u) + align_up(M * 8u, 16u) +
                           align_up((M + 1u) * 4u, 16u);
     if (before_waves - 16u + kBuildMinWaves * held + hist_bytes > (uint32_t)lds_cap ||
@@ -913,16 +921,15 @@ static ap_status plan_split(ap_workload* w, SplitPlan& plan, bool& applies,
     plan.params = sp;
     plan.batch = batch;
     // A small call - few rows, and the fused replay's wavefront per queue has little more to do than a lane of the list replay -
-    // is left to the fused replay: one launch instead of three.  It takes 65 ns a request and works on four queues of a row at a
-    // time (12 us + R * 0.016 us a row that is spread evenly, 12 us + R * 0.065 us one on a single replica); the list replay takes
-    // 115 ns a request of the longest list while the chip is nearly empty, and its launches 25 us together.  Both kinds of row have
-    // to gain: 64 rows of 256 requests on 4 replicas 14.4 against 20 us, 512 rows of 800 on one of 8 replicas 50 against 156; but
-    // 800 on one of 2 replicas that are mostly away, 57 against 32.  Replicas with a streamed part cost a launch more, 13 us, and
-    // the line lies as much again higher, for lists next to empty at 584 requests: there 97 rows of 577 on 8 replicas that are
-    // mostly always there take 16 against 41 us when they are spread evenly and 38 against 36 when they crowd one (512 rows, 25
-    // against 44 and 49 against 41).  Most is given up at 512 rows of 800 on 2 replicas with one long list: 60 against 43 us where
-    // they crowd the other, for 33 against 60 where they crowd that one and 40 against 46 where they are even.  With windows the
-    // longest list says little about the others: there even rows have to do without it in the first term.
+    // is left to the fused replay: one launch instead of three to five.  It takes 40 ns a request of a row's longest queue and works on four
+    // queues of a row at a time; the list replay takes 200 ns a request of the longest list while the chip is nearly empty, and the launches
+    // 20 to 30 us together.  Both kinds of row, even ones and those that crowd a replica, are meant to gain.  Lists and fused replay: 64 rows of
+    // 200 requests on 4 replicas that come and go, even 48 and 15 us, on one replica 58 and 19; 512 rows of 800 on 8 replicas that stay, even 51
+    // and 28, on one 185 and 53; but 512 of 800 on 2 replicas that are mostly away, 34 and 37, on one 35 and 55.  With windows the longest
+    // list says little about the others: there even rows have to do without it in the first term, and a crowded replica may have left early
+    // (512 rows of 800 on 8, even 31 and 27, on one that has 25 and 53; 256 rows on 500, 56 and 51, 25 and 51).  Replicas with a streamed part
+    // cost a launch or two more, and the line lies as much higher.  It was drawn when either took longer and is on the lists' side now: of what
+    // it leaves to them, 64 rows of 1200 on 8 replicas that stay take 61 us and would take 22, 2000 on 24 51 and 28.
     plan.short_chain = !w->pipeline && (uint64_t)R * M <= 800ull * M + (w->small_table ? 7ull * longest_list : 0ull) &&
                        65ull * R <= (any_streamed ? 38000ull : 13000ull) + 115ull * longest_list;
     // stream without histograms first when an even spread of the requests over the replicas would reject enough (never behind the

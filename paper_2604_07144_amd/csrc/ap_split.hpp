@@ -144,8 +144,8 @@ __global__ __launch_bounds__(kThreads) void k_pair_tables(const uint32_t* __rest
 
 // Ranks by LDS additions.  A wavefront's LDS instructions execute in order; of the lanes of one addition that name the same word, lower
 // ones have been seen to come first, always, but nothing promises it.  So every lane looks, once a tile's entries are in their runs, at
-// the entry before its own, and a tile in which one is larger has its runs sorted.  (A random read of 64 entries is 5 LDS cycles; ranks
-// that need no such look, from ballots, are 30 vector instructions.)
+// the entry before its own, and a tile in which one is larger has its runs sorted (tests/device hands places out in any order).  A random
+// read of 64 entries is 5 LDS cycles; ranks that need no such look, from ballots, are 30 vector instructions.
 __device__ __forceinline__ void sort_runs(uint16_t* list, const uint32_t* first_of, const uint32_t* desc, uint32_t M) {
     for (uint32_t m = threadIdx.x & 63u; m < M; m += kWave) sort_run(list + first_of[m], desc[m] >> 16);
 }
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kBuildMaxWaves * kWave, kHistMode == 0u ? 5 : 4) vo
     typedef __attribute__((address_space(3))) const four_words lds_four;
     const uint32_t R = p.R, M = p.M;
 
-    // Mode 0 never runs behind the streamed evaluation (its spilled scalars: 836 against 834 us for 8192 rows of 32768 requests).
+    // Mode 0 never runs behind the streamed evaluation, and need not ask.
     if (kHist && split_nothing_pending(p)) return;
     if (only_flagged) {                                                             // usually nothing is: leave at once
         bool any = false;
@@ -502,7 +502,7 @@ __device__ __forceinline__ uint32_t lanes_before(unsigned long long lanes, uint3
 // 126 to 111, four 110 to 107; from six on few tiles reach kCrowd, and even rows take 74 either way.  (Both forms behind a test in one loop cost
 // even rows 109: registers.)
 // Bound by LDS accesses, about 30 cycles for 64 requests: the addition, the run's beginning, the entry's store and the look at the entry
-// before it, all at random banks.  1024 rows of 131072 requests on 128 replicas 172 us (61 vector instructions for 64 requests and 287 us
+// before it, all at random banks.  1024 rows of 131072 requests on 128 replicas 166 us (61 vector instructions for 64 requests and 287 us
 // with places from one ballot per bit of the replica id), 4096 rows of 32768 on 64 that come and go 137 (222).
 __global__ __launch_bounds__(kBuildMaxWaves * kWave, 6) void k_list_candidates(SplitParams p, const uint16_t* __restrict__ assign, uint32_t c0,
                                                                       uint32_t n_cand, PendingWord flags) {
@@ -641,46 +641,39 @@ __device__ __forceinline__ void raise(uint32_t& a, uint32_t b) { asm("v_max_u32 
 // (Batcher's network) and the front is the kFront earliest again, which is good for kFront requests at least, and for any
 // number while slots are free: as a queue fills up, after its backlog has drained, on a light trace.
 // Starts do not decrease along a queue, so once a start reaches t_off every later request is rejected too: a tile in which no
-// lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.  (4096 rows of
-// 32768 requests on 64 crowded replicas that come and go: 438 to 407 us.)
+// lane's earliest slot comes free in time is only counted, and a workgroup without such a lane stages nothing more.
 // kSlots: B rounded up to 8, 12, 16, 24, 32, 48 or 64, and 4 below four; registers beyond B hold kNever and stay there.  Below four slots a
 // start may be later than all of them were four requests before, and the bound is another (see below): with s[3], which is none there, the
 // look was taken at every step, 300 rows of 16384 requests that crowd 8 of 48 replicas 676 us, 562 now (stay, any load), 368 and 255 (leave).
 //
-// Bound by instruction issue.  What every lane would evaluate for itself is done once while staging
-// (the request's prefill and decode time on this replica, from coefficients or tables), records are read from LDS four at a
-// time before they are needed, a tile's steps are counted once (the longest run sets the pace).  Of 64 slots a front of 16 takes 16
-// operations a request and a merge about 300 and its register moves, at most once in 16: half of the 64 medians over one sorted sequence, and a
-// quarter while slots are free (fronts of 8 and 32 are 38 and 42).  With 16, 24 and 32 slots it is a front of 8, below that the front is all.
-// Replay kernels with one sorted sequence, whose lower registers held still where slots were free, and now: 8192 rows of 32768 requests on 64
-// replicas of 64 slots that come and go 380 and 300 us, 4096 of them crowded 430 and 310; 1024 of 131072 on 128 crowded 665 and 550; calls of
-// 4096 rows of 16384 on 48 that come and go, half their slots in use: 16 slots 233 to 229 us, 24 265 to 249, 32 280 to 260, 48 320 to 275, 64 345 to 280.
-// Of the rest of a step, 36 operations were 22 when sums of four came in place of a 64-bit sum each, the latest finish from the slot times,
-// and served or not from the record: the same three kernels 300, 310 and 550 to 292, 296 and 540 us.  A wavefront of which no
-// queue has a slot that comes free in time leaves the tile (512 rows of 800 that crowd one of 500 replicas of 8 slots 62 to 8 us).
+// Bound by instruction issue, and where the longest of 64 lanes' runs sets the pace by the idle steps of the others.  What every lane would
+// evaluate for itself is done once while staging (the request's prefill and decode time on this replica, from coefficients or tables),
+// records are read from LDS four at a time before they are needed, a tile's steps are counted once.
+// Of 64 slots a front of 16 takes 16 operations a request and a merge about 300 and its register moves, at most once in 16: half of the 64
+// medians over one sorted sequence, and a quarter while slots are free (fronts of 8 and 32 are 38 and 42).  With 16, 24 and 32 slots it is a
+// front of 8, below that the front is all.  One sorted sequence, whose lower registers held still where slots were free, and this: kernels of
+// 8192 rows of 32768 requests on 64 replicas of 64 slots that come and go 380 and 300 us, of 1024 of 131072 on 128 crowded 665 and 550; calls of
+// 4096 rows of 16384 on 48 that come and go, half their slots in use: 16 slots 233 and 229 us, 32 280 and 260, 64 345 and 280.
 // Loads run ahead: a lane's descriptors a stage, its next block of entries a block, also into the next tile, and the
 // records of a stage four per thread at a time.  A register whose
 // load is in flight is neither moved nor chosen from in between (either waits for it), hence one block ahead, e_next as vectors
-// and the empty asm where they are waited for.  Blocks of eight come too late for queues of few slots: a wavefront by itself takes 200 ns
-// a request there, a line from HBM and the stores before it more than eight of those (400 rows of 16384 requests on one of 2 replicas of
-// 8 slots 3801 us before anything ran ahead, 3842 with blocks of eight, 3356 with sixteen; one row on both of 2, 1807, 1906 and 1757;
-// 100 rows of 131072 on 21 of 128 replicas of 64 slots 3680, 3340 and 3280; eight also where registers then left room for a wavefront more,
-// 8192 rows of 32768 on 64 that come and go 293 and now 289 in here).  With more than 48 slots a pair of steps that
+// and the empty asm where they are waited for.  Blocks of eight entries come too late for queues of few slots: a wavefront by itself takes
+// 200 ns a request there, a line from HBM and the stores before it more than eight of those (400 rows of 16384 requests on one of 2 replicas
+// of 8 slots 3842 us, 3356 with sixteen).  With more than 48 slots a pair of steps that
 // no lane needs is left out; up to there the branch costs more (crowds of one queue 6 % at 8 and 16 slots, 4 % at 24 to 48).
 // Where all lists are as long as the trace, a few neighbouring replicas share an XCD, whose L2 then holds their runs once.
 // A queue's words for the histograms follow one another (place_bins), four requests at a time where one of the four has a value
 // that a p99 value can reach: on a trace that is not hopelessly overloaded one in fifty to one in ten has, and a word per list
-// position was a gigabyte of 16-byte stores to as many cache lines, a third of the kernel's time.  1024 rows of 131072 requests on 128 crowded replicas: 1203 us before
-// all of this, 983 with a word per position, 693 now, and k_merge_candidates 198 and 31.  3001 rows of 20011 requests on 50 replicas,
-// half of which come and go, 186 to 166 us, and 4096 rows of 32768 on 64 crowded replicas that come and go 467 to 450.
+// position would be a gigabyte of 16-byte stores to as many cache lines for 1024 rows of 131072 requests.
 // kBins: 0 leaves no bins, 1 one word per request, 2 two words.  which: 0 every candidate, 1 only those settled by penalty,
 // 2 only the others; a workgroup without a lane to work on ends at once.
-// kFew: no more than a workgroup per compute unit; bins are then taken of every request, without a test whether any of them counts.  A
-// wavefront that has its SIMD to itself loses more over that branch than over the bins, and gains by it where the chip is full.  With bins
-// of every request and with the test, calls of 8192 requests on 64 replicas of 8 slots, rows that crowd 10 of them: 64 workgroups 261
-// and 288 us, 256 292 and 320, 512 339 and 367, 1024 557 and 572; even rows 100 and 104, 133 and 136, 191 and 191, 403 and 406;
-// 16384 on 24 of 16 slots, even, 64 279 and 282, 512 629 and 625; 559 rows of 60000 on 256 (768 workgroups) 489 and 468; 1024 of 131072
-// on 128 (512) 1080 and 1009.  The line is at the compute units: beyond it even rows, which are the larger calls, begin to lose.
+// kFew: no more than a workgroup per compute unit; bins are then taken of every four requests, without a test whether any of them counts.  A
+// crowded queue's wavefront, which has its SIMD to itself, gains 3 % by that at any number of workgroups, one of even rows gains or loses
+// little where replicas are of several kinds and loses up to a fifth where they are of one and few of its values count.  With the test and
+// without: 8192 requests on 64 replicas of 8 slots, 256 rows that crowd 10 of them 259 and 251 us, even rows 86 and 85; 16384 on 24 of 16 slots,
+// 256 rows, crowds 1130 and 1089, even 276 and 263; 131072 on 128 of 64 slots, 256 rows (128 workgroups), crowds 2680 and 2618, even 742 and 785, of
+// three kinds 904 and 892; 3 rows, even, 466 and 559; 1024 rows (512 workgroups), crowds 2965 and 2913, even 1078 and 1129.  The line is at the
+// compute units: beyond it even rows, which are the larger calls, lose as much as crowds gain.
 constexpr uint32_t kListWaves = 4;
 constexpr uint32_t kReplayListThreads = kListWaves * kWave;
 constexpr uint32_t kXcds = 8;                     // workgroups go to them in turn

@@ -153,8 +153,8 @@ def test_equally_long_lists_over_many_blocks_of_candidates(R, M, B, C):
 
 @pytest.mark.parametrize("M", [772, 773, 784, 794, 795])
 def test_tables_that_fill_the_lds(M):
-    """With the kernel's histograms no room in LDS for the listed requests per replica (773 to 794 replicas, three kinds): they
-    are added up in device memory.  Nothing rejected, a part listed and a part streamed, bins from both."""
+    """Large tables, up to the line from which they are left to the general replay (794 replicas of three kinds with 16-bit counts).  Nothing
+    rejected, a part listed and a part streamed, bins from both."""
     rng = np.random.default_rng(M)
     R, B = 3000, 4
     arrival = np.cumsum(np.concatenate([rng.integers(0, 3, R // 2), rng.integers(20_000, 60_000, R - R // 2)])).astype(np.uint64)
