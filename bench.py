@@ -34,19 +34,19 @@ KERNEL_SOURCE_DIR = os.path.join(ROOT, "paper_2604_07144_amd", "csrc")
 # Keyed by configuration; valid only for the library source (all of csrc/) whose hash is recorded with it.
 MEASURED_TRAFFIC = {
     # cfg: (sha256 of the kernel source, bytes per call)
-    4: ("7c43d55079426cec0ffb374a7fc8a66423e1e115c66128631b9b6ff90fadbafb", 4304596030),
-    3: ("7c43d55079426cec0ffb374a7fc8a66423e1e115c66128631b9b6ff90fadbafb", 1880229052),
+    4: ("e567379000d9e29a065e5f8210c62d40e031d8eaa73d8a57a6c2a09769e9f009", 4304568537),
+    3: ("e567379000d9e29a065e5f8210c62d40e031d8eaa73d8a57a6c2a09769e9f009", 1887872004),
 }
 # Wave-instructions per candidate-request of one ap_eval_candidates call (all its kernels), from rocprofv3 --pmc
 # SQ_INSTS_VALU / SQ_INSTS_SALU / SQ_INSTS_LDS; same validity rule.  The chip issues at most 256 CUs x 4 SIMDs x
 # 2.4 GHz / 4 cycles = 6.1e11 64-lane vector instructions per second.
 VALU_PEAK_PER_S = 256 * 4 * 2.4e9 / 4
 MEASURED_ALU = {
-    4: ("7c43d55079426cec0ffb374a7fc8a66423e1e115c66128631b9b6ff90fadbafb", {"valu": 0.1224, "salu": 0.0869, "lds": 0.0274}),
-    3: ("7c43d55079426cec0ffb374a7fc8a66423e1e115c66128631b9b6ff90fadbafb", {"valu": 1.1035, "salu": 0.3683, "lds": 0.1121}),
+    4: ("e567379000d9e29a065e5f8210c62d40e031d8eaa73d8a57a6c2a09769e9f009", {"valu": 0.1224, "salu": 0.0869, "lds": 0.0274}),
+    3: ("e567379000d9e29a065e5f8210c62d40e031d8eaa73d8a57a6c2a09769e9f009", {"valu": 1.1036, "salu": 0.3585, "lds": 0.1121}),
 }
 # the same for one ap_eval_children call on the sparse form of configs[4]
-MEASURED_TRAFFIC_CHILDREN = {4: ("7c43d55079426cec0ffb374a7fc8a66423e1e115c66128631b9b6ff90fadbafb", 131210332)}
+MEASURED_TRAFFIC_CHILDREN = {4: ("e567379000d9e29a065e5f8210c62d40e031d8eaa73d8a57a6c2a09769e9f009", 131209859)}
 
 
 def kernel_source_hash() -> str:
