@@ -401,3 +401,18 @@ def test_streamed_parts_that_are_lists_of_their_own(kind, lists):
     with GpuWorkload(tr) as g:
         assert g.route(600)["lists"] == lists
         assert_same(g.eval(np.resize(rows, (600, R)))[:20], oracle_for(tr).eval_batch(rows, nthreads=8), kind)
+
+
+def test_a_quiet_end_beyond_what_the_lists_have_room_for():
+    """A trace so long that the scratch area holds the lists of its busy part only: the quiet end stays streamed, although a shorter
+    one of that share would be listed as well."""
+    rng = np.random.default_rng(8)
+    M, B, R = 600, 2, 4_150_000                                          # 33744 bytes of lists a tile and row; 128 MiB are 3976 tiles
+    quiet = R // 33
+    arrival = np.cumsum(np.where(np.arange(R) < R - quiet, 1, 900)).astype(np.uint64)
+    t_off = np.where(np.arange(M) % 7 == 0, int(arrival[-1]) + 1, traces.UINT64_MAX).astype(np.uint64)
+    tr = traces.custom_trace(arrival, np.full(R, 10), rng.integers(1, 10, R), [(100, 1, 25, 0), (60, 1, 18, 0)] * (M // 2), None, t_off, B=B)
+    rows = rng.integers(0, M, size=(2, R)).astype(np.uint16)
+    with GpuWorkload(tr) as g:
+        assert g.route(2)["lists"] == 2
+        assert_same(g.eval(rows), oracle_for(tr).eval_batch(rows, nthreads=2), "a long trace with a quiet end")
